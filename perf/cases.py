@@ -284,6 +284,83 @@ def run(s):
     return {"scores": scores, "chunk_scores": s["cs"], "mask": s["mask"]}
 
 
+def _layer_keys(s, layer):
+    """Keys of one layer in 64 bits, [kv][T][d], whatever the layout they are held in."""
+    case, T = s["case"], s["T"]
+    k = s["k"][layer]
+    if case["op"] == "paged":
+        k = k.transpose(1, 2) if case["layout"] == "NHD" else k             # [pages][kv][P][d]
+        k = k[s["table"].long()].transpose(0, 1)
+        return k.reshape(k.shape[0], -1, k.shape[-1])[:, :T].double()
+    if case["op"] == "fp8":
+        k = k.view(torch.float8_e4m3fn).float().double()
+        scale = s["kscale"][layer].double()
+        return (k.transpose(0, 1) if case["layout"] == "NHD" else k) * scale[:, None, None]
+    return (k.transpose(0, 1) if case["layout"] == "NHD" else k).double()
+
+
+def _exact_scores(s):
+    case, lens = s["case"], s["lens"]
+    layers, H, kv, d = DRAFTS[case["draft"]]
+    n_q, G, take_max = case["n_q"], H // kv, case["agg"] == "max"
+    q = s["q"] if case["op"] == "batch" else s["q"][None]
+    out = [None] * len(lens)
+    for layer in range(layers):
+        keys, at = _layer_keys(s, layer), 0
+        for b, L in enumerate(lens):
+            if L == 0:
+                continue
+            rows = q[b, layer].double().reshape(kv, G * n_q, d)
+            logits = torch.matmul(rows, keys[:, at:at + L].transpose(1, 2).contiguous()).mul_(s["desc"].scale)
+            norm = torch.logsumexp(logits, dim=2)
+            if case["op"] == "look":
+                look = torch.matmul(rows, s["k_look"][layer].double().transpose(1, 2).contiguous()).mul_(s["desc"].scale)
+                n = torch.arange(n_q, device=DEV)
+                hidden = n[None, :] >= n[:, None] + case["look_self"]       # row n sees the keys generated before it
+                look = look.view(kv, G, n_q, n_q).masked_fill(hidden, -math.inf).view(kv, G * n_q, n_q)
+                norm = torch.logaddexp(norm, torch.logsumexp(look, dim=2))
+            prob = logits.sub_(norm[:, :, None]).exp_().view(kv * G, n_q, L).amax(dim=0)
+            if out[b] is None:
+                out[b] = prob
+            elif take_max:
+                out[b] = torch.maximum(out[b], prob)
+            else:
+                out[b] += prob
+            at += L
+    div = n_q * (1 if take_max else layers)
+    return [o.sum(dim=0) / div for o in out]
+
+
+def _exact_chunk_scores(scores, chunk):
+    L = scores.numel()
+    pooled = torch.nn.functional.avg_pool1d(scores[None, None], POOL, stride=1, padding=POOL // 2)[0, 0]
+    C = -(-L // chunk)
+    sums = torch.nn.functional.pad(pooled, (0, C * chunk - L)).view(C, chunk).sum(dim=1)
+    size = torch.full((C,), float(chunk), dtype=torch.float64, device=DEV)
+    size[-1] = L - (C - 1) * chunk
+    return sums / size
+
+
+def exact(case, seed):
+    """Scores and chunk scores in 64 bits, straight from the definition. What follows from them by comparing (kept
+    chunks, spans, mask, assembled prompt) has no nearer value."""
+    s = prepare(case, seed)
+    chunk = case["chunk"]
+    if case["op"] == "budget":
+        out = {n: None for n in ("sel", "spans", "n_spans", "k", "n_kept", "cs", "n_t", "mask", "n_proj", "out_ids",
+                                 "out_pos", "out_src", "out_len")}
+        out["cs"] = _exact_chunk_scores(s["scores"].double(), chunk)
+        return out
+    parts = _exact_scores(s)
+    cs, at = torch.zeros_like(s["cs"], dtype=torch.float64), 0
+    for b, part in enumerate(parts):
+        v = _exact_chunk_scores(part, chunk)
+        first = at // chunk + b if case["op"] == "batch" else 0
+        cs[first:first + v.numel()] = v
+        at += part.numel()
+    return {"scores": torch.cat(parts), "chunk_scores": cs, "mask": None}
+
+
 def work(case):
     """Keys, queries and offsets read once, scores, chunk scores and mask written once; one product of every query row
     with every key."""
