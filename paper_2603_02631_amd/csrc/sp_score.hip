@@ -41,6 +41,7 @@ using namespace sp_dev;
 constexpr int kThreads = 256;
 constexpr int kWaves = 4;
 constexpr int kMaxPrompts = 4096;
+constexpr int kMaxGroupPrompts = 32;       // prompts one launch of the fused kernel serves
 constexpr size_t kLdsBudget = 64 * 1024;
 constexpr int kProbTargetWgs = 1024;   // the prob pass splits layers until it has about this many workgroups
 
@@ -56,7 +57,7 @@ struct ScoreArgs {
     int64_t k_stride_token, k_stride_head;
     const TileInfo *tiles;    // null: single prompt, tile t starts at t * tile_keys
     const int32_t *prompt_tiles;  // [B+1] first tile of each prompt (batch only)
-    int64_t L;                // single prompt length
+    int64_t L;                // tokens of the call (single prompt: its length)
     float2 *part;             // [n_phases][n_tiles][rows_pad]
     float *lse_neg;           // [B][n_phases][rows_pad]  (-lse in raw-logit units, permuted)
     float *scores;
@@ -66,8 +67,7 @@ struct ScoreArgs {
     int64_t page_stride;
     const float *look;        // [n_phases][rows_pad] lookahead-key term of each row's normaliser, or null
     const float *kscale;      // 8-bit keys: [n_phases] scale of each (layer, kv head); null: bf16 keys
-    float *split_buf;         // layer-split results: MEAN [n_splits][n_tiles][TILE],
-                              //                      MAX  [n_splits][8*n_nblk][n_tiles][TILE]
+    float *split_buf;         // layer-split results: MEAN [n_splits][L], MAX [n_splits][8*n_nblk][L]
     int32_t n_splits, layers_per_split;
     int32_t n_tiles, n_prompts;
     int32_t n_layers, n_q_heads, n_kv_heads, group, n_q;
@@ -461,8 +461,8 @@ __global__ __launch_bounds__(kThreads, 3) void sp_prob_kernel(ScoreArgs a, Layer
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int n = 8 * b + 4 * hf + e;
-                    a.split_buf[(((int64_t)split * n_rows + n) * a.n_tiles + tile) * TILE + (wave * NS + s) * 32 + col] =
-                        fast_exp2(mx[s][b][e] * c);
+                    const int64_t j = ti.j0 + (wave * NS + s) * 32 + col;
+                    if (j < ti.end) a.split_buf[((int64_t)split * n_rows + n) * a.L + j] = fast_exp2(mx[s][b][e] * c);
                 }
         return;
     }
@@ -472,36 +472,46 @@ __global__ __launch_bounds__(kThreads, 3) void sp_prob_kernel(ScoreArgs a, Layer
         const int local = (wave * NS + s) * 32 + col;
         const int64_t j = ti.j0 + local;
         if (hf != 0) continue;
-        if (!whole) a.split_buf[((int64_t)split * a.n_tiles + tile) * TILE + local] = both;
-        else if (j < ti.end) a.scores[j] = both * a.out_scale;
+        if (j >= ti.end) continue;
+        if (!whole) a.split_buf[split * a.L + j] = both;
+        else a.scores[j] = both * a.out_scale;
     }
 }
 
 // ---------------------------------------------------------------------------
-// reduce: combines the layer ranges of a split prob pass, one thread per key,
-// ranges in ascending order. MEAN adds the ranges' sums; MAX takes, per
-// lookahead row, the largest probability over the ranges and adds the rows.
+// reduce: combines the layer ranges of a call, whichever kernel left them. MEAN
+// adds the ranges' sums; MAX takes, per lookahead row, the largest probability
+// over the ranges and adds the rows. A workgroup owns 64 keys; its four waves
+// take every fourth range (MEAN) or row (MAX), so that a short prompt still has
+// enough loads in flight, and their sums are added in wave order.
 // ---------------------------------------------------------------------------
-template <int TILE>
-__global__ __launch_bounds__(TILE) void sp_prob_reduce_kernel(ScoreArgs a)
+__global__ __launch_bounds__(256) void sp_split_reduce_kernel(const float *__restrict__ buf, int64_t total, int n_splits,
+                                                              int n_rows /* 0: MEAN */, float out_scale,
+                                                              const uint32_t *__restrict__ status,
+                                                              float *__restrict__ scores)
 {
-    const int tile = blockIdx.x, local = threadIdx.x;
-    const TileInfo ti = get_tile(a, tile, TILE);
-    const int64_t j = ti.j0 + local;
-    if (j >= ti.end) return;
+    __shared__ float part[4][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t j = (int64_t)blockIdx.x * 64 + lane;
+    const bool live = j < total;
+    const float *src = buf + (live ? j : 0);
     float sum = 0.f;
-    if (a.layer_agg == SP_LAYER_MEAN) {
-        for (int s = 0; s < a.n_splits; ++s) sum += a.split_buf[((int64_t)s * a.n_tiles + tile) * TILE + local];
+    if (n_rows == 0) {
+#pragma unroll 4
+        for (int s = wave; s < n_splits; s += 4) sum += src[s * total];
     } else {
-        const int n_rows = 8 * a.n_nblk;
-        for (int n = 0; n < n_rows; ++n) {
+        for (int n = wave; n < n_rows; n += 4) {
             float m = 0.f;
-            for (int s = 0; s < a.n_splits; ++s)
-                m = fmaxf(m, a.split_buf[(((int64_t)s * n_rows + n) * a.n_tiles + tile) * TILE + local]);
+#pragma unroll 8
+            for (int s = 0; s < n_splits; ++s) m = fmaxf(m, src[((int64_t)s * n_rows + n) * total]);
             sum += m;
         }
     }
-    a.scores[j] = sum * a.out_scale;
+    part[wave][lane] = sum;
+    __syncthreads();
+    if (wave != 0 || !live) return;
+    const float both = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+    scores[j] = *status != 0u ? __uint_as_float(0x7fc00000u) : both * out_scale;     // a failed call has no scores
 }
 
 // Tile table of a ragged batch: tiles never straddle prompts.
@@ -617,8 +627,6 @@ int fused_workgroups(const Plan &p, int64_t L)
     return n > 0x7fffffff ? 0x7fffffff : (int)n;
 }
 
-bool fused_applies(const Plan &p, int64_t L, int64_t k_stride_token);
-
 // Compute units of the current device (0 if it cannot be queried); the fused kernel needs one per workgroup.
 int device_compute_units()
 {
@@ -653,37 +661,36 @@ bool fused_applies_fp8(const Plan &p, const sp_score_desc *desc, int64_t L)
 
 // A ragged batch on the single-launch kernel: the prompts are packed into launches of at most one
 // workgroup per compute unit (first fit, longest first), each prompt with all its 512-key tiles in one
-// launch. Applies when every prompt is empty or at least one tile long and fits a launch, the batch has
-// enough tiles to be worth it, and every launch has at least as many workgroups as duty blocks.
+// launch. Possible when every prompt fits a launch and the batch holds at least one tile of keys.
 struct BatchGroups {
     std::vector<sp_fused::GroupTable> groups;
     std::vector<int> wgs;
+    int64_t tiles = 0;              // of all prompts
+    bool short_prompt = false;      // one of them is shorter than a tile
 };
 
 bool plan_fused_batch(const Plan &p, const int64_t *offsets, int B, int64_t k_stride_token, BatchGroups &out)
 {
     if (!fused_shape_ok(p) || k_stride_token > (int64_t(1) << 20)) return false;
     const int cap = std::min(256, device_compute_units());
-    if (cap < sp_fused::kMinWorkgroups) return false;
+    if (cap < sp_fused::kMinWorkgroups || offsets[B] < fused_tile(p)) return false;
     std::vector<std::pair<int, int>> order;        // (tiles, prompt)
-    int64_t total_tiles = 0;
     for (int b = 0; b < B; ++b) {
         const int64_t len = offsets[b + 1] - offsets[b];
         if (len == 0) continue;
-        if (len < fused_tile(p)) return false;
+        out.short_prompt |= len < fused_tile(p);
         const int64_t tiles = sp::ceil_div(len, fused_tile(p));
         if (tiles > cap) return false;
         order.emplace_back((int)tiles, b);
-        total_tiles += tiles;
+        out.tiles += (int)tiles;
     }
-    if (total_tiles < sp_fused::kMinWorkgroups) return false;
     std::stable_sort(order.begin(), order.end(), [](const std::pair<int, int> &x, const std::pair<int, int> &y) { return x.first > y.first; });
     out.groups.clear();
     out.wgs.clear();
     for (const auto &tp : order) {
         size_t g = 0;
         for (; g < out.groups.size(); ++g)
-            if (out.wgs[g] + tp.first <= cap && out.groups[g].n < sp_fused::kMaxGroupPrompts) break;
+            if (out.wgs[g] + tp.first <= cap && out.groups[g].n < kMaxGroupPrompts) break;
         if (g == out.groups.size()) {
             sp_fused::GroupTable t;
             std::memset(&t, 0, sizeof t);
@@ -693,13 +700,82 @@ bool plan_fused_batch(const Plan &p, const int64_t *offsets, int B, int64_t k_st
         sp_fused::GroupTable &t = out.groups[g];
         t.prompt[t.n] = tp.second;
         t.start[t.n] = offsets[tp.second];
-        t.len[t.n] = offsets[tp.second + 1] - offsets[tp.second];
+        t.len[t.n] = (int32_t)(offsets[tp.second + 1] - offsets[tp.second]);
+        t.layer0[t.n] = 0;
+        t.layers[t.n] = p.n_layers;
+        t.slice[t.n] = 0;
         t.w0[t.n] = out.wgs[g];
         out.wgs[g] += tp.first;
         t.w0[++t.n] = out.wgs[g];
     }
-    for (size_t g = 0; g < out.groups.size(); ++g)
-        if (out.groups[g].n * (p.rows_pad / 4) > out.wgs[g]) return false;      // more duty blocks than workgroups
+    return true;
+}
+
+// How many layer ranges a launch over all of `n_prompts` prompts is cut into: as many as its `tiles`
+// workgroups fit the device, so that the ranges run side by side. `room`: bytes for their exchange area.
+// A step of the kernel takes 2.1 us on 64 workgroups and 2.9 us on 256 (head_dim 64, 32 rows), so every
+// range more is time saved (16 layers, 8 kv heads, head_dim 64: 32K tokens 276 -> 111 us with four
+// ranges, 64K tokens 305 -> 211 us with two; 28 layers, head_dim 128: 32K tokens 542 -> 363 us).
+int fused_ranges(const Plan &p, int tiles, int n_prompts, size_t room)
+{
+    int n = std::min({std::min(256, device_compute_units()) / tiles, p.n_layers, sp_fused::kMaxGroup / n_prompts});
+    while (n > 1 && sp_fused::workspace_bytes(p.rows_pad, tiles * n, n_prompts * n) > room) --n;
+    if (n < 2) return 1;
+    return (int)sp::ceil_div(p.n_layers, sp::ceil_div(p.n_layers, n));       // no empty range
+}
+
+// Batches the single-launch kernel takes whatever their size: every prompt fills a tile, and one range of
+// layers fills enough of the device.
+bool whole_groups_pay(const Plan &, const BatchGroups &bg)
+{
+    return !bg.short_prompt && bg.tiles >= sp_fused::kMinWorkgroups;
+}
+
+// Otherwise (few workgroups, or tiles that short prompts leave half empty): whether the single-launch kernel
+// beats the three-kernel path. A launch costs its steps (a range's phases and five more to fill and drain
+// the pipeline) at 2.2 us; in that time the three kernels get through 6.3 MB of K. Measured crossings (fused / three kernels, us): 16 layers x 8 kv
+// heads, head_dim 64: 4096 tokens 40 / 40, 6144 40 / 49, 8192 43 / 58; 4 x 4 heads, head_dim 128: 8192
+// tokens 32 / 27, 16384 34 / 39; 28 x 8 heads, head_dim 128: 2048 tokens 46 / 59.
+bool steps_pay(const Plan &p, int64_t tokens, int ranges, int launches)
+{
+    const int64_t steps = sp::ceil_div(p.n_layers, ranges) * (p.n_phases / p.n_layers) + 5;
+    return tokens * p.n_phases * p.D * 2 >= launches * steps * 6300000;
+}
+
+// The table of a launch with every entry of `t` once per layer range.
+sp_fused::GroupTable split_layers(const sp_fused::GroupTable &t, int n_layers, int ranges)
+{
+    sp_fused::GroupTable r;
+    std::memset(&r, 0, sizeof r);
+    const int per_range = (int)sp::ceil_div(n_layers, ranges);
+    for (int s = 0; s < ranges; ++s)
+        for (int i = 0; i < t.n; ++i) {
+            r.prompt[r.n] = t.prompt[i];
+            r.start[r.n] = t.start[i];
+            r.len[r.n] = t.len[i];
+            r.layer0[r.n] = s * per_range;
+            r.layers[r.n] = std::min(per_range, n_layers - s * per_range);
+            r.slice[r.n] = s;
+            r.w0[r.n + 1] = r.w0[r.n] + t.w0[i + 1] - t.w0[i];
+            ++r.n;
+        }
+    return r;
+}
+
+// A single prompt on the single-launch kernel: a table of one entry.
+bool plan_fused_prompt(const Plan &p, int64_t L, int64_t k_stride_token, BatchGroups &out)
+{
+    if (!fused_shape_ok(p) || k_stride_token > (int64_t(1) << 20) || L < fused_tile(p)) return false;
+    const int n_wg = fused_workgroups(p, L);
+    if (n_wg > std::min(256, device_compute_units())) return false;
+    sp_fused::GroupTable t;
+    std::memset(&t, 0, sizeof t);
+    t.n = 1;
+    t.w0[1] = n_wg;
+    t.layers[0] = p.n_layers;
+    t.len[0] = (int32_t)L;
+    out.groups.assign(1, t);
+    out.wgs.assign(1, t.w0[1]);
     return true;
 }
 
@@ -718,10 +794,18 @@ WsLayout ws_layout(const Plan &p, int64_t n_tiles, int n_prompts)
     if (fused_shape_ok(p)) {
         int64_t n_wg = n_tiles * p.tile_keys / fused_tile(p) + n_prompts;
         if (n_wg > 1024) n_wg = 1024;
-        off += sp_fused::workspace_bytes(p.rows_pad, (int)n_wg, std::min(n_prompts, sp_fused::kMaxGroupPrompts));
+        off += sp_fused::workspace_bytes(p.rows_pad, (int)n_wg, std::min(n_prompts, kMaxGroupPrompts));
     }
     w.total = off;
     return w;
+}
+
+sp_status launch_reduce(const ScoreArgs &a, int n_splits, hipStream_t st)
+{
+    hipLaunchKernelGGL(sp_split_reduce_kernel, dim3((unsigned)sp::ceil_div(a.L, 64)), dim3(256), 0, st, (const float *)a.split_buf,
+                       a.L, n_splits, a.layer_agg == SP_LAYER_MAX ? 8 * a.n_nblk : 0, a.out_scale, (const uint32_t *)a.status, a.scores);
+    SP_HIP_CHECK(hipGetLastError());
+    return SP_OK;
 }
 
 template <int D, int NS, bool FP8 = false>
@@ -738,11 +822,7 @@ sp_status launch_all(const Plan &p, const ScoreArgs &a, const LayerPtrs &kp, hip
     else
         hipLaunchKernelGGL((sp_prob_kernel<D, NS, 2, FP8>), grid, block, p.lds_bytes, st, a, kp);
     SP_HIP_CHECK(hipGetLastError());
-    if (a.n_splits > 1) {
-        constexpr int TILE = kWaves * NS * 32;
-        hipLaunchKernelGGL((sp_prob_reduce_kernel<TILE>), dim3(a.n_tiles), dim3(TILE), 0, st, a);
-        SP_HIP_CHECK(hipGetLastError());
-    }
+    if (a.n_splits > 1) return launch_reduce(a, a.n_splits, st);
     return SP_OK;
 }
 
@@ -858,51 +938,56 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
         if (p.D == 64) return launch_all<64, 2, true>(p, a, kp, st);
         return launch_all<128, 1, true>(p, a, kp, st);
     }
-    if (!batch && fused_applies(p, total, desc->k_stride_token)) {
-        const int n_wg = fused_workgroups(p, total);
-        {
-            sp_fused::FusedArgs f;
-            std::memset(&f, 0, sizeof f);
-            f.q = a.q;
-            f.head_dim = p.D;
-            f.tile_keys = fused_tile(p);
-            f.k_stride_token = a.k_stride_token;
-            f.k_stride_head = a.k_stride_head;
-            f.L = total;
-            f.kscale = opt.kscale;
-            f.look = a.look;
-            f.block_table = a.block_table;
-            f.page_tokens = a.page_tokens;
-            f.page_stride = a.page_stride;
-            f.scores = scores_dev;
-            f.n_wg = n_wg;
-            f.n_layers = a.n_layers; f.n_q_heads = a.n_q_heads; f.n_kv_heads = a.n_kv_heads;
-            f.group = a.group; f.n_q = a.n_q;
-            f.n_nblk = a.n_nblk; f.n_gblk = a.n_gblk; f.rows_pad = a.rows_pad;
-            f.layer_agg = a.layer_agg;
-            f.c = a.c; f.inv_c = a.inv_c; f.out_scale = a.out_scale;
-            return sp_fused::launch(f, kp, nullptr, true, ws + w.fused, a.status, st);
-        }
-    }
+    sp_fused::FusedArgs f;
+    std::memset(&f, 0, sizeof f);
+    f.q = a.q;
+    f.head_dim = p.D;
+    f.tile_keys = fused_tile(p);
+    f.k_stride_token = a.k_stride_token;
+    f.k_stride_head = a.k_stride_head;
+    f.look = a.look;
+    f.block_table = a.block_table;
+    f.page_tokens = a.page_tokens;
+    f.page_stride = a.page_stride;
+    f.scores = scores_dev;
+    f.n_layers = a.n_layers; f.n_q_heads = a.n_q_heads; f.n_kv_heads = a.n_kv_heads;
+    f.group = a.group; f.n_q = a.n_q;
+    f.n_nblk = a.n_nblk; f.n_gblk = a.n_gblk; f.rows_pad = a.rows_pad;
+    f.layer_agg = a.layer_agg;
+    f.c = a.c; f.inv_c = a.inv_c; f.out_scale = a.out_scale;
     BatchGroups bg;
-    if (batch && !opt.k_look && !opt.block_table && plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg)) {
+    if (fp8_fused) {
+        f.L = total;
+        f.n_wg = fused_workgroups(p, total);
+        f.kscale = opt.kscale;
+        return sp_fused::launch(f, kp, nullptr, true, true, ws + w.fused, a.status, st);
+    }
+    bool fused = !opt.kscale && (batch ? plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg)
+                                       : plan_fused_prompt(p, total, desc->k_stride_token, bg));
+    int ranges = 1;
+    if (fused && bg.groups.size() == 1) {
+        // the exchange area of a launch in layer ranges takes the place of the general path's buffers
+        ranges = fused_ranges(p, bg.wgs[0], bg.groups[0].n, w.split - w.part);
+    }
+    if (fused && !(batch ? whole_groups_pay(p, bg) : bg.wgs[0] >= fused_min_workgroups(p)))
+        fused = (batch || ranges > 1) && steps_pay(p, total, ranges, (int)bg.groups.size());
+    if (fused) {
+        if (ranges > 1) {
+            const sp_fused::GroupTable t = split_layers(bg.groups[0], p.n_layers, ranges);
+            f.n_wg = bg.wgs[0] * ranges;
+            f.L = total;
+            f.split_out = a.split_buf;
+            f.split_stride = total;
+            const sp_status rs = sp_fused::launch(f, kp, &t, false, true, ws + w.part, a.status, st);
+            return rs == SP_OK ? launch_reduce(a, ranges, st) : rs;
+        }
         for (size_t g = 0; g < bg.groups.size(); ++g) {
-            sp_fused::FusedArgs f;
-            std::memset(&f, 0, sizeof f);
-            f.q = a.q;
-            f.head_dim = p.D;
-            f.tile_keys = fused_tile(p);
-            f.k_stride_token = a.k_stride_token;
-            f.k_stride_head = a.k_stride_head;
-            f.L = 0;
-            f.scores = scores_dev;
             f.n_wg = bg.wgs[g];
-            f.n_layers = a.n_layers; f.n_q_heads = a.n_q_heads; f.n_kv_heads = a.n_kv_heads;
-            f.group = a.group; f.n_q = a.n_q;
-            f.n_nblk = a.n_nblk; f.n_gblk = a.n_gblk; f.rows_pad = a.rows_pad;
-            f.layer_agg = a.layer_agg;
-            f.c = a.c; f.inv_c = a.inv_c; f.out_scale = a.out_scale;
-            const sp_status rs = sp_fused::launch(f, kp, &bg.groups[g], g == 0, ws + w.fused, a.status, st);
+            f.L = total;
+            // duties rotate over all prompts of a launch where they can: within a prompt of a dozen workgroups
+            // each would have one every other phase (8 prompts of 2K .. 32K tokens: 342 against 394 us)
+            const bool shared = !bg.short_prompt && bg.groups[g].n * (p.rows_pad / sp_fused::kDutyRows) <= bg.wgs[g];
+            const sp_status rs = sp_fused::launch(f, kp, batch ? &bg.groups[g] : nullptr, shared, g == 0, ws + w.fused, a.status, st);
             if (rs != SP_OK) return rs;
         }
         return SP_OK;
@@ -962,7 +1047,7 @@ extern "C" int32_t sp_score_batch_is_fused(const sp_score_desc *desc, const int6
     for (int b = 0; b < B; ++b)
         if (offsets_host[b + 1] < offsets_host[b]) return -1;
     BatchGroups bg;
-    return plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg) ? (int32_t)bg.groups.size() : 0;
+    return plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg) && whole_groups_pay(p, bg) ? (int32_t)bg.groups.size() : 0;
 }
 
 extern "C" sp_status sp_score(const sp_score_desc *desc, const void *q_dev, const void *const *k_layers_host,

@@ -46,9 +46,13 @@
 // Variants of the same loop: head_dim 128 (256 keys per workgroup, a wave's two
 // sub-tiles are the two halves of its 32 keys' rows: see the kernel's template
 // flag W), paged keys and lookahead keys in the normaliser (flag EXTRA), and
-// launches that carry several prompts of a ragged batch (a table of prompts,
-// also under EXTRA: each prompt has its own workgroups, duty blocks and row of
-// normalisers).
+// launches that carry a table of (prompt, layer range) entries (also under
+// EXTRA: each entry has its own workgroups, duty blocks and row of normalisers).
+// Entries are the prompts of a ragged batch, and the layer ranges of prompts
+// that fill only part of the device: a step takes about as long whether 64 or
+// 256 compute units take part (the exchange and a wave's chain of dependent
+// work set it), so a prompt of 98 workgroups runs its 16 layers as two ranges of
+// 8 on 196 of them, in half the steps; a small launch then adds the ranges up.
 #include "sp_score_fused.hpp"
 
 #include <atomic>
@@ -74,7 +78,7 @@ constexpr int kSlots = sp_fused::kSlots;  // exchange ring depth
 constexpr int kMaxRowsF = sp_fused::kMaxRows;   // 64 padded query rows per kv head
 constexpr int kPubWave = 0;                // the wave that publishes this workgroup's partials
 constexpr int kDutyWave = 1;               // the wave that combines this workgroup's duty rows
-constexpr int kDutyRows = 4;               // consecutive query rows one duty covers (32 bytes per source workgroup)
+constexpr int kDutyRows = sp_fused::kDutyRows;   // 4: 32 bytes per source workgroup
 constexpr int kLseWave = 2;                // the wave that fetches the normalisers
 constexpr uint32_t kPoisonTag = 0xffffffffu;   // normaliser entry of a duty that gave up
 
@@ -87,7 +91,7 @@ constexpr int kOffQ2 = kOffQ1 + 2 * kQTileBytes;                   // [2] Q of t
 constexpr int kWstatsBytes = kFWaves * kMaxRowsF * 8;              // (max, sum) of 64 rows from 8 waves
 constexpr int kOffWstats = kOffQ2 + 2 * kQTileBytes;               // [2]
 constexpr int kOffCinit = kOffWstats + 2 * kWstatsBytes;           // [2][64] accumulator seeds
-constexpr int kOffXduty = kOffCinit + 2 * kMaxRowsF * 4;           // 8 KB: partials of the duty rows
+constexpr int kOffXduty = kOffCinit + 2 * kMaxRowsF * 4;           // 8 KB: partials of the duty rows (direct exchange: of all rows)
 constexpr int kOffXlse = kOffXduty + 8192;                         // 1 KB: normaliser entries of one phase
 constexpr int kOffXlook = kOffXlse + 1024;                         // 1 KB: lookahead-key terms of one phase's rows
 constexpr int kOffFail = kOffXlook + 1024;
@@ -129,6 +133,14 @@ __device__ __forceinline__ void vm_wait()
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
+
+// What a variant of the kernel serves beyond one whole prompt of contiguous keys. Every one carries only its
+// own code: shared duties in the variant for ranges would cost the batches 3 %.
+enum Kind {
+    kPlain,
+    kExtra,     // + paged keys, lookahead keys, or the whole prompts of a batch, whose duties rotate over the launch
+    kRanges     // + paged keys, lookahead keys, and a table of entries that keep to themselves: layer ranges, short prompts
+};
 
 struct Ring {
     bf16x8 kf[kRing][kNS][kKS];           // K fragments of the phases in flight
@@ -502,7 +514,7 @@ __device__ __forceinline__ void stage_exchange_rows(uint32_t xlse_ad, const uint
                                                     int rows_pad, int lane)
 {
     if (look_row != nullptr) dma_v_device(look_row + 4 * min(lane, rows_pad / 4 - 1), xlse_ad + (kOffXlook - kOffXlse));
-    stage_entries(xlse_ad, lse_row, rows_pad / 2, lane);
+    if (lse_row != nullptr) stage_entries(xlse_ad, lse_row, rows_pad / 2, lane);
 }
 
 // ---- statistics pass of one phase: per-wave (max, sum exp) of every row into wstats ----
@@ -588,7 +600,7 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
 #pragma unroll
         for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][t], q1[t], d, 0, 0, 0);
         k_issue<kPerStep>(ki, voff, 0);
-        if (lse_row != nullptr) stage_exchange_rows(xlse_ad, lse_row, look_row, rows_pad, lane);
+        stage_exchange_rows(xlse_ad, lse_row, look_row, rows_pad, lane);
         __builtin_amdgcn_sched_barrier(0);
         float m = neg_inf(), l = 0.f;
         fold_logits(d, m, l, c, lo0, hi0, hf);
@@ -606,7 +618,7 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
     float m = neg_inf(), l = 0.f;
     fold_logits(da, m, l, c, lo0, hi0, hf);
     k_issue<kPerStep>(ki, voff, 0);
-    if (lse_row != nullptr) stage_exchange_rows(xlse_ad, lse_row, look_row, rows_pad, lane);
+    stage_exchange_rows(xlse_ad, lse_row, look_row, rows_pad, lane);
     __builtin_amdgcn_sched_barrier(0);
     if (NBLK == 2) {
         lift_at<kOffQ1 + PAR * kQTileBytes + 4096>(lc, qf);
@@ -682,7 +694,18 @@ __device__ __forceinline__ float read_look_staging(uint32_t lds0, int lane)
     return v;
 }
 
-// The partials of rows row0 .. row0+3 of one exchange slot from every workgroup: eight loads.
+// Direct exchange: all rows of one exchange slot from every workgroup of the entry, `entries` 8-byte
+// entries in one piece (at most 8 KB).
+__device__ __forceinline__ void stage_direct(uint32_t xduty, const uint64_t *slot_base, int entries, int lane)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        if (128 * i < entries) dma_v_device(slot_base + min(128 * i + 2 * lane, entries - 2), xduty + i * 1024);      // uniform
+}
+
+// The partials of rows row0 .. row0+3 of one exchange slot from every workgroup: eight loads, or (SKIP) two for
+// every 64 workgroups there are.
+template <bool SKIP>
 __device__ __forceinline__ void stage_duty_block(uint32_t xduty, const uint64_t *slot_base, int rows_pad, int n_wg,
                                                  int row0, int lane)
 {
@@ -690,7 +713,7 @@ __device__ __forceinline__ void stage_duty_block(uint32_t xduty, const uint64_t 
     for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-            dma_v_device(slot_base + (size_t)min(lane + 64 * q, n_wg - 1) * rows_pad + row0 + 2 * h,
+            if (!SKIP || 64 * q < n_wg) dma_v_device(slot_base + (size_t)min(lane + 64 * q, n_wg - 1) * rows_pad + row0 + 2 * h,
                          xduty + (2 * q + h) * 1024);
 }
 
@@ -716,13 +739,63 @@ __device__ __forceinline__ void raise_failure(const FusedArgs &a, int *fail)
     __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Direct exchange: the normaliser (negated) of row `lane` of a phase from the staged partials of the entry's
+// src_n workgroups, `src` their place in memory. With 32 rows the two halves of the wave take the even and the
+// odd workgroups: entry i of a lane sits 512 i bytes behind its first either way. Fixed order, so every
+// workgroup finds the same bits.
+template <int NB, int GB>
+__device__ __forceinline__ float direct_combine(const FusedArgs &a, const uint64_t *src, int src_n, uint32_t par, uint32_t lds0,
+                                                int *fail, int lane, float c, float inv_c)
+{
+    constexpr int kRowsPad = 32 * NB * GB, kPer = 64 / kRowsPad;      // workgroups per 512 bytes
+    static_assert(kRowsPad == 32 || kRowsPad == 64, "one or two row blocks");
+    const int row = lane & (kRowsPad - 1);
+    const int mine = (src_n - lane / kRowsPad + kPer - 1) / kPer;     // entries of this lane
+    int g, n;
+    const bool valid_row = row_valid<NB>(a, row, g, n);
+    constexpr int kMaxE = (sp_fused::direct_max(kRowsPad) + kPer - 1) / kPer;     // 4 or 15
+    uint64_t e[16];
+    const uint32_t ad = lds0 + kOffXduty + 8u * (uint32_t)lane;
+    for (unsigned spins = 0;;) {
+#define SP_READ4(B)                                                                                                     \
+    __asm__ volatile(                                                                                                   \
+        "ds_read_b64 %0, %4 offset:" #B "\n\tds_read_b64 %1, %4 offset:" #B "+512\n\t"                                 \
+        "ds_read_b64 %2, %4 offset:" #B "+1024\n\tds_read_b64 %3, %4 offset:" #B "+1536\n\ts_waitcnt lgkmcnt(0)"       \
+        : "=&v"(e[B / 512]), "=&v"(e[B / 512 + 1]), "=&v"(e[B / 512 + 2]), "=&v"(e[B / 512 + 3])                        \
+        : "v"(ad) : "memory")
+        SP_READ4(0);
+        if (kMaxE > 4) { SP_READ4(2048); SP_READ4(4096); SP_READ4(6144); }
+#undef SP_READ4
+        uint32_t bad = 0u;
+#pragma unroll
+        for (int i = 0; i < kMaxE; ++i)
+            bad |= (uint32_t)(i < mine) & ((uint32_t)((uint32_t)(e[i] >> 63) != par) | (uint32_t)(((e[i] >> 32) & 0x7fffffffu) == 0));
+        if (!__any(valid_row && bad != 0u) && a.force_miss == 0) break;
+        if (*fail != 0) break;
+        if (++spins > a.spin_max) { raise_failure(a, fail); break; }
+        stage_direct(lds0 + kOffXduty, src, src_n * kRowsPad, lane);        // bounded polling
+        vm_wait<0>();
+    }
+    float m = neg_inf(), l = 0.f;
+#pragma unroll
+    for (int i = 0; i < kMaxE; ++i) m = i < mine ? fmaxf(m, __uint_as_float((uint32_t)e[i])) : m;
+    if (kRowsPad == 32) m = fmaxf(m, __shfl_xor(m, 32));
+#pragma unroll
+    for (int i = 0; i < kMaxE; ++i) {
+        const float p = __uint_as_float((uint32_t)(e[i] >> 32) & 0x7fffffffu) * fast_exp2((__uint_as_float((uint32_t)e[i]) - m) * c);
+        l += i < mine ? p : 0.f;
+    }
+    if (kRowsPad == 32) l += __shfl_xor(l, 32);
+    return -(m + fast_log2(l) * inv_c);
+}
+
 // Uniform state that walks along with the steps.
 struct Walk {
     PhaseCtr k;       // phase s + 1: next statistics pass (its K tile is being fetched)
     const char *kptr; // this wave's first key of that phase
     PhaseCtr c;       // phase s - 4: this step's probability pass
     int slot0;        // transit slot of sub-tile 0 of phase s: 2s mod 3
-    int dfirst;       // workgroup that combines block 0 of phase s - 2; blocks rotate over the workgroups
+    int dfirst;       // workgroup (of those that share the duties) that combines block 0 of phase s - 2
 };
 
 // One step `s` of the software pipeline: everything between two workgroup barriers. Per wave, in
@@ -741,13 +814,13 @@ struct Walk {
 // 4 K loads (prob), [normaliser load], 4 K loads (stats); the bracketed ones exist on some waves or
 // in some steps only, so every wait counts only operations that are certainly issued behind the
 // ones it needs.
-// EXTRA selects the variant that also serves paged keys (an upper bound on the tile's rows) and
-// lookahead keys in the normaliser; the plain variant carries none of their code or registers.
-template <int NB, int GB, int SLOT, int PAR, bool EXTRA, bool W, bool F8>
+// KIND (see there): the plain variant carries none of the others' code or registers.
+template <int NB, int GB, int SLOT, int PAR, Kind KIND, bool W, bool F8>
 __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, const GroupTable &gt, int s, int n_phases, Ring &ring,
                                      Acc<NB> &acc, const LaneConst &lc, Walk &wk, unsigned char *lds, uint32_t lds0,
                                      uint64_t wave_off, int r_range)
 {
+    constexpr bool EXTRA = KIND != kPlain, RANGES = KIND == kRanges;
     // Other lane-derived values are recomputed every step instead of being kept in registers across
     // the whole loop (the opaque copy stops the compiler from hoisting them).
     int tid = threadIdx.x;
@@ -768,16 +841,20 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     const float c_pub = F8 ? a.c * a.kscale[clampi(pp, 0, n_phases - 1)] : a.c;
     const float c_duty = F8 ? a.c * a.kscale[clampi(pd, 0, n_phases - 1)] : a.c;
     const float ks_prob = F8 ? a.kscale[clampi(pc, 0, n_phases - 1)] : 1.f;
-    // Duty blocks of a phase: kDutyRows consecutive rows of one prompt (launches over several prompts have
-    // blocks_per_prompt of them for each); block i goes to workgroup dfirst + i. src_w0 / src_n: the
-    // workgroups whose partials the block combines (its prompt's), lse_idx: the prompt's row of normalisers.
-    const int blocks_per_prompt = a.rows_pad / kDutyRows;
-    int duty_blk = wk.dfirst <= w ? w - wk.dfirst : w - wk.dfirst + a.n_wg;
-    if (pd < 0 || pd >= n_phases || duty_blk >= blocks_per_prompt * a.n_gp) duty_blk = -1;
-    int src_w0 = 0, src_n = a.n_wg, lse_idx = 0;
-    if (EXTRA && a.n_gp > 1 && duty_blk >= 0) {
-        lse_idx = duty_blk / blocks_per_prompt;
-        duty_blk -= lse_idx * blocks_per_prompt;
+    // Duty blocks of a phase: kDutyRows consecutive rows of one entry. Block i goes to workgroup dfirst + i of the
+    // launch, so that the duties of small prompts rotate over everybody (that keeps the prompts within a few
+    // phases of each other: every phase of one needs a duty workgroup, which needs that phase of it); RANGES: of
+    // the entry, so that entries of unequal length share nothing and none waits for another's pace. src_w0 /
+    // src_n: the workgroups whose partials the block combines (its entry's), lse_idx: the entry's row of normalisers.
+    constexpr int kRowsPad = 32 * NB * GB, kBlocks = kRowsPad / kDutyRows;
+    const bool direct = RANGES && a.ent_n <= sp_fused::direct_max(kRowsPad);
+    const int duty_w0 = RANGES ? a.ent_w0 : 0, duty_n = RANGES ? a.ent_n : a.n_wg, duty_blocks = RANGES ? kBlocks : kBlocks * a.n_gp;
+    int duty_blk = wk.dfirst <= w - duty_w0 ? w - duty_w0 - wk.dfirst : w - duty_w0 - wk.dfirst + duty_n;
+    if (pd < 0 || pd >= n_phases || duty_blk >= duty_blocks || direct) duty_blk = -1;
+    int src_w0 = duty_w0, src_n = duty_n, lse_idx = RANGES ? a.p_idx : 0;
+    if (KIND == kExtra && a.n_gp > 1 && duty_blk >= 0) {
+        lse_idx = duty_blk / kBlocks;
+        duty_blk -= lse_idx * kBlocks;
         src_w0 = gt.w0[lse_idx];
         src_n = gt.w0[lse_idx + 1] - src_w0;
     }
@@ -823,8 +900,10 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         }
     } else if (wave == kDutyWave) {
         if (duty_blk >= 0)
-            stage_duty_block(lds0 + kOffXduty, a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad, a.rows_pad,
+            stage_duty_block<EXTRA>(lds0 + kOffXduty, a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad, a.rows_pad,
                              src_n, duty_blk * kDutyRows, lane);
+    } else if (RANGES && wave == kLseWave && direct && pl >= 0 && pl < n_phases) {
+        stage_direct(lds0 + kOffXduty, a.part + ((size_t)(pl % kSlots) * a.n_wg + a.ent_w0) * kRowsPad, a.ent_n * kRowsPad, lane);
     }
     const char *kbase = wk.kptr;
     int slot_next = wk.slot0 + 2;         // sub-tile 0 of phase s + 1
@@ -850,7 +929,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         if (do_prob) {
             const uint32_t cinit_ad = lds0 + kOffCinit + (1 - PAR) * (kMaxRowsF * 4) + ((uint32_t)(lane & 32) << 1);
             prob_pass<NB, GB, 1 - PAR, W, F8>(ring.kf[SLOT], lc, cinit_ad, acc, ki, voff, ks_prob);
-            if (wk.c.kv == a.n_kv_heads - 1 && (a.layer_agg == SP_LAYER_MEAN || wk.c.layer == a.n_layers - 1))
+            if (wk.c.kv == a.n_kv_heads - 1 && (a.layer_agg == SP_LAYER_MEAN || wk.c.layer == (RANGES ? a.last_layer : a.n_layers - 1)))
                 close_layer<NB, W ? 1 : kNS>(acc, a.c);
         } else {
             k_issue<kSI - kMid>(ki, voff, kMid);
@@ -864,9 +943,9 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         ki.lds_dst = lds0 + sub_slot_off(wave, slot_next, 1);
         ki.base = kbase + (W ? (int64_t)(kD * kElem) : (int64_t)32 * stride_bytes);     // W: the rows' second halves
         ki.step_bytes = (F8 ? 16u : 8u) * stride_bytes;
-        const uint64_t *lse_row = wave == kLseWave ? a.lse + ((size_t)(clampi(pl, 0, n_phases - 1) % kSlots) * a.n_gp + a.p_idx) * a.rows_pad : nullptr;
+        const uint64_t *lse_row = wave == kLseWave && !direct ? a.lse + ((size_t)(clampi(pl, 0, n_phases - 1) % kSlots) * a.n_gp + a.p_idx) * a.rows_pad : nullptr;
         const float *look_row = nullptr;
-        if (EXTRA && a.look != nullptr) look_row = a.look + (size_t)clampi(pl, 0, n_phases - 1) * a.rows_pad;
+        if (EXTRA && a.look != nullptr && wave == kLseWave) look_row = a.look + (size_t)((RANGES ? a.phase0 : 0) + clampi(pl, 0, n_phases - 1)) * a.rows_pad;
         // r_range = r_lo | r_hi << 16 (r_hi = 512 without EXTRA): this wave's share of it
         constexpr int kWaveKeys = W ? 32 : kNS * 32;
         const int lo0 = (r_range & 0xffff) - wave * kWaveKeys;
@@ -877,13 +956,13 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
                                      sub_slot_off(wave, wk.slot0, 1), wstats_ad, lo0, hi0, lane, ki, voff, lse_row,
                                      look_row, a.rows_pad, lds0 + kOffXlse);
         } else {
-            if (lse_row != nullptr) stage_exchange_rows(lds0 + kOffXlse, lse_row, look_row, a.rows_pad, lane);
+            stage_exchange_rows(lds0 + kOffXlse, lse_row, look_row, a.rows_pad, lane);
             k_issue<kSI>(ki, voff, 0);
         }
     }
 
     // ---- pre-barrier: exchange data in, seeds out ----
-    if (wave == kLseWave) vm_wait<kLoadsBehindLse<NB * GB, F8>>(); else vm_wait<2 * kSI>();
+    if (wave == kLseWave && !(RANGES && direct && a.look == nullptr)) vm_wait<kLoadsBehindLse<NB * GB, F8>>(); else vm_wait<2 * kSI>();
     int *fail = reinterpret_cast<int *>(lds + kOffFail);
     if (wave == kDutyWave) {
         if (duty_blk >= 0) {
@@ -926,7 +1005,8 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
                     m = wave_max(m);
                     float l = 0.f;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) l += pl4[q] * fast_exp2((pm[q] - m) * c_duty);
+                    for (int q = 0; q < 4; ++q)
+                        if (!EXTRA || 64 * q < src_n) l += pl4[q] * fast_exp2((pm[q] - m) * c_duty);      // uniform
                     l = wave_sum(l);
                     const float v = -(m + fast_log2(l) * (F8 ? 1.0f / c_duty : a.inv_c));
                     if (lane == r) mine = v;
@@ -940,10 +1020,16 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
             }
         }
     } else if (wave == kLseWave) {
+        float direct_v = 0.f;
+        if (RANGES && direct && pl >= 0 && pl < n_phases)
+            direct_v = direct_combine<NB, GB>(a, a.part + ((size_t)(pl % kSlots) * a.n_wg + a.ent_w0) * kRowsPad, a.ent_n,
+                                              (uint32_t)(pl / kSlots) & 1u, lds0, fail, lane, a.c, a.inv_c);
         if (pl >= 0 && pl < n_phases && lane < a.rows_pad) {
             int g, n;
             float v = neg_inf();
             if (row_valid<NB>(a, lane, g, n)) {
+              if (RANGES && direct) v = direct_v;
+              else {
                 const uint64_t *src = a.lse + ((size_t)(pl % kSlots) * a.n_gp + a.p_idx) * a.rows_pad + lane;
                 uint64_t entry = read_lse_staging(lds0, lane);
                 if ((uint32_t)(entry >> 32) != (uint32_t)(pl + 1) && *fail == 0) {
@@ -954,6 +1040,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
                     }
                 }
                 v = __uint_as_float((uint32_t)entry);
+              }
                 if (EXTRA && a.look != nullptr) {
                     // the row's softmax also runs over its visible lookahead keys: log-sum-exp of the
                     // prompt's normaliser and theirs (-inf when the row sees none), in raw-logit units
@@ -980,8 +1067,8 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     phase_advance(wk.c, s - 3, n_phases, a.n_kv_heads);
     wk.slot0 = slot_next;
     if (s - 1 > 0 && s - 1 < n_phases) {
-        wk.dfirst += (a.rows_pad / kDutyRows) * a.n_gp;
-        if (wk.dfirst >= a.n_wg) wk.dfirst -= a.n_wg;
+        wk.dfirst += duty_blocks;
+        if (wk.dfirst >= duty_n) wk.dfirst -= duty_n;
     }
     lds_barrier();
 }
@@ -1030,11 +1117,12 @@ __device__ __forceinline__ void fold_model_constants(FusedArgs &a)
 // k-step 4s + t), Q tiles hold 32 rows as two half-tiles, and a logit is one chain of eight MFMA steps.
 // F8: 8-bit keys (head_dim 64): rows of 64 codes, sub-tiles of 2 KB fetched by two instructions of 16 rows,
 // widened to bf16 at the lift; every phase has its own key scale.
-template <int NB, int GB, bool EXTRA, class M, bool W = false, bool F8 = false>
+template <int NB, int GB, Kind KIND, class M, bool W = false, bool F8 = false>
 __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, LayerPtrs kp, GroupTable gt)
 {
     static_assert(!W || (NB == 1 && GB == 1 && !M::kFixed), "head_dim 128: one block of 32 query rows");
-    static_assert(!F8 || !EXTRA, "8-bit keys: plain variants only");
+    static_assert(!F8 || KIND == kPlain, "8-bit keys: plain variants only");
+    constexpr bool EXTRA = KIND != kPlain, RANGES = KIND == kRanges;
     constexpr int kSI = F8 ? kSubInstr / 2 : kSubInstr;
     constexpr uint32_t kElem = F8 ? 1u : 2u;
     constexpr int kTile = W ? kFTile / 2 : kFTile;            // keys per workgroup
@@ -1045,18 +1133,19 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, hf = lane >> 5, col = lane & 31;
     const int w = blockIdx.x;
-    const int n_phases = a.n_layers * a.n_kv_heads;
+    int n_phases = a.n_layers * a.n_kv_heads;
     // Contiguous keys: the last workgroup's tile is shifted back so that it ends with the prompt (the
     // caller guarantees L >= 512): every workgroup loads 512 real keys; rows below r_lo belong to the
     // previous workgroup. Paged keys: pages are allocated whole and hold a multiple of 512 keys, so the
     // last tile stays where it is and rows from r_hi on (allocated, never written) are ignored.
-    // Several prompts in one launch (their keys packed back to back, every prompt at least one tile long):
-    // prompt p owns workgroups gt.w0[p] .. gt.w0[p+1]-1 and is a prompt of its own in everything
-    // below: tile positions count from its first key, its queries are its own, partials are combined
-    // among its workgroups only and its normalisers have their own row.
+    // Several entries in one launch (a prompt's layer range each; prompts are packed back to back, every
+    // one at least one tile long): entry p owns workgroups gt.w0[p] .. gt.w0[p+1]-1 and is a call of its
+    // own in everything below: tile positions count from its prompt's first key, its queries and layers
+    // are its own, partials are combined among its workgroups only and its normalisers have their own row.
     const bool paged = EXTRA && a.block_table != nullptr;
     int64_t p_start = 0, p_len = a.L;
-    int wl = w;                               // this workgroup's index within its prompt
+    int wl = w;                               // this workgroup's index within its entry
+    int layer0 = 0, slice = 0;
     if (EXTRA && gt.n > 0) {
         int p = 0;
         while (p + 1 < gt.n && w >= gt.w0[p + 1]) ++p;
@@ -1066,11 +1155,25 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
         a.q += (size_t)gt.prompt[p] * ((size_t)a.n_layers * a.n_q_heads * a.n_q * kHeadDim);
         a.p_idx = p;
         a.n_gp = gt.n;
+        if (RANGES) {
+            layer0 = gt.layer0[p];
+            n_phases = gt.layers[p] * a.n_kv_heads;
+            slice = gt.slice[p];
+            a.q += (size_t)layer0 * ((size_t)a.n_q_heads * a.n_q * kHeadDim);
+            a.ent_w0 = gt.w0[p];
+            a.ent_n = gt.w0[p + 1] - a.ent_w0;
+            a.phase0 = layer0 * a.n_kv_heads;
+            // a range of the maximum over layers stays open: its rows' maxima are the result
+            a.last_layer = a.split_out != nullptr ? -1 : layer0 + gt.layers[p] - 1;
+        }
     } else {
         a.p_idx = 0;
         a.n_gp = 1;
     }
-    const int64_t j0l = (paged || (int64_t)(wl + 1) * kTile <= p_len) ? (int64_t)wl * kTile : p_len - kTile;
+    int64_t j0l = (paged || (int64_t)(wl + 1) * kTile <= p_len) ? (int64_t)wl * kTile : p_len - kTile;
+    // A prompt of a batch that is shorter than a tile: the tile starts with it and the keys of the prompts behind
+    // it are ignored; at the end of the packed keys (L of them, at least one tile) it ends with them instead.
+    if (RANGES && p_len < kTile && !paged) j0l = p_start + kTile <= a.L ? 0 : a.L - kTile - p_start;
     const int64_t j0 = p_start + j0l;         // first key of the tile in the layer's key array
     const int r_lo = (int)((int64_t)wl * kTile - j0l);
     const int r_hi = (int)(p_len - j0l < kTile ? p_len - j0l : kTile);
@@ -1140,7 +1243,7 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     for (int s2 = 0; s2 < kNS; ++s2) {
         KIssue ki;
         ki.lds_dst = lds0 + sub_slot_off(wave_u, 0, s2);
-        ki.base = reinterpret_cast<const char *>(kp.p[0]) + wave_off + (W ? (uint64_t)(s2 * kD * kElem) : (uint64_t)(s2 * 32) * stride_bytes);
+        ki.base = reinterpret_cast<const char *>(kp.p[layer0]) + wave_off + (W ? (uint64_t)(s2 * kD * kElem) : (uint64_t)(s2 * 32) * stride_bytes);
         ki.step_bytes = (F8 ? 16u : 8u) * stride_bytes;
         k_issue<kSI>(ki, lc.koff, 0);
     }
@@ -1149,8 +1252,10 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
 
     Walk wk;
     wk.k = phase_at(1, n_phases, a.n_kv_heads);
+    wk.k.layer += layer0;
     wk.kptr = reinterpret_cast<const char *>(kp.p[wk.k.layer]) + (uint64_t)wk.k.kv * (uint64_t)a.k_stride_head * kElem + wave_off;
     wk.c = phase_at(0, n_phases, a.n_kv_heads);
+    wk.c.layer += layer0;
     wk.slot0 = 0;
     wk.dfirst = 0;
     if (!EXTRA) { a.p_idx = 0; a.n_gp = 1; }
@@ -1160,13 +1265,34 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     // instruction stream uniform. The last probability pass (phase n_phases - 1) runs in step n_phases + 3.
     const int n_steps = (n_phases + kLag + 1 + 3) / 4 * 4;
     for (int s0 = 0; s0 < n_steps; s0 += 4) {
-        step<NB, GB, 0, 0, EXTRA, W, F8>(a, kp, gt, s0 + 0, n_phases, ring, acc, lc, wk, lds, lds0, wave_off, r_range);
-        step<NB, GB, 1, 1, EXTRA, W, F8>(a, kp, gt, s0 + 1, n_phases, ring, acc, lc, wk, lds, lds0, wave_off, r_range);
-        step<NB, GB, 2, 0, EXTRA, W, F8>(a, kp, gt, s0 + 2, n_phases, ring, acc, lc, wk, lds, lds0, wave_off, r_range);
-        step<NB, GB, 3, 1, EXTRA, W, F8>(a, kp, gt, s0 + 3, n_phases, ring, acc, lc, wk, lds, lds0, wave_off, r_range);
+        step<NB, GB, 0, 0, KIND, W, F8>(a, kp, gt, s0 + 0, n_phases, ring, acc, lc, wk, lds, lds0, wave_off, r_range);
+        step<NB, GB, 1, 1, KIND, W, F8>(a, kp, gt, s0 + 1, n_phases, ring, acc, lc, wk, lds, lds0, wave_off, r_range);
+        step<NB, GB, 2, 0, KIND, W, F8>(a, kp, gt, s0 + 2, n_phases, ring, acc, lc, wk, lds, lds0, wave_off, r_range);
+        step<NB, GB, 3, 1, KIND, W, F8>(a, kp, gt, s0 + 3, n_phases, ring, acc, lc, wk, lds, lds0, wave_off, r_range);
     }
     vm_wait<0>();               // no direct-to-LDS load may outlive the workgroup
     lds_barrier();
+    if (RANGES && a.split_out != nullptr) {
+        // one layer range of several: MEAN leaves the range's sum per key, MAX the probability of every
+        // lookahead row's maximum (exp is monotone: the maximum over ranges can be taken after it). The
+        // reduce launch looks at the status word.
+#pragma unroll
+        for (int s = 0; s < kWaveKeys / 32; ++s) {
+            const int key = wave * kWaveKeys + s * 32 + col;
+            const bool mine = key >= r_lo && key < r_hi;
+            if (a.layer_agg == SP_LAYER_MEAN) {
+                const float both = acc.total[s] + __shfl_xor(acc.total[s], 32);
+                if (hf == 0 && mine) a.split_out[slice * a.split_stride + j0 + key] = both;
+            } else {
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (mine) a.split_out[((int64_t)slice * (8 * NB) + 8 * b + 4 * hf + e) * a.split_stride + j0 + key] = fast_exp2(acc.mx[s][b][e] * a.c);
+            }
+        }
+        return;
+    }
     // the call has failed if any workgroup raised the status word; this workgroup's own failures are in it
     const bool failed = __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
 #pragma unroll
@@ -1208,12 +1334,12 @@ size_t workspace_bytes(int rows_pad, int n_wg, int n_prompts)
 bool fits_one_per_cu()
 {
     int n1 = 0, n2 = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n1, sp_fused_kernel<1, 1, true, AnyModel>, kFThreads, 0) != hipSuccess) return false;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n2, sp_fused_kernel<2, 1, true, AnyModel>, kFThreads, 0) != hipSuccess) return false;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n1, sp_fused_kernel<1, 1, kRanges, AnyModel>, kFThreads, 0) != hipSuccess) return false;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n2, sp_fused_kernel<2, 1, kRanges, AnyModel>, kFThreads, 0) != hipSuccess) return false;
     return n1 >= 1 && n2 >= 1;
 }
 
-sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool clear_status, void *ws,
+sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool shared, bool clear_status, void *ws,
                  uint32_t *status_word, hipStream_t st)
 {
     GroupTable gt;
@@ -1228,12 +1354,21 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
         if (a.L < tile || sp::ceil_div(a.L, tile) != a.n_wg)
             return sp::fail(SP_ERR_INVALID_ARG, "fused score kernel: %d workgroups for %lld keys", a.n_wg, (long long)a.L);
     } else {
-        if (gt.n < 0 || gt.n > sp_fused::kMaxGroupPrompts || gt.w0[0] != 0 || gt.w0[gt.n] != a.n_wg)
+        if (gt.n < 0 || gt.n > sp_fused::kMaxGroup || gt.w0[0] != 0 || gt.w0[gt.n] != a.n_wg)
             return sp::fail(SP_ERR_INVALID_ARG, "fused score kernel: group table does not cover %d workgroups", a.n_wg);
-        for (int i = 0; i < gt.n; ++i)
-            if (gt.len[i] < tile || sp::ceil_div(gt.len[i], tile) != gt.w0[i + 1] - gt.w0[i])
-                return sp::fail(SP_ERR_INVALID_ARG, "fused score kernel: prompt %d of the group: %d workgroups for %lld keys", i,
+        for (int i = 0; i < gt.n; ++i) {
+            if (gt.len[i] < 1 || (gt.len[i] < tile && (a.L < tile || a.block_table)) || gt.start[i] < 0 ||
+                gt.start[i] + gt.len[i] > a.L || sp::ceil_div(gt.len[i], tile) != gt.w0[i + 1] - gt.w0[i])
+                return sp::fail(SP_ERR_INVALID_ARG, "fused score kernel: entry %d of the group: %d workgroups for %lld keys", i,
                                 gt.w0[i + 1] - gt.w0[i], (long long)gt.len[i]);
+            if (shared && (gt.len[i] < tile || gt.layers[i] != a.n_layers))
+                return sp::fail(SP_ERR_INVALID_ARG, "fused score kernel: entry %d of the group cannot share duties", i);
+            if (gt.layer0[i] < 0 || gt.layers[i] < 1 || gt.layer0[i] + gt.layers[i] > a.n_layers)
+                return sp::fail(SP_ERR_INVALID_ARG, "fused score kernel: entry %d of the group: layers %d + %d of %d", i, gt.layer0[i],
+                                gt.layers[i], a.n_layers);
+        }
+        if (shared && gt.n * (a.rows_pad / kDutyRows) > a.n_wg)
+            return sp::fail(SP_ERR_INVALID_ARG, "fused score kernel: %d entries of %d rows share %d workgroups", gt.n, a.rows_pad, a.n_wg);
     }
     uint64_t *base = static_cast<uint64_t *>(ws);
     const size_t n_part = (size_t)kSlots * a.rows_pad * a.n_wg, n_lse = (size_t)kSlots * a.rows_pad * (gt.n > 0 ? gt.n : 1);
@@ -1250,64 +1385,44 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
     // compute unit (LDS), so the grid may not exceed the number of compute units. All waits in the
     // kernel are bounded; should residency fail (the device shared with other work), the call ends
     // with NaN scores and the status word set instead of hanging.
+    const bool ranges = gt.n > 0 && !shared;
     const bool extra = a.look != nullptr || a.block_table != nullptr || gt.n > 0;
     const dim3 grid(a.n_wg), block(kFThreads);
-    if (a.kscale != nullptr) {              // 8-bit keys
-        if (extra) return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, 8-bit keys: one prompt, contiguous keys only");
-        if (a.head_dim == 2 * kD) {
-            if (a.n_nblk != 1 || a.n_gblk != 1)
-                return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, head_dim 128: %d x %d row blocks", a.n_nblk, a.n_gblk);
-            hipLaunchKernelGGL((sp_fused_kernel<1, 1, false, AnyModel, true, true>), grid, block, 0, st, a, kp, gt);
-            SP_HIP_CHECK(hipGetLastError());
-            return SP_OK;
-        }
-        const bool draft8 = a.n_layers == 16 && a.n_q_heads == 32 && a.n_kv_heads == 8 && a.k_stride_token == kD &&
-                            a.c == kScaleEighthLog2e && a.inv_c == 1.0f / kScaleEighthLog2e;
-        if (draft8 && a.n_q == 16 && a.n_wg == 256) hipLaunchKernelGGL((sp_fused_kernel<2, 1, false, Draft16x32x8<16, 256>, false, true>), grid, block, 0, st, a, kp, gt);
-        else if (draft8 && a.n_q == 16) hipLaunchKernelGGL((sp_fused_kernel<2, 1, false, Draft16x32x8<16, 0>, false, true>), grid, block, 0, st, a, kp, gt);
-        else if (draft8 && a.n_q == 8) hipLaunchKernelGGL((sp_fused_kernel<1, 1, false, Draft16x32x8<8, 0>, false, true>), grid, block, 0, st, a, kp, gt);
-        else if (a.n_nblk == 2 && a.n_gblk == 1) hipLaunchKernelGGL((sp_fused_kernel<2, 1, false, AnyModel, false, true>), grid, block, 0, st, a, kp, gt);
-        else if (a.n_nblk == 1 && a.n_gblk == 2) hipLaunchKernelGGL((sp_fused_kernel<1, 2, false, AnyModel, false, true>), grid, block, 0, st, a, kp, gt);
-        else if (a.n_nblk == 1 && a.n_gblk == 1) hipLaunchKernelGGL((sp_fused_kernel<1, 1, false, AnyModel, false, true>), grid, block, 0, st, a, kp, gt);
-        else return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel: %d x %d row blocks", a.n_nblk, a.n_gblk);
-        SP_HIP_CHECK(hipGetLastError());
-        return SP_OK;
-    }
-    if (a.head_dim == 2 * kD) {
-        if (a.n_nblk != 1 || a.n_gblk != 1)
-            return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, head_dim 128: %d x %d row blocks", a.n_nblk, a.n_gblk);
-        if (extra) hipLaunchKernelGGL((sp_fused_kernel<1, 1, true, AnyModel, true>), grid, block, 0, st, a, kp, gt);
-        else hipLaunchKernelGGL((sp_fused_kernel<1, 1, false, AnyModel, true>), grid, block, 0, st, a, kp, gt);
-        SP_HIP_CHECK(hipGetLastError());
-        return SP_OK;
-    }
+#define SP_FUSED(...) hipLaunchKernelGGL((sp_fused_kernel<__VA_ARGS__>), grid, block, 0, st, a, kp, gt)
+    // one variant for whole prompts with extras, one for tables of entries, one for plain prompts
+#define SP_FUSED_KINDS(NB, GB, ...)                             \
+    do {                                                        \
+        if (ranges) SP_FUSED(NB, GB, kRanges, __VA_ARGS__);     \
+        else if (extra) SP_FUSED(NB, GB, kExtra, __VA_ARGS__);  \
+        else SP_FUSED(NB, GB, kPlain, __VA_ARGS__);             \
+    } while (0)
+    using Draft16 = Draft16x32x8<16, 0>;
+    using Draft8 = Draft16x32x8<8, 0>;
+    const int blocks = a.n_nblk * 10 + a.n_gblk;
+    if (a.head_dim == 2 * kD ? blocks != 11 : blocks != 11 && blocks != 12 && blocks != 21)
+        return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, head_dim %d: %d x %d row blocks", a.head_dim, a.n_nblk, a.n_gblk);
+    if (a.kscale != nullptr && extra) return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, 8-bit keys: one prompt, contiguous keys only");
     // the fixed-model instantiations apply when every folded constant equals the call's value
-    const bool draft_shape = a.kscale == nullptr && a.head_dim == kD && a.n_layers == 16 && a.n_q_heads == 32 && a.n_kv_heads == 8 && a.k_stride_token == kD &&
-                             a.c == kScaleEighthLog2e && a.inv_c == 1.0f / kScaleEighthLog2e;
-    const bool draft = !extra && draft_shape;
-    const bool draft_batch = draft_shape && gt.n > 0 && a.look == nullptr && a.block_table == nullptr;    // several prompts a launch
-    if (draft_batch && a.n_q == 16) {
-        hipLaunchKernelGGL((sp_fused_kernel<2, 1, true, Draft16x32x8<16, 0>>), grid, block, 0, st, a, kp, gt);
-    } else if (draft_batch && a.n_q == 8) {
-        hipLaunchKernelGGL((sp_fused_kernel<1, 1, true, Draft16x32x8<8, 0>>), grid, block, 0, st, a, kp, gt);
-    } else if (draft && a.n_q == 16) {
-        if (a.n_wg == 256) hipLaunchKernelGGL((sp_fused_kernel<2, 1, false, Draft16x32x8<16, 256>>), grid, block, 0, st, a, kp, gt);
-        else hipLaunchKernelGGL((sp_fused_kernel<2, 1, false, Draft16x32x8<16, 0>>), grid, block, 0, st, a, kp, gt);
-    } else if (draft && a.n_q == 8) {
-        if (a.n_wg == 256) hipLaunchKernelGGL((sp_fused_kernel<1, 1, false, Draft16x32x8<8, 256>>), grid, block, 0, st, a, kp, gt);
-        else hipLaunchKernelGGL((sp_fused_kernel<1, 1, false, Draft16x32x8<8, 0>>), grid, block, 0, st, a, kp, gt);
-    } else if (a.n_nblk == 2 && a.n_gblk == 1) {
-        if (extra) hipLaunchKernelGGL((sp_fused_kernel<2, 1, true, AnyModel>), grid, block, 0, st, a, kp, gt);
-        else hipLaunchKernelGGL((sp_fused_kernel<2, 1, false, AnyModel>), grid, block, 0, st, a, kp, gt);
-    } else if (a.n_nblk == 1 && a.n_gblk == 2) {
-        if (extra) hipLaunchKernelGGL((sp_fused_kernel<1, 2, true, AnyModel>), grid, block, 0, st, a, kp, gt);
-        else hipLaunchKernelGGL((sp_fused_kernel<1, 2, false, AnyModel>), grid, block, 0, st, a, kp, gt);
-    } else if (a.n_nblk == 1 && a.n_gblk == 1) {
-        if (extra) hipLaunchKernelGGL((sp_fused_kernel<1, 1, true, AnyModel>), grid, block, 0, st, a, kp, gt);
-        else hipLaunchKernelGGL((sp_fused_kernel<1, 1, false, AnyModel>), grid, block, 0, st, a, kp, gt);
-    } else {
-        return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel: %d x %d row blocks", a.n_nblk, a.n_gblk);
-    }
+    const bool draft = a.head_dim == kD && a.n_layers == 16 && a.n_q_heads == 32 && a.n_kv_heads == 8 && a.k_stride_token == kD &&
+                       a.c == kScaleEighthLog2e && a.inv_c == 1.0f / kScaleEighthLog2e;
+    if (a.kscale != nullptr) {              // 8-bit keys
+        if (a.head_dim == 2 * kD) SP_FUSED(1, 1, kPlain, AnyModel, true, true);
+        else if (draft && a.n_q == 16 && a.n_wg == 256) SP_FUSED(2, 1, kPlain, Draft16x32x8<16, 256>, false, true);
+        else if (draft && a.n_q == 16) SP_FUSED(2, 1, kPlain, Draft16, false, true);
+        else if (draft && a.n_q == 8) SP_FUSED(1, 1, kPlain, Draft8, false, true);
+        else if (blocks == 21) SP_FUSED(2, 1, kPlain, AnyModel, false, true);
+        else if (blocks == 12) SP_FUSED(1, 2, kPlain, AnyModel, false, true);
+        else SP_FUSED(1, 1, kPlain, AnyModel, false, true);
+    } else if (a.head_dim == 2 * kD) SP_FUSED_KINDS(1, 1, AnyModel, true);
+    else if (draft && !extra && a.n_q == 16 && a.n_wg == 256) SP_FUSED(2, 1, kPlain, Draft16x32x8<16, 256>);
+    else if (draft && !extra && a.n_q == 8 && a.n_wg == 256) SP_FUSED(1, 1, kPlain, Draft16x32x8<8, 256>);
+    else if (draft && a.n_q == 16) SP_FUSED_KINDS(2, 1, Draft16);
+    else if (draft && a.n_q == 8) SP_FUSED_KINDS(1, 1, Draft8);
+    else if (blocks == 21) SP_FUSED_KINDS(2, 1, AnyModel);
+    else if (blocks == 12) SP_FUSED_KINDS(1, 2, AnyModel);
+    else SP_FUSED_KINDS(1, 1, AnyModel);
+#undef SP_FUSED_KINDS
+#undef SP_FUSED
     SP_HIP_CHECK(hipGetLastError());
     return SP_OK;
 }

@@ -10,19 +10,29 @@ constexpr int kTileKeys = 512;   // keys owned by one workgroup at head_dim 64; 
 constexpr int kMaxRowsWide = 32; // head_dim 128: padded query rows per kv head
 constexpr int kMaxRows = 64;     // padded query rows per kv head the kernel holds on chip
 constexpr int kSlots = 8;        // depth of the exchange ring
-constexpr int kMinWorkgroups = 64;       // head_dim 64: shorter prompts are faster on the two-pass path
+constexpr int kDutyRows = 4;     // consecutive query rows one workgroup's duty covers
+constexpr int kMinWorkgroups = 64;       // head_dim 64: with all layers in one range, shorter prompts are faster on the two-pass path
 constexpr int kMinWorkgroupsWide = 96;   // head_dim 128 (measured crossover near 24K tokens)
-constexpr int kMaxGroupPrompts = 32;   // prompts one launch can serve
+constexpr int kMaxGroup = 64;          // entries of a launch's table
 
-// Prompts of a ragged batch that share a launch: prompt i of the group is prompt `prompt[i]` of the
-// batch (its queries), owns keys [start[i], start[i] + len[i]) of the packed key arrays (len >= one
-// tile) and workgroups w0[i] .. w0[i+1]-1. n == 0: a single prompt described by FusedArgs::L.
+// The (prompt, layer range) pairs that share a launch. Entry i scores layers layer0[i] .. layer0[i] +
+// layers[i] - 1 of prompt `prompt[i]` of the batch (its queries), whose keys are [start[i], start[i] +
+// len[i]) of the packed key arrays (len >= one tile), on workgroups w0[i] .. w0[i+1]-1. An entry is on
+// its own in everything: its partials are combined among its workgroups and it has its own row of
+// normalisers. n == 0: all layers of a single prompt described by FusedArgs::L.
+// An entry has at least as many workgroups as duty blocks (rows_pad / kDutyRows) or few enough for
+// every one to combine all partials by itself (direct_max), so any number does.
+// 32-bit fields only: a smaller one would be read with a vector load, which the kernel's exact
+// counting of vector-memory operations does not know about.
 struct GroupTable {
     int32_t n;
-    int32_t w0[kMaxGroupPrompts + 1];
-    int32_t prompt[kMaxGroupPrompts];
-    int64_t start[kMaxGroupPrompts];
-    int64_t len[kMaxGroupPrompts];
+    int32_t w0[kMaxGroup + 1];
+    int32_t prompt[kMaxGroup];
+    int32_t layer0[kMaxGroup];
+    int32_t layers[kMaxGroup];
+    int32_t slice[kMaxGroup];       // which row (MEAN) or rows (MAX) of split_out the entry fills
+    int32_t len[kMaxGroup];
+    int64_t start[kMaxGroup];
 };
 
 struct FusedArgs {
@@ -43,8 +53,12 @@ struct FusedArgs {
     int64_t page_tokens;         // layer's pool, page p at element offset p * page_stride; null: contiguous keys
     int64_t page_stride;
     float *scores;
+    float *split_out;            // layers in ranges: results per range instead of scores (see sp_split_reduce_kernel), or null
+    int64_t split_stride;        // tokens of the whole call: one row of split_out
     int32_t n_wg;
-    int32_t n_gp, p_idx;         // set in the kernel: prompts in the launch, this workgroup's prompt among them
+    int32_t n_gp, p_idx;         // set in the kernel: entries of the launch, this workgroup's entry among them,
+    int32_t ent_w0, ent_n;       // its first workgroup and number of workgroups,
+    int32_t phase0, last_layer;  // first phase, layer after which an open maximum is closed
     int32_t n_layers, n_q_heads, n_kv_heads, group, n_q;
     int32_t n_nblk, n_gblk, rows_pad;
     int32_t layer_agg;
@@ -53,14 +67,22 @@ struct FusedArgs {
 
 size_t workspace_bytes(int rows_pad, int n_wg, int n_prompts);
 
+// Entries of fewer workgroups than duty blocks exchange directly: every workgroup combines all partials of
+// its entry by itself. Only those: at 16 or 32 workgroups an entry the extra loads (8 KB a workgroup and phase
+// past the caches) cost more than the saved round trip (8192 tokens, 16 layers x 8 kv heads, head_dim 64:
+// 47 us against 43; 28 x 8, head_dim 128: 130 us against 102).
+constexpr int direct_max(int rows_pad) { return rows_pad / kDutyRows - 1; }
+
 // True when the device can hold one workgroup of the fused kernel per compute unit.
 bool fits_one_per_cu();
 
 // Enqueues the clear kernel and the fused kernel. `ws` must hold workspace_bytes(); `status_word`
 // (device) is cleared first and raised if the call gives up.
-// `group` (or null for one prompt) describes the prompts of the launch; the status word is cleared only
+// `group` (or null for one prompt) describes the entries of the launch; the status word is cleared only
 // when clear_status is set (the first launch of a call).
-sp_status launch(FusedArgs a, const sp_dev::LayerPtrs &kp, const GroupTable *group, bool clear_status, void *ws,
+// `shared`: the duties rotate over all workgroups of the launch (whole prompts of at least a tile only, at
+// least as many workgroups as duty blocks); otherwise every entry keeps to itself.
+sp_status launch(FusedArgs a, const sp_dev::LayerPtrs &kp, const GroupTable *group, bool shared, bool clear_status, void *ws,
                  uint32_t *status_word, hipStream_t st);
 
 // Test hook: polls before a bounded wait gives up (default 2^20) and whether duty waves treat their

@@ -262,6 +262,47 @@ def test_fused_score_matches_oracle(shape):
     assert got_nhd.tobytes() == got.tobytes()        # same keys through token-major strides
 
 
+# Prompts that fill only part of the device: the layers run in ranges side by side and a last launch adds them up.
+RANGE_SHAPES = [
+    # name, Lyr, H, Hkv, d, n_q, lengths  (one: sp_score; several: sp_score_batch)
+    ("ranges_16_of_1_layer", 16, 32, 8, 64, 8, [6200]),              # 13 workgroups, 56-key tail
+    ("ranges_8_of_2_layers_rows64", 16, 32, 8, 64, 16, [8200]),      # 17 workgroups, 8-key tail
+    ("ranges_two_gblocks", 12, 32, 4, 64, 8, [14000]),               # 28 workgroups: 6 ranges of 2 layers
+    ("ranges_uneven_d128", 7, 8, 4, 128, 8, [13001]),                # 51 workgroups: layers 2 + 2 + 2 + 1
+    ("ranges_d128_padding", 14, 8, 4, 128, 5, [4097]),               # 17 workgroups, 1-key tail
+    ("ranges_batch", 12, 16, 4, 64, 8, [7600, 0, 2600, 3500]),       # 28 workgroups of three prompts: 9 -> 6 ranges
+    ("ranges_batch_d128", 9, 8, 4, 128, 8, [9000, 300, 5000]),       # 58 workgroups: layers 3 + 3 + 3
+    # prompts shorter than a tile: their tile starts with them, or ends with the packed keys (last prompt)
+    ("ranges_short_prompts", 16, 32, 8, 64, 8, [4700, 60, 3000, 1, 511]),
+    ("ranges_short_prompts_rows64", 14, 16, 4, 64, 16, [11000, 77, 600, 300]),
+    ("ranges_short_prompts_d128", 14, 8, 4, 128, 8, [255, 3000, 2049, 64, 1500, 1]),
+]
+
+
+@pytest.mark.parametrize("shape", RANGE_SHAPES, ids=[s[0] for s in RANGE_SHAPES])
+def test_score_in_layer_ranges_matches_oracle(shape):
+    from gpu_util import assert_scores_close, gpu_score, gpu_score_batch
+    name, Lyr, H, Hkv, d, n_q, lens = shape
+    lengths = np.array(lens, dtype=np.int64)
+    say(f"[score-ranges] {name} Lyr={Lyr} H={H} Hkv={Hkv} d={d} n_q={n_q} lengths={lens}")
+    w = dataclasses.replace(small_workload(name, Lyr, H, Hkv, d, n_q, 0, cfg_id=500 + RANGE_SHAPES.index(shape), hh=(1, 1000)),
+                            batch=len(lengths))
+    q = synth.gen_q(w, len(lengths))
+    ks = [synth.gen_k_layer(w, l, q, lengths, synth.heavy_hitter_positions(w, lengths)) for l in range(Lyr)]
+    offsets = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    run = (lambda mode, k, lay: gpu_score(q[0], k, w.scale, mode, layout=lay)) if len(lens) == 1 else \
+          (lambda mode, k, lay: gpu_score_batch(q, k, offsets, w.scale, mode, layout=lay))
+    for mode in (0, 1):
+        got = run(mode, ks, "HND")
+        for b, Lb in enumerate(lengths):
+            if Lb:
+                sl = slice(int(offsets[b]), int(offsets[b + 1]))
+                assert_scores_close(got[sl], oracle.score(q[b], [np.ascontiguousarray(k[:, sl, :]) for k in ks], w.scale, mode))
+        assert run(mode, ks, "HND").tobytes() == got.tobytes()
+        nhd = [np.ascontiguousarray(k.transpose(1, 0, 2)) for k in ks]
+        assert run(mode, nhd, "NHD").tobytes() == got.tobytes()
+
+
 def test_fused_score_gives_up_as_a_whole():
     """The bounded waits of the single-launch kernel, driven to give up from the host (the test hook
     makes the combining waves treat their partial results as never arriving, with a spin limit of a few
