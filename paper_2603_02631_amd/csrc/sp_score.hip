@@ -43,6 +43,7 @@ constexpr int kWaves = 4;
 constexpr int kMaxPrompts = 4096;
 constexpr int kMaxGroupPrompts = 32;       // prompts one launch of the fused kernel serves
 constexpr size_t kLdsBudget = 64 * 1024;
+constexpr int kMaxLookRows = 224;           // padded query rows of the widest supported group
 constexpr int kProbTargetWgs = 1024;   // the prob pass splits layers until it has about this many workgroups
 
 struct TileInfo {
@@ -324,31 +325,51 @@ __global__ __launch_bounds__(kMergeThreads) void sp_merge_kernel(ScoreArgs a)
 
 // ---------------------------------------------------------------------------
 // look: log-sum-exp (raw-logit units) of every query row over the lookahead
-// keys it sees, one workgroup per (layer, kv head), one thread per padded row.
-// Lookahead row n sees the keys of rows 0 .. n-1, and its own with look_self
-// (a decode step attends to the tokens generated before it; Algorithm 1's
-// ForwardWithAttn with lookahead = i). Rows that see none get -inf.
-// k_look is dense [Lyr][Hkv][n_q][d].
+// keys it sees, one workgroup per (layer, kv head). Lookahead row n sees the
+// keys of rows 0 .. n-1, and its own with look_self (a decode step attends to the
+// tokens generated before it; Algorithm 1's ForwardWithAttn with lookahead = i).
+// Rows that see none get -inf. k_look is dense [Lyr][Hkv][n_q][d].
+// Bound by the latency of its loads (a few KB a workgroup): one thread per
+// (row, key) pair, so that all of a workgroup's logits are one round of 16-byte
+// loads; one thread per row walking its keys element by element took 46 us
+// for 128 workgroups of 32 rows and 8 keys.
 // ---------------------------------------------------------------------------
+template <int D>
 __global__ __launch_bounds__(kThreads) void sp_look_kernel(ScoreArgs a, const uint16_t *__restrict__ k_look,
-                                                           int look_self, int D, float *__restrict__ out)
+                                                           int look_self, float *__restrict__ out)
 {
-    const int phase = blockIdx.x, row = threadIdx.x;
-    if (row >= a.rows_pad) return;
+    __shared__ float logit[kMaxLookRows][17];                    // [padded row][key], odd stride: no bank conflicts down a row
+    const int phase = blockIdx.x;
     const int layer = phase / a.n_kv_heads, kv = phase - layer * a.n_kv_heads;
+    const uint16_t *kb = k_look + ((int64_t)layer * a.n_kv_heads + kv) * a.n_q * D;
+    for (int i = threadIdx.x; i < a.rows_pad * 16; i += kThreads) {
+        const int row = i >> 4, j = i & 15;
+        int g, n;
+        if (!row_to_gn(a, row, g, n) || j >= min(n + (look_self ? 1 : 0), a.n_q)) continue;
+        const u32x4 *qr = reinterpret_cast<const u32x4 *>(
+            a.q + (((int64_t)layer * a.n_q_heads + (int64_t)kv * a.group + g) * a.n_q + n) * D);
+        const u32x4 *kr = reinterpret_cast<const u32x4 *>(kb + j * D);
+        float dot = 0.f;
+#pragma unroll
+        for (int c = 0; c < D / 8; ++c) {
+            const u32x4 x = qr[c], y = kr[c];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                dot = fmaf(__uint_as_float(x[e] << 16), __uint_as_float(y[e] << 16), dot);
+                dot = fmaf(__uint_as_float(x[e] & 0xffff0000u), __uint_as_float(y[e] & 0xffff0000u), dot);
+            }
+        }
+        logit[row][j] = dot;
+    }
+    __syncthreads();
+    const int row = threadIdx.x;
+    if (row >= a.rows_pad) return;
     int g, n;
     float v = neg_inf();
     if (row_to_gn(a, row, g, n)) {
-        const uint16_t *qr = a.q + (((int64_t)layer * a.n_q_heads + (int64_t)kv * a.group + g) * a.n_q + n) * D;
-        const uint16_t *kb = k_look + ((int64_t)layer * a.n_kv_heads + kv) * a.n_q * D;
         const int n_vis = min(n + (look_self ? 1 : 0), a.n_q);
         float m = neg_inf(), l = 0.f;
-        for (int j = 0; j < n_vis; ++j) {
-            float dot = 0.f;
-            for (int e = 0; e < D; ++e)
-                dot = fmaf(__uint_as_float((uint32_t)qr[e] << 16), __uint_as_float((uint32_t)kb[(int64_t)j * D + e] << 16), dot);
-            lse_merge(m, l, dot, 1.f, a.c);
-        }
+        for (int j = 0; j < n_vis; ++j) lse_merge(m, l, logit[row][j], 1.f, a.c);
         if (l > 0.f) v = m + fast_log2(l) * a.inv_c;
     }
     out[(int64_t)phase * a.rows_pad + row] = v;
@@ -927,8 +948,9 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     a.kscale = opt.kscale;
     if (opt.k_look) {
         float *look = reinterpret_cast<float *>(ws + w.look);
-        hipLaunchKernelGGL(sp_look_kernel, dim3(p.n_phases), dim3(kThreads), 0, st, a,
-                           static_cast<const uint16_t *>(opt.k_look), (int)opt.look_self, p.D, look);
+        const auto kernel = p.D == 64 ? sp_look_kernel<64> : sp_look_kernel<128>;
+        hipLaunchKernelGGL(kernel, dim3(p.n_phases), dim3(kThreads), 0, st, a, static_cast<const uint16_t *>(opt.k_look),
+                           (int)opt.look_self, look);
         SP_HIP_CHECK(hipGetLastError());
         a.look = look;
     }
