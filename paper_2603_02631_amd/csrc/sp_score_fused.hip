@@ -89,8 +89,8 @@ constexpr int kWideHalf = 4096;                                    // head_dim 1
 constexpr int kOffQ1 = 0;                                          // [2] Q of the statistics pass, by phase parity
 constexpr int kOffQ2 = kOffQ1 + 2 * kQTileBytes;                   // [2] Q of the probability pass
 constexpr int kWstatsBytes = kFWaves * kMaxRowsF * 8;              // (max, sum) of 64 rows from 8 waves
-constexpr int kOffWstats = kOffQ2 + 2 * kQTileBytes;               // [2]
-constexpr int kOffCinit = kOffWstats + 2 * kWstatsBytes;           // [2][64] accumulator seeds
+constexpr int kOffWstats = kOffQ2 + 2 * kQTileBytes;               // [2], pairs of tiles: [4]
+constexpr int kOffCinit = kOffWstats + 4 * kWstatsBytes;           // [2][64] accumulator seeds
 constexpr int kOffXduty = kOffCinit + 2 * kMaxRowsF * 4;           // 8 KB: partials of the duty rows (direct exchange: of all rows)
 constexpr int kOffXlse = kOffXduty + 8192;                         // 1 KB: normaliser entries of one phase
 constexpr int kOffXlook = kOffXlse + 1024;                         // 1 KB: lookahead-key terms of one phase's rows
@@ -573,17 +573,16 @@ __device__ __forceinline__ void store_row_stats(uint32_t ad, float m, float l, f
 
 // Lifts the K tile of the phase into kf, then runs the MFMA steps one ahead of the arithmetic on
 // their results, so that the matrix pipe works under the exponentials of the previous step. One
-// tile load is issued after each of the four steps (with one row block: two per step). On the
-// normaliser wave (lse_row != nullptr) the request for the normalisers follows the first step: late
-// enough for the duty workgroups' stores to be visible, early enough to land before the barrier.
+// tile load is issued after each of the four steps (with one row block: two per step). late() requests
+// exchange data after the first step: late enough for other workgroups' stores to be visible, early
+// enough to land before the barrier.
 template <int NBLK, bool F8>
 constexpr int kLoadsBehindLse = F8 ? 1 : kSubInstr - kSubInstr / (NBLK * kNS);
 
-template <int NBLK, int PAR, bool W, bool F8>
+template <int NBLK, int PAR, bool W, bool F8, class Late>
 __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], const LaneConst &lc, uint32_t koff0,
                                            uint32_t koff1, uint32_t wstats_ad, int lo0, int hi0, int lane,
-                                           const KIssue &ki, const uint32_t (&voff)[2], const uint64_t *lse_row,
-                                           const float *look_row, int rows_pad, uint32_t xlse_ad)
+                                           const KIssue &ki, const uint32_t (&voff)[2], const Late &late)
 {
     // tile-load instructions issued after each MFMA step (8-bit keys: two in all, after the first two steps)
     constexpr int kPerStep = F8 ? 1 : kSubInstr / (NBLK * kNS);
@@ -600,7 +599,7 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
 #pragma unroll
         for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][t], q1[t], d, 0, 0, 0);
         k_issue<kPerStep>(ki, voff, 0);
-        stage_exchange_rows(xlse_ad, lse_row, look_row, rows_pad, lane);
+        late();
         __builtin_amdgcn_sched_barrier(0);
         float m = neg_inf(), l = 0.f;
         fold_logits(d, m, l, c, lo0, hi0, hf);
@@ -618,7 +617,7 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
     float m = neg_inf(), l = 0.f;
     fold_logits(da, m, l, c, lo0, hi0, hf);
     k_issue<kPerStep>(ki, voff, 0);
-    stage_exchange_rows(xlse_ad, lse_row, look_row, rows_pad, lane);
+    late();
     __builtin_amdgcn_sched_barrier(0);
     if (NBLK == 2) {
         lift_at<kOffQ1 + PAR * kQTileBytes + 4096>(lc, qf);
@@ -639,6 +638,31 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
         k_issue<kLate>(ki, voff, 3 * kPerStep);
         __builtin_amdgcn_sched_barrier(0);
     }
+}
+
+// The eight per-wave statistics of row `lane` of one buffer, one round trip to LDS.
+template <int OFF>
+__device__ __forceinline__ void read_wave_stats(uint32_t lds0, int lane, float (&m)[kFWaves], float (&l)[kFWaves])
+{
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    const uint32_t ad = lds0 + 8u * (uint32_t)lane;
+    f32x2 r[kFWaves];
+    static_assert(kFWaves == 8 && kMaxRowsF * 8 == 512, "layout of the asm block");
+    __asm__ volatile(
+        "ds_read_b64 %0, %8 offset:%9\n\t"
+        "ds_read_b64 %1, %8 offset:%9+512\n\t"
+        "ds_read_b64 %2, %8 offset:%9+1024\n\t"
+        "ds_read_b64 %3, %8 offset:%9+1536\n\t"
+        "ds_read_b64 %4, %8 offset:%9+2048\n\t"
+        "ds_read_b64 %5, %8 offset:%9+2560\n\t"
+        "ds_read_b64 %6, %8 offset:%9+3072\n\t"
+        "ds_read_b64 %7, %8 offset:%9+3584\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
+        : "v"(ad), "i"(OFF)
+        : "memory");
+#pragma unroll
+    for (int i = 0; i < kFWaves; ++i) { m[i] = r[i].x; l[i] = r[i].y; }
 }
 
 // Exchange data requested with direct-to-LDS loads lands in two small staging areas, each private
@@ -792,9 +816,10 @@ __device__ __forceinline__ float direct_combine(const FusedArgs &a, const uint64
 // Uniform state that walks along with the steps.
 struct Walk {
     PhaseCtr k;       // phase s + 1: next statistics pass (its K tile is being fetched)
-    const char *kptr; // this wave's first key of that phase
+    const char *kptr; // this wave's first key of that phase (PAIR: in the first tile)
     PhaseCtr c;       // phase s - 4: this step's probability pass
     int slot0;        // transit slot of sub-tile 0 of phase s: 2s mod 3
+    uint64_t pair_off;    // PAIR: bytes from a wave's first key in the first tile to its first key in the second
     int dfirst;       // workgroup (of those that share the duties) that combines block 0 of phase s - 2
 };
 
@@ -815,10 +840,10 @@ struct Walk {
 // in some steps only, so every wait counts only operations that are certainly issued behind the
 // ones it needs.
 // KIND (see there): the plain variant carries none of the others' code or registers.
-template <int NB, int GB, int SLOT, int PAR, Kind KIND, bool W, bool F8>
+template <int NB, int GB, int SLOT, int PAR, Kind KIND, bool W, bool F8, bool PAIR>
 __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, const GroupTable &gt, int s, int n_phases, Ring &ring,
-                                     Acc<NB> &acc, const LaneConst &lc, Walk &wk, unsigned char *lds, uint32_t lds0,
-                                     uint64_t wave_off, int r_range)
+                                     Acc<NB> (&accs)[PAIR ? 2 : 1], const LaneConst &lc, Walk &wk, unsigned char *lds, uint32_t lds0,
+                                     uint64_t wave_off, const int (&r_ranges)[PAIR ? 2 : 1])
 {
     constexpr bool EXTRA = KIND != kPlain, RANGES = KIND == kRanges;
     // Other lane-derived values are recomputed every step instead of being kept in registers across
@@ -827,17 +852,23 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     __asm__ volatile("" : "+v"(tid));
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int w = blockIdx.x;
-    const int pp = s - 1;                 // phase whose partials are published
-    const int pc = s - 1 - kLag;          // phase of this step's probability pass
-    const int pd = s - 2;                 // phase whose duty rows are combined in this step
-    const int pl = s - kLag;              // phase whose normalisers are fetched in this step
-    const bool do_stats = s < n_phases, do_prob = pc >= 0 && pc < n_phases;
+    // Phases this step works on; < 0 or >= n_phases: nothing to do. PAIR: step s handles tile s % 2 (= PAR) of
+    // phase s / 2; publishing and duties happen in even steps, when both tiles of a phase have been seen.
+    const int ps = PAIR ? s >> 1 : s;                             // statistics pass
+    const int pf = PAIR ? (s + 1) >> 1 : s + 1;                   // being fetched: the next step's statistics pass
+    const int pp = PAIR ? (PAR == 0 ? (s - 2) >> 1 : -1) : s - 1; // partials are published
+    const int pd = PAIR ? pp : s - 2;                             // duty rows are combined
+    const int pl = PAIR ? (s - 3) >> 1 : s - kLag;                // normalisers are fetched
+    const int pc = PAIR ? (s - 4) >> 1 : s - 1 - kLag;            // probability pass
+    const bool do_stats = ps < n_phases, do_prob = pc >= 0 && pc < n_phases;
+    Acc<NB> &acc = accs[PAIR ? PAR : 0];
+    const int r_range = r_ranges[PAIR ? PAR : 0];
     constexpr int kSI = F8 ? kSubInstr / 2 : kSubInstr;     // tile-load instructions per sub-tile
     constexpr int kMid = F8 ? 1 : 2;                        // of them, for sub-tile 0: issued right after the barrier
     constexpr uint32_t kElem = F8 ? 1u : 2u;                // bytes per key element
     const uint32_t stride_bytes = (uint32_t)a.k_stride_token * kElem;
     // 8-bit keys: the exponent's scale of a phase is c times that phase's key scale
-    const float c_stats = F8 ? a.c * a.kscale[clampi(s, 0, n_phases - 1)] : a.c;
+    const float c_stats = F8 ? a.c * a.kscale[clampi(ps, 0, n_phases - 1)] : a.c;
     const float c_pub = F8 ? a.c * a.kscale[clampi(pp, 0, n_phases - 1)] : a.c;
     const float c_duty = F8 ? a.c * a.kscale[clampi(pd, 0, n_phases - 1)] : a.c;
     const float ks_prob = F8 ? a.kscale[clampi(pc, 0, n_phases - 1)] : 1.f;
@@ -859,57 +890,47 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         src_n = gt.w0[lse_idx + 1] - src_w0;
     }
 
+    auto request_duty = [&]() {
+        if (duty_blk >= 0)
+            stage_duty_block<EXTRA>(lds0 + kOffXduty, a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad, a.rows_pad,
+                                    src_n, duty_blk * kDutyRows, lane);
+    };
+
     // ---- mid ----
     if (wave == kPubWave) {
         if (pp >= 0 && pp < n_phases) {
             // one wave combines the eight per-wave statistics of every row (lane = row), maximum first,
             // then one exponential per source, and publishes the rows with one contiguous store
-            float pm[kFWaves], pl8[kFWaves];
-            {
-                typedef __attribute__((ext_vector_type(2))) float f32x2;
-                const uint32_t ad = lds0 + 8u * (uint32_t)lane;
-                f32x2 r[kFWaves];
-                static_assert(kFWaves == 8 && kMaxRowsF * 8 == 512, "layout of the asm block");
-                __asm__ volatile(
-                    "ds_read_b64 %0, %8 offset:%9\n\t"
-                    "ds_read_b64 %1, %8 offset:%9+512\n\t"
-                    "ds_read_b64 %2, %8 offset:%9+1024\n\t"
-                    "ds_read_b64 %3, %8 offset:%9+1536\n\t"
-                    "ds_read_b64 %4, %8 offset:%9+2048\n\t"
-                    "ds_read_b64 %5, %8 offset:%9+2560\n\t"
-                    "ds_read_b64 %6, %8 offset:%9+3072\n\t"
-                    "ds_read_b64 %7, %8 offset:%9+3584\n\t"
-                    "s_waitcnt lgkmcnt(0)"
-                    : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
-                    : "v"(ad), "i"(kOffWstats + (1 - PAR) * kWstatsBytes)
-                    : "memory");
+            constexpr int kSets = PAIR ? 2 : 1;          // of eight per-wave statistics
+            float pm[kSets][kFWaves], pl8[kSets][kFWaves];
+            read_wave_stats<kOffWstats + (PAIR ? (SLOT ^ 2) : 1 - PAR) * kWstatsBytes>(lds0, lane, pm[0], pl8[0]);
+            if constexpr (PAIR) read_wave_stats<kOffWstats + ((SLOT ^ 2) + 1) % 4 * kWstatsBytes>(lds0, lane, pm[1], pl8[1]);
+            float m = neg_inf();
 #pragma unroll
-                for (int i = 0; i < kFWaves; ++i) { pm[i] = r[i].x; pl8[i] = r[i].y; }
-            }
-            float m = pm[0];
+            for (int h = 0; h < kSets; ++h)
 #pragma unroll
-            for (int i = 1; i < kFWaves; ++i) m = fmaxf(m, pm[i]);
+                for (int i = 0; i < kFWaves; ++i) m = fmaxf(m, pm[h][i]);
             float l = 0.f;
 #pragma unroll
-            for (int i = 0; i < kFWaves; ++i) l += pl8[i] * fast_exp2((pm[i] - m) * c_pub);
+            for (int h = 0; h < kSets; ++h)
+#pragma unroll
+                for (int i = 0; i < kFWaves; ++i) l += pl8[h][i] * fast_exp2((pm[h][i] - m) * c_pub);
             if (lane < a.rows_pad) {
                 const uint64_t bits = (uint64_t)__float_as_uint(m) | ((uint64_t)__float_as_uint(l) << 32) |
                                       ((uint64_t)((pp / kSlots) & 1) << 63);
                 st64(a.part + ((size_t)(pp % kSlots) * a.n_wg + w) * a.rows_pad + lane, bits);
             }
         }
-    } else if (wave == kDutyWave) {
-        if (duty_blk >= 0)
-            stage_duty_block<EXTRA>(lds0 + kOffXduty, a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad, a.rows_pad,
-                             src_n, duty_blk * kDutyRows, lane);
+    } else if (!PAIR && wave == kDutyWave) {
+        request_duty();
     } else if (RANGES && wave == kLseWave && direct && pl >= 0 && pl < n_phases) {
         stage_direct(lds0 + kOffXduty, a.part + ((size_t)(pl % kSlots) * a.n_wg + a.ent_w0) * kRowsPad, a.ent_n * kRowsPad, lane);
     }
-    const char *kbase = wk.kptr;
+    const char *kbase = wk.kptr + (PAIR && PAR == 0 ? wk.pair_off : 0);      // PAIR: the second tile is fetched in even steps
     int slot_next = wk.slot0 + 2;         // sub-tile 0 of phase s + 1
     slot_next = slot_next >= kSubSlots ? slot_next - kSubSlots : slot_next;
     // past the last phase the loads shrink to one 16-byte piece per instruction: the count stays fixed
-    const uint32_t live = s + 1 < n_phases ? 0xffffffffu : 0u;
+    const uint32_t live = pf < n_phases ? 0xffffffffu : 0u;
     const uint32_t voff[2] = {lc.koff[0] & live, lc.koff[1] & live};
     KIssue ki;
     ki.lds_dst = lds0 + sub_slot_off(wave, slot_next, 0);
@@ -917,7 +938,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     ki.step_bytes = (F8 ? 16u : 8u) * stride_bytes;
     if (lc.qoff >= 0) {       // padding rows of the Q tiles stay zero; the Q blocks of consecutive phases are contiguous
         const uint32_t qblock = (uint32_t)(a.group * a.n_q * kD * 2) * (W ? 2u : 1u);
-        const char *q1src = reinterpret_cast<const char *>(a.q) + (uint32_t)min(s + 1, n_phases - 1) * qblock;
+        const char *q1src = reinterpret_cast<const char *>(a.q) + (uint32_t)min(pf, n_phases - 1) * qblock;
         const char *q2src = reinterpret_cast<const char *>(a.q) + (uint32_t)clampi(pl, 0, n_phases - 1) * qblock;
         dma_u<kOffQ1 + (1 - PAR) * kQTileBytes>((uint32_t)lc.qoff, q1src, lds0 + wave * 1024);
         dma_u<kOffQ2 + PAR * kQTileBytes>((uint32_t)lc.qoff, q2src, lds0 + wave * 1024);
@@ -946,23 +967,28 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         const uint64_t *lse_row = wave == kLseWave && !direct ? a.lse + ((size_t)(clampi(pl, 0, n_phases - 1) % kSlots) * a.n_gp + a.p_idx) * a.rows_pad : nullptr;
         const float *look_row = nullptr;
         if (EXTRA && a.look != nullptr && wave == kLseWave) look_row = a.look + (size_t)((RANGES ? a.phase0 : 0) + clampi(pl, 0, n_phases - 1)) * a.rows_pad;
+        // requests after the first MFMA step: the normalisers; PAIR: also the duty rows, published at the start of
+        // this very step (their normalisers are due at the next one's end)
+        auto late = [&]() {
+            stage_exchange_rows(lds0 + kOffXlse, lse_row, look_row, a.rows_pad, lane);
+            if (PAIR && PAR == 0 && wave == kDutyWave) request_duty();
+        };
         // r_range = r_lo | r_hi << 16 (r_hi = 512 without EXTRA): this wave's share of it
         constexpr int kWaveKeys = W ? 32 : kNS * 32;
         const int lo0 = (r_range & 0xffff) - wave * kWaveKeys;
         const int hi0 = EXTRA ? (r_range >> 16) - wave * kWaveKeys : kWaveKeys;
         if (do_stats) {
-            const uint32_t wstats_ad = lds0 + kOffWstats + PAR * kWstatsBytes + wave * (kMaxRowsF * 8) + ((uint32_t)(lane & 31) << 3);
+            const uint32_t wstats_ad = lds0 + kOffWstats + (PAIR ? SLOT : PAR) * kWstatsBytes + wave * (kMaxRowsF * 8) + ((uint32_t)(lane & 31) << 3);
             stats_pass<NB * GB, PAR, W, F8>(c_stats, ring.kf[SLOT], lc, sub_slot_off(wave, wk.slot0, 0),
-                                     sub_slot_off(wave, wk.slot0, 1), wstats_ad, lo0, hi0, lane, ki, voff, lse_row,
-                                     look_row, a.rows_pad, lds0 + kOffXlse);
+                                     sub_slot_off(wave, wk.slot0, 1), wstats_ad, lo0, hi0, lane, ki, voff, late);
         } else {
-            stage_exchange_rows(lds0 + kOffXlse, lse_row, look_row, a.rows_pad, lane);
+            late();
             k_issue<kSI>(ki, voff, 0);
         }
     }
 
     // ---- pre-barrier: exchange data in, seeds out ----
-    if (wave == kLseWave && !(RANGES && direct && a.look == nullptr)) vm_wait<kLoadsBehindLse<NB * GB, F8>>(); else vm_wait<2 * kSI>();
+    if ((wave == kLseWave && !(RANGES && direct && a.look == nullptr)) || (PAIR && PAR == 0 && wave == kDutyWave)) vm_wait<kLoadsBehindLse<NB * GB, F8>>(); else vm_wait<2 * kSI>();
     int *fail = reinterpret_cast<int *>(lds + kOffFail);
     if (wave == kDutyWave) {
         if (duty_blk >= 0) {
@@ -1055,7 +1081,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     }
 
     // ---- walk on ----
-    if (s + 2 < n_phases) {               // K pointer of the next step's fetch
+    if (PAIR ? PAR == 0 && pf + 1 < n_phases : s + 2 < n_phases) {               // K pointer of the next phase to fetch
         if (++wk.k.kv == a.n_kv_heads) {
             wk.k.kv = 0;
             ++wk.k.layer;
@@ -1064,9 +1090,9 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
             wk.kptr += (uint64_t)a.k_stride_head * kElem;
         }
     }
-    phase_advance(wk.c, s - 3, n_phases, a.n_kv_heads);
+    if (!PAIR || PAR == 1) phase_advance(wk.c, pc + 1, n_phases, a.n_kv_heads);
     wk.slot0 = slot_next;
-    if (s - 1 > 0 && s - 1 < n_phases) {
+    if (pd + 1 > 0 && pd + 1 < n_phases && (!PAIR || PAR == 0)) {
         wk.dfirst += duty_blocks;
         if (wk.dfirst >= duty_n) wk.dfirst -= duty_n;
     }
@@ -1117,11 +1143,17 @@ __device__ __forceinline__ void fold_model_constants(FusedArgs &a)
 // k-step 4s + t), Q tiles hold 32 rows as two half-tiles, and a logit is one chain of eight MFMA steps.
 // F8: 8-bit keys (head_dim 64): rows of 64 codes, sub-tiles of 2 KB fetched by two instructions of 16 rows,
 // widened to bf16 at the lift; every phase has its own key scale.
-template <int NB, int GB, Kind KIND, class M, bool W = false, bool F8 = false>
+// PAIR: prompts of up to two tiles per compute unit (head_dim 64: 256K tokens, 128: 128K). A workgroup owns two
+// tiles and a phase takes two steps, one a tile, on the same fragment ring: two phases instead of four are in
+// flight, so the normalisers have to come back within four steps less the two of their own phase. Duties are therefore
+// combined in the step in which the partials are published, which has twice a tile's time (5.5 us of HBM time)
+// to go around. One read of K instead of the general path's two.
+template <int NB, int GB, Kind KIND, class M, bool W = false, bool F8 = false, bool PAIR = false>
 __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, LayerPtrs kp, GroupTable gt)
 {
     static_assert(!W || (NB == 1 && GB == 1 && !M::kFixed), "head_dim 128: one block of 32 query rows");
     static_assert(!F8 || KIND == kPlain, "8-bit keys: plain variants only");
+    static_assert(!PAIR || (!F8 && NB == 1 && KIND != kRanges), "pairs of tiles: whole prompts, one block of lookahead rows");
     constexpr bool EXTRA = KIND != kPlain, RANGES = KIND == kRanges;
     constexpr int kSI = F8 ? kSubInstr / 2 : kSubInstr;
     constexpr uint32_t kElem = F8 ? 1u : 2u;
@@ -1170,14 +1202,20 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
         a.p_idx = 0;
         a.n_gp = 1;
     }
-    int64_t j0l = (paged || (int64_t)(wl + 1) * kTile <= p_len) ? (int64_t)wl * kTile : p_len - kTile;
+    constexpr int kOwn = PAIR ? 2 * kTile : kTile;            // keys of this workgroup
+    int64_t j0l = (paged || (int64_t)(wl + 1) * kOwn <= p_len) ? (int64_t)wl * kOwn : p_len - kOwn;
     // A prompt of a batch that is shorter than a tile: the tile starts with it and the keys of the prompts behind
     // it are ignored; at the end of the packed keys (L of them, at least one tile) it ends with them instead.
     if (RANGES && p_len < kTile && !paged) j0l = p_start + kTile <= a.L ? 0 : a.L - kTile - p_start;
     const int64_t j0 = p_start + j0l;         // first key of the tile in the layer's key array
-    const int r_lo = (int)((int64_t)wl * kTile - j0l);
-    const int r_hi = (int)(p_len - j0l < kTile ? p_len - j0l : kTile);
-    const int r_range = r_lo | (r_hi << 16);
+    // this workgroup's keys r_lo <= key < r_hi of each tile; PAIR, paged: a second tile without keys is the first
+    // one again (its own may have no page)
+    int r_ranges[PAIR ? 2 : 1];
+    const int own_lo = (int)((int64_t)wl * kOwn - j0l), own_hi = (int)(p_len - j0l < kOwn ? p_len - j0l : kOwn);
+    const bool second = PAIR && own_hi > kTile;
+#pragma unroll
+    for (int t = 0; t < (PAIR ? 2 : 1); ++t)
+        r_ranges[t] = clampi(own_lo - t * kTile, 0, kTile) | (clampi(own_hi - t * kTile, 0, kTile) << 16);
     const uint32_t lds0 = lds_addr(lds);
     const uint32_t stride_bytes = (uint32_t)a.k_stride_token * kElem;
 
@@ -1217,7 +1255,9 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     }
 
     Ring ring;
-    Acc<NB> acc;
+    Acc<NB> accs[PAIR ? 2 : 1];
+#pragma unroll
+    for (auto &acc : accs)
 #pragma unroll
     for (int s = 0; s < kNS; ++s) {
         acc.total[s] = 0.f;
@@ -1229,13 +1269,16 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
 
     // byte offset of this wave's first key within a (layer, kv head): uniform, kept in scalar registers
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    uint64_t wave_off = (uint64_t)(j0 + wave_u * kWaveKeys) * (uint64_t)a.k_stride_token * kElem;
-    if (paged) {
-        const int64_t page = j0 / a.page_tokens;
-        wave_off = ((uint64_t)a.block_table[page] * (uint64_t)a.page_stride +
-                    (uint64_t)(j0 - page * a.page_tokens + wave_u * kWaveKeys) * (uint64_t)a.k_stride_token) * 2u;
-    }
-    wave_off = (uint64_t)uniform32((uint32_t)wave_off) | ((uint64_t)uniform32((uint32_t)(wave_off >> 32)) << 32);
+    auto key_offset = [&](int64_t j) -> uint64_t {
+        uint64_t off = (uint64_t)(j + wave_u * kWaveKeys) * (uint64_t)a.k_stride_token * kElem;
+        if (paged) {
+            const int64_t page = j / a.page_tokens;
+            off = ((uint64_t)a.block_table[page] * (uint64_t)a.page_stride +
+                   (uint64_t)(j - page * a.page_tokens + wave_u * kWaveKeys) * (uint64_t)a.k_stride_token) * 2u;
+        }
+        return (uint64_t)uniform32((uint32_t)off) | ((uint64_t)uniform32((uint32_t)(off >> 32)) << 32);
+    };
+    const uint64_t wave_off = key_offset(j0);
 
     // prologue: this wave's slice of Q(0) and both sub-tiles of K(0); everything lands before step 0
     if (lc.qoff >= 0) dma_u<kOffQ1>((uint32_t)lc.qoff, a.q, lds0 + wave_u * 1024);
@@ -1251,7 +1294,8 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     lds_barrier();
 
     Walk wk;
-    wk.k = phase_at(1, n_phases, a.n_kv_heads);
+    wk.k = phase_at(PAIR ? 0 : 1, n_phases, a.n_kv_heads);
+    wk.pair_off = second ? key_offset(j0 + kTile) - wave_off : 0;
     wk.k.layer += layer0;
     wk.kptr = reinterpret_cast<const char *>(kp.p[wk.k.layer]) + (uint64_t)wk.k.kv * (uint64_t)a.k_stride_head * kElem + wave_off;
     wk.c = phase_at(0, n_phases, a.n_kv_heads);
@@ -1263,12 +1307,12 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     // The body is unrolled four times so that the fragment ring slot (s % 4) and the buffer parity
     // (s % 2) are compile-time; the trip count is rounded up, surplus steps do no work but keep the
     // instruction stream uniform. The last probability pass (phase n_phases - 1) runs in step n_phases + 3.
-    const int n_steps = (n_phases + kLag + 1 + 3) / 4 * 4;
+    const int n_steps = ((PAIR ? 2 * n_phases : n_phases) + kLag + 1 + 3) / 4 * 4;
     for (int s0 = 0; s0 < n_steps; s0 += 4) {
-        step<NB, GB, 0, 0, KIND, W, F8>(a, kp, gt, s0 + 0, n_phases, ring, acc, lc, wk, lds, lds0, wave_off, r_range);
-        step<NB, GB, 1, 1, KIND, W, F8>(a, kp, gt, s0 + 1, n_phases, ring, acc, lc, wk, lds, lds0, wave_off, r_range);
-        step<NB, GB, 2, 0, KIND, W, F8>(a, kp, gt, s0 + 2, n_phases, ring, acc, lc, wk, lds, lds0, wave_off, r_range);
-        step<NB, GB, 3, 1, KIND, W, F8>(a, kp, gt, s0 + 3, n_phases, ring, acc, lc, wk, lds, lds0, wave_off, r_range);
+        step<NB, GB, 0, 0, KIND, W, F8, PAIR>(a, kp, gt, s0 + 0, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+        step<NB, GB, 1, 1, KIND, W, F8, PAIR>(a, kp, gt, s0 + 1, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+        step<NB, GB, 2, 0, KIND, W, F8, PAIR>(a, kp, gt, s0 + 2, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+        step<NB, GB, 3, 1, KIND, W, F8, PAIR>(a, kp, gt, s0 + 3, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
     }
     vm_wait<0>();               // no direct-to-LDS load may outlive the workgroup
     lds_barrier();
@@ -1279,7 +1323,8 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
 #pragma unroll
         for (int s = 0; s < kWaveKeys / 32; ++s) {
             const int key = wave * kWaveKeys + s * 32 + col;
-            const bool mine = key >= r_lo && key < r_hi;
+            const bool mine = key >= (r_ranges[0] & 0xffff) && key < (r_ranges[0] >> 16);
+            const Acc<NB> &acc = accs[0];
             if (a.layer_agg == SP_LAYER_MEAN) {
                 const float both = acc.total[s] + __shfl_xor(acc.total[s], 32);
                 if (hf == 0 && mine) a.split_out[slice * a.split_stride + j0 + key] = both;
@@ -1296,10 +1341,12 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     // the call has failed if any workgroup raised the status word; this workgroup's own failures are in it
     const bool failed = __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
 #pragma unroll
+    for (int t = 0; t < (PAIR ? 2 : 1); ++t)
+#pragma unroll
     for (int s = 0; s < kWaveKeys / 32; ++s) {
-        const float both = acc.total[s] + __shfl_xor(acc.total[s], 32);
+        const float both = accs[t].total[s] + __shfl_xor(accs[t].total[s], 32);
         const int key = wave * kWaveKeys + s * 32 + col;
-        if (hf == 0 && key >= r_lo && key < r_hi) a.scores[j0 + key] = failed ? __uint_as_float(0x7fc00000u) : both * a.out_scale;   // quiet NaN marks a failed call
+        if (hf == 0 && key >= (r_ranges[t] & 0xffff) && key < (r_ranges[t] >> 16)) a.scores[j0 + t * kTile + key] = failed ? __uint_as_float(0x7fc00000u) : both * a.out_scale;   // quiet NaN marks a failed call
     }
 }
 
@@ -1348,7 +1395,9 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
     // The kernel places workgroup w of a prompt at key w * tile: the grid must be exactly the prompts' tiles
     // (a surplus workgroup of a paged prompt would look up a page the table does not have).
     const int64_t tile = a.tile_keys;
-    if (!(a.head_dim == kD && tile == kFTile) && !(a.head_dim == 2 * kD && tile == kFTile / 2))
+    const int base_tile = a.head_dim == 2 * kD ? kFTile / 2 : kFTile;
+    const bool pair = tile == 2 * base_tile;
+    if ((a.head_dim != kD && a.head_dim != 2 * kD) || (tile != base_tile && !pair))
         return sp::fail(SP_ERR_INVALID_ARG, "fused score kernel: head_dim %d with %d keys per workgroup", a.head_dim, a.tile_keys);
     if (gt.n == 0) {
         if (a.L < tile || sp::ceil_div(a.L, tile) != a.n_wg)
@@ -1405,7 +1454,17 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
     // the fixed-model instantiations apply when every folded constant equals the call's value
     const bool draft = a.head_dim == kD && a.n_layers == 16 && a.n_q_heads == 32 && a.n_kv_heads == 8 && a.k_stride_token == kD &&
                        a.c == kScaleEighthLog2e && a.inv_c == 1.0f / kScaleEighthLog2e;
-    if (a.kscale != nullptr) {              // 8-bit keys
+    if (pair) {
+        if (a.kscale != nullptr || gt.n > 0 || a.n_nblk != 1)
+            return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, two tiles a workgroup: one prompt, bf16 keys, up to 8 lookahead rows");
+        if (a.head_dim == 2 * kD && extra) SP_FUSED(1, 1, kExtra, AnyModel, true, false, true);
+        else if (a.head_dim == 2 * kD) SP_FUSED(1, 1, kPlain, AnyModel, true, false, true);
+        else if (blocks == 12 && extra) SP_FUSED(1, 2, kExtra, AnyModel, false, false, true);
+        else if (blocks == 12) SP_FUSED(1, 2, kPlain, AnyModel, false, false, true);
+        else if (extra) SP_FUSED(1, 1, kExtra, AnyModel, false, false, true);
+        else if (draft && a.n_q == 8) SP_FUSED(1, 1, kPlain, Draft8, false, false, true);
+        else SP_FUSED(1, 1, kPlain, AnyModel, false, false, true);
+    } else if (a.kscale != nullptr) {       // 8-bit keys
         if (a.head_dim == 2 * kD) SP_FUSED(1, 1, kPlain, AnyModel, true, true);
         else if (draft && a.n_q == 16 && a.n_wg == 256) SP_FUSED(2, 1, kPlain, Draft16x32x8<16, 256>, false, true);
         else if (draft && a.n_q == 16) SP_FUSED(2, 1, kPlain, Draft16, false, true);

@@ -38,7 +38,7 @@ struct GroupTable {
 struct FusedArgs {
     const uint16_t *q;           // [Lyr][H][n_q][head_dim]
     int32_t head_dim;            // 64 or 128
-    int32_t tile_keys;           // keys per workgroup: 512 at head_dim 64, 256 at head_dim 128
+    int32_t tile_keys;           // keys per workgroup: 512 at head_dim 64, 256 at head_dim 128, or two such tiles
     int64_t k_stride_token, k_stride_head;
     int64_t L;
     uint64_t *part;              // [kSlots][n_wg][rows_pad]  (max, sum exp) partials, parity in bit 63

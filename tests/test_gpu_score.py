@@ -303,6 +303,45 @@ def test_score_in_layer_ranges_matches_oracle(shape):
         assert run(mode, nhd, "NHD").tobytes() == got.tobytes()
 
 
+# More than one tile per compute unit: a workgroup owns two.
+PAIR_SHAPES = [
+    # name, Lyr, H, Hkv, d, n_q, L, page_tokens (0: contiguous keys, also with lookahead keys)
+    ("pair_one_key_more", 1, 4, 1, 64, 8, 131073, 0),                # the last workgroup shifted back by 1023 keys
+    ("pair_three_phases", 3, 2, 1, 64, 5, 140001, 0),
+    ("pair_two_gblocks", 1, 8, 1, 64, 8, 150000, 0),
+    ("pair_full_grid", 1, 4, 2, 64, 8, 262144, 0),
+    ("pair_d128", 2, 4, 2, 128, 8, 65537, 0),
+    ("pair_d128_full_grid", 1, 2, 1, 128, 8, 131072, 0),
+    ("pair_paged_second_tile_empty", 2, 4, 1, 64, 8, 131072 + 500, 512),
+    ("pair_paged_d128_tail", 1, 4, 2, 128, 8, 70000, 4096),
+    ("pair_draft_model", 16, 32, 8, 64, 8, 131072 + 777, 0),
+]
+
+
+@pytest.mark.parametrize("shape", PAIR_SHAPES, ids=[s[0] for s in PAIR_SHAPES])
+def test_score_with_two_tiles_a_workgroup_matches_oracle(shape):
+    from gpu_util import assert_scores_close, gpu_score, gpu_score_look, gpu_score_paged, make_paged
+    name, Lyr, H, Hkv, d, n_q, L, page = shape
+    say(f"[score-pair] {name} Lyr={Lyr} H={H} Hkv={Hkv} d={d} n_q={n_q} L={L} page={page}")
+    w = small_workload(name, Lyr, H, Hkv, d, n_q, L, cfg_id=600 + PAIR_SHAPES.index(shape), hh=(1, 1000))
+    inp = synth.make_score_inputs(w)
+    q, k = inp["q"][0], inp["k"]
+    if page:
+        pools, table = make_paged(k, page, "HND", seed=w.cfg_id)
+        run = lambda mode: gpu_score_paged(q, pools, table, page, L, w.scale, mode, "HND")
+    else:
+        run = lambda mode: gpu_score(q, k, w.scale, mode)
+    for mode in ((0,) if Lyr > 4 else (0, 1)):
+        got = run(mode)
+        assert_scores_close(got, oracle.score(q, k, w.scale, mode))
+        assert run(mode).tobytes() == got.tobytes()
+    if not page and Lyr <= 4:
+        kl = synth.gen_look_keys(w, inp["q"])
+        assert_scores_close(gpu_score_look(q, k, kl, 1, w.scale, 0), oracle.score_look(q, k, kl, 1, w.scale, 0))
+        nhd = [np.ascontiguousarray(x.transpose(1, 0, 2)) for x in k]
+        assert gpu_score(q, nhd, w.scale, mode, layout="NHD").tobytes() == got.tobytes()
+
+
 def test_fused_score_gives_up_as_a_whole():
     """The bounded waits of the single-launch kernel, driven to give up from the host (the test hook
     makes the combining waves treat their partial results as never arriving, with a spin limit of a few
