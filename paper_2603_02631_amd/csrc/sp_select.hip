@@ -12,9 +12,9 @@
 //                    on order-preserving integer images of the fp32 chunk
 //                    scores finds the k-th largest score exactly; chunks above
 //                    it are kept, chunks equal to it are kept in index order
-//                    until k is reached (lower index wins a tie). Two block
-//                    scans then emit the kept indices in ascending order and
-//                    the merged spans.
+//                    until k is reached (lower index wins a tie); the kept
+//                    set as a bit string gives the indices in ascending order
+//                    and the merged spans.
 // Everything is integer or fixed-order fp32 work, so results are deterministic.
 //
 // sp_select_budget (Section 3.1: a fixed target-side length of the compressed
@@ -167,55 +167,47 @@ __device__ __forceinline__ int block_scan_incl(int v, int *wave_tot /*[16]*/, in
     return x + base;
 }
 
-// R > 0: the keys of up to R * 1024 chunks are read once and kept in registers (every pass over the
-// chunk scores would otherwise pay a trip to memory); R = 0: any number of chunks, re-read per pass.
-template <int R>
-__device__ __forceinline__ void topk_body(const float *__restrict__ cs, int64_t n_chunks, int64_t k,
-                                          const int64_t *__restrict__ k_dev, int chunk, int64_t L, int32_t *sel,
-                                          int64_t *__restrict__ spans, int32_t *__restrict__ n_spans)
+// The k-th largest key's bucket: keys whose bits under `mask` equal `prefix`, of which the first `need` in index
+// order are kept (all of them if the search could stop before the last bit), besides every larger one.
+struct Threshold {
+    uint32_t prefix, mask;
+    int64_t need;
+};
+
+// Radix select by one workgroup, most significant byte first. Per pass all threads count their candidates into
+// a 256-bin histogram; wave 0 alone scans the bins from the top (four per lane, one shuffle scan), picks the bin
+// that holds the k-th, and clears the histogram for the next pass: two barriers per pass. The search ends as
+// soon as the bin holds exactly the keys still needed (one of distinct scores: three passes, seldom four).
+// Scores share a handful of exponents, so in the first pass a wave adds up its keys of one bin before it
+// touches the counter: one by one, 64 keys of a bin take 64 turns at it.
+// count(f) calls f(key, live) for each of this thread's keys, the same number of times in every thread of a wave.
+template <class Count>
+__device__ __forceinline__ Threshold radix_select(int64_t k, const Count &count)
 {
     __shared__ int hist[256];
-    if (k_dev) {                             // k chosen on the device (budget search); always within 1..n_chunks
-        k = *k_dev;
-        k = k < 1 ? 1 : (k > n_chunks ? n_chunks : k);
-    }
-    __shared__ int wave_tot[kTopkThreads / 64];
     __shared__ uint32_t s_prefix;
     __shared__ int64_t s_need;
+    __shared__ int s_found;
     const int tid = threadIdx.x;
-
-    uint32_t cached[R > 0 ? R : 1];
-    if (R > 0) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t i = (int64_t)r * kTopkThreads + tid;
-            cached[r] = i < n_chunks ? order_key(cs[i]) : 0u;
-        }
-    }
-    // key of chunk i = seg * kTopkThreads + tid (seg is a compile-time index wherever R > 0)
-    auto key_of = [&](int seg, int64_t i) -> uint32_t { return R > 0 ? cached[seg] : order_key(cs[i]); };
-
-    // ---- radix select: key of the k-th largest chunk score ----
-    // Per pass: all threads count their candidates into a 256-bin histogram; wave 0 alone scans the
-    // bins from the top (four per lane, one shuffle scan), picks the bin that holds the k-th, and clears
-    // the histogram for the next pass: two barriers per pass.
-    uint32_t prefix = 0, mask = 0;
-    int64_t need = k;                        // how many still to take from the current bucket
+    Threshold t{0u, 0u, k};
     if (tid < 256) hist[tid] = 0;
     __syncthreads();
     for (int shift = 24; shift >= 0; shift -= 8) {
-        if (R > 0) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int64_t i = (int64_t)r * kTopkThreads + tid;
-                const uint32_t key = cached[r];
-                if (i < n_chunks && (key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
-            }
+        if (shift == 24) {
+            count([&](uint32_t key, bool live) {
+                const uint32_t bin = key >> 24;
+                uint64_t left = __ballot(live);
+                while (left != 0) {                    // uniform: one turn per bin the wave's keys fall into
+                    const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)bin, __ffsll((unsigned long long)left) - 1);
+                    const uint64_t same = __ballot(live && bin == b) & left;
+                    if ((tid & 63) == 0) atomicAdd(&hist[b], __popcll(same));
+                    left &= ~same;
+                }
+            });
         } else {
-            for (int64_t i = tid; i < n_chunks; i += kTopkThreads) {
-                const uint32_t key = order_key(cs[i]);
-                if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
-            }
+            count([&](uint32_t key, bool live) {
+                if (live && (key & t.mask) == t.prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
+            });
         }
         __syncthreads();
         if (tid < 64) {
@@ -236,42 +228,140 @@ __device__ __forceinline__ void topk_body(const float *__restrict__ cs, int64_t 
             int64_t before = incl - lane_sum;        // candidates in the bins above this lane's
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (before < need && before + h[j] >= need) {
-                    s_prefix = prefix | ((uint32_t)(255 - 4 * tid - j) << shift);
-                    s_need = need - before;
+                if (before < t.need && before + h[j] >= t.need) {
+                    s_prefix = t.prefix | ((uint32_t)(255 - 4 * tid - j) << shift);
+                    s_need = t.need - before;
+                    s_found = h[j];
                 }
                 before += h[j];
             }
         }
         __syncthreads();
-        prefix = s_prefix;
-        need = s_need;
-        mask |= 255u << shift;
+        t.prefix = s_prefix;
+        t.need = s_need;
+        t.mask |= 255u << shift;
+        if (s_found == t.need) break;                // uniform
     }
-    const uint32_t thr = prefix;             // exact key of the k-th largest score
-    // `need` = number of chunks equal to thr to keep, taken in index order.
+    return t;
+}
+
+// Lowest n set bits of x.
+__device__ __forceinline__ uint64_t lowest_bits(uint64_t x, int64_t n)
+{
+    if (n <= 0) return 0;
+    for (int64_t drop = __popcll(x) - n; drop > 0; --drop) x &= ~(1ull << (63 - __clzll((long long)x)));
+    return x;
+}
+
+// Up to R * 1024 chunks, whose keys stay in registers. The kept set is a bit string in LDS, 64 chunks a word:
+// one wave decides the ties and turns the words' population counts into output positions, the starts and ends of
+// its runs are the spans, and every thread writes its own chunks' entries; nothing written is read back.
+// Bound by its chain of dependent steps: the workgroup reads 8 KB. With a block scan per 1024 chunks, the kept
+// indices read back for the spans, and four passes of the radix select always, 2048 chunks took 11 us.
+template <int R>
+__device__ __forceinline__ void topk_words(const float *__restrict__ cs, int64_t n_chunks, int64_t k, int chunk, int64_t L,
+                                           int32_t *__restrict__ sel, int64_t *__restrict__ spans, int32_t *__restrict__ n_spans)
+{
+    constexpr int kWords = R * kTopkThreads / 64;
+    static_assert(kWords <= 128, "two words a lane");
+    __shared__ uint64_t s_gt[kWords], s_eq[kWords], s_start[kWords], s_end[kWords];
+    __shared__ int32_t s_pos[kWords], s_id[kWords];       // kept chunks and spans before the word
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t key[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t i = (int64_t)r * kTopkThreads + tid;
+        key[r] = i < n_chunks ? order_key(cs[i]) : 0u;
+    }
+    const Threshold t = radix_select(k, [&](auto &&f) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) f(key[r], (int64_t)r * kTopkThreads + tid < n_chunks);
+    });
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const bool live = (int64_t)r * kTopkThreads + tid < n_chunks;
+        const uint64_t gt = __ballot(live && (key[r] & t.mask) > t.prefix), eq = __ballot(live && (key[r] & t.mask) == t.prefix);
+        if (lane == 0) { s_gt[r * (kTopkThreads / 64) + wave] = gt; s_eq[r * (kTopkThreads / 64) + wave] = eq; }
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const bool has = 2 * lane < kWords;               // lane l: words 2l and 2l + 1
+        const uint64_t q0 = has ? s_eq[2 * lane] : 0, q1 = has ? s_eq[2 * lane + 1] : 0;
+        const int e0 = __popcll(q0), e = e0 + __popcll(q1);
+        int ei = e;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int y = __shfl_up(ei, off);
+            if (lane >= off) ei += y;
+        }
+        const int64_t room = t.need - (ei - e);           // equal keys still to keep from this lane's first word on
+        const uint64_t k0 = (has ? s_gt[2 * lane] : 0) | lowest_bits(q0, room);
+        const uint64_t k1 = (has ? s_gt[2 * lane + 1] : 0) | lowest_bits(q1, room - e0);
+        int before = __shfl_up((int)(k1 >> 63), 1), after = __shfl_down((int)(k0 & 1), 1);
+        if (lane == 0) before = 0;
+        if (lane == 63) after = 0;
+        const uint64_t b0 = k0 & ~((k0 << 1) | (uint64_t)before), b1 = k1 & ~((k1 << 1) | (k0 >> 63));
+        const uint64_t f0 = k0 & ~((k0 >> 1) | (k1 << 63)), f1 = k1 & ~((k1 >> 1) | ((uint64_t)after << 63));
+        const int p0 = __popcll(k0) | __popcll(b0) << 16, p = p0 + (__popcll(k1) | __popcll(b1) << 16);
+        int pi = p;                                       // both counts fit 16 bits
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int y = __shfl_up(pi, off);
+            if (lane >= off) pi += y;
+        }
+        const int px = pi - p, py = px + p0;
+        if (has) {
+            s_gt[2 * lane] = k0;      s_gt[2 * lane + 1] = k1;
+            s_start[2 * lane] = b0;   s_start[2 * lane + 1] = b1;
+            s_end[2 * lane] = f0;     s_end[2 * lane + 1] = f1;
+            s_pos[2 * lane] = px & 0xffff; s_pos[2 * lane + 1] = py & 0xffff;
+            s_id[2 * lane] = px >> 16;     s_id[2 * lane + 1] = py >> 16;
+        }
+        if (lane == 63) *n_spans = pi >> 16;
+    }
+    __syncthreads();
+    const uint64_t below = (1ull << lane) - 1;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int w = r * (kTopkThreads / 64) + wave;
+        const uint64_t kept = s_gt[w], start = s_start[w];
+        if (((kept >> lane) & 1) == 0) continue;
+        const int64_t i = (int64_t)r * kTopkThreads + tid;
+        sel[s_pos[w] + __popcll(kept & below)] = (int32_t)i;
+        const int64_t id = s_id[w] + __popcll(start & (below << 1 | 1)) - 1;
+        if ((start >> lane) & 1) spans[2 * id] = i * chunk;
+        if ((s_end[w] >> lane) & 1) spans[2 * id + 1] = (i + 1) * chunk < L ? (i + 1) * chunk : L;
+    }
+}
+
+// Any number of chunks, their scores read again in every pass.
+__device__ __forceinline__ void topk_stream(const float *__restrict__ cs, int64_t n_chunks, int64_t k, int chunk, int64_t L,
+                                            int32_t *sel, int64_t *__restrict__ spans, int32_t *__restrict__ n_spans)
+{
+    __shared__ int wave_tot[kTopkThreads / 64];
+    const int tid = threadIdx.x;
+    const Threshold t = radix_select(k, [&](auto &&f) {
+        for (int64_t base = 0; base < n_chunks; base += kTopkThreads) {
+            const int64_t i = base + tid;
+            f(i < n_chunks ? order_key(cs[i]) : 0u, i < n_chunks);
+        }
+    });
 
     // ---- emit kept chunk indices in ascending order ----
-    // Kept: every chunk above thr and the first `need` chunks equal to thr. One scan per segment of a
-    // packed pair (above in the low half, equal in the high half) gives each chunk's output position:
-    // chunks above before it plus min(equal chunks before it, need).
+    // One scan per segment of a packed pair (above in the low half, equal in the high half) gives each chunk's
+    // output position: chunks above before it plus min(equal chunks before it, need).
     int64_t eq_seen = 0, gt_seen = 0;
-    const int n_seg = (int)((n_chunks + kTopkThreads - 1) / kTopkThreads);
-#pragma unroll
-    for (int seg = 0; seg < (R > 0 ? R : n_seg); ++seg) {
-        if (R > 0 && seg >= n_seg) break;            // uniform
-        const int64_t base = (int64_t)seg * kTopkThreads;
+    for (int64_t base = 0; base < n_chunks; base += kTopkThreads) {
         const int64_t i = base + tid;
-        uint32_t key = 0;
-        if (i < n_chunks) key = key_of(seg, i);
-        const int is_eq = (i < n_chunks && key == thr) ? 1 : 0;
-        const int is_gt = (i < n_chunks && key > thr) ? 1 : 0;
+        const uint32_t key = i < n_chunks ? order_key(cs[i]) & t.mask : 0u;
+        const int is_eq = (i < n_chunks && key == t.prefix) ? 1 : 0;
+        const int is_gt = (i < n_chunks && key > t.prefix) ? 1 : 0;
         int total;
         const int incl = block_scan_incl(is_gt | (is_eq << 16), wave_tot, total);
         const int64_t gt_before = gt_seen + (incl & 0xffff) - is_gt;
         const int64_t eq_before = eq_seen + (incl >> 16) - is_eq;
-        if (is_gt) sel[gt_before + (eq_before < need ? eq_before : need)] = (int32_t)i;
-        else if (is_eq && eq_before < need) sel[gt_before + eq_before] = (int32_t)i;
+        if (is_gt) sel[gt_before + (eq_before < t.need ? eq_before : t.need)] = (int32_t)i;
+        else if (is_eq && eq_before < t.need) sel[gt_before + eq_before] = (int32_t)i;
         gt_seen += total & 0xffff;
         eq_seen += total >> 16;
     }
@@ -301,6 +391,20 @@ __device__ __forceinline__ void topk_body(const float *__restrict__ cs, int64_t 
         span_base += tot;
     }
     if (tid == 0) *n_spans = (int32_t)span_base;
+}
+
+// R > 0: up to R * 1024 chunks; R = 0: any number.
+template <int R>
+__device__ __forceinline__ void topk_body(const float *__restrict__ cs, int64_t n_chunks, int64_t k,
+                                          const int64_t *__restrict__ k_dev, int chunk, int64_t L, int32_t *sel,
+                                          int64_t *__restrict__ spans, int32_t *__restrict__ n_spans)
+{
+    if (k_dev) {                             // k chosen on the device (budget search); always within 1..n_chunks
+        k = *k_dev;
+        k = k < 1 ? 1 : (k > n_chunks ? n_chunks : k);
+    }
+    if constexpr (R > 0) topk_words<R>(cs, n_chunks, k, chunk, L, sel, spans, n_spans);
+    else topk_stream(cs, n_chunks, k, chunk, L, sel, spans, n_spans);
 }
 
 template <int R>

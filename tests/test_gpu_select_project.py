@@ -94,6 +94,21 @@ def test_select_exact_ties_take_lower_index():
     np.testing.assert_array_equal(sel, [0, 1, 2, 3, 4])
 
 
+@pytest.mark.parametrize("C", [1, 63, 64, 65, 1023, 1024, 1025, 2047, 2048, 2049, 8191, 8192, 8193])
+def test_select_at_the_edges_of_the_bit_string(C):
+    """Chunk counts around the 64-chunk words, the 1024-chunk segments and the two sizes held in registers;
+    ties on both sides of every edge, all counts to keep at its ends (chunk = pool = 1: scores are the chunk scores)."""
+    from gpu_util import gpu_select
+    rng = np.random.default_rng(C)
+    say(f"[select] words C={C}")
+    for vals in (rng.integers(-2, 3, size=C).astype(np.float32), np.zeros(C, np.float32), rng.standard_normal(C).astype(np.float32)):
+        for k in sorted({1, C // 2 + 1, max(C - 1, 1), C}):
+            sel, spans, _ = gpu_select(vals, 1, 1, k)
+            want = oracle.topk(vals.astype(np.float64), k)
+            np.testing.assert_array_equal(sel, want)
+            np.testing.assert_array_equal(spans, oracle.merge(want, 1, C))
+
+
 def test_select_without_chunk_score_output_and_determinism():
     from gpu_util import gpu_select
     say("[select] no chunk-score output")
