@@ -685,9 +685,11 @@ bool pair_applies(const Plan &p, int64_t L, int64_t k_stride_token)
 
 // 8-bit keys: the single-launch kernel's variants for them fetch the codes in 16-byte pieces (strides in
 // multiples of 16 elements).
+bool fp8_strides_ok(const sp_score_desc *desc) { return desc->k_stride_token % 16 == 0 && desc->k_stride_head % 16 == 0; }
+
 bool fused_applies_fp8(const Plan &p, const sp_score_desc *desc, int64_t L)
 {
-    return desc->k_stride_token % 16 == 0 && desc->k_stride_head % 16 == 0 && fused_applies(p, L, desc->k_stride_token);
+    return fp8_strides_ok(desc) && fused_applies(p, L, desc->k_stride_token);
 }
 
 // A ragged batch on the single-launch kernel: the prompts are packed into launches of at most one
@@ -964,12 +966,8 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
         SP_HIP_CHECK(hipGetLastError());
         a.look = look;
     }
-    // 8-bit keys outside the single-launch kernel's variant for them take the three-kernel path
-    const bool fp8_fused = opt.kscale && !batch && fused_applies_fp8(p, desc, total);
-    if (opt.kscale && !fp8_fused) {
-        if (p.D == 64) return launch_all<64, 2, true>(p, a, kp, st);
-        return launch_all<128, 1, true>(p, a, kp, st);
-    }
+    // the single-launch kernel fetches 8-bit keys in 16-byte pieces
+    const bool may_fuse = !opt.kscale || fp8_strides_ok(desc);
     sp_fused::FusedArgs f;
     std::memset(&f, 0, sizeof f);
     f.q = a.q;
@@ -977,6 +975,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     f.tile_keys = fused_tile(p);
     f.k_stride_token = a.k_stride_token;
     f.k_stride_head = a.k_stride_head;
+    f.kscale = opt.kscale;
     f.look = a.look;
     f.block_table = a.block_table;
     f.page_tokens = a.page_tokens;
@@ -988,19 +987,13 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     f.layer_agg = a.layer_agg;
     f.c = a.c; f.inv_c = a.inv_c; f.out_scale = a.out_scale;
     BatchGroups bg;
-    if (fp8_fused) {
-        f.L = total;
-        f.n_wg = fused_workgroups(p, total);
-        f.kscale = opt.kscale;
-        return sp_fused::launch(f, kp, nullptr, true, true, ws + w.fused, a.status, st);
-    }
-    if (!opt.kscale && !batch && pair_applies(p, total, desc->k_stride_token)) {
+    if (may_fuse && !batch && pair_applies(p, total, desc->k_stride_token)) {
         f.tile_keys = 2 * fused_tile(p);
         f.L = total;
         f.n_wg = (int)sp::ceil_div(total, f.tile_keys);
         return sp_fused::launch(f, kp, nullptr, true, true, ws + w.fused, a.status, st);
     }
-    bool fused = !opt.kscale && (batch ? plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg)
+    bool fused = may_fuse && (batch ? plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg)
                                        : plan_fused_prompt(p, total, desc->k_stride_token, bg));
     int ranges = 1;
     if (fused && bg.groups.size() == 1) {
@@ -1039,6 +1032,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
         a.tiles = tiles;
         a.prompt_tiles = pt;
     }
+    if (opt.kscale) return p.D == 64 ? launch_all<64, 2, true>(p, a, kp, st) : launch_all<128, 1, true>(p, a, kp, st);
     if (p.D == 64) return launch_all<64, 2>(p, a, kp, st);
     return launch_all<128, 1>(p, a, kp, st);
 }

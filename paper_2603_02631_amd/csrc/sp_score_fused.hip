@@ -366,6 +366,15 @@ __device__ __forceinline__ void phase_advance(PhaseCtr &c, int p_next, int n_pha
     }
 }
 
+// 8-bit keys: scale of a phase, through the scalar cache (the array is constant for the whole launch, and the
+// constant address space says so). As vector loads these values made the compiler wait for every tile load in
+// flight before their first use, in every step.
+__device__ __forceinline__ float key_scale(const FusedArgs &a, int phase)
+{
+    typedef const __attribute__((address_space(4))) float *scalar_ptr;
+    return reinterpret_cast<scalar_ptr>(reinterpret_cast<uintptr_t>(a.kscale))[phase];
+}
+
 // padded query row -> (group head, lookahead row); see the row order in sp_score.hip
 template <int NB>
 __device__ __forceinline__ bool row_valid(const FusedArgs &a, int row, int &g, int &n)
@@ -868,10 +877,11 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     constexpr uint32_t kElem = F8 ? 1u : 2u;                // bytes per key element
     const uint32_t stride_bytes = (uint32_t)a.k_stride_token * kElem;
     // 8-bit keys: the exponent's scale of a phase is c times that phase's key scale
-    const float c_stats = F8 ? a.c * a.kscale[clampi(ps, 0, n_phases - 1)] : a.c;
-    const float c_pub = F8 ? a.c * a.kscale[clampi(pp, 0, n_phases - 1)] : a.c;
-    const float c_duty = F8 ? a.c * a.kscale[clampi(pd, 0, n_phases - 1)] : a.c;
-    const float ks_prob = F8 ? a.kscale[clampi(pc, 0, n_phases - 1)] : 1.f;
+    const float c_stats = F8 ? a.c * key_scale(a, clampi(ps, 0, n_phases - 1)) : a.c;
+    const float c_pub = F8 ? a.c * key_scale(a, clampi(pp, 0, n_phases - 1)) : a.c;
+    const float c_duty = F8 ? a.c * key_scale(a, clampi(pd, 0, n_phases - 1)) : a.c;
+    const float c_direct = F8 ? a.c * key_scale(a, clampi(pl, 0, n_phases - 1)) : a.c;
+    const float ks_prob = F8 ? key_scale(a, clampi(pc, 0, n_phases - 1)) : 1.f;
     // Duty blocks of a phase: kDutyRows consecutive rows of one entry. Block i goes to workgroup dfirst + i of the
     // launch, so that the duties of small prompts rotate over everybody (that keeps the prompts within a few
     // phases of each other: every phase of one needs a duty workgroup, which needs that phase of it); RANGES: of
@@ -1049,7 +1059,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         float direct_v = 0.f;
         if (RANGES && direct && pl >= 0 && pl < n_phases)
             direct_v = direct_combine<NB, GB>(a, a.part + ((size_t)(pl % kSlots) * a.n_wg + a.ent_w0) * kRowsPad, a.ent_n,
-                                              (uint32_t)(pl / kSlots) & 1u, lds0, fail, lane, a.c, a.inv_c);
+                                              (uint32_t)(pl / kSlots) & 1u, lds0, fail, lane, c_direct, F8 ? 1.0f / c_direct : a.inv_c);
         if (pl >= 0 && pl < n_phases && lane < a.rows_pad) {
             int g, n;
             float v = neg_inf();
@@ -1152,8 +1162,8 @@ template <int NB, int GB, Kind KIND, class M, bool W = false, bool F8 = false, b
 __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, LayerPtrs kp, GroupTable gt)
 {
     static_assert(!W || (NB == 1 && GB == 1 && !M::kFixed), "head_dim 128: one block of 32 query rows");
-    static_assert(!F8 || KIND == kPlain, "8-bit keys: plain variants only");
-    static_assert(!PAIR || (!F8 && NB == 1 && KIND != kRanges), "pairs of tiles: whole prompts, one block of lookahead rows");
+    static_assert(!F8 || KIND != kExtra, "8-bit keys: contiguous keys of one prompt");
+    static_assert(!PAIR || (NB == 1 && KIND != kRanges), "pairs of tiles: whole prompts, one block of lookahead rows");
     constexpr bool EXTRA = KIND != kPlain, RANGES = KIND == kRanges;
     constexpr int kSI = F8 ? kSubInstr / 2 : kSubInstr;
     constexpr uint32_t kElem = F8 ? 1u : 2u;
@@ -1195,6 +1205,7 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
             a.ent_w0 = gt.w0[p];
             a.ent_n = gt.w0[p + 1] - a.ent_w0;
             a.phase0 = layer0 * a.n_kv_heads;
+            if (F8) a.kscale += a.phase0;
             // a range of the maximum over layers stays open: its rows' maxima are the result
             a.last_layer = a.split_out != nullptr ? -1 : layer0 + gt.layers[p] - 1;
         }
@@ -1450,13 +1461,19 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
     const int blocks = a.n_nblk * 10 + a.n_gblk;
     if (a.head_dim == 2 * kD ? blocks != 11 : blocks != 11 && blocks != 12 && blocks != 21)
         return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, head_dim %d: %d x %d row blocks", a.head_dim, a.n_nblk, a.n_gblk);
-    if (a.kscale != nullptr && extra) return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, 8-bit keys: one prompt, contiguous keys only");
+    if (a.kscale != nullptr && extra && !(ranges && a.look == nullptr && a.block_table == nullptr))
+        return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, 8-bit keys: one prompt, contiguous keys only");
     // the fixed-model instantiations apply when every folded constant equals the call's value
     const bool draft = a.head_dim == kD && a.n_layers == 16 && a.n_q_heads == 32 && a.n_kv_heads == 8 && a.k_stride_token == kD &&
                        a.c == kScaleEighthLog2e && a.inv_c == 1.0f / kScaleEighthLog2e;
     if (pair) {
-        if (a.kscale != nullptr || gt.n > 0 || a.n_nblk != 1)
-            return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, two tiles a workgroup: one prompt, bf16 keys, up to 8 lookahead rows");
+        if (gt.n > 0 || a.n_nblk != 1)
+            return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, two tiles a workgroup: one prompt, up to 8 lookahead rows");
+        if (a.kscale != nullptr) {
+            if (a.head_dim == 2 * kD) SP_FUSED(1, 1, kPlain, AnyModel, true, true, true);
+            else if (blocks == 12) SP_FUSED(1, 2, kPlain, AnyModel, false, true, true);
+            else SP_FUSED(1, 1, kPlain, AnyModel, false, true, true);
+        } else
         if (a.head_dim == 2 * kD && extra) SP_FUSED(1, 1, kExtra, AnyModel, true, false, true);
         else if (a.head_dim == 2 * kD) SP_FUSED(1, 1, kPlain, AnyModel, true, false, true);
         else if (blocks == 12 && extra) SP_FUSED(1, 2, kExtra, AnyModel, false, false, true);
@@ -1465,7 +1482,11 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
         else if (draft && a.n_q == 8) SP_FUSED(1, 1, kPlain, Draft8, false, false, true);
         else SP_FUSED(1, 1, kPlain, AnyModel, false, false, true);
     } else if (a.kscale != nullptr) {       // 8-bit keys
-        if (a.head_dim == 2 * kD) SP_FUSED(1, 1, kPlain, AnyModel, true, true);
+        if (ranges && a.head_dim == 2 * kD) SP_FUSED(1, 1, kRanges, AnyModel, true, true);
+        else if (ranges && blocks == 21) SP_FUSED(2, 1, kRanges, AnyModel, false, true);
+        else if (ranges && blocks == 12) SP_FUSED(1, 2, kRanges, AnyModel, false, true);
+        else if (ranges) SP_FUSED(1, 1, kRanges, AnyModel, false, true);
+        else if (a.head_dim == 2 * kD) SP_FUSED(1, 1, kPlain, AnyModel, true, true);
         else if (draft && a.n_q == 16 && a.n_wg == 256) SP_FUSED(2, 1, kPlain, Draft16x32x8<16, 256>, false, true);
         else if (draft && a.n_q == 16) SP_FUSED(2, 1, kPlain, Draft16, false, true);
         else if (draft && a.n_q == 8) SP_FUSED(1, 1, kPlain, Draft8, false, true);

@@ -42,6 +42,15 @@ FP8_SHAPES = [
     ("fp8_fused_draft_model_nq8", 16, 32, 8, 64, 8, 33000),
     ("fp8_fused_draft_model_nq16", 16, 32, 8, 64, 16, 32768 + 513),
     ("fp8_fused_draft_model_nq16_full_grid", 16, 32, 8, 64, 16, 131072 - 100),
+    # layers in ranges side by side (short prompts), and two tiles a workgroup (long ones)
+    ("fp8_ranges_draft_model_nq8", 16, 32, 8, 64, 8, 6200),
+    ("fp8_ranges_rows64", 16, 32, 8, 64, 16, 8200),
+    ("fp8_ranges_two_gblocks", 12, 32, 4, 64, 8, 14000),
+    ("fp8_ranges_d128_uneven", 7, 8, 4, 128, 8, 13001),
+    ("fp8_ranges_d128_direct", 28, 16, 8, 128, 8, 1700),
+    ("fp8_pair", 2, 4, 1, 64, 8, 131073),
+    ("fp8_pair_two_gblocks", 1, 16, 2, 64, 5, 140000),
+    ("fp8_pair_d128", 1, 4, 2, 128, 8, 65536 + 300),
 ]
 
 
