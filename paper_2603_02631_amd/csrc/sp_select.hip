@@ -3,11 +3,9 @@
 // "MergeAdjacentChunks"; Appendix A.1.2; Appendix A.3).
 //
 // Two kernels:
-//   sp_chunk_kernel  one wavefront per chunk. The wave stages the chunk's
-//                    scores plus a (w-1)/2 halo through its own LDS slice in
-//                    segments, each lane forms the window sums of four
-//                    consecutive tokens, and a fixed-order shuffle tree gives
-//                    the chunk mean. The pooled vector is never written out.
+//   sp_chunk_kernel  one wavefront per chunk: the mean of the chunk's window
+//                    sums as one weighted sum, reduced by a fixed-order shuffle
+//                    tree. The pooled vector is never written out.
 //   sp_topk_kernel   one workgroup. MSB-first radix select (4 passes of 8 bits)
 //                    on order-preserving integer images of the fp32 chunk
 //                    scores finds the k-th largest score exactly; chunks above
@@ -44,57 +42,81 @@
 namespace {
 
 constexpr int kChunkThreads = 256;           // 4 waves, one chunk each
-constexpr int kSeg = 256;                    // tokens staged per wave per step
-constexpr int kMaxPool = 129;                // halo (w-1)/2 <= 64 fits the staging slice
-constexpr int kSegLds = kSeg + kMaxPool - 1; // staged floats per wave
+constexpr int kMaxPool = 129;
 constexpr int kTopkThreads = 1024;
+
+// Sum over the wave, the same in all lanes: four butterfly steps of data-parallel-primitive moves within the rows of
+// 16, then the four rows' sums (no trip through LDS as shuffles make).
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v)
+{
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float wave_sum(float v)
+{
+    v = dpp_add<0xB1>(v);           // quad_perm [1,0,3,2]
+    v = dpp_add<0x4E>(v);           // quad_perm [2,3,0,1]
+    v = dpp_add<0x141>(v);          // mirror within 8 lanes
+    v = dpp_add<0x140>(v);          // mirror within 16 lanes
+    auto row = [&](int lane) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane)); };
+    return (row(0) + row(16)) + (row(32) + row(48));
+}
+
+// Chunk scores of chunks ci, ci + stride, .. (N of them, those past the last excepted) by one wave, the same in all
+// lanes. The mean of the chunk's window sums is a weighted sum of its tokens and the (w - 1) / 2 on either side, a
+// token's weight being the number of the chunk's windows that contain it: one load and one fma per token instead
+// of pool_w additions, nothing staged.
+template <int N>
+__device__ __forceinline__ void chunk_means(const float *__restrict__ scores, int64_t L, int pool_w, int chunk, int64_t n_chunks,
+                                            int64_t ci, int stride, float (&mean)[N])
+{
+    const int lane = threadIdx.x & 63, half = (pool_w - 1) / 2;
+    const float *src[N];            // the first token's score; positions below count from half tokens before it
+    int size[N], lo[N], hi[N];
+    int n_tok = 0;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const int64_t begin = (ci + u * stride) * chunk;
+        const bool live = ci + u * stride < n_chunks;
+        size[u] = live ? (int)(begin + chunk < L ? chunk : L - begin) : 1;
+        src[u] = scores + (live ? begin : 0);
+        lo[u] = begin < half ? half - (int)begin : 0;                       // tokens before the prompt are zeros,
+        hi[u] = live ? size[u] + half + (int)(L - begin - size[u] < half ? L - begin - size[u] : half) : 0;     // and those behind it
+        n_tok = hi[u] > n_tok ? hi[u] : n_tok;
+        mean[u] = 0.f;
+    }
+    for (int t = lane; t < n_tok; t += 64) {
+        float v[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) v[u] = t >= lo[u] && t < hi[u] ? src[u][t - half] : 0.f;
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            // windows centred on this chunk's tokens t - 2 half .. t contain the token
+            const int first = t - 2 * half > 0 ? t - 2 * half : 0, last = t < size[u] - 1 ? t : size[u] - 1;
+            mean[u] = fmaf((float)(last - first + 1), v[u], mean[u]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) mean[u] = wave_sum(mean[u]) / ((float)pool_w * (float)size[u]) + 0.0f;
+}
 
 __device__ __forceinline__ void chunk_body(const float *__restrict__ scores, int64_t L, int pool_w, int chunk,
                                            int64_t n_chunks, float *__restrict__ cs_ws, float *__restrict__ cs_out,
                                            const int64_t *__restrict__ draft_off, int64_t *__restrict__ bnd,
                                            int32_t *__restrict__ rank, int32_t *__restrict__ hist)
 {
-    __shared__ float stage[kChunkThreads / 64][kSegLds + 3];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t ci = (int64_t)blockIdx.x * (kChunkThreads / 64) + wave;
     if (ci >= n_chunks) return;              // whole wave leaves together; no block barrier is used
-    float *st = stage[wave];
-    const int half = (pool_w - 1) / 2;
-    const int64_t begin = ci * chunk;
-    const int64_t end = (begin + chunk < L) ? begin + chunk : L;
-    float part = 0.f;
-    for (int64_t seg = begin; seg < end; seg += kSeg) {
-        const int n_tok = (int)((end - seg < kSeg) ? end - seg : kSeg);
-        const int n_stage = n_tok + 2 * half;
-        for (int i = lane; i < n_stage; i += 64) {
-            const int64_t j = seg - half + i;
-            st[i] = (j >= 0 && j < L) ? scores[j] : 0.f;
-        }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        // lane handles tokens 4*lane .. 4*lane+3 of the segment; each window is summed on its own
-        const int t0 = 4 * lane;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (t0 + e < n_tok) {
-                float win = 0.f;
-                for (int i = 0; i < pool_w; ++i) win += st[t0 + e + i];
-                part += win;
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) part += __shfl_xor(part, off);
+    float v[1];
+    chunk_means<1>(scores, L, pool_w, chunk, n_chunks, ci, 0, v);
     if (lane == 0) {
-        const float v = part / ((float)pool_w * (float)(end - begin)) + 0.0f;
-        cs_ws[ci] = v;
-        if (cs_out) cs_out[ci] = v;
+        cs_ws[ci] = v[0];
+        if (cs_out) cs_out[ci] = v[0];
         if (bnd) {
             // set-up for the budget search: character offset of the chunk's first token (one more entry:
             // the end of the text), cleared rank counters and histogram bins (one more: "never kept")
-            bnd[ci] = draft_off[begin];
+            bnd[ci] = draft_off[ci * chunk];
             rank[ci] = 0;
             hist[ci] = 0;
             if (ci == n_chunks - 1) {
@@ -258,8 +280,8 @@ __device__ __forceinline__ uint64_t lowest_bits(uint64_t x, int64_t n)
 // its runs are the spans, and every thread writes its own chunks' entries; nothing written is read back.
 // Bound by its chain of dependent steps: the workgroup reads 8 KB. With a block scan per 1024 chunks, the kept
 // indices read back for the spans, and four passes of the radix select always, 2048 chunks took 11 us.
-template <int R>
-__device__ __forceinline__ void topk_words(const float *__restrict__ cs, int64_t n_chunks, int64_t k, int chunk, int64_t L,
+template <int R, class Score>
+__device__ __forceinline__ void topk_words(const Score &score, int64_t n_chunks, int64_t k, int chunk, int64_t L,
                                            int32_t *__restrict__ sel, int64_t *__restrict__ spans, int32_t *__restrict__ n_spans)
 {
     constexpr int kWords = R * kTopkThreads / 64;
@@ -271,7 +293,7 @@ __device__ __forceinline__ void topk_words(const float *__restrict__ cs, int64_t
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int64_t i = (int64_t)r * kTopkThreads + tid;
-        key[r] = i < n_chunks ? order_key(cs[i]) : 0u;
+        key[r] = i < n_chunks ? order_key(score(i)) : 0u;
     }
     const Threshold t = radix_select(k, [&](auto &&f) {
 #pragma unroll
@@ -403,7 +425,7 @@ __device__ __forceinline__ void topk_body(const float *__restrict__ cs, int64_t 
         k = *k_dev;
         k = k < 1 ? 1 : (k > n_chunks ? n_chunks : k);
     }
-    if constexpr (R > 0) topk_words<R>(cs, n_chunks, k, chunk, L, sel, spans, n_spans);
+    if constexpr (R > 0) topk_words<R>([&](int64_t i) { return cs[i]; }, n_chunks, k, chunk, L, sel, spans, n_spans);
     else topk_stream(cs, n_chunks, k, chunk, L, sel, spans, n_spans);
 }
 
@@ -415,6 +437,66 @@ __global__ __launch_bounds__(kTopkThreads) void sp_topk_kernel(const float *__re
                                                                int32_t *__restrict__ n_spans)
 {
     topk_body<R>(cs, n_chunks, k, k_dev, chunk, L, sel, spans, n_spans);
+}
+
+// Short prompts: chunk scores and selection by one workgroup, the scores through LDS.
+constexpr int kOneChunks = 2 * kTopkThreads;
+
+__device__ __forceinline__ void select_one_body(const float *__restrict__ scores, int64_t L, int pool_w, int chunk,
+                                                int64_t n_chunks, int64_t k, float *__restrict__ cs_out, int32_t *__restrict__ sel,
+                                                int64_t *__restrict__ spans, int32_t *__restrict__ n_spans)
+{
+    constexpr int kWaves = kTopkThreads / 64, kUnroll = 4;       // chunks of a wave in flight
+    __shared__ float cs[kOneChunks];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int64_t c0 = wave; c0 < n_chunks; c0 += kWaves * kUnroll) {
+        float v[kUnroll];
+        chunk_means<kUnroll>(scores, L, pool_w, chunk, n_chunks, c0, kWaves, v);
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u)
+            if (lane == u && c0 + u * kWaves < n_chunks) cs[c0 + u * kWaves] = v[u];
+    }
+    __syncthreads();
+    if (cs_out)
+        for (int64_t i = threadIdx.x; i < n_chunks; i += kTopkThreads) cs_out[i] = cs[i];
+    topk_words<kOneChunks / kTopkThreads>([&](int64_t i) { return cs[i]; }, n_chunks, k, chunk, L, sel, spans, n_spans);
+}
+
+__global__ __launch_bounds__(kTopkThreads) void sp_select_one_kernel(const float *__restrict__ scores, int64_t L, int pool_w,
+                                                                     int chunk, int64_t n_chunks, int64_t k,
+                                                                     float *__restrict__ cs_out, int32_t *__restrict__ sel,
+                                                                     int64_t *__restrict__ spans, int32_t *__restrict__ n_spans)
+{
+    select_one_body(scores, L, pool_w, chunk, n_chunks, k, cs_out, sel, spans, n_spans);
+}
+
+__global__ __launch_bounds__(kTopkThreads) void sp_select_one_batch_kernel(const float *__restrict__ scores,
+                                                                           const int64_t *__restrict__ off, int pool_w,
+                                                                           const int64_t *__restrict__ kept_off, int chunk,
+                                                                           float *__restrict__ cs_out, int32_t *__restrict__ sel,
+                                                                           int64_t *__restrict__ spans,
+                                                                           int32_t *__restrict__ n_spans)
+{
+    const int b = blockIdx.x;
+    const int64_t o = off[b], L = off[b + 1] - o;
+    const int64_t n_chunks = (L + chunk - 1) / chunk;
+    const int64_t k0 = kept_off[b];
+    int64_t k = kept_off[b + 1] - k0;
+    if (n_chunks == 0 || k < 1) {            // uniform
+        if (threadIdx.x == 0) n_spans[b] = 0;
+        return;
+    }
+    k = k > n_chunks ? n_chunks : k;
+    select_one_body(scores + o, L, pool_w, chunk, n_chunks, k, cs_out ? cs_out + batch_chunk_slot(o, b, chunk) : nullptr, sel + k0,
+                    spans + 2 * k0, n_spans + b);
+}
+
+// Whether one workgroup does a prompt: a wave takes every 16th chunk, 64 tokens a load. Four loads a wave (2048
+// tokens in chunks of 32) take no longer than the two launches on the device and spare the host one of them (1024
+// tokens: 6.2 against 6.4 us, called back to back 9.7 against 12.2); sixteen (8192 tokens) take 12.7 against 7.3 us.
+bool one_workgroup(int64_t n_chunks, int chunk, int pool_w)
+{
+    return n_chunks <= kOneChunks && sp::ceil_div(n_chunks, kTopkThreads / 64) * sp::ceil_div((int64_t)chunk + pool_w - 1, 64) <= 4;
 }
 
 // Ragged batch: one workgroup per prompt; prompt b keeps k_b = kept_off[b+1] - kept_off[b] chunks and
@@ -634,6 +716,12 @@ sp_status select_launch(const float *scores_dev, int64_t L, int32_t pool_w, int3
                         int32_t *sel_chunks_dev, int64_t *spans_dev, int32_t *n_spans_dev, float *chunk_scores_dev,
                         float *cs, hipStream_t st)
 {
+    if (one_workgroup(C, chunk, pool_w)) {
+        hipLaunchKernelGGL(sp_select_one_kernel, dim3(1), dim3(kTopkThreads), 0, st, scores_dev, L, (int)pool_w, (int)chunk, C, k,
+                           chunk_scores_dev, sel_chunks_dev, spans_dev, n_spans_dev);
+        SP_HIP_CHECK(hipGetLastError());
+        return SP_OK;
+    }
     const int waves_per_block = kChunkThreads / 64;
     const unsigned grid = (unsigned)((C + waves_per_block - 1) / waves_per_block);
     hipLaunchKernelGGL(sp_chunk_kernel, dim3(grid), dim3(kChunkThreads), 0, st, scores_dev, L, (int)pool_w,
@@ -718,6 +806,12 @@ extern "C" sp_status sp_select_batch(const float *scores_dev, const int64_t *off
     if (max_chunks == 0) max_chunks = 1;     // all prompts empty: the top-k launch still writes n_spans = 0
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     float *cs = static_cast<float *>(ws_dev);
+    if (one_workgroup(max_chunks, chunk, pool_w)) {
+        hipLaunchKernelGGL(sp_select_one_batch_kernel, dim3((unsigned)B), dim3(kTopkThreads), 0, st, scores_dev, offsets_dev,
+                           (int)pool_w, kept_off_dev, (int)chunk, chunk_scores_dev, sel_chunks_dev, spans_dev, n_spans_dev);
+        SP_HIP_CHECK(hipGetLastError());
+        return SP_OK;
+    }
     const int waves_per_block = kChunkThreads / 64;
     hipLaunchKernelGGL(sp_chunk_batch_kernel, dim3((unsigned)sp::ceil_div(max_chunks, waves_per_block), (unsigned)B),
                        dim3(kChunkThreads), 0, st, scores_dev, offsets_dev, (int)pool_w, (int)chunk, cs, chunk_scores_dev);
