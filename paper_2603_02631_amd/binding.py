@@ -121,6 +121,12 @@ def _ptr(t, what: str = "buffer", nbytes: int = 0) -> Optional[int]:
     A tensor is checked before its address leaves Python: it has to live on the GPU, be contiguous
     and hold at least ``nbytes`` bytes (what the call will read or write), so that a short or
     host-side buffer becomes an :class:`SpError` instead of an out-of-bounds device access."""
+    # a good tensor takes four attribute reads: a call of a dozen pointers costs more here than in its launches
+    try:
+        if t.is_cuda and t.is_contiguous() and t.nbytes >= nbytes:
+            return t.data_ptr()
+    except AttributeError:
+        pass
     if t is None:
         return None
     if isinstance(t, int):
@@ -146,10 +152,17 @@ def _k_bytes(desc: "ScoreDesc", tokens: int) -> int:
     return ((desc.n_kv_heads - 1) * desc.k_stride_head + (tokens - 1) * desc.k_stride_token + desc.head_dim) * 2
 
 
+_raw_stream = None      # (device index -> raw stream, -> current device index) of torch, resolved at the first use
+
+
 def _stream(stream) -> Optional[int]:
+    global _raw_stream
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream or None
+        if _raw_stream is None:
+            import torch
+            torch.cuda.init()
+            _raw_stream = (torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+        return _raw_stream[0](_raw_stream[1]()) or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None
