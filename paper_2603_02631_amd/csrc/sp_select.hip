@@ -29,11 +29,13 @@
 //   sp_chunk_kernel       also leaves the chunk boundaries' character offsets in a
 //                         compact array and clears the counters of the next two;
 //   sp_rank_kernel        rank of every chunk by counting: tiles of 256 chunks
-//                         against tiles of 256 chunks, one workgroup per pair;
-//   sp_token_rank_kernel  one thread per target token: binary searches of the
+//                         against tiles of 64 chunks, one workgroup per pair;
+//   sp_token_rank_kernel  one thread per target token: binary search of the
 //                         compact boundary array, r(t), histogram;
-//   sp_budget_kernel      one workgroup: prefix sum, largest k within the budget;
-//   sp_topk_kernel        as above, reading k from device memory.
+//   sp_budget_select_kernel  one workgroup: prefix sum, largest k within the
+//                         budget, and the chunks of rank < k with their spans.
+// Beyond 8192 chunks the last one is two: sp_budget_kernel for k, and
+// sp_topk_kernel as above, reading k from device memory.
 #include "sp_common.hpp"
 
 #include <algorithm>
@@ -275,35 +277,23 @@ __device__ __forceinline__ uint64_t lowest_bits(uint64_t x, int64_t n)
     return x;
 }
 
-// Up to R * 1024 chunks, whose keys stay in registers. The kept set is a bit string in LDS, 64 chunks a word:
-// one wave decides the ties and turns the words' population counts into output positions, the starts and ends of
-// its runs are the spans, and every thread writes its own chunks' entries; nothing written is read back.
-// Bound by its chain of dependent steps: the workgroup reads 8 KB. With a block scan per 1024 chunks, the kept
-// indices read back for the spans, and four passes of the radix select always, 2048 chunks took 11 us.
-template <int R, class Score>
-__device__ __forceinline__ void topk_words(const Score &score, int64_t n_chunks, int64_t k, int chunk, int64_t L,
-                                           int32_t *__restrict__ sel, int64_t *__restrict__ spans, int32_t *__restrict__ n_spans)
+// Kept chunks and merged spans of up to R * 1024 chunks; chunk r * 1024 + thread is kept if gt[r], or if eq[r] and
+// it is among the first `need` of those in index order. The kept set is a bit string in LDS, 64 chunks a word: one
+// wave decides the ties and turns the words' population counts into output positions, the starts and ends of its
+// runs are the spans, and every thread writes its own chunks' entries; nothing written is read back.
+template <int R>
+__device__ __forceinline__ void emit_kept(const bool (&gt)[R], const bool (&eq)[R], int64_t need, int chunk, int64_t L,
+                                          int32_t *__restrict__ sel, int64_t *__restrict__ spans, int32_t *__restrict__ n_spans)
 {
     constexpr int kWords = R * kTopkThreads / 64;
     static_assert(kWords <= 128, "two words a lane");
     __shared__ uint64_t s_gt[kWords], s_eq[kWords], s_start[kWords], s_end[kWords];
     __shared__ int32_t s_pos[kWords], s_id[kWords];       // kept chunks and spans before the word
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t key[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int64_t i = (int64_t)r * kTopkThreads + tid;
-        key[r] = i < n_chunks ? order_key(score(i)) : 0u;
-    }
-    const Threshold t = radix_select(k, [&](auto &&f) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) f(key[r], (int64_t)r * kTopkThreads + tid < n_chunks);
-    });
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const bool live = (int64_t)r * kTopkThreads + tid < n_chunks;
-        const uint64_t gt = __ballot(live && (key[r] & t.mask) > t.prefix), eq = __ballot(live && (key[r] & t.mask) == t.prefix);
-        if (lane == 0) { s_gt[r * (kTopkThreads / 64) + wave] = gt; s_eq[r * (kTopkThreads / 64) + wave] = eq; }
+        const uint64_t g = __ballot(gt[r]), e = __ballot(eq[r]);
+        if (lane == 0) { s_gt[r * (kTopkThreads / 64) + wave] = g; s_eq[r * (kTopkThreads / 64) + wave] = e; }
     }
     __syncthreads();
     if (wave == 0) {
@@ -316,7 +306,7 @@ __device__ __forceinline__ void topk_words(const Score &score, int64_t n_chunks,
             const int y = __shfl_up(ei, off);
             if (lane >= off) ei += y;
         }
-        const int64_t room = t.need - (ei - e);           // equal keys still to keep from this lane's first word on
+        const int64_t room = need - (ei - e);           // equal keys still to keep from this lane's first word on
         const uint64_t k0 = (has ? s_gt[2 * lane] : 0) | lowest_bits(q0, room);
         const uint64_t k1 = (has ? s_gt[2 * lane + 1] : 0) | lowest_bits(q1, room - e0);
         int before = __shfl_up((int)(k1 >> 63), 1), after = __shfl_down((int)(k0 & 1), 1);
@@ -354,6 +344,34 @@ __device__ __forceinline__ void topk_words(const Score &score, int64_t n_chunks,
         if ((start >> lane) & 1) spans[2 * id] = i * chunk;
         if ((s_end[w] >> lane) & 1) spans[2 * id + 1] = (i + 1) * chunk < L ? (i + 1) * chunk : L;
     }
+}
+
+// Up to R * 1024 chunks, whose keys stay in registers.
+// Bound by its chain of dependent steps: the workgroup reads 8 KB. With a block scan per 1024 chunks, the kept
+// indices read back for the spans, and four passes of the radix select always, 2048 chunks took 11 us instead of 8.
+template <int R, class Score>
+__device__ __forceinline__ void topk_words(const Score &score, int64_t n_chunks, int64_t k, int chunk, int64_t L,
+                                           int32_t *__restrict__ sel, int64_t *__restrict__ spans, int32_t *__restrict__ n_spans)
+{
+    const int tid = threadIdx.x;
+    uint32_t key[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t i = (int64_t)r * kTopkThreads + tid;
+        key[r] = i < n_chunks ? order_key(score(i)) : 0u;
+    }
+    const Threshold t = radix_select(k, [&](auto &&f) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) f(key[r], (int64_t)r * kTopkThreads + tid < n_chunks);
+    });
+    bool gt[R], eq[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const bool live = (int64_t)r * kTopkThreads + tid < n_chunks;
+        gt[r] = live && (key[r] & t.mask) > t.prefix;
+        eq[r] = live && (key[r] & t.mask) == t.prefix;
+    }
+    emit_kept<R>(gt, eq, t.need, chunk, L, sel, spans, n_spans);
 }
 
 // Any number of chunks, their scores read again in every pass.
@@ -528,24 +546,25 @@ constexpr int kRankThreads = 256;
 constexpr int kMaxBudgetChunks = 1 << 16;
 
 // rank[j] = number of chunks that come before chunk j in the order (score descending, index
-// ascending). Workgroup (x, y) counts, for the 256 chunks of tile x, the chunks of tile y that come
-// before them and adds the counts to rank (cleared beforehand): C^2 comparisons over (C / 256)^2
-// workgroups.
+// ascending). Workgroup (x, y) counts, for the 256 chunks of tile x, the 64 chunks of tile y that come
+// before them and adds the counts to rank (cleared beforehand): C^2 comparisons over C^2 / 2^14
+// workgroups (2048 chunks: 256; with tiles of 256 x 256 they were 64, and 8.4 us).
+constexpr int kRankTile = 64;
 __global__ __launch_bounds__(kRankThreads) void sp_rank_kernel(const float *__restrict__ cs, int n_chunks,
                                                                int32_t *__restrict__ rank)
 {
-    __shared__ uint4 tile[kRankThreads / 4];
+    __shared__ uint4 tile[kRankTile / 4];
     const int j = blockIdx.x * kRankThreads + threadIdx.x;
-    const int base = blockIdx.y * kRankThreads;
-    const int i = base + threadIdx.x;
+    const int base = blockIdx.y * kRankTile;
     // entries past the last chunk get key 0, the image of no finite score: they never count
-    reinterpret_cast<uint32_t *>(tile)[threadIdx.x] = i < n_chunks ? order_key(cs[i]) : 0u;
+    if (threadIdx.x < kRankTile)
+        reinterpret_cast<uint32_t *>(tile)[threadIdx.x] = base + (int)threadIdx.x < n_chunks ? order_key(cs[base + threadIdx.x]) : 0u;
+    const uint32_t mine = j < n_chunks ? order_key(cs[j]) : 0u;
     __syncthreads();
     if (j >= n_chunks) return;
-    const uint32_t mine = order_key(cs[j]);
     int before = 0;
-#pragma unroll 4
-    for (int t = 0; t < kRankThreads / 4; ++t) {
+#pragma unroll
+    for (int t = 0; t < kRankTile / 4; ++t) {
         const uint4 o = tile[t];
         const int i0 = base + 4 * t;
         before += (o.x > mine) || (o.x == mine && i0 < j);
@@ -556,50 +575,52 @@ __global__ __launch_bounds__(kRankThreads) void sp_rank_kernel(const float *__re
     if (before) atomicAdd(&rank[j], before);
 }
 
-// Character offset of chunk boundary m (0 .. C; boundary C is the end of the text), from the compact
-// array the chunk kernel has filled (a few KB: the searches below stay in the caches).
-__device__ __forceinline__ int64_t boundary(const int64_t *__restrict__ bnd, int64_t, int, int m) { return bnd[m]; }
-
 // First boundary index in [lo, hi] whose offset is > x (STRICT) or >= x; hi + 1 if none.
 template <bool STRICT>
-__device__ __forceinline__ int first_boundary(const int64_t *__restrict__ doff, int64_t L, int chunk, int lo, int hi,
-                                              int64_t x)
+__device__ __forceinline__ int first_boundary(const int64_t *bnd, int lo, int hi, int64_t x)
 {
     int a = lo, b = hi + 1;
     while (a < b) {
         const int mid = a + ((b - a) >> 1);
-        const int64_t e = boundary(doff, L, chunk, mid);
+        const int64_t e = bnd[mid];
         if (STRICT ? (e > x) : (e >= x)) b = mid; else a = mid + 1;
     }
     return a;
 }
 
-__global__ __launch_bounds__(kRankThreads) void sp_token_rank_kernel(const int64_t *__restrict__ doff, int64_t L,
-                                                                     int chunk, int n_chunks,
-                                                                     const int64_t *__restrict__ toff, int64_t M,
-                                                                     const int32_t *__restrict__ rank,
-                                                                     int32_t *__restrict__ hist)
+// LDS: the boundaries' offsets (up to kLdsBounds of them) are staged, so that the searches do not go to memory for
+// every step (2048 chunks: a search is 11 dependent loads).
+constexpr int kTokenThreads = 1024;
+constexpr int kLdsBounds = 4097;
+template <bool LDS>
+__global__ __launch_bounds__(kTokenThreads) void sp_token_rank_kernel(const int64_t *__restrict__ g_bnd, int n_chunks,
+                                                                      const int64_t *__restrict__ toff, int64_t M,
+                                                                      const int32_t *__restrict__ rank,
+                                                                      int32_t *__restrict__ hist)
 {
-    const int64_t t = (int64_t)blockIdx.x * kRankThreads + threadIdx.x;
+    __shared__ int64_t s_bnd[LDS ? kLdsBounds : 1];
+    const int64_t t = (int64_t)blockIdx.x * kTokenThreads + threadIdx.x;
     const bool live = t < M;
     const int64_t a = live ? toff[t] : 0, b = live ? toff[t + 1] : 0;
     const int C = n_chunks;
+    if (LDS) {
+        for (int i = threadIdx.x; i <= C; i += kTokenThreads) s_bnd[i] = g_bnd[i];
+        __syncthreads();
+    }
+    const int64_t *bnd = LDS ? s_bnd : g_bnd;
     int r = C;                                   // bin C: kept by no selection
     if (!live) {
         r = -1;
     } else if (b > a) {
         // chunks j with a < e[j+1] and b > e[j]: a contiguous range
-        const int j_lo = first_boundary<true>(doff, L, chunk, 1, C, a) - 1;        // first j with e[j+1] > a
-        const int j_hi = first_boundary<false>(doff, L, chunk, 0, C - 1, b) - 1;   // last j with e[j] < b
-        if (j_lo < C && j_hi >= 0)
-            for (int j = j_lo; j <= j_hi; ++j) r = min(r, rank[j]);
+        for (int j = first_boundary<true>(bnd, 1, C, a) - 1; j < C && bnd[j] < b; ++j) r = min(r, rank[j]);
     } else {
-        const int m1 = first_boundary<false>(doff, L, chunk, 0, C, a);             // first boundary >= a
+        const int m1 = first_boundary<false>(bnd, 0, C, a);                        // first boundary >= a
         if (m1 <= C && m1 >= 1) {
-            if (boundary(doff, L, chunk, m1) != a) {
+            if (bnd[m1] != a) {
                 r = rank[m1 - 1];                                                   // strictly inside chunk m1 - 1
             } else {
-                const int m2 = first_boundary<true>(doff, L, chunk, m1, C, a) - 1;  // last boundary == a
+                const int m2 = first_boundary<true>(bnd, m1, C, a) - 1;             // last boundary == a
                 if (m2 < C) {                    // chunks m1-1 .. m2 all have to be selected
                     int worst = 0;
                     for (int j = m1 - 1; j <= m2; ++j) worst = max(worst, rank[j]);
@@ -660,6 +681,56 @@ __global__ __launch_bounds__(kTopkThreads) void sp_budget_kernel(const int32_t *
         *k_out = within >= 1 ? within : 1;
         if (kept_out) *kept_out = within >= 1 ? kept_within : (int64_t)s_first;
     }
+}
+
+// The same with the selection itself, for up to R * 1024 chunks: chunk i is kept iff rank[i] < k. A thread holds R
+// consecutive bins, so one block scan does for all of them.
+template <int R>
+__global__ __launch_bounds__(kTopkThreads) void sp_budget_select_kernel(const int32_t *__restrict__ hist, const int32_t *__restrict__ rank,
+                                                                        int n_chunks, int64_t budget, int chunk, int64_t L,
+                                                                        int64_t *__restrict__ k_out, int64_t *__restrict__ kept_out,
+                                                                        int32_t *__restrict__ sel, int64_t *__restrict__ spans,
+                                                                        int32_t *__restrict__ n_spans)
+{
+    __shared__ int wave_tot[kTopkThreads / 64], wave_ok[kTopkThreads / 64], wave_best[kTopkThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int h[R], mine[R], sum = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        h[r] = tid * R + r < n_chunks ? hist[tid * R + r] : 0;
+        mine[r] = r * kTopkThreads + tid < n_chunks ? rank[r * kTopkThreads + tid] : n_chunks;
+        sum += h[r];
+    }
+    int total;
+    int kept = block_scan_incl(sum, wave_tot, total) - sum;               // kept(tid * R)
+    int ok = 0, best = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        kept += h[r];                                                     // kept(k) is monotone in k
+        if (tid * R + r < n_chunks && kept <= budget) { ++ok; best = kept; }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        ok += __shfl_xor(ok, off);
+        best = max(best, __shfl_xor(best, off));
+    }
+    if (lane == 0) { wave_ok[wave] = ok; wave_best[wave] = best; }
+    __syncthreads();
+    int within = 0, kept_within = 0;
+#pragma unroll
+    for (int w = 0; w < kTopkThreads / 64; ++w) {
+        within += wave_ok[w];
+        kept_within = max(kept_within, wave_best[w]);
+    }
+    const int k = within >= 1 ? within : 1;
+    if (tid == 0) {
+        *k_out = k;
+        if (kept_out) *kept_out = within >= 1 ? kept_within : h[0];
+    }
+    bool gt[R], eq[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) { gt[r] = mine[r] < k; eq[r] = false; }
+    emit_kept<R>(gt, eq, 0, chunk, L, sel, spans, n_spans);
 }
 
 void launch_topk(hipStream_t st, const float *cs, int64_t C, int64_t k, const int64_t *k_dev, int chunk, int64_t L,
@@ -927,12 +998,20 @@ extern "C" sp_status sp_select_budget(const float *scores_dev, int64_t L, int32_
                        dim3(kChunkThreads), 0, st, scores_dev, L, (int)pool_w, (int)chunk, C, cs, chunk_scores_dev,
                        draft_off_dev, bnd, rank, hist);
     SP_HIP_CHECK(hipGetLastError());
-    const unsigned n_tiles = (unsigned)((C + kRankThreads - 1) / kRankThreads);
-    hipLaunchKernelGGL(sp_rank_kernel, dim3(n_tiles, n_tiles), dim3(kRankThreads), 0, st, (const float *)cs, (int)C, rank);
+    hipLaunchKernelGGL(sp_rank_kernel, dim3((unsigned)sp::ceil_div(C, kRankThreads), (unsigned)sp::ceil_div(C, kRankTile)),
+                       dim3(kRankThreads), 0, st, (const float *)cs, (int)C, rank);
     SP_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(sp_token_rank_kernel, dim3((unsigned)((M + kRankThreads - 1) / kRankThreads)), dim3(kRankThreads),
-                       0, st, (const int64_t *)bnd, L, (int)chunk, (int)C, target_off_dev, M, (const int32_t *)rank, hist);
+    const auto token_rank = C < kLdsBounds ? sp_token_rank_kernel<true> : sp_token_rank_kernel<false>;
+    hipLaunchKernelGGL(token_rank, dim3((unsigned)sp::ceil_div(M, kTokenThreads)), dim3(kTokenThreads), 0, st,
+                       (const int64_t *)bnd, (int)C, target_off_dev, M, (const int32_t *)rank, hist);
     SP_HIP_CHECK(hipGetLastError());
+    if (C <= 8 * kTopkThreads) {
+        const auto budget_select = C <= 2 * kTopkThreads ? sp_budget_select_kernel<2> : sp_budget_select_kernel<8>;
+        hipLaunchKernelGGL(budget_select, dim3(1), dim3(kTopkThreads), 0, st, (const int32_t *)hist, (const int32_t *)rank, (int)C,
+                           budget, (int)chunk, L, k_dev, n_kept_dev, sel_chunks_dev, spans_dev, n_spans_dev);
+        SP_HIP_CHECK(hipGetLastError());
+        return SP_OK;
+    }
     hipLaunchKernelGGL(sp_budget_kernel, dim3(1), dim3(kTopkThreads), 0, st, (const int32_t *)hist, (int)C, budget, k_dev,
                        n_kept_dev);
     SP_HIP_CHECK(hipGetLastError());
