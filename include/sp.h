@@ -176,8 +176,9 @@ sp_status sp_score_fp8(const sp_score_desc *desc, const void *q_dev,
 /* Which implementation sp_score picks for this shape and length on the current
  * device: 1 = the single-launch kernel that keeps K on chip and reads it from
  * HBM once, 0 = the three-kernel path or, where that is faster, the single-launch
- * kernel with the layers in ranges side by side (shorter prompts) or with two tiles a
- * workgroup (longer ones); -1 = invalid or unsupported desc.
+ * kernel with the layers in ranges side by side (shorter prompts), with two tiles a
+ * workgroup (longer ones) or with two blocks of query rows at head_dim 128 (33 to 64
+ * padded rows, up to 8 lookahead rows); -1 = invalid or unsupported desc.
  * The single-launch kernel takes one workgroup per compute unit, each owning T keys:
  * head_dim 64: T = 512, query groups of up to 64 padded rows, 64 to 256
  * workgroups (about 32K to 128K tokens); head_dim 128: T = 256, up to 32 padded

@@ -631,11 +631,18 @@ struct WsLayout {
     size_t status, part, lse, tiles, prompt_tiles, split, look, fused, total;
 };
 
+// Two blocks of query rows at head_dim 128 (bf16 keys, one tile a workgroup): their exchange area always takes the
+// place of the general path's buffers, so the workspace is as large as without them.
+bool fused_big(const Plan &p) { return p.D == 128 && p.NB == 1 && p.n_gblk == 2; }
+
 // Shapes the fused single-launch kernel can hold on chip (any L; the length test is separate).
 bool fused_shape_ok(const Plan &p)
 {
-    return p.D == 64 ? p.rows_pad <= sp_fused::kMaxRows : p.rows_pad <= sp_fused::kMaxRowsWide;
+    return p.D == 64 ? p.rows_pad <= sp_fused::kMaxRows : p.rows_pad <= sp_fused::kMaxRowsWide || fused_big(p);
 }
+
+// The shapes sp_score_is_fused speaks of and the workspace reserves an exchange area for.
+bool fused_base_shape(const Plan &p) { return fused_shape_ok(p) && !fused_big(p); }
 
 // Keys a workgroup of the fused kernel owns: 512 at head_dim 64, 256 at head_dim 128 (twice the tile of
 // the two-pass path), and the fewest workgroups it is used with.
@@ -667,7 +674,7 @@ int device_compute_units()
 // The fused kernel runs one workgroup of 512 keys per compute unit: long single prompts only.
 bool fused_applies(const Plan &p, int64_t L, int64_t k_stride_token)
 {
-    if (!fused_shape_ok(p)) return false;
+    if (!fused_base_shape(p)) return false;
     if (k_stride_token > (int64_t(1) << 20)) return false;       // lane offsets within a tile are 32-bit
     const int n_wg = fused_workgroups(p, L);
     return n_wg >= fused_min_workgroups(p) && n_wg <= 256 && n_wg <= device_compute_units();
@@ -677,7 +684,7 @@ bool fused_applies(const Plan &p, int64_t L, int64_t k_stride_token)
 // x 8 kv heads, head_dim 64, 256K tokens: 897 us against 1510 on the three-kernel path).
 bool pair_applies(const Plan &p, int64_t L, int64_t k_stride_token)
 {
-    if (!fused_shape_ok(p) || p.NB != 1 || k_stride_token > (int64_t(1) << 20)) return false;
+    if (!fused_base_shape(p) || p.NB != 1 || k_stride_token > (int64_t(1) << 20)) return false;
     const int cus = std::min(256, device_compute_units());
     const int64_t tiles = sp::ceil_div(L, fused_tile(p));
     return cus >= 128 && tiles > cus && tiles <= 2 * (int64_t)cus;
@@ -759,7 +766,7 @@ int fused_ranges(const Plan &p, int tiles, int n_prompts, size_t room)
 
 // Batches the single-launch kernel takes whatever their size: every prompt fills a tile, and one range of
 // layers fills enough of the device.
-bool whole_groups_pay(const Plan &, const BatchGroups &bg)
+bool whole_groups_pay(const BatchGroups &bg)
 {
     return !bg.short_prompt && bg.tiles >= sp_fused::kMinWorkgroups;
 }
@@ -768,11 +775,12 @@ bool whole_groups_pay(const Plan &, const BatchGroups &bg)
 // beats the three-kernel path. A launch costs its steps (a range's phases and five more to fill and drain
 // the pipeline) at 2.2 us; in that time the three kernels get through 6.3 MB of K. Measured crossings (fused / three kernels, us): 16 layers x 8 kv
 // heads, head_dim 64: 4096 tokens 40 / 40, 6144 40 / 49, 8192 43 / 58; 4 x 4 heads, head_dim 128: 8192
-// tokens 32 / 27, 16384 34 / 39; 28 x 8 heads, head_dim 128: 2048 tokens 46 / 59.
+// tokens 32 / 27, 16384 34 / 39; 28 x 8 heads, head_dim 128: 2048 tokens 46 / 59. With two blocks of query rows at
+// head_dim 128 a step takes 2.8 us (24 x 4 heads: 3000 tokens in 13 steps 54 / 52, 4500 52 / 77, 20001 138 / 264).
 bool steps_pay(const Plan &p, int64_t tokens, int ranges, int launches)
 {
     const int64_t steps = sp::ceil_div(p.n_layers, ranges) * (p.n_phases / p.n_layers) + 5;
-    return tokens * p.n_phases * p.D * 2 >= launches * steps * 6300000;
+    return tokens * p.n_phases * p.D * 2 >= launches * steps * (fused_big(p) ? 8000000 : 6300000);
 }
 
 // The table of a launch with every entry of `t` once per layer range.
@@ -824,7 +832,7 @@ WsLayout ws_layout(const Plan &p, int64_t n_tiles, int n_prompts)
     w.split = off; off = sp::align_up(off + sizeof(float) * split_buf_floats(p, n_tiles), 256);
     w.look = off; off = sp::align_up(off + sizeof(float) * (size_t)p.n_phases * p.rows_pad, 256);
     w.fused = off;
-    if (fused_shape_ok(p)) {
+    if (fused_base_shape(p)) {
         int64_t n_wg = n_tiles * p.tile_keys / fused_tile(p) + n_prompts;
         if (n_wg > 1024) n_wg = 1024;
         off += sp_fused::workspace_bytes(p.rows_pad, (int)n_wg, std::min(n_prompts, kMaxGroupPrompts));
@@ -967,7 +975,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
         a.look = look;
     }
     // the single-launch kernel fetches 8-bit keys in 16-byte pieces
-    const bool may_fuse = !opt.kscale || fp8_strides_ok(desc);
+    const bool may_fuse = !opt.kscale || (fp8_strides_ok(desc) && !fused_big(p));
     sp_fused::FusedArgs f;
     std::memset(&f, 0, sizeof f);
     f.q = a.q;
@@ -996,12 +1004,16 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     bool fused = may_fuse && (batch ? plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg)
                                        : plan_fused_prompt(p, total, desc->k_stride_token, bg));
     int ranges = 1;
+    const bool big = fused_big(p);
     if (fused && bg.groups.size() == 1) {
         // the exchange area of a launch in layer ranges takes the place of the general path's buffers
         ranges = fused_ranges(p, bg.wgs[0], bg.groups[0].n, w.split - w.part);
     }
-    if (fused && !(batch ? whole_groups_pay(p, bg) : bg.wgs[0] >= fused_min_workgroups(p)))
-        fused = (batch || ranges > 1) && steps_pay(p, total, ranges, (int)bg.groups.size());
+    if (fused && (big || !(batch ? whole_groups_pay(bg) : bg.wgs[0] >= fused_min_workgroups(p))))
+        fused = (batch || ranges > 1 || bg.wgs[0] >= fused_min_workgroups(p)) && steps_pay(p, total, ranges, (int)bg.groups.size());
+    if (fused && big)           // no exchange area of their own: see fused_big
+        for (size_t g = 0; g < bg.groups.size(); ++g)
+            fused = fused && sp_fused::workspace_bytes(p.rows_pad, bg.wgs[g], bg.groups[g].n) <= w.split - w.part;
     if (fused) {
         if (ranges > 1) {
             const sp_fused::GroupTable t = split_layers(bg.groups[0], p.n_layers, ranges);
@@ -1018,7 +1030,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
             // duties rotate over all prompts of a launch where they can: within a prompt of a dozen workgroups
             // each would have one every other phase (8 prompts of 2K .. 32K tokens: 342 against 394 us)
             const bool shared = !bg.short_prompt && bg.groups[g].n * (p.rows_pad / sp_fused::kDutyRows) <= bg.wgs[g];
-            const sp_status rs = sp_fused::launch(f, kp, batch ? &bg.groups[g] : nullptr, shared, g == 0, ws + w.fused, a.status, st);
+            const sp_status rs = sp_fused::launch(f, kp, batch ? &bg.groups[g] : nullptr, shared, g == 0, ws + (big ? w.part : w.fused), a.status, st);
             if (rs != SP_OK) return rs;
         }
         return SP_OK;
@@ -1079,7 +1091,7 @@ extern "C" int32_t sp_score_batch_is_fused(const sp_score_desc *desc, const int6
     for (int b = 0; b < B; ++b)
         if (offsets_host[b + 1] < offsets_host[b]) return -1;
     BatchGroups bg;
-    return plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg) && whole_groups_pay(p, bg) ? (int32_t)bg.groups.size() : 0;
+    return fused_base_shape(p) && plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg) && whole_groups_pay(bg) ? (int32_t)bg.groups.size() : 0;
 }
 
 extern "C" sp_status sp_score(const sp_score_desc *desc, const void *q_dev, const void *const *k_layers_host,

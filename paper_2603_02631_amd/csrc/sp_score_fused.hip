@@ -45,7 +45,8 @@
 //
 // Variants of the same loop: head_dim 128 (256 keys per workgroup, a wave's two
 // sub-tiles are the two halves of its 32 keys' rows: see the kernel's template
-// flag W), paged keys and lookahead keys in the normaliser (flag EXTRA), and
+// flag W; with two blocks of query rows Q takes twice the LDS and the transit
+// ring has two slots), two tiles a workgroup (flag PAIR), paged keys and lookahead keys in the normaliser (flag EXTRA), and
 // launches that carry a table of (prompt, layer range) entries (also under
 // EXTRA: each entry has its own workgroups, duty blocks and row of normalisers).
 // Entries are the prompts of a ragged batch, and the layer ranges of prompts
@@ -82,23 +83,30 @@ constexpr int kDutyRows = sp_fused::kDutyRows;   // 4: 32 bytes per source workg
 constexpr int kLseWave = 2;                // the wave that fetches the normalisers
 constexpr uint32_t kPoisonTag = 0xffffffffu;   // normaliser entry of a duty that gave up
 
-// LDS map in bytes. Everything but the K transit ring sits below 64 KB, so that reads of it can
-// carry the buffer's place in the instruction's offset field.
-constexpr int kQTileBytes = kMaxRowsF * kD * 2;                    // one Q tile: 64 rows x 128 bytes
-constexpr int kWideHalf = 4096;                                    // head_dim 128: dims 64..127 of a Q tile's 32 rows sit here
-constexpr int kOffQ1 = 0;                                          // [2] Q of the statistics pass, by phase parity
-constexpr int kOffQ2 = kOffQ1 + 2 * kQTileBytes;                   // [2] Q of the probability pass
+// LDS map in bytes. Q comes first and everything read with a compile-time offset sits below 64 KB, so that such reads
+// can carry the buffer's place in the instruction's offset field. BIG: two blocks of query rows at head_dim 128; their
+// Q tiles take twice the room, and the K transit ring has two slots a wave instead of three (all of a phase's tile
+// loads are then issued in the statistics pass, once the lift has emptied both slots).
+constexpr int kWideHalf = 4096;                                    // head_dim 128: dims 64..127 of a block's 32 rows sit here
 constexpr int kWstatsBytes = kFWaves * kMaxRowsF * 8;              // (max, sum) of 64 rows from 8 waves
-constexpr int kOffWstats = kOffQ2 + 2 * kQTileBytes;               // [2], pairs of tiles: [4]
-constexpr int kOffCinit = kOffWstats + 4 * kWstatsBytes;           // [2][64] accumulator seeds
-constexpr int kOffXduty = kOffCinit + 2 * kMaxRowsF * 4;           // 8 KB: partials of the duty rows (direct exchange: of all rows)
-constexpr int kOffXlse = kOffXduty + 8192;                         // 1 KB: normaliser entries of one phase
-constexpr int kOffXlook = kOffXlse + 1024;                         // 1 KB: lookahead-key terms of one phase's rows
-constexpr int kOffFail = kOffXlook + 1024;
-constexpr int kOffKring = (kOffFail + 16 + 1023) / 1024 * 1024;    // [8 waves][3 slots][32 rows x 128 bytes]
 constexpr int kSubBytes = 32 * kD * 2;
-constexpr int kLdsBytes = kOffKring + kFWaves * kSubSlots * kSubBytes;
-static_assert(kOffKring < 65536, "offset fields hold 16 bits");
+constexpr int kOffXlook = 1024;                                    // of the lookahead-key terms behind the normaliser entries
+template <bool BIG>
+struct Map {
+    static constexpr int kQTileBytes = kMaxRowsF * kD * 2 * (BIG ? 2 : 1);     // one Q tile: 64 rows x 128 (BIG: 256) bytes
+    static constexpr int kQBlock = BIG ? 2 * kWideHalf : kWideHalf;            // 32 rows
+    static constexpr int kQ1 = 0;                                  // [2] Q of the statistics pass, by phase parity
+    static constexpr int kQ2 = kQ1 + 2 * kQTileBytes;              // [2] Q of the probability pass
+    static constexpr int kWstats = kQ2 + 2 * kQTileBytes;          // [2], pairs of tiles: [4]
+    static constexpr int kCinit = kWstats + 4 * kWstatsBytes;      // [2][64] accumulator seeds
+    static constexpr int kXduty = kCinit + 2 * kMaxRowsF * 4;      // 8 KB: partials of the duty rows (direct exchange: of all rows)
+    static constexpr int kXlse = kXduty + 8192;                    // 1 KB: normaliser entries of one phase, 1 KB: lookahead-key terms
+    static constexpr int kFail = kXlse + 2048;
+    static constexpr int kKring = (kFail + 16 + 1023) / 1024 * 1024;   // [8 waves][slots][32 rows x 128 bytes]
+    static constexpr int kSlotsPerWave = BIG ? 2 : kSubSlots;
+    static constexpr int kBytes = kKring + kFWaves * kSlotsPerWave * kSubBytes;
+    static_assert(kQ2 + 2 * kQTileBytes <= 65536 && kBytes <= 160 * 1024, "offset fields hold 16 bits; 160 KB a compute unit");
+};
 
 #define SP_LPTR(p) ((__attribute__((address_space(3))) void *)(p))
 
@@ -152,7 +160,7 @@ struct LaneConst {
     uint32_t ld[kKS];       // LDS byte address of this lane's fragment chunk t in a tile at LDS offset 0
     uint32_t ld8[kKS];      // the same in a sub-tile of 8-bit keys (rows of 64 bytes, 8 bytes per chunk)
     uint32_t koff[2];       // byte offset of this lane's chunk in an even / odd tile-load instruction (full tiles)
-    int32_t qoff;           // byte offset of this lane's chunk of its wave's Q slice in a (layer, kv head) block; < 0: padding
+    int32_t qoff[2];        // byte offset of this lane's chunk of its wave's Q slice in a (layer, kv head) block; < 0: padding (BIG: per row block)
 };
 
 // All LDS traffic of the main loop is written as asm: the compiler cannot tell which in-flight
@@ -417,11 +425,13 @@ __device__ __forceinline__ void k_issue(const KIssue &ki, const uint32_t (&voff)
 }
 
 // Sub-tile s2 of phase p lives in slot (2p + s2) mod 3 of its wave's transit ring; slot0 = 2p mod 3.
+template <bool BIG>
 __device__ __forceinline__ uint32_t sub_slot_off(int wave, int slot0, int s2)
 {
+    if (BIG) return (uint32_t)(Map<BIG>::kKring + (wave * 2 + s2) * kSubBytes);
     int slot = slot0 + s2;
     slot = slot >= kSubSlots ? slot - kSubSlots : slot;
-    return (uint32_t)(kOffKring + (wave * kSubSlots + slot) * kSubBytes);
+    return (uint32_t)(Map<BIG>::kKring + (wave * kSubSlots + slot) * kSubBytes);
 }
 
 template <int NB>
@@ -441,25 +451,34 @@ __device__ __forceinline__ void prob_pass(const bf16x8 (&kf)[kNS][kKS], const La
                                           Acc<NB> &acc, const KIssue &ki, const uint32_t (&voff)[2], float ks)
 {
     static_assert(NB * GB == 1 || NB * GB == 2, "one load per row block, or one per step");
+    using MP = Map<W && NB * GB == 2>;
     constexpr int kMid = F8 ? 1 : 2;
     if constexpr (W) {
         // head_dim 128: one chain of eight MFMA steps over both halves of the 32 keys' rows
-        static_assert(NB == 1 && GB == 1, "one block of 32 query rows");
-        bf16x8 q0[kKS], q1[kKS];
-        f32x16 d;
-        lift_q_and_seed<kOffQ2 + PAR * kQTileBytes>(lc, cinit_ad, q0, d);
-        lift_at<kOffQ2 + PAR * kQTileBytes + kWideHalf>(lc, q1);
+        static_assert(NB == 1, "one block of lookahead rows");
 #pragma unroll
-        for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q0[t], kf[0][t], d, 0, 0, 0);
-        k_issue<1>(ki, voff, kMid);
+        for (int gb = 0; gb < GB; ++gb) {
+            bf16x8 q0[kKS], q1[kKS];
+            f32x16 d;
+            if (gb == 0) {
+                lift_q_and_seed<MP::kQ2 + PAR * MP::kQTileBytes>(lc, cinit_ad, q0, d);
+                lift_at<MP::kQ2 + PAR * MP::kQTileBytes + kWideHalf>(lc, q1);
+            } else {
+                lift_q_and_seed<MP::kQ2 + PAR * MP::kQTileBytes + MP::kQBlock>(lc, cinit_ad + 128, q0, d);
+                lift_at<MP::kQ2 + PAR * MP::kQTileBytes + MP::kQBlock + kWideHalf>(lc, q1);
+            }
 #pragma unroll
-        for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q1[t], kf[1][t], d, 0, 0, 0);
+            for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q0[t], kf[0][t], d, 0, 0, 0);
+            if (GB == 1) k_issue<1>(ki, voff, kMid);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (F8) acc.mx[0][0][e] = fmaxf(acc.mx[0][0][e], fmaxf(max3(d[e], d[4 + e], d[8 + e]), d[12 + e]) * ks);
-            else acc.mx[0][0][e] = max3(max3(d[e], d[4 + e], d[8 + e]), d[12 + e], acc.mx[0][0][e]);
+            for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q1[t], kf[1][t], d, 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (F8) acc.mx[0][0][e] = fmaxf(acc.mx[0][0][e], fmaxf(max3(d[e], d[4 + e], d[8 + e]), d[12 + e]) * ks);
+                else acc.mx[0][0][e] = max3(max3(d[e], d[4 + e], d[8 + e]), d[12 + e], acc.mx[0][0][e]);
+            }
+            if (GB == 1 && !F8) k_issue<1>(ki, voff, kMid + 1);
         }
-        if (!F8) k_issue<1>(ki, voff, kMid + 1);
         __builtin_amdgcn_sched_barrier(0);
         return;
     }
@@ -470,8 +489,8 @@ __device__ __forceinline__ void prob_pass(const bf16x8 (&kf)[kNS][kKS], const La
             const int blk = gb * NB + nb;
             bf16x8 qf[kKS];
             f32x16 ci;
-            if (blk == 0) lift_q_and_seed<kOffQ2 + PAR * kQTileBytes>(lc, cinit_ad, qf, ci);
-            else lift_q_and_seed<kOffQ2 + PAR * kQTileBytes + 4096>(lc, cinit_ad + 128, qf, ci);
+            if (blk == 0) lift_q_and_seed<MP::kQ2 + PAR * MP::kQTileBytes>(lc, cinit_ad, qf, ci);
+            else lift_q_and_seed<MP::kQ2 + PAR * MP::kQTileBytes + MP::kQBlock>(lc, cinit_ad + 128, qf, ci);
 #pragma unroll
             for (int s = 0; s < kNS; ++s) {
                 f32x16 d = ci;
@@ -522,7 +541,7 @@ __device__ __forceinline__ void stage_entries(uint32_t lds_dst, const uint64_t *
 __device__ __forceinline__ void stage_exchange_rows(uint32_t xlse_ad, const uint64_t *lse_row, const float *look_row,
                                                     int rows_pad, int lane)
 {
-    if (look_row != nullptr) dma_v_device(look_row + 4 * min(lane, rows_pad / 4 - 1), xlse_ad + (kOffXlook - kOffXlse));
+    if (look_row != nullptr) dma_v_device(look_row + 4 * min(lane, rows_pad / 4 - 1), xlse_ad + kOffXlook);
     if (lse_row != nullptr) stage_entries(xlse_ad, lse_row, rows_pad / 2, lane);
 }
 
@@ -585,42 +604,60 @@ __device__ __forceinline__ void store_row_stats(uint32_t ad, float m, float l, f
 // tile load is issued after each of the four steps (with one row block: two per step). late() requests
 // exchange data after the first step: late enough for other workgroups' stores to be visible, early
 // enough to land before the barrier.
-template <int NBLK, bool F8>
-constexpr int kLoadsBehindLse = F8 ? 1 : kSubInstr - kSubInstr / (NBLK * kNS);
+template <int NBLK, bool F8, bool BIG>
+constexpr int kLoadsBehindLse = BIG ? 6 : F8 ? 1 : kSubInstr - kSubInstr / (NBLK * kNS);
 
 template <int NBLK, int PAR, bool W, bool F8, class Late>
 __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], const LaneConst &lc, uint32_t koff0,
                                            uint32_t koff1, uint32_t wstats_ad, int lo0, int hi0, int lane,
-                                           const KIssue &ki, const uint32_t (&voff)[2], const Late &late)
+                                           const KIssue &ki0, const KIssue &ki, const uint32_t (&voff)[2], const Late &late)
 {
     // tile-load instructions issued after each MFMA step (8-bit keys: two in all, after the first two steps)
     constexpr int kPerStep = F8 ? 1 : kSubInstr / (NBLK * kNS);
     constexpr int kLate = F8 ? 0 : kPerStep;             // after the third and fourth step
+    using MP = Map<W && NBLK == 2>;
     const int hf = lane >> 5;
     if constexpr (W) {
         // head_dim 128: the two sub-tiles are the two halves of the rows of this wave's 32 keys
-        static_assert(NBLK == 1, "one block of 32 query rows");
         bf16x8 q0[kKS], q1[kKS];
-        if (F8) lift_k8_and_q<kOffQ1 + PAR * kQTileBytes>(lc, koff0, koff1, kf, q0);
-        else lift_k_and_q<kOffQ1 + PAR * kQTileBytes>(lc, koff0, koff1, kf, q0);
-        lift_at<kOffQ1 + PAR * kQTileBytes + kWideHalf>(lc, q1);
+        if (F8) lift_k8_and_q<MP::kQ1 + PAR * MP::kQTileBytes>(lc, koff0, koff1, kf, q0);
+        else lift_k_and_q<MP::kQ1 + PAR * MP::kQTileBytes>(lc, koff0, koff1, kf, q0);
+        lift_at<MP::kQ1 + PAR * MP::kQTileBytes + kWideHalf>(lc, q1);
         f32x16 d = logits32(kf[0], q0);
 #pragma unroll
         for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][t], q1[t], d, 0, 0, 0);
-        k_issue<kPerStep>(ki, voff, 0);
+        k_issue<NBLK == 2 ? 2 : kPerStep>(NBLK == 2 ? ki0 : ki, voff, 0);
         late();
         __builtin_amdgcn_sched_barrier(0);
         float m = neg_inf(), l = 0.f;
-        fold_logits(d, m, l, c, lo0, hi0, hf);
-        store_row_stats(wstats_ad, m, l, c, hf);
-        k_issue<kPerStep>(ki, voff, kPerStep);
+        if constexpr (NBLK == 2) {
+            // BIG: both slots are free now, all eight loads of the next tile go out from here on
+            lift_at<MP::kQ1 + PAR * MP::kQTileBytes + MP::kQBlock>(lc, q0);
+            lift_at<MP::kQ1 + PAR * MP::kQTileBytes + MP::kQBlock + kWideHalf>(lc, q1);
+            f32x16 d1 = logits32(kf[0], q0);
+            fold_logits(d, m, l, c, lo0, hi0, hf);
+            store_row_stats(wstats_ad, m, l, c, hf);
+            k_issue<2>(ki0, voff, 2);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < kKS; ++t) d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][t], q1[t], d1, 0, 0, 0);
+            k_issue<2>(ki, voff, 0);
+            m = neg_inf(); l = 0.f;
+            fold_logits(d1, m, l, c, lo0, hi0, hf);
+            store_row_stats(wstats_ad + 256, m, l, c, hf);
+            k_issue<2>(ki, voff, 2);
+        } else {
+            fold_logits(d, m, l, c, lo0, hi0, hf);
+            store_row_stats(wstats_ad, m, l, c, hf);
+            k_issue<kPerStep>(ki, voff, kPerStep);
+        }
         __builtin_amdgcn_sched_barrier(0);
         return;
     }
     const int lo1 = lo0 - 32, hi1 = hi0 - 32;      // this wave's keys lo0 <= key < hi0 (of 64) are the workgroup's
     bf16x8 qf[kKS];
-    if (F8) lift_k8_and_q<kOffQ1 + PAR * kQTileBytes>(lc, koff0, koff1, kf, qf);
-    else lift_k_and_q<kOffQ1 + PAR * kQTileBytes>(lc, koff0, koff1, kf, qf);
+    if (F8) lift_k8_and_q<MP::kQ1 + PAR * MP::kQTileBytes>(lc, koff0, koff1, kf, qf);
+    else lift_k_and_q<MP::kQ1 + PAR * MP::kQTileBytes>(lc, koff0, koff1, kf, qf);
     f32x16 da = logits32(kf[0], qf);
     f32x16 db = logits32(kf[1], qf);
     float m = neg_inf(), l = 0.f;
@@ -629,7 +666,7 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
     late();
     __builtin_amdgcn_sched_barrier(0);
     if (NBLK == 2) {
-        lift_at<kOffQ1 + PAR * kQTileBytes + 4096>(lc, qf);
+        lift_at<MP::kQ1 + PAR * MP::kQTileBytes + MP::kQBlock>(lc, qf);
         da = logits32(kf[0], qf);
     }
     fold_logits(db, m, l, c, lo1, hi1, hf);
@@ -650,25 +687,24 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
 }
 
 // The eight per-wave statistics of row `lane` of one buffer, one round trip to LDS.
-template <int OFF>
-__device__ __forceinline__ void read_wave_stats(uint32_t lds0, int lane, float (&m)[kFWaves], float (&l)[kFWaves])
+__device__ __forceinline__ void read_wave_stats(uint32_t buf, int lane, float (&m)[kFWaves], float (&l)[kFWaves])
 {
     typedef __attribute__((ext_vector_type(2))) float f32x2;
-    const uint32_t ad = lds0 + 8u * (uint32_t)lane;
+    const uint32_t ad = buf + 8u * (uint32_t)lane;
     f32x2 r[kFWaves];
     static_assert(kFWaves == 8 && kMaxRowsF * 8 == 512, "layout of the asm block");
     __asm__ volatile(
-        "ds_read_b64 %0, %8 offset:%9\n\t"
-        "ds_read_b64 %1, %8 offset:%9+512\n\t"
-        "ds_read_b64 %2, %8 offset:%9+1024\n\t"
-        "ds_read_b64 %3, %8 offset:%9+1536\n\t"
-        "ds_read_b64 %4, %8 offset:%9+2048\n\t"
-        "ds_read_b64 %5, %8 offset:%9+2560\n\t"
-        "ds_read_b64 %6, %8 offset:%9+3072\n\t"
-        "ds_read_b64 %7, %8 offset:%9+3584\n\t"
+        "ds_read_b64 %0, %8\n\t"
+        "ds_read_b64 %1, %8 offset:512\n\t"
+        "ds_read_b64 %2, %8 offset:1024\n\t"
+        "ds_read_b64 %3, %8 offset:1536\n\t"
+        "ds_read_b64 %4, %8 offset:2048\n\t"
+        "ds_read_b64 %5, %8 offset:2560\n\t"
+        "ds_read_b64 %6, %8 offset:3072\n\t"
+        "ds_read_b64 %7, %8 offset:3584\n\t"
         "s_waitcnt lgkmcnt(0)"
         : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
-        : "v"(ad), "i"(OFF)
+        : "v"(ad)
         : "memory");
 #pragma unroll
     for (int i = 0; i < kFWaves; ++i) { m[i] = r[i].x; l[i] = r[i].y; }
@@ -681,11 +717,11 @@ __device__ __forceinline__ void read_wave_stats(uint32_t lds0, int lane, float (
 // chunk (2q + h) * 64 + lane holds rows 2h and 2h+1 of the block from workgroup lane + 64q.
 struct DutyBlock { uint64_t e[kDutyRows][4]; };     // [row of the block][workgroup lane + 64q]
 
-__device__ __forceinline__ DutyBlock read_duty_staging(uint32_t lds0, int lane)
+__device__ __forceinline__ DutyBlock read_duty_staging(uint32_t xduty, int lane)
 {
     static_assert(kDutyRows == 4, "layout of the asm block");
     typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
-    const uint32_t ad = lds0 + kOffXduty + 16u * (uint32_t)lane;
+    const uint32_t ad = xduty + 16u * (uint32_t)lane;
     u64x2 r[8];
     __asm__ volatile(
         "ds_read_b128 %0, %8\n\t"
@@ -711,17 +747,17 @@ __device__ __forceinline__ DutyBlock read_duty_staging(uint32_t lds0, int lane)
     return d;
 }
 
-__device__ __forceinline__ uint64_t read_lse_staging(uint32_t lds0, int lane)
+__device__ __forceinline__ uint64_t read_lse_staging(uint32_t xlse, int lane)
 {
-    const uint32_t ad = lds0 + kOffXlse + 8u * (uint32_t)lane;
+    const uint32_t ad = xlse + 8u * (uint32_t)lane;
     uint64_t v;
     __asm__ volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v) : "v"(ad) : "memory");
     return v;
 }
 
-__device__ __forceinline__ float read_look_staging(uint32_t lds0, int lane)
+__device__ __forceinline__ float read_look_staging(uint32_t xlse, int lane)
 {
-    const uint32_t ad = lds0 + kOffXlook + 4u * (uint32_t)lane;
+    const uint32_t ad = xlse + kOffXlook + 4u * (uint32_t)lane;
     float v;
     __asm__ volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v) : "v"(ad) : "memory");
     return v;
@@ -777,7 +813,7 @@ __device__ __forceinline__ void raise_failure(const FusedArgs &a, int *fail)
 // odd workgroups: entry i of a lane sits 512 i bytes behind its first either way. Fixed order, so every
 // workgroup finds the same bits.
 template <int NB, int GB>
-__device__ __forceinline__ float direct_combine(const FusedArgs &a, const uint64_t *src, int src_n, uint32_t par, uint32_t lds0,
+__device__ __forceinline__ float direct_combine(const FusedArgs &a, const uint64_t *src, int src_n, uint32_t par, uint32_t xduty,
                                                 int *fail, int lane, float c, float inv_c)
 {
     constexpr int kRowsPad = 32 * NB * GB, kPer = 64 / kRowsPad;      // workgroups per 512 bytes
@@ -788,7 +824,7 @@ __device__ __forceinline__ float direct_combine(const FusedArgs &a, const uint64
     const bool valid_row = row_valid<NB>(a, row, g, n);
     constexpr int kMaxE = (sp_fused::direct_max(kRowsPad) + kPer - 1) / kPer;     // 4 or 15
     uint64_t e[16];
-    const uint32_t ad = lds0 + kOffXduty + 8u * (uint32_t)lane;
+    const uint32_t ad = xduty + 8u * (uint32_t)lane;
     for (unsigned spins = 0;;) {
 #define SP_READ4(B)                                                                                                     \
     __asm__ volatile(                                                                                                   \
@@ -806,7 +842,7 @@ __device__ __forceinline__ float direct_combine(const FusedArgs &a, const uint64
         if (!__any(valid_row && bad != 0u) && a.force_miss == 0) break;
         if (*fail != 0) break;
         if (++spins > a.spin_max) { raise_failure(a, fail); break; }
-        stage_direct(lds0 + kOffXduty, src, src_n * kRowsPad, lane);        // bounded polling
+        stage_direct(xduty, src, src_n * kRowsPad, lane);        // bounded polling
         vm_wait<0>();
     }
     float m = neg_inf(), l = 0.f;
@@ -854,7 +890,8 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
                                      Acc<NB> (&accs)[PAIR ? 2 : 1], const LaneConst &lc, Walk &wk, unsigned char *lds, uint32_t lds0,
                                      uint64_t wave_off, const int (&r_ranges)[PAIR ? 2 : 1])
 {
-    constexpr bool EXTRA = KIND != kPlain, RANGES = KIND == kRanges;
+    constexpr bool EXTRA = KIND != kPlain, RANGES = KIND == kRanges, BIG = W && NB * GB == 2;
+    using MP = Map<BIG>;
     // Other lane-derived values are recomputed every step instead of being kept in registers across
     // the whole loop (the opaque copy stops the compiler from hoisting them).
     int tid = threadIdx.x;
@@ -902,7 +939,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
 
     auto request_duty = [&]() {
         if (duty_blk >= 0)
-            stage_duty_block<EXTRA>(lds0 + kOffXduty, a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad, a.rows_pad,
+            stage_duty_block<EXTRA>(lds0 + MP::kXduty, a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad, a.rows_pad,
                                     src_n, duty_blk * kDutyRows, lane);
     };
 
@@ -913,8 +950,8 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
             // then one exponential per source, and publishes the rows with one contiguous store
             constexpr int kSets = PAIR ? 2 : 1;          // of eight per-wave statistics
             float pm[kSets][kFWaves], pl8[kSets][kFWaves];
-            read_wave_stats<kOffWstats + (PAIR ? (SLOT ^ 2) : 1 - PAR) * kWstatsBytes>(lds0, lane, pm[0], pl8[0]);
-            if constexpr (PAIR) read_wave_stats<kOffWstats + ((SLOT ^ 2) + 1) % 4 * kWstatsBytes>(lds0, lane, pm[1], pl8[1]);
+            read_wave_stats(lds0 + MP::kWstats + (PAIR ? (SLOT ^ 2) : 1 - PAR) * kWstatsBytes, lane, pm[0], pl8[0]);
+            if constexpr (PAIR) read_wave_stats(lds0 + MP::kWstats + ((SLOT ^ 2) + 1) % 4 * kWstatsBytes, lane, pm[1], pl8[1]);
             float m = neg_inf();
 #pragma unroll
             for (int h = 0; h < kSets; ++h)
@@ -934,7 +971,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     } else if (!PAIR && wave == kDutyWave) {
         request_duty();
     } else if (RANGES && wave == kLseWave && direct && pl >= 0 && pl < n_phases) {
-        stage_direct(lds0 + kOffXduty, a.part + ((size_t)(pl % kSlots) * a.n_wg + a.ent_w0) * kRowsPad, a.ent_n * kRowsPad, lane);
+        stage_direct(lds0 + MP::kXduty, a.part + ((size_t)(pl % kSlots) * a.n_wg + a.ent_w0) * kRowsPad, a.ent_n * kRowsPad, lane);
     }
     const char *kbase = wk.kptr + (PAIR && PAR == 0 ? wk.pair_off : 0);      // PAIR: the second tile is fetched in even steps
     int slot_next = wk.slot0 + 2;         // sub-tile 0 of phase s + 1
@@ -942,36 +979,39 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     // past the last phase the loads shrink to one 16-byte piece per instruction: the count stays fixed
     const uint32_t live = pf < n_phases ? 0xffffffffu : 0u;
     const uint32_t voff[2] = {lc.koff[0] & live, lc.koff[1] & live};
-    KIssue ki;
-    ki.lds_dst = lds0 + sub_slot_off(wave, slot_next, 0);
-    ki.base = kbase;
-    ki.step_bytes = (F8 ? 16u : 8u) * stride_bytes;
-    if (lc.qoff >= 0) {       // padding rows of the Q tiles stay zero; the Q blocks of consecutive phases are contiguous
+    KIssue ki0;
+    ki0.lds_dst = lds0 + sub_slot_off<BIG>(wave, slot_next, 0);
+    ki0.base = kbase;
+    ki0.step_bytes = (F8 ? 16u : 8u) * stride_bytes;
+#pragma unroll
+    for (int blk = 0; blk < (BIG ? 2 : 1); ++blk) if (lc.qoff[blk] >= 0) {       // padding rows of the Q tiles stay zero; the Q blocks of consecutive phases are contiguous
         const uint32_t qblock = (uint32_t)(a.group * a.n_q * kD * 2) * (W ? 2u : 1u);
         const char *q1src = reinterpret_cast<const char *>(a.q) + (uint32_t)min(pf, n_phases - 1) * qblock;
         const char *q2src = reinterpret_cast<const char *>(a.q) + (uint32_t)clampi(pl, 0, n_phases - 1) * qblock;
-        dma_u<kOffQ1 + (1 - PAR) * kQTileBytes>((uint32_t)lc.qoff, q1src, lds0 + wave * 1024);
-        dma_u<kOffQ2 + PAR * kQTileBytes>((uint32_t)lc.qoff, q2src, lds0 + wave * 1024);
+        const uint32_t dst = lds0 + wave * 1024 + blk * MP::kQBlock;
+        dma_u<MP::kQ1 + (1 - PAR) * MP::kQTileBytes>((uint32_t)lc.qoff[blk], q1src, dst);
+        dma_u<MP::kQ2 + PAR * MP::kQTileBytes>((uint32_t)lc.qoff[blk], q2src, dst);
     }
-    k_issue<kMid>(ki, voff, 0);
+    if (!BIG) k_issue<kMid>(ki0, voff, 0);
 
     // ---- probability pass of phase pc; sub-tile 0 of K(s+1) ----
     {
         if (do_prob) {
-            const uint32_t cinit_ad = lds0 + kOffCinit + (1 - PAR) * (kMaxRowsF * 4) + ((uint32_t)(lane & 32) << 1);
-            prob_pass<NB, GB, 1 - PAR, W, F8>(ring.kf[SLOT], lc, cinit_ad, acc, ki, voff, ks_prob);
+            const uint32_t cinit_ad = lds0 + MP::kCinit + (1 - PAR) * (kMaxRowsF * 4) + ((uint32_t)(lane & 32) << 1);
+            prob_pass<NB, GB, 1 - PAR, W, F8>(ring.kf[SLOT], lc, cinit_ad, acc, ki0, voff, ks_prob);
             if (wk.c.kv == a.n_kv_heads - 1 && (a.layer_agg == SP_LAYER_MEAN || wk.c.layer == (RANGES ? a.last_layer : a.n_layers - 1)))
                 close_layer<NB, W ? 1 : kNS>(acc, a.c);
-        } else {
-            k_issue<kSI - kMid>(ki, voff, kMid);
+        } else if (!BIG) {
+            k_issue<kSI - kMid>(ki0, voff, kMid);
         }
     }
 
     // ---- lift K(s), statistics pass of phase s; sub-tile 1 of K(s+1) ----
-    vm_wait<kSI>();                       // behind sub-tile 1 of K(s): at least the loads of sub-tile 0 of K(s+1)
+    // behind sub-tile 1 of K(s): at least the loads of sub-tile 0 of K(s+1); BIG: nothing that is certain
+    if (BIG) vm_wait<0>(); else vm_wait<kSI>();
     {
         KIssue ki;
-        ki.lds_dst = lds0 + sub_slot_off(wave, slot_next, 1);
+        ki.lds_dst = lds0 + sub_slot_off<BIG>(wave, slot_next, 1);
         ki.base = kbase + (W ? (int64_t)(kD * kElem) : (int64_t)32 * stride_bytes);     // W: the rows' second halves
         ki.step_bytes = (F8 ? 16u : 8u) * stride_bytes;
         const uint64_t *lse_row = wave == kLseWave && !direct ? a.lse + ((size_t)(clampi(pl, 0, n_phases - 1) % kSlots) * a.n_gp + a.p_idx) * a.rows_pad : nullptr;
@@ -980,7 +1020,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         // requests after the first MFMA step: the normalisers; PAIR: also the duty rows, published at the start of
         // this very step (their normalisers are due at the next one's end)
         auto late = [&]() {
-            stage_exchange_rows(lds0 + kOffXlse, lse_row, look_row, a.rows_pad, lane);
+            stage_exchange_rows(lds0 + MP::kXlse, lse_row, look_row, a.rows_pad, lane);
             if (PAIR && PAR == 0 && wave == kDutyWave) request_duty();
         };
         // r_range = r_lo | r_hi << 16 (r_hi = 512 without EXTRA): this wave's share of it
@@ -988,18 +1028,20 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         const int lo0 = (r_range & 0xffff) - wave * kWaveKeys;
         const int hi0 = EXTRA ? (r_range >> 16) - wave * kWaveKeys : kWaveKeys;
         if (do_stats) {
-            const uint32_t wstats_ad = lds0 + kOffWstats + (PAIR ? SLOT : PAR) * kWstatsBytes + wave * (kMaxRowsF * 8) + ((uint32_t)(lane & 31) << 3);
-            stats_pass<NB * GB, PAR, W, F8>(c_stats, ring.kf[SLOT], lc, sub_slot_off(wave, wk.slot0, 0),
-                                     sub_slot_off(wave, wk.slot0, 1), wstats_ad, lo0, hi0, lane, ki, voff, late);
+            const uint32_t wstats_ad = lds0 + MP::kWstats + (PAIR ? SLOT : PAR) * kWstatsBytes + wave * (kMaxRowsF * 8) + ((uint32_t)(lane & 31) << 3);
+            stats_pass<NB * GB, PAR, W, F8>(c_stats, ring.kf[SLOT], lc, sub_slot_off<BIG>(wave, wk.slot0, 0),
+                                     sub_slot_off<BIG>(wave, wk.slot0, 1), wstats_ad, lo0, hi0, lane, ki0, ki, voff, late);
         } else {
             late();
+            if (BIG) k_issue<kSI>(ki0, voff, 0);
             k_issue<kSI>(ki, voff, 0);
         }
     }
 
     // ---- pre-barrier: exchange data in, seeds out ----
-    if ((wave == kLseWave && !(RANGES && direct && a.look == nullptr)) || (PAIR && PAR == 0 && wave == kDutyWave)) vm_wait<kLoadsBehindLse<NB * GB, F8>>(); else vm_wait<2 * kSI>();
-    int *fail = reinterpret_cast<int *>(lds + kOffFail);
+    if ((wave == kLseWave && !(RANGES && direct && a.look == nullptr)) || (PAIR && PAR == 0 && wave == kDutyWave)) vm_wait<kLoadsBehindLse<NB * GB, F8, BIG>>();
+    else vm_wait<2 * kSI>();
+    int *fail = reinterpret_cast<int *>(lds + MP::kFail);
     if (wave == kDutyWave) {
         if (duty_blk >= 0) {
             uint32_t row_mask = 0;
@@ -1012,7 +1054,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
                 const uint32_t par = (uint32_t)(pd / kSlots) & 1u;
                 const uint64_t *src = a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad + duty_blk * kDutyRows;
                 // fast path: the partials requested at the start of this step are all there; otherwise poll (bounded)
-                DutyBlock de = read_duty_staging(lds0, lane);
+                DutyBlock de = read_duty_staging(lds0 + MP::kXduty, lane);
                 bool ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && a.force_miss == 0;
                 if (!ready && *fail == 0) {
                     unsigned spins = 0;
@@ -1059,7 +1101,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         float direct_v = 0.f;
         if (RANGES && direct && pl >= 0 && pl < n_phases)
             direct_v = direct_combine<NB, GB>(a, a.part + ((size_t)(pl % kSlots) * a.n_wg + a.ent_w0) * kRowsPad, a.ent_n,
-                                              (uint32_t)(pl / kSlots) & 1u, lds0, fail, lane, c_direct, F8 ? 1.0f / c_direct : a.inv_c);
+                                              (uint32_t)(pl / kSlots) & 1u, lds0 + MP::kXduty, fail, lane, c_direct, F8 ? 1.0f / c_direct : a.inv_c);
         if (pl >= 0 && pl < n_phases && lane < a.rows_pad) {
             int g, n;
             float v = neg_inf();
@@ -1067,7 +1109,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
               if (RANGES && direct) v = direct_v;
               else {
                 const uint64_t *src = a.lse + ((size_t)(pl % kSlots) * a.n_gp + a.p_idx) * a.rows_pad + lane;
-                uint64_t entry = read_lse_staging(lds0, lane);
+                uint64_t entry = read_lse_staging(lds0 + MP::kXlse, lane);
                 if ((uint32_t)(entry >> 32) != (uint32_t)(pl + 1) && *fail == 0) {
                     unsigned spins = 0;
                     while ((uint32_t)(entry >> 32) != (uint32_t)(pl + 1)) {
@@ -1080,12 +1122,12 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
                 if (EXTRA && a.look != nullptr) {
                     // the row's softmax also runs over its visible lookahead keys: log-sum-exp of the
                     // prompt's normaliser and theirs (-inf when the row sees none), in raw-logit units
-                    const float lp = -v, lk = read_look_staging(lds0, lane), top = fmaxf(lp, lk);
+                    const float lp = -v, lk = read_look_staging(lds0 + MP::kXlse, lane), top = fmaxf(lp, lk);
                     v = -(top + fast_log2(fast_exp2((lp - top) * a.c) + fast_exp2((lk - top) * a.c)) * a.inv_c);
                 }
             }
             const int rho = lane & 31;
-            lds_store_f32(lds0 + kOffCinit + PAR * (kMaxRowsF * 4) +
+            lds_store_f32(lds0 + MP::kCinit + PAR * (kMaxRowsF * 4) +
                               4u * (uint32_t)((lane & ~31) + ((rho >> 2) & 1) * 16 + 4 * (rho >> 3) + (rho & 3)), v);
         }
     }
@@ -1161,7 +1203,10 @@ __device__ __forceinline__ void fold_model_constants(FusedArgs &a)
 template <int NB, int GB, Kind KIND, class M, bool W = false, bool F8 = false, bool PAIR = false>
 __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, LayerPtrs kp, GroupTable gt)
 {
-    static_assert(!W || (NB == 1 && GB == 1 && !M::kFixed), "head_dim 128: one block of 32 query rows");
+    static_assert(!W || (NB == 1 && !M::kFixed), "head_dim 128: one block of lookahead rows");
+    constexpr bool BIG = W && NB * GB == 2;
+    static_assert(!BIG || (!PAIR && !F8), "head_dim 128, two blocks of query rows: bf16 keys, one tile a workgroup");
+    using MP = Map<BIG>;
     static_assert(!F8 || KIND != kExtra, "8-bit keys: contiguous keys of one prompt");
     static_assert(!PAIR || (NB == 1 && KIND != kRanges), "pairs of tiles: whole prompts, one block of lookahead rows");
     constexpr bool EXTRA = KIND != kPlain, RANGES = KIND == kRanges;
@@ -1170,7 +1215,7 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     constexpr int kTile = W ? kFTile / 2 : kFTile;            // keys per workgroup
     constexpr int kWaveKeys = kTile / kFWaves;
     constexpr int kHeadDim = W ? 2 * kD : kD;
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[kLdsBytes];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[MP::kBytes];
     fold_model_constants<M>(a);
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, hf = lane >> 5, col = lane & 31;
@@ -1232,12 +1277,12 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
 
     // zero the Q tiles (their padding rows are never loaded), seed the accumulator seeds with -inf
     {
-        u32x4 *z = reinterpret_cast<u32x4 *>(lds + kOffQ1);
+        u32x4 *z = reinterpret_cast<u32x4 *>(lds + MP::kQ1);
         const u32x4 zero = {0u, 0u, 0u, 0u};
-        for (int i = tid; i < 4 * kQTileBytes / 16; i += kFThreads) z[i] = zero;
-        float *ci = reinterpret_cast<float *>(lds + kOffCinit);
+        for (int i = tid; i < 4 * MP::kQTileBytes / 16; i += kFThreads) z[i] = zero;
+        float *ci = reinterpret_cast<float *>(lds + MP::kCinit);
         if (tid < 2 * kMaxRowsF) ci[tid] = neg_inf();
-        if (tid == 0) *reinterpret_cast<int *>(lds + kOffFail) = 0;
+        if (tid == 0) *reinterpret_cast<int *>(lds + MP::kFail) = 0;
     }
     __syncthreads();
 
@@ -1258,11 +1303,14 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
             lc.koff[0] = lc.koff[1] = rowpart + ((((uint32_t)lane & 3u) ^ (((uint32_t)lane >> 4) & 3u)) << 4);
         }
         // a wave's slice of a Q tile: 8 rows (W: of one half-tile, waves 4..7 take the second halves)
-        const int row = (W ? (wave & 3) : wave) * 8 + (lane >> 3);
-        int g, n;
-        lc.qoff = -1;
-        if (row < a.rows_pad && row_valid<NB>(a, row, g, n))
-            lc.qoff = ((g * a.n_q + n) * kHeadDim + (W ? (wave >> 2) * kD : 0) + (((lane & 7) ^ ((row >> 1) & 7)) << 3)) * 2;
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk) {
+            const int row = (BIG ? 32 * blk : 0) + (W ? (wave & 3) : wave) * 8 + (lane >> 3);
+            int g, n;
+            lc.qoff[blk] = -1;
+            if ((BIG || blk == 0) && row < a.rows_pad && row_valid<NB>(a, row, g, n))
+                lc.qoff[blk] = ((g * a.n_q + n) * kHeadDim + (W ? (wave >> 2) * kD : 0) + (((lane & 7) ^ ((row >> 1) & 7)) << 3)) * 2;
+        }
     }
 
     Ring ring;
@@ -1292,11 +1340,13 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     const uint64_t wave_off = key_offset(j0);
 
     // prologue: this wave's slice of Q(0) and both sub-tiles of K(0); everything lands before step 0
-    if (lc.qoff >= 0) dma_u<kOffQ1>((uint32_t)lc.qoff, a.q, lds0 + wave_u * 1024);
+#pragma unroll
+    for (int blk = 0; blk < (BIG ? 2 : 1); ++blk)
+        if (lc.qoff[blk] >= 0) dma_u<MP::kQ1>((uint32_t)lc.qoff[blk], a.q, lds0 + wave_u * 1024 + blk * MP::kQBlock);
 #pragma unroll
     for (int s2 = 0; s2 < kNS; ++s2) {
         KIssue ki;
-        ki.lds_dst = lds0 + sub_slot_off(wave_u, 0, s2);
+        ki.lds_dst = lds0 + sub_slot_off<BIG>(wave_u, 0, s2);
         ki.base = reinterpret_cast<const char *>(kp.p[layer0]) + wave_off + (W ? (uint64_t)(s2 * kD * kElem) : (uint64_t)(s2 * 32) * stride_bytes);
         ki.step_bytes = (F8 ? 16u : 8u) * stride_bytes;
         k_issue<kSI>(ki, lc.koff, 0);
@@ -1459,7 +1509,7 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
     using Draft16 = Draft16x32x8<16, 0>;
     using Draft8 = Draft16x32x8<8, 0>;
     const int blocks = a.n_nblk * 10 + a.n_gblk;
-    if (a.head_dim == 2 * kD ? blocks != 11 : blocks != 11 && blocks != 12 && blocks != 21)
+    if (a.head_dim == 2 * kD ? blocks != 11 && (blocks != 12 || a.kscale || pair) : blocks != 11 && blocks != 12 && blocks != 21)
         return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, head_dim %d: %d x %d row blocks", a.head_dim, a.n_nblk, a.n_gblk);
     if (a.kscale != nullptr && extra && !(ranges && a.look == nullptr && a.block_table == nullptr))
         return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, 8-bit keys: one prompt, contiguous keys only");
@@ -1493,7 +1543,8 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
         else if (blocks == 21) SP_FUSED(2, 1, kPlain, AnyModel, false, true);
         else if (blocks == 12) SP_FUSED(1, 2, kPlain, AnyModel, false, true);
         else SP_FUSED(1, 1, kPlain, AnyModel, false, true);
-    } else if (a.head_dim == 2 * kD) SP_FUSED_KINDS(1, 1, AnyModel, true);
+    } else if (a.head_dim == 2 * kD && blocks == 12) SP_FUSED_KINDS(1, 2, AnyModel, true);
+    else if (a.head_dim == 2 * kD) SP_FUSED_KINDS(1, 1, AnyModel, true);
     else if (draft && !extra && a.n_q == 16 && a.n_wg == 256) SP_FUSED(2, 1, kPlain, Draft16x32x8<16, 256>);
     else if (draft && !extra && a.n_q == 8 && a.n_wg == 256) SP_FUSED(1, 1, kPlain, Draft16x32x8<8, 256>);
     else if (draft && a.n_q == 16) SP_FUSED_KINDS(2, 1, Draft16);

@@ -276,6 +276,11 @@ RANGE_SHAPES = [
     ("ranges_short_prompts", 16, 32, 8, 64, 8, [4700, 60, 3000, 1, 511]),
     ("ranges_short_prompts_rows64", 14, 16, 4, 64, 16, [11000, 77, 600, 300]),
     ("ranges_short_prompts_d128", 14, 8, 4, 128, 8, [255, 3000, 2049, 64, 1500, 1]),
+    # head_dim 128 with two blocks of query rows (five to eight heads a kv head)
+    ("ranges_d128_g8", 24, 32, 4, 128, 8, [6001]),                   # 24 workgroups: 8 ranges of 3 layers
+    ("ranges_d128_g5_padding", 24, 20, 4, 128, 5, [6200]),
+    ("whole_d128_g8", 12, 8, 1, 128, 8, [45000]),                    # 176 workgroups, one range
+    ("ranges_batch_d128_g8", 24, 32, 4, 128, 8, [6000, 300, 2000]),
 ]
 
 
@@ -340,6 +345,21 @@ def test_score_with_two_tiles_a_workgroup_matches_oracle(shape):
         assert_scores_close(gpu_score_look(q, k, kl, 1, w.scale, 0), oracle.score_look(q, k, kl, 1, w.scale, 0))
         nhd = [np.ascontiguousarray(x.transpose(1, 0, 2)) for x in k]
         assert gpu_score(q, nhd, w.scale, mode, layout="NHD").tobytes() == got.tobytes()
+
+
+def test_wide_query_groups_with_lookahead_and_paged_keys():
+    """head_dim 128 with eight heads a kv head on the single-launch kernel: lookahead keys in the normaliser, paged keys."""
+    from gpu_util import assert_scores_close, gpu_score_look, gpu_score_paged, make_paged
+    Lyr, H, Hkv, d, n_q, L, page = 24, 32, 4, 128, 8, 6001, 512
+    say(f"[score-wide] L={L}")
+    w = small_workload("wide_group", Lyr, H, Hkv, d, n_q, L, cfg_id=650, hh=(1, 1000))
+    inp = synth.make_score_inputs(w)
+    q, k = inp["q"][0], inp["k"]
+    kl = synth.gen_look_keys(w, inp["q"])
+    for mode in (0, 1):
+        assert_scores_close(gpu_score_look(q, k, kl, 1, w.scale, mode), oracle.score_look(q, k, kl, 1, w.scale, mode))
+    pools, table = make_paged(k, page, "HND", seed=w.cfg_id)
+    assert_scores_close(gpu_score_paged(q, pools, table, page, L, w.scale, 0, "HND"), oracle.score(q, k, w.scale, 0))
 
 
 def test_fused_score_gives_up_as_a_whole():
