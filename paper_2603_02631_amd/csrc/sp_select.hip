@@ -74,27 +74,27 @@ __device__ __forceinline__ void chunk_means(const float *__restrict__ scores, in
 {
     const int lane = threadIdx.x & 63, half = (pool_w - 1) / 2;
     const float *src[N];            // the first token's score; positions below count from half tokens before it
-    int size[N], lo[N], hi[N];
-    int n_tok = 0;
+    uint32_t size[N], lo[N], hi[N];         // a chunk and its neighbours may pass 2^31 tokens
+    uint32_t n_tok = 0;
 #pragma unroll
     for (int u = 0; u < N; ++u) {
         const int64_t begin = (ci + u * stride) * chunk;
         const bool live = ci + u * stride < n_chunks;
-        size[u] = live ? (int)(begin + chunk < L ? chunk : L - begin) : 1;
+        size[u] = live ? (uint32_t)(begin + chunk < L ? chunk : L - begin) : 1;
         src[u] = scores + (live ? begin : 0);
-        lo[u] = begin < half ? half - (int)begin : 0;                       // tokens before the prompt are zeros,
-        hi[u] = live ? size[u] + half + (int)(L - begin - size[u] < half ? L - begin - size[u] : half) : 0;     // and those behind it
+        lo[u] = begin < half ? (uint32_t)(half - begin) : 0;                       // tokens before the prompt are zeros,
+        hi[u] = live ? size[u] + half + (uint32_t)(L - begin - size[u] < half ? L - begin - size[u] : half) : 0;     // and those behind it
         n_tok = hi[u] > n_tok ? hi[u] : n_tok;
         mean[u] = 0.f;
     }
-    for (int t = lane; t < n_tok; t += 64) {
+    for (uint32_t t = lane; t < n_tok; t += 64) {
         float v[N];
 #pragma unroll
-        for (int u = 0; u < N; ++u) v[u] = t >= lo[u] && t < hi[u] ? src[u][t - half] : 0.f;
+        for (int u = 0; u < N; ++u) v[u] = t >= lo[u] && t < hi[u] ? src[u][(int64_t)t - half] : 0.f;
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             // windows centred on this chunk's tokens t - 2 half .. t contain the token
-            const int first = t - 2 * half > 0 ? t - 2 * half : 0, last = t < size[u] - 1 ? t : size[u] - 1;
+            const uint32_t first = t > 2u * half ? t - 2u * half : 0u, last = t < size[u] - 1 ? t : size[u] - 1;
             mean[u] = fmaf((float)(last - first + 1), v[u], mean[u]);
         }
     }
