@@ -106,6 +106,7 @@ sp_status sp_score_workspace(const sp_score_desc *desc, int64_t total_tokens,
  * second), after which the call has failed as a whole: every score of the call
  * is NaN and the workspace's status word (see sp_score_workspace) is 1. It
  * never hangs, and a failed call means "run again", never a wrong value.
+ * Calls of one process on several streams take turns on the device with it.
  */
 sp_status sp_score(const sp_score_desc *desc, const void *q_dev,
                    const void *const *k_layers_host, int64_t L,

@@ -32,6 +32,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <vector>
 
 namespace {
@@ -867,6 +868,61 @@ sp_status launch_all(const Plan &p, const ScoreArgs &a, const LayerPtrs &kp, hip
     return SP_OK;
 }
 
+// The workgroups of a single-launch kernel wait for each other. Two such kernels on different streams can each hold
+// compute units that the other one needs (every XCD dispatches its share of a grid on its own, so one may start with
+// the first kernel and another with the second), and both would wait until they give up. The launches of a process
+// on one device therefore take turns: a call on another stream than the last one's waits, on the device, for that
+// call's kernels. One event per device, kept until the process ends; the record costs a call on one stream about a
+// microsecond. Not in a captured graph, which knows nothing of its replays' neighbours: see capturing.
+class Turn {
+public:
+    explicit Turn(hipStream_t st, bool take = true) : st_(st)
+    {
+        if (!take) return;
+        static Slot slots[64];
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return;
+        Slot &s = slots[dev];
+        lock_ = std::unique_lock<std::mutex>(s.m);
+        if (!s.done && hipEventCreateWithFlags(&s.done, hipEventDisableTiming) != hipSuccess) {
+            s.done = nullptr;
+            (void)hipGetLastError();
+            return;
+        }
+        slot_ = &s;
+        // the per-thread stream has one handle for all threads
+        if (s.used && (s.last != st || st == hipStreamPerThread) && hipStreamWaitEvent(st, s.done, 0) != hipSuccess) (void)hipGetLastError();
+    }
+    ~Turn()
+    {
+        if (!slot_) return;
+        if (hipEventRecord(slot_->done, st_) != hipSuccess) { (void)hipGetLastError(); return; }
+        slot_->used = true;
+        slot_->last = st_;
+    }
+    Turn(const Turn &) = delete;
+    Turn &operator=(const Turn &) = delete;
+
+private:
+    struct Slot {
+        std::mutex m;
+        hipEvent_t done = nullptr;
+        hipStream_t last = nullptr;
+        bool used = false;
+    };
+    hipStream_t st_;
+    Slot *slot_ = nullptr;
+    std::unique_lock<std::mutex> lock_;
+};
+
+// A captured call takes the single-launch kernel only where sp_score_is_fused says so, since it takes no turns.
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) { (void)hipGetLastError(); return true; }
+    return status != hipStreamCaptureStatusNone;
+}
+
 // What the variants of sp_score add to the plain call.
 struct ScoreOptions {
     const void *k_look = nullptr;            // lookahead keys in the normaliser
@@ -995,7 +1051,9 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     f.layer_agg = a.layer_agg;
     f.c = a.c; f.inv_c = a.inv_c; f.out_scale = a.out_scale;
     BatchGroups bg;
-    if (may_fuse && !batch && pair_applies(p, total, desc->k_stride_token)) {
+    const bool captured = may_fuse && capturing(st);
+    if (may_fuse && !captured && !batch && pair_applies(p, total, desc->k_stride_token)) {
+        const Turn turn(st);
         f.tile_keys = 2 * fused_tile(p);
         f.L = total;
         f.n_wg = (int)sp::ceil_div(total, f.tile_keys);
@@ -1005,16 +1063,17 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
                                        : plan_fused_prompt(p, total, desc->k_stride_token, bg));
     int ranges = 1;
     const bool big = fused_big(p);
-    if (fused && bg.groups.size() == 1) {
+    if (fused && !captured && bg.groups.size() == 1) {
         // the exchange area of a launch in layer ranges takes the place of the general path's buffers
         ranges = fused_ranges(p, bg.wgs[0], bg.groups[0].n, w.split - w.part);
     }
     if (fused && (big || !(batch ? whole_groups_pay(bg) : bg.wgs[0] >= fused_min_workgroups(p))))
-        fused = (batch || ranges > 1 || bg.wgs[0] >= fused_min_workgroups(p)) && steps_pay(p, total, ranges, (int)bg.groups.size());
+        fused = !captured && (batch || ranges > 1 || bg.wgs[0] >= fused_min_workgroups(p)) && steps_pay(p, total, ranges, (int)bg.groups.size());
     if (fused && big)           // no exchange area of their own: see fused_big
         for (size_t g = 0; g < bg.groups.size(); ++g)
             fused = fused && sp_fused::workspace_bytes(p.rows_pad, bg.wgs[g], bg.groups[g].n) <= w.split - w.part;
     if (fused) {
+        const Turn turn(st, !captured);
         if (ranges > 1) {
             const sp_fused::GroupTable t = split_layers(bg.groups[0], p.n_layers, ranges);
             f.n_wg = bg.wgs[0] * ranges;

@@ -474,3 +474,55 @@ def test_score_over_paged_keys_matches_oracle(shape):
         got = gpu_score_paged(q, pools, table, P, L, w.scale, mode, layout)
         assert_scores_close(got, want)
         say(f"  mode {mode}: max rel err {np.max(np.abs(got - want) / want):.2e}")
+@pytest.mark.parametrize("n_streams", [2, 4])
+def test_scores_on_several_streams_at_once(n_streams):
+    """Single-launch kernels on different streams take turns: every call ends with the scores it has alone."""
+    import torch
+    import paper_2603_02631_amd as sp
+    dev = "cuda:0"
+    say(f"[score-streams] {n_streams} streams")
+    calls = []
+    for i, L in enumerate([8200, 20001, 6200, 33000][:n_streams]):
+        g = torch.Generator(device=dev).manual_seed(i)
+        q = torch.randn((16, 32, 8, 64), device=dev, generator=g).to(torch.bfloat16)
+        k = [torch.randn((8, L, 64), device=dev, generator=g).to(torch.bfloat16) for _ in range(16)]
+        desc = sp.ScoreDesc(16, 32, 8, 64, 8, 0.125, sp.SP_LAYER_MEAN, 64, L * 64)
+        ws = torch.empty(sp.sp_score_workspace(desc, L, 1), dtype=torch.uint8, device=dev)
+        out = torch.zeros(L, dtype=torch.float32, device=dev)
+        sp.sp_score(desc, q, k, L, out, ws)
+        calls.append((desc, q, k, L, out, ws, out.clone(), torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for desc, q, k, L, out, ws, _, stream in calls:
+            with torch.cuda.stream(stream):
+                out.fill_(-1.0)
+                sp.sp_score(desc, q, k, L, out, ws)
+    torch.cuda.synchronize()
+    for *_, out, ws, want, _ in calls:
+        assert torch.equal(out, want)
+
+
+def test_captured_score_of_a_short_prompt():
+    """A captured call takes the general path; every replay agrees with the eager call."""
+    import torch
+    import paper_2603_02631_amd as sp
+    dev, L = "cuda:0", 8200
+    say("[score-capture]")
+    g = torch.Generator(device=dev).manual_seed(3)
+    q = torch.randn((16, 32, 8, 64), device=dev, generator=g).to(torch.bfloat16)
+    k = [torch.randn((8, L, 64), device=dev, generator=g).to(torch.bfloat16) for _ in range(16)]
+    desc = sp.ScoreDesc(16, 32, 8, 64, 8, 0.125, sp.SP_LAYER_MEAN, 64, L * 64)
+    ws = torch.empty(sp.sp_score_workspace(desc, L, 1), dtype=torch.uint8, device=dev)
+    eager, out = torch.zeros(L, device=dev), torch.zeros(L, device=dev)
+    sp.sp_score(desc, q, k, L, eager, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sp.sp_score(desc, q, k, L, out, ws)
+    for _ in range(3):
+        out.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        torch.testing.assert_close(out, eager, rtol=1e-4, atol=0.0)     # fp32 exponentials of two summation orders
+        sp.sp_score(desc, q, k, L, eager, ws)
+        torch.cuda.synchronize()
