@@ -419,9 +419,10 @@ sp_status sp_hbm_read_probe(const void *buf_dev, size_t bytes, uint64_t *sink_de
 
 /* Test hook for the failure path of the single-launch score kernel; not for
  * production use. Launches that follow give a wait up after `spin_limit` polls
- * (default 1 << 20), and with force_miss != 0 the waves that combine partial
+ * (default 1 << 20), and with force_miss == 1 the waves that combine partial
  * results treat them as never arriving, so that the bounded waits give up on an
- * idle device and every kernel still runs to its end. Process-wide. */
+ * idle device and every kernel still runs to its end; force_miss == 2 + b does so
+ * in the launches that hold prompt b of their call only. Process-wide. */
 void sp_debug_fused_giveup(uint32_t spin_limit, int32_t force_miss);
 
 /* Description of the last error raised on the calling thread ("" if none).

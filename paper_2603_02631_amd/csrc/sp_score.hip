@@ -536,6 +536,14 @@ __global__ __launch_bounds__(256) void sp_split_reduce_kernel(const float *__res
     scores[j] = *status != 0u ? __uint_as_float(0x7fc00000u) : both * out_scale;     // a failed call has no scores
 }
 
+// Last launch of a batch of several launches: a call fails as a whole, and a launch that gave up may follow one that
+// has left valid scores.
+__global__ __launch_bounds__(256) void sp_fail_all_kernel(const uint32_t *__restrict__ status, int64_t total, float *__restrict__ scores)
+{
+    if (*status == 0u) return;
+    for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < total; j += (int64_t)gridDim.x * 256) scores[j] = __uint_as_float(0x7fc00000u);
+}
+
 // Tile table of a ragged batch: tiles never straddle prompts.
 __global__ void sp_tiles_kernel(const int64_t *offsets, int n_prompts, int tile_keys, TileInfo *tiles,
                                 int32_t *prompt_tiles, int n_tiles_cap)
@@ -1091,6 +1099,11 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
             const bool shared = !bg.short_prompt && bg.groups[g].n * (p.rows_pad / sp_fused::kDutyRows) <= bg.wgs[g];
             const sp_status rs = sp_fused::launch(f, kp, batch ? &bg.groups[g] : nullptr, shared, g == 0, ws + (big ? w.part : w.fused), a.status, st);
             if (rs != SP_OK) return rs;
+        }
+        if (bg.groups.size() > 1) {
+            hipLaunchKernelGGL(sp_fail_all_kernel, dim3((unsigned)std::min<int64_t>(sp::ceil_div(total, 1024), 64)), dim3(256), 0, st,
+                               (const uint32_t *)a.status, total, scores_dev);
+            SP_HIP_CHECK(hipGetLastError());
         }
         return SP_OK;
     }

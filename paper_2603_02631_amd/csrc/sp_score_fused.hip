@@ -1419,8 +1419,8 @@ __global__ void sp_fused_clear_kernel(uint64_t *p, size_t n, uint32_t *err)
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0;
 }
 
-// Test hook (see sp_debug_fused_giveup): polls before a wait gives up, and whether duty waves treat
-// their partials as never arriving.
+// Test hook (see sp_debug_fused_giveup): polls before a wait gives up, and the launches whose duty waves
+// treat their partials as never arriving (0: none, 1: all, 2 + b: those that hold prompt b).
 std::atomic<uint32_t> g_spin_max{1u << 20};     // about a second
 std::atomic<int32_t> g_force_miss{0};
 
@@ -1486,7 +1486,9 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
     a.lse = base + n_part;
     a.err = status_word;
     a.spin_max = g_spin_max.load(std::memory_order_relaxed);
-    a.force_miss = g_force_miss.load(std::memory_order_relaxed);
+    const int32_t miss = g_force_miss.load(std::memory_order_relaxed);
+    a.force_miss = miss == 1 || (miss == 2 && gt.n == 0);
+    for (int i = 0; i < gt.n && miss >= 2; ++i) a.force_miss |= gt.prompt[i] == miss - 2;
     const size_t n_clear = n_part + n_lse;
     hipLaunchKernelGGL(sp_fused_clear_kernel, dim3((unsigned)((n_clear + 255) / 256 > 1024 ? 1024 : (n_clear + 255) / 256)),
                        dim3(256), 0, st, base, n_clear, clear_status ? status_word : (uint32_t *)nullptr);

@@ -396,6 +396,39 @@ def test_fused_score_gives_up_as_a_whole():
     assert_scores_close(scores.cpu().numpy(), oracle.score(inp["q"][0], inp["k"], w.scale, 0))
 
 
+@pytest.mark.parametrize("prompt", [0, 2])
+def test_batch_of_several_launches_gives_up_as_a_whole(prompt):
+    """Two launches (128 + 128 workgroups and 64): one of them gives up, the other one's prompts lose their scores too."""
+    import torch
+    import paper_2603_02631_amd as sp
+    from gpu_util import DEV, status_word, workspace
+    Lyr, H, Hkv, d, n_q = 2, 8, 2, 64, 8
+    off = [0, 65536, 131072, 163840]
+    say(f"[score-batch] give-up of the launch that holds prompt {prompt}")
+    g = torch.Generator(device=DEV).manual_seed(5)
+    q = torch.randn((3, Lyr, H, n_q, d), device=DEV, generator=g).to(torch.bfloat16)
+    k = [torch.randn((Hkv, off[-1], d), device=DEV, generator=g).to(torch.bfloat16) for _ in range(Lyr)]
+    desc = sp.ScoreDesc(Lyr, H, Hkv, d, n_q, 0.125, sp.SP_LAYER_MEAN, d, off[-1] * d)
+    assert sp.sp_score_batch_is_fused(desc, off) == 2
+    ws = workspace(sp.sp_score_workspace(desc, off[-1], 3))
+    od = torch.tensor(off, dtype=torch.int64, device=DEV)
+    scores = torch.zeros(off[-1], dtype=torch.float32, device=DEV)
+    try:
+        sp.sp_debug_fused_giveup(4, 2 + prompt)
+        sp.sp_score_batch(desc, q, k, off, od, scores, ws)
+        torch.cuda.synchronize()
+    finally:
+        sp.sp_debug_fused_giveup(1 << 20, 0)
+    assert status_word(ws) == 1
+    assert bool(torch.isnan(scores).all())
+    sp.sp_score_batch(desc, q, k, off, od, scores, ws)
+    torch.cuda.synchronize()
+    assert status_word(ws) == 0
+    for b in range(3):
+        s = scores[off[b]:off[b + 1]]
+        assert bool(torch.isfinite(s).all()) and 0.99 < float(s.double().sum()) < H
+
+
 LOOK_SHAPES = [
     # name, Lyr, H, Hkv, d, n_q, L   (general path: short prompts, head_dim 128; fused path: long prompts)
     ("look_g4_nq16_d64", 3, 8, 2, 64, 16, 1500),
