@@ -100,13 +100,21 @@ sp_status sp_score_workspace(const sp_score_desc *desc, int64_t total_tokens,
  * device pointers. scores_dev: float[L]. L == 0 is a no-op returning SP_OK.
  * The softmax is exact (row maximum and sum over all L keys, fp32); the result
  * is deterministic: the same inputs give bit-identical scores.
- * The single-launch kernel (see sp_score_is_fused) needs all its workgroups
- * resident at once, which an otherwise idle device guarantees; if other work
- * occupies the device, its waits on other workgroups are bounded (about a
- * second), after which the call has failed as a whole: every score of the call
- * is NaN and the workspace's status word (see sp_score_workspace) is 1. It
- * never hangs, and a failed call means "run again", never a wrong value.
+ * The single-launch kernel needs all its workgroups resident at once, which an
+ * otherwise idle device guarantees; if other work occupies the device, its waits
+ * on other workgroups are bounded and it gives up. It never hangs.
+ *  - Calls for which sp_score_is_fused answers 1 wait for about a second and
+ *    have then failed as a whole: every score of the call is NaN and the
+ *    workspace's status word (see sp_score_workspace) is 1. A failed call means
+ *    "run again", never a wrong value.
+ *  - Every other call never fails: some of them use the single-launch kernel too
+ *    where it is faster, but give up after some 30 ms, and a last launch then
+ *    computes the scores without it (tens of milliseconds to a second).
  * Calls of one process on several streams take turns on the device with it.
+ * Calls recorded into a graph do not: such a call uses the single-launch kernel
+ * only where sp_score_is_fused answers 1, and its replays must then not overlap
+ * another such call or replay. (Elsewhere the recorded call takes the
+ * three-kernel path, so its scores may differ from the eager call's by rounding.)
  */
 sp_status sp_score(const sp_score_desc *desc, const void *q_dev,
                    const void *const *k_layers_host, int64_t L,
@@ -174,13 +182,14 @@ sp_status sp_score_fp8(const sp_score_desc *desc, const void *q_dev,
                        int64_t L, float *scores_dev, void *ws_dev, size_t ws_bytes,
                        void *hip_stream);
 
-/* Which implementation sp_score picks for this shape and length on the current
- * device: 1 = the single-launch kernel that keeps K on chip and reads it from
- * HBM once, 0 = the three-kernel path or, where that is faster, the single-launch
- * kernel with the layers in ranges side by side (shorter prompts), with two tiles a
- * workgroup (longer ones) or with two blocks of query rows at head_dim 128 (33 to 64
- * padded rows, up to 8 lookahead rows); -1 = invalid or unsupported desc.
- * The single-launch kernel takes one workgroup per compute unit, each owning T keys:
+/* Whether sp_score needs the device's compute units to itself for this shape and
+ * length on the current device, i.e. can fail (see there): 1 = it relies on the
+ * single-launch kernel, which keeps K on chip and reads it from HBM once, 0 = the
+ * call never fails: the three-kernel path or, where that is faster, the single-launch
+ * kernel with a stand-in: the layers in ranges side by side (shorter prompts), two
+ * tiles a workgroup (longer ones), or two blocks of query rows at head_dim 128 (33 to
+ * 64 padded rows, up to 8 lookahead rows); -1 = invalid or unsupported desc.
+ * In the calls answered with 1 the kernel takes one workgroup per compute unit, each owning T keys:
  * head_dim 64: T = 512, query groups of up to 64 padded rows, 64 to 256
  * workgroups (about 32K to 128K tokens); head_dim 128: T = 256, up to 32 padded
  * rows, 96 to 256 workgroups (about 24K to 64K tokens). Results are the same
@@ -208,7 +217,8 @@ sp_status sp_score_batch(const sp_score_desc *desc, const void *q_dev,
  * single-launch kernel in n launches (every prompt empty or at least T tokens
  * long and no longer than T tokens per compute unit, T as above; at least 64
  * workgroups in all; prompts share launches, each with all its keys in one),
- * 0 = the three-kernel path, -1 = invalid
+ * 0 = a call that never fails (see sp_score_is_fused): the three-kernel path or,
+ * where that is faster, the single-launch kernel with a stand-in; -1 = invalid
  * arguments. Same results either way (to rounding). Host-only. */
 int32_t sp_score_batch_is_fused(const sp_score_desc *desc,
                                 const int64_t *offsets_host, int32_t B);

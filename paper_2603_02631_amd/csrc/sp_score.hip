@@ -187,6 +187,43 @@ __device__ __forceinline__ void stage_k(u32x4 *ks, const uint16_t *kb, int64_t s
     }
 }
 
+// Folds one 32-key sub-tile's logits of a query row, of which `left` keys exist, into the row's running statistics.
+// acc[r]: key 8*(r/4) + 4*hf + r%4 of the sub-tile.
+__device__ __forceinline__ void fold_keys(const f32x16 &acc, int64_t left, int hf, float c, float &m, float &l)
+{
+    if (left >= 32) {
+        float tm = acc[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) tm = fmaxf(tm, acc[r]);
+        const float mn = fmaxf(m, tm);
+        l *= fast_exp2((m - mn) * c);
+        m = mn;
+        const float mc = mn * c;
+        float sum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum += fast_exp2(fmaf(acc[r], c, -mc));
+        l += sum;
+    } else if (left > 0) {
+        float tm = neg_inf();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int key = 8 * (r >> 2) + 4 * hf + (r & 3);
+            if (key < left) tm = fmaxf(tm, acc[r]);
+        }
+        if (tm > neg_inf()) {
+            const float mn = fmaxf(m, tm);
+            l *= fast_exp2((m - mn) * c);
+            m = mn;
+            const float mc = mn * c;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int key = 8 * (r >> 2) + 4 * hf + (r & 3);
+                if (key < left) l += fast_exp2(fmaf(acc[r], c, -mc));
+            }
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // stats: partial (max, sum exp) of every query row of one (layer, kv head)
 // over one key tile.
@@ -230,38 +267,7 @@ __global__ __launch_bounds__(kThreads, 4) void sp_stats_kernel(ScoreArgs a, Laye
 #pragma unroll
             for (int t = 0; t < KS; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s][t], qf[t], acc, 0, 0, 0);
             // acc[r]: key (wave*NS+s)*32 + 8*(r/4) + 4*hf + r%4 of the tile, query row blk*32 + col
-            const int64_t left = ti.end - (ti.j0 + (wave * NS + s) * 32);
-            if (left >= 32) {
-                float tm = acc[0];
-#pragma unroll
-                for (int r = 1; r < 16; ++r) tm = fmaxf(tm, acc[r]);
-                const float mn = fmaxf(m, tm);
-                l *= fast_exp2((m - mn) * c);
-                m = mn;
-                const float mc = mn * c;
-                float sum = 0.f;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) sum += fast_exp2(fmaf(acc[r], c, -mc));
-                l += sum;
-            } else if (left > 0) {
-                float tm = neg_inf();
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int key = 8 * (r >> 2) + 4 * hf + (r & 3);
-                    if (key < left) tm = fmaxf(tm, acc[r]);
-                }
-                if (tm > neg_inf()) {
-                    const float mn = fmaxf(m, tm);
-                    l *= fast_exp2((m - mn) * c);
-                    m = mn;
-                    const float mc = mn * c;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int key = 8 * (r >> 2) + 4 * hf + (r & 3);
-                        if (key < left) l += fast_exp2(fmaf(acc[r], c, -mc));
-                    }
-                }
-            }
+            fold_keys(acc, ti.end - (ti.j0 + (wave * NS + s) * 32), hf, c, m, l);
         }
         const float m2 = __shfl_xor(m, 32), l2 = __shfl_xor(l, 32);
         lse_merge(m, l, m2, l2, c);
@@ -287,6 +293,23 @@ __global__ __launch_bounds__(kThreads, 4) void sp_stats_kernel(ScoreArgs a, Laye
 // prob pass reads it from: within a block, row rho = 8*q + 4*hf + e goes to
 // hf*16 + 4*q + e. Padding rows get -inf so they never win a maximum.
 // ---------------------------------------------------------------------------
+// -lse of a row from its statistics over all keys of its prompt.
+__device__ __forceinline__ float row_normaliser(const ScoreArgs &a, int phase, int row, float m, float l, float c, float inv_c)
+{
+    int g, n;
+    const bool valid = row_to_gn(a, row, g, n) && l > 0.f;
+    float v = valid ? -(m + fast_log2(l) * inv_c) : neg_inf();
+    if (valid && a.look != nullptr) {
+        // the softmax also runs over the row's visible lookahead keys: log-sum-exp of both parts
+        const float lp = -v, lk = a.look[(int64_t)phase * a.rows_pad + row], top = fmaxf(lp, lk);
+        v = -(top + fast_log2(fast_exp2((lp - top) * a.c) + fast_exp2((lk - top) * a.c)) * a.inv_c);
+    }
+    return v;
+}
+
+// Where the prob pass reads row rho of a block from.
+__device__ __forceinline__ int seed_pos(int rho) { return ((rho >> 2) & 1) * 16 + 4 * (rho >> 3) + (rho & 3); }
+
 constexpr int kMergeSlices = 32;             // thread groups of 32 rows that share a prompt's tiles
 constexpr int kMergeThreads = 32 * kMergeSlices;
 
@@ -311,16 +334,8 @@ __global__ __launch_bounds__(kMergeThreads) void sp_merge_kernel(ScoreArgs a)
     if (slice == 0) {
 #pragma unroll
         for (int s = 1; s < kMergeSlices; ++s) lse_merge(m, l, red[s][rho].x, red[s][rho].y, c);
-        int g, n;
-        const bool valid = row_to_gn(a, row, g, n) && l > 0.f;
-        float v = valid ? -(m + fast_log2(l) * inv_c) : neg_inf();
-        if (valid && a.look != nullptr) {
-            // the softmax also runs over the row's visible lookahead keys: log-sum-exp of both parts
-            const float lp = -v, lk = a.look[(int64_t)phase * a.rows_pad + row], top = fmaxf(lp, lk);
-            v = -(top + fast_log2(fast_exp2((lp - top) * a.c) + fast_exp2((lk - top) * a.c)) * a.inv_c);
-        }
-        const int pos = ((rho >> 2) & 1) * 16 + 4 * (rho >> 3) + (rho & 3);
-        a.lse_neg[((int64_t)prompt * n_phases + phase) * a.rows_pad + blk * 32 + pos] = v;
+        const float v = row_normaliser(a, phase, row, m, l, c, inv_c);
+        a.lse_neg[((int64_t)prompt * n_phases + phase) * a.rows_pad + blk * 32 + seed_pos(rho)] = v;
     }
 }
 
@@ -380,6 +395,57 @@ __global__ __launch_bounds__(kThreads) void sp_look_kernel(ScoreArgs a, const ui
 // prob: per key, sum over lookahead rows (and layers) of the head-maximum of
 // the attention probability.
 // ---------------------------------------------------------------------------
+// Logits less the normalisers of one (layer, kv head)'s rows over this wave's keys, folded into the maxima over heads.
+template <int D, int NS, int NB, bool FP8>
+__device__ __forceinline__ void fold_heads(const u32x4 *qs, const float *ci, const bf16x8 (&kf)[NS][D / 16], int n_gblk, int col, int hf,
+                                           float ksc, float (&mx)[NS][NB][4])
+{
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        for (int gb = 0; gb < n_gblk; ++gb) {
+            const int blk = gb * NB + nb;
+            bf16x8 qf[D / 16];
+            load_frag<D>(qs, blk * 32 + col, hf, qf);
+            f32x16 cinit;
+            const float4 *cp = reinterpret_cast<const float4 *>(ci + blk * 32 + hf * 16);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float4 x = cp[v];
+                cinit[4 * v + 0] = x.x; cinit[4 * v + 1] = x.y;
+                cinit[4 * v + 2] = x.z; cinit[4 * v + 3] = x.w;
+            }
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                f32x16 acc = cinit;
+#pragma unroll
+                for (int t = 0; t < D / 16; ++t)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[t], kf[s][t], acc, 0, 0, 0);
+                // acc[r]: group head r/4, lookahead row 8*nb + 4*hf + r%4, key (wave*NS+s)*32 + col
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float v = fmaxf(fmaxf(acc[e], acc[4 + e]), fmaxf(acc[8 + e], acc[12 + e]));
+                    mx[s][nb][e] = fmaxf(mx[s][nb][e], FP8 ? v * ksc : v);
+                }
+            }
+        }
+    }
+}
+
+// Sum of the probabilities of one key's row maxima, which start over.
+template <int NB>
+__device__ __forceinline__ float close_rows(float (&mx)[NB][4], float c)
+{
+    float sum = 0.f;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            sum += fast_exp2(mx[b][e] * c);
+            mx[b][e] = neg_inf();
+        }
+    return sum;
+}
+
 template <int D, int NS, int NB, bool FP8>
 __global__ __launch_bounds__(kThreads, 3) void sp_prob_kernel(ScoreArgs a, LayerPtrs kp)
 {
@@ -427,49 +493,11 @@ __global__ __launch_bounds__(kThreads, 3) void sp_prob_kernel(ScoreArgs a, Layer
 #pragma unroll
             for (int s = 0; s < NS; ++s) load_frag<D>(ks, (wave * NS + s) * 32 + col, hf, kf[s]);
 
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                for (int gb = 0; gb < a.n_gblk; ++gb) {
-                    const int blk = gb * NB + nb;
-                    bf16x8 qf[KS];
-                    load_frag<D>(qs, blk * 32 + col, hf, qf);
-                    f32x16 cinit;
-                    const float4 *cp = reinterpret_cast<const float4 *>(ci + blk * 32 + hf * 16);
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const float4 x = cp[v];
-                        cinit[4 * v + 0] = x.x; cinit[4 * v + 1] = x.y;
-                        cinit[4 * v + 2] = x.z; cinit[4 * v + 3] = x.w;
-                    }
-#pragma unroll
-                    for (int s = 0; s < NS; ++s) {
-                        f32x16 acc = cinit;
-#pragma unroll
-                        for (int t = 0; t < KS; ++t)
-                            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[t], kf[s][t], acc, 0, 0, 0);
-                        // acc[r]: group head r/4, lookahead row 8*nb + 4*hf + r%4, key (wave*NS+s)*32 + col
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float v = fmaxf(fmaxf(acc[e], acc[4 + e]), fmaxf(acc[8 + e], acc[12 + e]));
-                            mx[s][nb][e] = fmaxf(mx[s][nb][e], FP8 ? v * ksc : v);
-                        }
-                    }
-                }
-            }
+            fold_heads<D, NS, NB, FP8>(qs, ci, kf, a.n_gblk, col, hf, ksc, mx);
         }
         if (a.layer_agg == SP_LAYER_MEAN || (whole && layer == a.n_layers - 1)) {
 #pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                float sum = 0.f;
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        sum += fast_exp2(mx[s][b][e] * c);
-                        mx[s][b][e] = neg_inf();
-                    }
-                total[s] += sum;
-            }
+            for (int s = 0; s < NS; ++s) total[s] += close_rows<NB>(mx[s], c);
         }
     }
     if (!whole && a.layer_agg == SP_LAYER_MAX) {
@@ -507,16 +535,12 @@ __global__ __launch_bounds__(kThreads, 3) void sp_prob_kernel(ScoreArgs a, Layer
 // take every fourth range (MEAN) or row (MAX), so that a short prompt still has
 // enough loads in flight, and their sums are added in wave order.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void sp_split_reduce_kernel(const float *__restrict__ buf, int64_t total, int n_splits,
-                                                              int n_rows /* 0: MEAN */, float out_scale,
-                                                              const uint32_t *__restrict__ status,
-                                                              float *__restrict__ scores)
+__device__ __forceinline__ float reduce_ranges(const float *__restrict__ buf, int64_t total, int n_splits, int n_rows /* 0: MEAN */)
 {
     __shared__ float part[4][64];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t j = (int64_t)blockIdx.x * 64 + lane;
-    const bool live = j < total;
-    const float *src = buf + (live ? j : 0);
+    const float *src = buf + (j < total ? j : 0);
     float sum = 0.f;
     if (n_rows == 0) {
 #pragma unroll 4
@@ -531,9 +555,143 @@ __global__ __launch_bounds__(256) void sp_split_reduce_kernel(const float *__res
     }
     part[wave][lane] = sum;
     __syncthreads();
-    if (wave != 0 || !live) return;
-    const float both = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+    return (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+}
+
+__global__ __launch_bounds__(256) void sp_split_reduce_kernel(const float *__restrict__ buf, int64_t total, int n_splits,
+                                                              int n_rows, float out_scale,
+                                                              const uint32_t *__restrict__ status,
+                                                              float *__restrict__ scores)
+{
+    const float both = reduce_ranges(buf, total, n_splits, n_rows);
+    const int64_t j = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    if (threadIdx.x >= 64 || j >= total) return;
     scores[j] = *status != 0u ? __uint_as_float(0x7fc00000u) : both * out_scale;     // a failed call has no scores
+}
+
+// ---------------------------------------------------------------------------
+// finish: last launch of a call that took the single-launch kernel although
+// sp_score_is_fused does not say so. Such a call never fails: as a rule this
+// launch adds up the layer ranges (n_ranges > 1) or has nothing to do, but where
+// the single-launch kernel gave up (other work held compute units its workgroups
+// wait for) it computes the scores afresh, in workgroups that need none of each
+// other: every one finds all rows' normalisers by itself, reading its prompt's
+// keys of a (layer, kv head) once, before the probabilities of its own tile. That
+// reads K once per tile instead of twice in all; with the wait before it, a call
+// that comes here takes tens of milliseconds.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ TileInfo find_tile(const ScoreArgs &a, const int64_t *offsets, int tile, int tile_keys)
+{
+    TileInfo t = get_tile(a, tile, tile_keys);
+    if (offsets == nullptr) return t;
+    int64_t first = 0;
+    for (int p = 0; p < a.n_prompts; ++p) {
+        const int64_t beg = offsets[p], end = offsets[p + 1], n = (end - beg + tile_keys - 1) / tile_keys;
+        if (tile < first + n) {
+            t.j0 = beg + (tile - first) * tile_keys;
+            t.end = end; t.prompt = p; t.first_tile = (int32_t)first;
+            break;
+        }
+        first += n;
+    }
+    return t;
+}
+
+size_t finish_lds_bytes(int tile_keys, int D, int rows_pad)
+{
+    return (size_t)(tile_keys + rows_pad) * D * 2 + (size_t)rows_pad * (2 * kWaves * sizeof(float2) + sizeof(float));
+}
+
+template <int D, int NS, int NB, bool FP8>
+__global__ __launch_bounds__(kThreads) void sp_finish_kernel(ScoreArgs a, LayerPtrs kp, const int64_t *__restrict__ offsets,
+                                                             const uint32_t *__restrict__ gave_up, int n_ranges)
+{
+    constexpr int KS = D / 16;
+    constexpr int TILE = kWaves * NS * 32;
+    extern __shared__ u32x4 lds[];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, hf = lane >> 5, col = lane & 31;
+    if (blockIdx.x == 0 && tid == 0) *a.status = 0u;
+    float both = 0.f;
+    if (n_ranges > 1) both = reduce_ranges(a.split_buf, a.L, n_ranges, a.layer_agg == SP_LAYER_MAX ? 8 * NB : 0);
+    if (*gave_up == 0u) {
+        const int64_t j = (int64_t)blockIdx.x * 64 + tid;
+        if (n_ranges > 1 && tid < 64 && j < a.L) a.scores[j] = both * a.out_scale;
+        return;
+    }
+    u32x4 *ks = lds;
+    u32x4 *qs = lds + TILE * (D / 8);
+    float2 *st = reinterpret_cast<float2 *>(qs + a.rows_pad * (D / 8));        // [wave][half of the wave][row]
+    float *ci = reinterpret_cast<float *>(st + 2 * kWaves * a.rows_pad);
+    for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
+        const TileInfo mine = find_tile(a, offsets, tile, TILE);
+        TileInfo ti = mine;
+        auto stage = [&](int layer, int kv) {
+            if (FP8) stage_k_fp8<D, NS>(ks, key_base_fp8(a, kp, layer, kv), a.k_stride_token, ti.j0, ti.end, tid);
+            else stage_k<D, NS>(ks, key_base(a, kp, layer, kv, ti), a.k_stride_token, ti.j0, ti.end, tid);
+        };
+        bf16x8 kf[NS][KS];
+        float mx[NS][NB][4], total[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            total[s] = 0.f;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) mx[s][b][e] = neg_inf();
+        }
+        for (int layer = 0; layer < a.n_layers; ++layer) {
+            for (int kv = 0; kv < a.n_kv_heads; ++kv) {
+                const int phase = layer * a.n_kv_heads + kv;
+                const float ksc = FP8 ? a.kscale[phase] : 1.0f, c = a.c * ksc;
+                __syncthreads();
+                stage_q<D>(qs, a, mine.prompt, layer, kv, tid);
+                for (int i = tid; i < 2 * kWaves * a.rows_pad; i += kThreads) st[i] = make_float2(neg_inf(), 0.f);
+                for (ti.j0 = mine.j0 - (int64_t)(tile - mine.first_tile) * TILE; ti.j0 < mine.end; ti.j0 += TILE) {
+                    __syncthreads();
+                    stage(layer, kv);
+                    __syncthreads();
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) load_frag<D>(ks, (wave * NS + s) * 32 + col, hf, kf[s]);
+                    for (int blk = 0; blk < a.rows_pad >> 5; ++blk) {
+                        bf16x8 qf[KS];
+                        load_frag<D>(qs, blk * 32 + col, hf, qf);
+                        float2 &slot = st[(wave * 2 + hf) * a.rows_pad + blk * 32 + col];
+                        float m = slot.x, l = slot.y;
+#pragma unroll
+                        for (int s = 0; s < NS; ++s) {
+                            f32x16 acc = {0.f};
+#pragma unroll
+                            for (int t = 0; t < KS; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s][t], qf[t], acc, 0, 0, 0);
+                            fold_keys(acc, ti.end - (ti.j0 + (wave * NS + s) * 32), hf, c, m, l);
+                        }
+                        slot = make_float2(m, l);
+                    }
+                }
+                ti.j0 = mine.j0;
+                __syncthreads();
+                stage(layer, kv);
+                for (int row = tid; row < a.rows_pad; row += kThreads) {
+                    float m = neg_inf(), l = 0.f;
+                    for (int i = 0; i < 2 * kWaves; ++i) lse_merge(m, l, st[i * a.rows_pad + row].x, st[i * a.rows_pad + row].y, c);
+                    ci[(row & ~31) + seed_pos(row & 31)] = row_normaliser(a, phase, row, m, l, c, FP8 ? 1.0f / c : a.inv_c);
+                }
+                __syncthreads();
+#pragma unroll
+                for (int s = 0; s < NS; ++s) load_frag<D>(ks, (wave * NS + s) * 32 + col, hf, kf[s]);
+                fold_heads<D, NS, NB, FP8>(qs, ci, kf, a.n_gblk, col, hf, ksc, mx);
+            }
+            if (a.layer_agg == SP_LAYER_MEAN || layer == a.n_layers - 1) {
+#pragma unroll
+                for (int s = 0; s < NS; ++s) total[s] += close_rows<NB>(mx[s], a.c);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const float sum = total[s] + __shfl_xor(total[s], 32);
+            const int64_t j = mine.j0 + (wave * NS + s) * 32 + col;
+            if (hf == 0 && j < mine.end) a.scores[j] = sum * a.out_scale;
+        }
+    }
 }
 
 // Last launch of a batch of several launches: a call fails as a whole, and a launch that gave up may follow one that
@@ -858,6 +1016,27 @@ sp_status launch_reduce(const ScoreArgs &a, int n_splits, hipStream_t st)
     return SP_OK;
 }
 
+template <int D, int NS, bool FP8>
+sp_status launch_finish_as(const Plan &p, const ScoreArgs &a, const LayerPtrs &kp, const int64_t *offsets, const uint32_t *gave_up,
+                           int n_ranges, hipStream_t st)
+{
+    const int64_t grid = n_ranges > 1 ? sp::ceil_div(a.L, 64) : std::min(a.n_tiles, 512);
+    const auto kernel = p.NB == 1 ? sp_finish_kernel<D, NS, 1, FP8> : sp_finish_kernel<D, NS, 2, FP8>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreads), finish_lds_bytes(p.tile_keys, p.D, p.rows_pad), st, a, kp, offsets,
+                       gave_up, n_ranges);
+    SP_HIP_CHECK(hipGetLastError());
+    return SP_OK;
+}
+
+sp_status launch_finish(const Plan &p, const ScoreArgs &a, const LayerPtrs &kp, const int64_t *offsets, const uint32_t *gave_up,
+                        int n_ranges, hipStream_t st)
+{
+    if (a.kscale) return p.D == 64 ? launch_finish_as<64, 2, true>(p, a, kp, offsets, gave_up, n_ranges, st)
+                                   : launch_finish_as<128, 1, true>(p, a, kp, offsets, gave_up, n_ranges, st);
+    return p.D == 64 ? launch_finish_as<64, 2, false>(p, a, kp, offsets, gave_up, n_ranges, st)
+                     : launch_finish_as<128, 1, false>(p, a, kp, offsets, gave_up, n_ranges, st);
+}
+
 template <int D, int NS, bool FP8 = false>
 sp_status launch_all(const Plan &p, const ScoreArgs &a, const LayerPtrs &kp, hipStream_t st)
 {
@@ -1060,12 +1239,22 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     f.c = a.c; f.inv_c = a.inv_c; f.out_scale = a.out_scale;
     BatchGroups bg;
     const bool captured = may_fuse && capturing(st);
+    // What sp_score_is_fused and sp_score_batch_is_fused announce may give up; every other call on the single-launch kernel is
+    // finished by a launch that can do without it, and gives up early (see kYieldSpins).
+    const auto finish = [&](int n_ranges) {
+        return launch_finish(p, a, kp, batch ? offsets_dev : nullptr, a.status + 1, n_ranges, st);
+    };
     if (may_fuse && !captured && !batch && pair_applies(p, total, desc->k_stride_token)) {
-        const Turn turn(st);
         f.tile_keys = 2 * fused_tile(p);
         f.L = total;
         f.n_wg = (int)sp::ceil_div(total, f.tile_keys);
-        return sp_fused::launch(f, kp, nullptr, true, true, ws + w.fused, a.status, st);
+        f.spin_max = sp_fused::kYieldSpins;
+        {
+            const Turn turn(st);
+            const sp_status rs = sp_fused::launch(f, kp, nullptr, true, true, ws + w.fused, a.status + 1, st);
+            if (rs != SP_OK) return rs;
+        }
+        return finish(1);
     }
     bool fused = may_fuse && (batch ? plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg)
                                        : plan_fused_prompt(p, total, desc->k_stride_token, bg));
@@ -1075,31 +1264,37 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
         // the exchange area of a launch in layer ranges takes the place of the general path's buffers
         ranges = fused_ranges(p, bg.wgs[0], bg.groups[0].n, w.split - w.part);
     }
-    if (fused && (big || !(batch ? whole_groups_pay(bg) : bg.wgs[0] >= fused_min_workgroups(p))))
+    const bool announced = fused && !big && (batch ? whole_groups_pay(bg) : bg.wgs[0] >= fused_min_workgroups(p));
+    if (fused && !announced)
         fused = !captured && (batch || ranges > 1 || bg.wgs[0] >= fused_min_workgroups(p)) && steps_pay(p, total, ranges, (int)bg.groups.size());
     if (fused && big)           // no exchange area of their own: see fused_big
         for (size_t g = 0; g < bg.groups.size(); ++g)
             fused = fused && sp_fused::workspace_bytes(p.rows_pad, bg.wgs[g], bg.groups[g].n) <= w.split - w.part;
     if (fused) {
-        const Turn turn(st, !captured);
+        uint32_t *const err = announced ? a.status : a.status + 1;
+        f.L = total;
+        f.spin_max = announced ? UINT32_MAX : sp_fused::kYieldSpins;
         if (ranges > 1) {
             const sp_fused::GroupTable t = split_layers(bg.groups[0], p.n_layers, ranges);
             f.n_wg = bg.wgs[0] * ranges;
-            f.L = total;
             f.split_out = a.split_buf;
             f.split_stride = total;
-            const sp_status rs = sp_fused::launch(f, kp, &t, false, true, ws + w.part, a.status, st);
-            return rs == SP_OK ? launch_reduce(a, ranges, st) : rs;
-        }
-        for (size_t g = 0; g < bg.groups.size(); ++g) {
-            f.n_wg = bg.wgs[g];
-            f.L = total;
-            // duties rotate over all prompts of a launch where they can: within a prompt of a dozen workgroups
-            // each would have one every other phase (8 prompts of 2K .. 32K tokens: 342 against 394 us)
-            const bool shared = !bg.short_prompt && bg.groups[g].n * (p.rows_pad / sp_fused::kDutyRows) <= bg.wgs[g];
-            const sp_status rs = sp_fused::launch(f, kp, batch ? &bg.groups[g] : nullptr, shared, g == 0, ws + (big ? w.part : w.fused), a.status, st);
+            const Turn turn(st);
+            const sp_status rs = sp_fused::launch(f, kp, &t, false, true, ws + w.part, err, st);
             if (rs != SP_OK) return rs;
+        } else {
+            const Turn turn(st, !captured);
+            for (size_t g = 0; g < bg.groups.size(); ++g) {
+                f.n_wg = bg.wgs[g];
+                // duties rotate over all prompts of a launch where they can: within a prompt of a dozen workgroups
+                // each would have one every other phase (8 prompts of 2K .. 32K tokens: 342 against 394 us)
+                const bool shared = !bg.short_prompt && bg.groups[g].n * (p.rows_pad / sp_fused::kDutyRows) <= bg.wgs[g];
+                const sp_status rs = sp_fused::launch(f, kp, batch ? &bg.groups[g] : nullptr, shared, g == 0, ws + (big ? w.part : w.fused), err, st);
+                if (rs != SP_OK) return rs;
+            }
         }
+        if (!announced) return finish(ranges);
+        if (ranges > 1) return launch_reduce(a, ranges, st);
         if (bg.groups.size() > 1) {
             hipLaunchKernelGGL(sp_fail_all_kernel, dim3((unsigned)std::min<int64_t>(sp::ceil_div(total, 1024), 64)), dim3(256), 0, st,
                                (const uint32_t *)a.status, total, scores_dev);

@@ -56,6 +56,7 @@
 // 8 on 196 of them, in half the steps; a small launch then adds the ranges up.
 #include "sp_score_fused.hpp"
 
+#include <algorithm>
 #include <atomic>
 #include <cstring>
 
@@ -1485,7 +1486,7 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
     a.part = base;
     a.lse = base + n_part;
     a.err = status_word;
-    a.spin_max = g_spin_max.load(std::memory_order_relaxed);
+    a.spin_max = std::min(a.spin_max, g_spin_max.load(std::memory_order_relaxed));
     const int32_t miss = g_force_miss.load(std::memory_order_relaxed);
     a.force_miss = miss == 1 || (miss == 2 && gt.n == 0);
     for (int i = 0; i < gt.n && miss >= 2; ++i) a.force_miss |= gt.prompt[i] == miss - 2;

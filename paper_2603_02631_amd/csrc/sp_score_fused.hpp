@@ -77,13 +77,17 @@ constexpr int direct_max(int rows_pad) { return rows_pad / kDutyRows - 1; }
 bool fits_one_per_cu();
 
 // Enqueues the clear kernel and the fused kernel. `ws` must hold workspace_bytes(); `status_word`
-// (device) is cleared first and raised if the call gives up.
+// (device) is cleared first and raised if the call gives up, after at most `a.spin_max` polls in a wait.
 // `group` (or null for one prompt) describes the entries of the launch; the status word is cleared only
 // when clear_status is set (the first launch of a call).
 // `shared`: the duties rotate over all workgroups of the launch (whole prompts of at least a tile only, at
 // least as many workgroups as duty blocks); otherwise every entry keeps to itself.
 sp_status launch(FusedArgs a, const sp_dev::LayerPtrs &kp, const GroupTable *group, bool shared, bool clear_status, void *ws,
                  uint32_t *status_word, hipStream_t st);
+
+// Polls (about 30 ms) after which a launch gives up that a later launch can stand in for: early, so that it frees its
+// compute units for a launch that nothing stands in for, and late enough for the workgroups of ordinary kernels to leave.
+constexpr uint32_t kYieldSpins = 1u << 15;
 
 // Test hook: polls before a bounded wait gives up (default 2^20) and whether duty waves treat their
 // partials as never arriving; applies to launches that follow.

@@ -28,9 +28,20 @@ def make_desc(n_layers, H, Hkv, d, n_q, scale, layer_agg, layout, T) -> sp.Score
     return sp.ScoreDesc(n_layers, H, Hkv, d, n_q, float(scale), int(layer_agg), st, sh)
 
 
+_last_workspace: Optional[torch.Tensor] = None
+
+
 def workspace(nbytes: int) -> torch.Tensor:
     # filled with ones so that a status word nobody cleared reads as non-zero
-    return torch.full((max(nbytes, 256),), 0xFF, dtype=torch.uint8, device=DEV)
+    global _last_workspace
+    _last_workspace = torch.full((max(nbytes, 256),), 0xFF, dtype=torch.uint8, device=DEV)
+    return _last_workspace
+
+
+def last_call_gave_up() -> bool:
+    """Whether the single-launch kernel gave up in the last call that took its workspace from here, and the call's last
+    launch stood in for it (the word behind the status word)."""
+    return int(_last_workspace[4:8].cpu().numpy().view(np.uint32)[0]) == 1
 
 
 def status_word(ws: torch.Tensor) -> int:

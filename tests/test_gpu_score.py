@@ -429,6 +429,78 @@ def test_batch_of_several_launches_gives_up_as_a_whole(prompt):
         assert bool(torch.isfinite(s).all()) and 0.99 < float(s.double().sum()) < H
 
 
+# Calls that take the single-launch kernel although sp_score_is_fused does not say so.
+STAND_IN_SHAPES = [
+    # name, entry, Lyr, H, Hkv, d, n_q, lengths
+    ("ranges", "prompt", 16, 32, 8, 64, 8, [6200]),
+    ("ranges_rows64", "prompt", 16, 32, 8, 64, 16, [20100]),
+    ("ranges_two_gblocks", "prompt", 12, 32, 4, 64, 8, [24000]),
+    ("ranges_d128_padding", "prompt", 14, 8, 4, 128, 5, [8000]),
+    ("ranges_d128_g8", "prompt", 24, 32, 4, 128, 8, [6001]),
+    ("whole_d128_g8", "prompt", 12, 8, 1, 128, 8, [50000]),
+    ("direct_d128", "prompt", 28, 16, 8, 128, 8, [1700]),
+    ("pair", "prompt", 2, 4, 1, 64, 8, [131073]),
+    ("pair_d128", "prompt", 1, 4, 2, 128, 8, [70000]),
+    ("batch_ranges_short_prompts", "batch", 16, 32, 8, 64, 8, [4700, 60, 0, 3000, 1, 511]),
+    ("batch_one_range_short_prompt", "batch", 4, 8, 2, 64, 8, [110000, 100, 0, 3000]),
+    ("batch_ranges_d128_g8", "batch", 24, 32, 4, 128, 8, [6000, 300, 2000]),
+    ("look_ranges", "look", 16, 32, 8, 64, 8, [6200]),
+    ("paged_ranges", "paged", 16, 32, 8, 64, 8, [6200]),
+    ("paged_pair", "paged", 2, 4, 1, 64, 8, [131072 + 500]),
+    ("fp8_ranges", "fp8", 16, 32, 8, 64, 8, [30000]),
+    ("fp8_direct_d128", "fp8", 28, 16, 8, 128, 8, [1700]),
+    ("fp8_pair", "fp8", 2, 4, 1, 64, 8, [131073]),
+]
+
+
+@pytest.mark.parametrize("shape", STAND_IN_SHAPES, ids=[s[0] for s in STAND_IN_SHAPES])
+def test_calls_that_are_not_announced_as_fused_never_fail(shape):
+    """sp_score_is_fused (sp_score_batch_is_fused) answers 0: where the single-launch kernel gives up, driven to it from
+    the host, the call still ends with the scores and status 0; the same call without it does not need the stand-in."""
+    import paper_2603_02631_amd as sp
+    import gpu_util as u
+    name, entry, Lyr, H, Hkv, d, n_q, lens = shape
+    say(f"[score-stand-in] {name} {entry} Lyr={Lyr} H={H} Hkv={Hkv} d={d} n_q={n_q} lengths={lens}")
+    lengths = np.array(lens, dtype=np.int64)
+    total = int(lengths.sum())
+    w = dataclasses.replace(small_workload(name, Lyr, H, Hkv, d, n_q, 0, cfg_id=700 + STAND_IN_SHAPES.index(shape), hh=(1, 1000)),
+                            batch=len(lengths))
+    q = synth.gen_q(w, len(lengths))
+    ks = [synth.gen_k_layer(w, l, q, lengths, synth.heavy_hitter_positions(w, lengths)) for l in range(Lyr)]
+    offsets = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    kl = synth.gen_look_keys(w, q)
+    if entry == "fp8":
+        codes, kscale = zip(*[synth.quantise_k_e4m3(k) for k in ks])
+        codes, kscale = list(codes), np.stack(kscale)
+    if entry == "paged":
+        pools, table = u.make_paged(ks, 512, "HND", seed=w.cfg_id)
+    desc = u.make_desc(Lyr, H, Hkv, d, n_q, w.scale, 0, "HND", total)
+    query = {"batch": lambda: sp.sp_score_batch_is_fused(desc, offsets), "fp8": lambda: sp.sp_score_fp8_is_fused(desc, total)}
+    assert query.get(entry, lambda: sp.sp_score_is_fused(desc, total))() == 0
+    for mode in (0, 1):
+        run = {"prompt": lambda: u.gpu_score(q[0], ks, w.scale, mode),
+               "batch": lambda: u.gpu_score_batch(q, ks, offsets, w.scale, mode),
+               "look": lambda: u.gpu_score_look(q[0], ks, kl, 1, w.scale, mode),
+               "paged": lambda: u.gpu_score_paged(q[0], pools, table, 512, total, w.scale, mode),
+               "fp8": lambda: u.gpu_score_fp8(q[0], codes, kscale, w.scale, mode)}[entry]
+        try:
+            sp.sp_debug_fused_giveup(4, 1)
+            got = run()
+            assert u.last_call_gave_up()
+        finally:
+            sp.sp_debug_fused_giveup(1 << 20, 0)
+        plain = run()
+        assert not u.last_call_gave_up()
+        for b, Lb in enumerate(lengths):
+            if Lb:
+                sl = slice(int(offsets[b]), int(offsets[b + 1]))
+                part = [np.ascontiguousarray(k[:, sl, :]) for k in ks]
+                want = oracle.score_look(q[b], part, kl, 1, w.scale, mode) if entry == "look" else \
+                    oracle.score_fp8(q[b], codes, kscale.astype(np.float64), w.scale, mode) if entry == "fp8" else oracle.score(q[b], part, w.scale, mode)
+                u.assert_scores_close(got[sl], want)
+                u.assert_scores_close(plain[sl], want)
+
+
 LOOK_SHAPES = [
     # name, Lyr, H, Hkv, d, n_q, L   (general path: short prompts, head_dim 128; fused path: long prompts)
     ("look_g4_nq16_d64", 3, 8, 2, 64, 16, 1500),
