@@ -29,6 +29,8 @@
 #include "sp_score_dev.hpp"
 #include "sp_score_fused.hpp"
 
+#include <dlfcn.h>
+
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -1059,46 +1061,93 @@ sp_status launch_all(const Plan &p, const ScoreArgs &a, const LayerPtrs &kp, hip
 // compute units that the other one needs (every XCD dispatches its share of a grid on its own, so one may start with
 // the first kernel and another with the second), and both would wait until they give up. The launches of a process
 // on one device therefore take turns: a call on another stream than the last one's waits, on the device, for that
-// call's kernels. One event per device, kept until the process ends; the record costs a call 3 us (8K tokens,
-// whole pass: 58.2 -> 61.6 us; 62.3 with a system-scope fence, which the order alone does not need). Not in a captured graph, which knows nothing of its replays' neighbours: see capturing.
+// call's kernel. The event for it costs every call 3.6 us (4 layers, 33000 tokens: 26.3 -> 29.9 us; 28.8 as the stop
+// event of the launch itself), so none is recorded while all calls come from one stream. The first call from another
+// stream can then not wait for what the old one still has in its queue; until that stream's next call, calls from
+// others are `unordered`: they give up early and have a stand-in, so that neither side fails.
+// Not in a captured graph, which knows nothing of its replays' neighbours: see capturing.
+
+// A stream's identity: handles are reused after hipStreamDestroy, ids are not; the per-thread stream has one handle
+// for all threads.
+struct StreamKey {
+    hipStream_t handle;
+    unsigned long long id;
+    bool operator==(const StreamKey &o) const { return handle == o.handle && id == o.id; }
+};
+
+bool special_stream(hipStream_t st) { return st == nullptr || st == hipStreamLegacy || st == hipStreamPerThread; }
+
+StreamKey key_of(hipStream_t st)
+{
+    // looked up at run time: not in every runtime of this major version
+    using GetId = hipError_t (*)(hipStream_t, unsigned long long *);
+    static const GetId get_id = reinterpret_cast<GetId>(dlsym(RTLD_DEFAULT, "hipStreamGetId"));
+    static thread_local char tag;
+    StreamKey k{st, 0};
+    if (st == hipStreamPerThread) k.id = (unsigned long long)(uintptr_t)&tag;
+    else if (!special_stream(st) && get_id && get_id(st, &k.id) != hipSuccess) (void)hipGetLastError();
+    return k;
+}
+
 class Turn {
 public:
-    explicit Turn(hipStream_t st, bool take = true) : st_(st)
+    explicit Turn(hipStream_t st, bool take = true) : st_(st), key_(key_of(st))
     {
         if (!take) return;
         static Slot slots[64];
         int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return;
-        Slot &s = slots[dev];
-        lock_ = std::unique_lock<std::mutex>(s.m);
-        if (!s.done && hipEventCreateWithFlags(&s.done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
-            s.done = nullptr;
-            (void)hipGetLastError();
-            return;
+        unordered_ = true;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) { (void)hipGetLastError(); return; }
+        slot_ = &slots[dev];
+        lock_ = std::unique_lock<std::mutex>(slot_->m);
+        Slot &s = *slot_;
+        const bool same = s.used && s.last == key_;
+        if (!s.used || (same && !s.several)) { unordered_ = false; return; }
+        if (!s.several) {
+            s.several = true;
+            s.n_loose = 1;
+            s.loose = s.last;
         }
-        slot_ = &s;
-        // the per-thread stream has one handle for all threads
-        if (s.used && (s.last != st || st == hipStreamPerThread) && hipStreamWaitEvent(st, s.done, 0) != hipSuccess) (void)hipGetLastError();
+        s.run = same ? s.run + 1 : 0;
+        // what this stream left without an event runs before this call anyway
+        if (s.n_loose == 1 && s.loose == key_) s.n_loose = 0;
+        const bool waits = same || s.done == nullptr || hipStreamWaitEvent(st, s.done, 0) == hipSuccess;
+        if (!waits) (void)hipGetLastError();
+        unordered_ = !waits || s.n_loose != 0;
     }
     ~Turn()
     {
         if (!slot_) return;
-        if (hipEventRecord(slot_->done, st_) != hipSuccess) { (void)hipGetLastError(); return; }
-        slot_->used = true;
-        slot_->last = st_;
+        Slot &s = *slot_;
+        s.used = true;
+        s.last = key_;
+        if (!s.several) return;
+        if (s.run >= kSettled && s.n_loose == 0) { s.several = false; return; }
+        if (!s.done && hipEventCreateWithFlags(&s.done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) s.done = nullptr;
+        if (s.done && hipEventRecord(s.done, st_) == hipSuccess) return;
+        (void)hipGetLastError();
+        if (s.n_loose == 0 || !(s.loose == key_)) ++s.n_loose;      // two streams without an event: calls stay unordered
+        s.loose = key_;
     }
     Turn(const Turn &) = delete;
     Turn &operator=(const Turn &) = delete;
 
+    // No wait for some call of this process that may still be running: the launch has to make way for it.
+    bool unordered() const { return unordered_; }
+
 private:
+    static constexpr int kSettled = 256;      // calls in a row from one stream after which it counts as the only one again
     struct Slot {
         std::mutex m;
-        hipEvent_t done = nullptr;
-        hipStream_t last = nullptr;
-        bool used = false;
+        hipEvent_t done = nullptr;        // behind the last call's kernel, while there are several streams
+        StreamKey last{}, loose{};        // loose: the stream whose latest calls have no event behind them
+        int n_loose = 0, run = 0;
+        bool used = false, several = false;
     };
     hipStream_t st_;
+    StreamKey key_;
     Slot *slot_ = nullptr;
+    bool unordered_ = false;
     std::unique_lock<std::mutex> lock_;
 };
 
@@ -1239,25 +1288,12 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     f.c = a.c; f.inv_c = a.inv_c; f.out_scale = a.out_scale;
     BatchGroups bg;
     const bool captured = may_fuse && capturing(st);
-    // What sp_score_is_fused and sp_score_batch_is_fused announce may give up; every other call on the single-launch kernel is
-    // finished by a launch that can do without it, and gives up early (see kYieldSpins).
-    const auto finish = [&](int n_ranges) {
-        return launch_finish(p, a, kp, batch ? offsets_dev : nullptr, a.status + 1, n_ranges, st);
-    };
-    if (may_fuse && !captured && !batch && pair_applies(p, total, desc->k_stride_token)) {
-        f.tile_keys = 2 * fused_tile(p);
-        f.L = total;
-        f.n_wg = (int)sp::ceil_div(total, f.tile_keys);
-        f.spin_max = sp_fused::kYieldSpins;
-        {
-            const Turn turn(st);
-            const sp_status rs = sp_fused::launch(f, kp, nullptr, true, true, ws + w.fused, a.status + 1, st);
-            if (rs != SP_OK) return rs;
-        }
-        return finish(1);
-    }
-    bool fused = may_fuse && (batch ? plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg)
-                                       : plan_fused_prompt(p, total, desc->k_stride_token, bg));
+    // What sp_score_is_fused and sp_score_batch_is_fused announce may fail. Every other call on the single-launch kernel,
+    // and one that could not be ordered behind its neighbours, gives up early (see kYieldSpins) and is finished by a
+    // launch that can do without that kernel.
+    const bool pair = may_fuse && !captured && !batch && pair_applies(p, total, desc->k_stride_token);
+    bool fused = may_fuse && !pair && (batch ? plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg)
+                                             : plan_fused_prompt(p, total, desc->k_stride_token, bg));
     int ranges = 1;
     const bool big = fused_big(p);
     if (fused && !captured && bg.groups.size() == 1) {
@@ -1270,30 +1306,37 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     if (fused && big)           // no exchange area of their own: see fused_big
         for (size_t g = 0; g < bg.groups.size(); ++g)
             fused = fused && sp_fused::workspace_bytes(p.rows_pad, bg.wgs[g], bg.groups[g].n) <= w.split - w.part;
-    if (fused) {
-        uint32_t *const err = announced ? a.status : a.status + 1;
-        f.L = total;
-        f.spin_max = announced ? UINT32_MAX : sp_fused::kYieldSpins;
-        if (ranges > 1) {
-            const sp_fused::GroupTable t = split_layers(bg.groups[0], p.n_layers, ranges);
-            f.n_wg = bg.wgs[0] * ranges;
-            f.split_out = a.split_buf;
-            f.split_stride = total;
-            const Turn turn(st);
-            const sp_status rs = sp_fused::launch(f, kp, &t, false, true, ws + w.part, err, st);
-            if (rs != SP_OK) return rs;
-        } else {
+    if (fused || pair) {
+        bool stand_in = !announced;
+        {
             const Turn turn(st, !captured);
-            for (size_t g = 0; g < bg.groups.size(); ++g) {
-                f.n_wg = bg.wgs[g];
-                // duties rotate over all prompts of a launch where they can: within a prompt of a dozen workgroups
-                // each would have one every other phase (8 prompts of 2K .. 32K tokens: 342 against 394 us)
-                const bool shared = !bg.short_prompt && bg.groups[g].n * (p.rows_pad / sp_fused::kDutyRows) <= bg.wgs[g];
-                const sp_status rs = sp_fused::launch(f, kp, batch ? &bg.groups[g] : nullptr, shared, g == 0, ws + (big ? w.part : w.fused), err, st);
-                if (rs != SP_OK) return rs;
+            stand_in = stand_in || turn.unordered();
+            uint32_t *const err = stand_in ? a.status + 1 : a.status;
+            f.L = total;
+            f.spin_max = stand_in ? sp_fused::kYieldSpins : UINT32_MAX;
+            sp_status rs = SP_OK;
+            if (pair) {
+                f.tile_keys = 2 * fused_tile(p);
+                f.n_wg = (int)sp::ceil_div(total, f.tile_keys);
+                rs = sp_fused::launch(f, kp, nullptr, true, true, ws + w.fused, err, st);
+            } else if (ranges > 1) {
+                const sp_fused::GroupTable t = split_layers(bg.groups[0], p.n_layers, ranges);
+                f.n_wg = bg.wgs[0] * ranges;
+                f.split_out = a.split_buf;
+                f.split_stride = total;
+                rs = sp_fused::launch(f, kp, &t, false, true, ws + w.part, err, st);
+            } else {
+                for (size_t g = 0; g < bg.groups.size() && rs == SP_OK; ++g) {
+                    f.n_wg = bg.wgs[g];
+                    // duties rotate over all prompts of a launch where they can: within a prompt of a dozen workgroups
+                    // each would have one every other phase (8 prompts of 2K .. 32K tokens: 342 against 394 us)
+                    const bool shared = !bg.short_prompt && bg.groups[g].n * (p.rows_pad / sp_fused::kDutyRows) <= bg.wgs[g];
+                    rs = sp_fused::launch(f, kp, batch ? &bg.groups[g] : nullptr, shared, g == 0, ws + (big ? w.part : w.fused), err, st);
+                }
             }
+            if (rs != SP_OK) return rs;
         }
-        if (!announced) return finish(ranges);
+        if (stand_in) return launch_finish(p, a, kp, batch ? offsets_dev : nullptr, a.status + 1, ranges, st);
         if (ranges > 1) return launch_reduce(a, ranges, st);
         if (bg.groups.size() > 1) {
             hipLaunchKernelGGL(sp_fail_all_kernel, dim3((unsigned)std::min<int64_t>(sp::ceil_div(total, 1024), 64)), dim3(256), 0, st,

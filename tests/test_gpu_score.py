@@ -607,6 +607,53 @@ def test_scores_on_several_streams_at_once(n_streams):
         assert torch.equal(out, want)
 
 
+def test_calls_that_cannot_be_ordered_never_fail():
+    """Calls of one stream leave nothing that another stream could wait for. Until that stream calls again, calls from
+    another one have a stand-in, also where sp_score_is_fused answers 1; driven to give up from the host."""
+    import torch
+    import paper_2603_02631_amd as sp
+    from gpu_util import DEV, assert_scores_close, dev_bits, make_desc, status_word, workspace
+    Lyr, H, Hkv, d, n_q = 1, 4, 1, 64, 8
+    calls = []
+    for L in (70000, 40000):
+        w = small_workload("unordered", Lyr, H, Hkv, d, n_q, L, cfg_id=291, hh=(1, 1000))
+        inp = synth.make_score_inputs(w)
+        desc = make_desc(Lyr, H, Hkv, d, n_q, w.scale, 0, "HND", L)
+        assert sp.sp_score_is_fused(desc, L) == 1
+        calls.append((desc, dev_bits(inp["q"][0]), [dev_bits(k) for k in inp["k"]], L, torch.zeros(L, dtype=torch.float32, device=DEV),
+                      workspace(sp.sp_score_workspace(desc, L, 1)), oracle.score(inp["q"][0], inp["k"], w.scale, 0)))
+    other = torch.cuda.Stream()
+
+    def call(c, stream=None):
+        with torch.cuda.stream(stream):
+            sp.sp_score(*c[:6])
+        torch.cuda.synchronize()
+
+    def gives_up(c, stream=None):
+        try:
+            sp.sp_debug_fused_giveup(4, 1)
+            call(c, stream)
+        finally:
+            sp.sp_debug_fused_giveup(1 << 20, 0)
+        return status_word(c[5]) == 1 and bool(torch.isnan(c[4]).all())
+
+    say("[score-unordered]")
+    for _ in range(600):                        # one stream only, whatever ran before
+        sp.sp_score(*calls[0][:6])
+    assert gives_up(calls[0])
+    for c in calls:
+        assert not gives_up(c, other)
+        assert status_word(c[5]) == 0
+        assert_scores_close(c[4].cpu().numpy(), c[6])
+    call(calls[0])                              # the first stream's earlier calls lie before this one's event
+    for stream in (other, None):
+        for c in calls:
+            assert gives_up(c, stream)
+            call(c, stream)
+            assert status_word(c[5]) == 0
+            assert_scores_close(c[4].cpu().numpy(), c[6])
+
+
 def test_captured_score_of_a_short_prompt():
     """A captured call takes the general path; every replay agrees with the eager call."""
     import torch
