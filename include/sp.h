@@ -217,7 +217,8 @@ sp_status sp_score_batch(const sp_score_desc *desc, const void *q_dev,
 /* How sp_score_batch runs this batch on the current device: n > 0 = on the
  * single-launch kernel in n launches (every prompt empty or at least T tokens
  * long and no longer than T tokens per compute unit, T as above; at least 64
- * workgroups in all; prompts share launches, each with all its keys in one),
+ * workgroups in all; prompts share launches, each with all its keys in one, and
+ * no launch has more blocks of four padded query rows than workgroups),
  * 0 = a call that never fails (see sp_score_is_fused): the three-kernel path or,
  * where that is faster, the single-launch kernel with a stand-in; -1 = invalid
  * arguments. Same results either way (to rounding). Host-only. */

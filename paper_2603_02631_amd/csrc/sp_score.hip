@@ -876,7 +876,13 @@ struct BatchGroups {
     std::vector<int> wgs;
     int64_t tiles = 0;              // of all prompts
     bool short_prompt = false;      // one of them is shorter than a tile
+    bool shared = true;             // in every launch the duties can rotate over all prompts (see score_impl)
 };
+
+bool duties_shared(const Plan &p, const BatchGroups &bg, size_t g)
+{
+    return !bg.short_prompt && bg.groups[g].n * (p.rows_pad / sp_fused::kDutyRows) <= bg.wgs[g];
+}
 
 bool plan_fused_batch(const Plan &p, const int64_t *offsets, int B, int64_t k_stride_token, BatchGroups &out)
 {
@@ -917,6 +923,7 @@ bool plan_fused_batch(const Plan &p, const int64_t *offsets, int B, int64_t k_st
         out.wgs[g] += tp.first;
         t.w0[++t.n] = out.wgs[g];
     }
+    for (size_t g = 0; g < out.groups.size(); ++g) out.shared &= duties_shared(p, out, g);
     return true;
 }
 
@@ -933,11 +940,11 @@ int fused_ranges(const Plan &p, int tiles, int n_prompts, size_t room)
     return (int)sp::ceil_div(p.n_layers, sp::ceil_div(p.n_layers, n));       // no empty range
 }
 
-// Batches the single-launch kernel takes whatever their size: every prompt fills a tile, and one range of
-// layers fills enough of the device.
+// Batches the single-launch kernel takes whatever their size: every prompt fills a tile, no launch has more duty blocks
+// than workgroups, and one range of layers fills enough of the device.
 bool whole_groups_pay(const BatchGroups &bg)
 {
-    return !bg.short_prompt && bg.tiles >= sp_fused::kMinWorkgroups;
+    return bg.shared && bg.tiles >= sp_fused::kMinWorkgroups;
 }
 
 // Otherwise (few workgroups, or tiles that short prompts leave half empty): whether the single-launch kernel
@@ -1330,8 +1337,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
                     f.n_wg = bg.wgs[g];
                     // duties rotate over all prompts of a launch where they can: within a prompt of a dozen workgroups
                     // each would have one every other phase (8 prompts of 2K .. 32K tokens: 342 against 394 us)
-                    const bool shared = !bg.short_prompt && bg.groups[g].n * (p.rows_pad / sp_fused::kDutyRows) <= bg.wgs[g];
-                    rs = sp_fused::launch(f, kp, batch ? &bg.groups[g] : nullptr, shared, g == 0, ws + (big ? w.part : w.fused), err, st);
+                    rs = sp_fused::launch(f, kp, batch ? &bg.groups[g] : nullptr, duties_shared(p, bg, g), g == 0, ws + (big ? w.part : w.fused), err, st);
                 }
             }
             if (rs != SP_OK) return rs;

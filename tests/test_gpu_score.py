@@ -241,6 +241,19 @@ def test_which_prompts_take_the_single_launch_kernel():
     assert fused(64, 8, 16, 40000) == 0          # 128 padded rows
 
 
+def test_which_batches_take_the_single_launch_kernel():
+    """sp_score_batch_is_fused: 90 workgroups with the duty blocks (8 a prompt of 32 padded rows) of 10 prompts, or of 30."""
+    import paper_2603_02631_amd as sp
+    from gpu_util import make_desc
+    def fused(n, tiles, shorten=0):
+        off = np.arange(n + 1) * tiles * 512
+        off[-1] -= shorten
+        return sp.sp_score_batch_is_fused(make_desc(2, 8, 2, 64, 8, 0.1, 0, "HND", int(off[-1])), off)
+    assert [fused(10, 9), fused(11, 8), fused(12, 8), fused(30, 3), fused(7, 9)] == [1, 1, 1, 0, 0]
+    assert fused(13, 7) == 0 and fused(90, 3) == 0              # 91 workgroups, 104 duty blocks; three launches
+    assert fused(8, 64) == 2 and fused(8, 64, 64 * 512 - 1) == 0     # a prompt shorter than a tile
+
+
 @pytest.mark.parametrize("shape", FUSED_SHAPES, ids=[s[0] for s in FUSED_SHAPES])
 def test_fused_score_matches_oracle(shape):
     import paper_2603_02631_amd as sp
