@@ -850,13 +850,15 @@ bool fused_applies(const Plan &p, int64_t L, int64_t k_stride_token)
 }
 
 // Prompts that need more than one tile per compute unit, and no more than two: K is still read once (16 layers
-// x 8 kv heads, head_dim 64, 256K tokens: 897 us against 1510 on the three-kernel path).
-bool pair_applies(const Plan &p, int64_t L, int64_t k_stride_token)
+// x 8 kv heads, head_dim 64: 256K tokens 904 us against 1552 on the three-kernel path, one token beyond 128K 686 against
+// 783). 8-bit keys at head_dim 64 leave the three kernels half the bytes and cross an eighth later (140000 tokens 672 /
+// 658, 200000 690 / 940; 64 rows 140000 818 / 829). Up to eight lookahead rows: there is no variant for more.
+bool pair_applies(const Plan &p, bool fp8, int64_t L, int64_t k_stride_token)
 {
     if (!fused_base_shape(p) || p.NB != 1 || k_stride_token > (int64_t(1) << 20)) return false;
     const int cus = std::min(256, device_compute_units());
     const int64_t tiles = sp::ceil_div(L, fused_tile(p));
-    return cus >= 128 && tiles > cus && tiles <= 2 * (int64_t)cus;
+    return cus >= 128 && tiles > (fp8 && p.D == 64 ? cus + cus / 8 : cus) && tiles <= 2 * (int64_t)cus;
 }
 
 // 8-bit keys: the single-launch kernel's variants for them fetch the codes in 16-byte pieces (strides in
@@ -947,16 +949,31 @@ bool whole_groups_pay(const BatchGroups &bg)
     return bg.shared && bg.tiles >= sp_fused::kMinWorkgroups;
 }
 
-// Otherwise (few workgroups, or tiles that short prompts leave half empty): whether the single-launch kernel
-// beats the three-kernel path. A launch costs its steps (a range's phases and five more to fill and drain
-// the pipeline) at 2.2 us; in that time the three kernels get through 6.3 MB of K. Measured crossings (fused / three kernels, us): 16 layers x 8 kv
-// heads, head_dim 64: 4096 tokens 40 / 40, 6144 40 / 49, 8192 43 / 58; 4 x 4 heads, head_dim 128: 8192
-// tokens 32 / 27, 16384 34 / 39; 28 x 8 heads, head_dim 128: 2048 tokens 46 / 59. With two blocks of query rows at
-// head_dim 128 a step takes 2.8 us (24 x 4 heads: 3000 tokens in 13 steps 54 / 52, 4500 52 / 77, 20001 138 / 264).
-bool steps_pay(const Plan &p, int64_t tokens, int ranges, int launches)
+// Otherwise (few workgroups, or tiles that short prompts leave half empty): whether the single-launch kernel beats the
+// three-kernel path. A launch costs its steps (a range's phases and five more to fill and drain the pipeline); the three
+// kernels take the longer the more keys their tiles hold, `keys` with the empty places. Each variant has its line,
+// in MB of bf16 keys: `per_step` for each step, or `steep` for each step less `base` where the fixed cost of the three
+// launches counts. Measured (tokens: three kernels / single launch, us; 16 layers x 8 kv heads unless noted):
+//   32 rows                      4600 40 / 40, 6000 45 / 37, 9000 58 / 53, 12000 69 / 54; 28 layers, head_dim 128: 1500 46 / 33;
+//                                4 x 4 heads, head_dim 128: 12000 31 / 31; 30 prompts of 1100 .. 1500 271 / 189
+//   64 rows, 9+ lookahead rows   4600 48 / 47, 6200 54 / 48, 9000 66 / 77, 10500 74 / 77, 12000 80 / 77, 16384 115 / 77;
+//                                24 prompts of 60 .. 4000 282 / 292, 30 of 1100 .. 1500 352 / 292
+//   64 rows, 5+ heads a kv head  4600 48 / 51, 6200 53 / 51, 9000 66 / 82, 12000 80 / 83, 16384 116 / 83
+//   64 rows, head_dim 128        24 x 4 heads: 3000 45 / 49, 3600 49 / 47, 4500 66 / 48; 24 prompts of 60 .. 4000 457 / 418
+//   8-bit keys, 32 rows          6000 40 / 41, 8192 46 / 38, 10000 51 / 59, 12000 58 / 58, 16384 80 / 57; 25000 124 / 95;
+//                                28 layers, head_dim 128 (32 rows): 1500 43 / 35, as with bf16 keys
+//   8-bit keys, 64 rows          6200 53 / 51, 9000 63 / 83, 12000 74 / 82, 16384 101 / 80, 24000 127 / 138, 25000 161 / 146, 30000 176 / 136
+bool steps_pay(const Plan &p, bool fp8, int64_t keys, int ranges, int launches)
 {
-    const int64_t steps = sp::ceil_div(p.n_layers, ranges) * (p.n_phases / p.n_layers) + 5;
-    return tokens * p.n_phases * p.D * 2 >= launches * steps * (fused_big(p) ? 8000000 : 6300000);
+    struct Line { double per_step, steep, base; };
+    const bool wide = p.rows_pad > 32;
+    const Line line = p.D == 128 ? (wide ? Line{8.0, 8.0, 0} : Line{6.3, 6.3, 0})
+                    : fp8        ? (wide ? Line{11.0, 14.9, 94} : Line{10.5, 13.2, 77})
+                    : !wide      ? Line{6.3, 6.3, 0}
+                    : p.NB == 2  ? Line{8.5, 12.5, 75}
+                                 : Line{9.4, 14.0, 91};
+    const double steps = (double)launches * (sp::ceil_div(p.n_layers, ranges) * (p.n_phases / p.n_layers) + 5);
+    return (double)keys * p.n_phases * p.D * 2e-6 >= std::min(line.per_step * steps, line.steep * steps - line.base * launches);
 }
 
 // The table of a launch with every entry of `t` once per layer range.
@@ -1298,7 +1315,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     // What sp_score_is_fused and sp_score_batch_is_fused announce may fail. Every other call on the single-launch kernel,
     // and one that could not be ordered behind its neighbours, gives up early (see kYieldSpins) and is finished by a
     // launch that can do without that kernel.
-    const bool pair = may_fuse && !captured && !batch && pair_applies(p, total, desc->k_stride_token);
+    const bool pair = may_fuse && !captured && !batch && pair_applies(p, opt.kscale != nullptr, total, desc->k_stride_token);
     bool fused = may_fuse && !pair && (batch ? plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg)
                                              : plan_fused_prompt(p, total, desc->k_stride_token, bg));
     int ranges = 1;
@@ -1309,7 +1326,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     }
     const bool announced = fused && !big && (batch ? whole_groups_pay(bg) : bg.wgs[0] >= fused_min_workgroups(p));
     if (fused && !announced)
-        fused = !captured && (batch || ranges > 1 || bg.wgs[0] >= fused_min_workgroups(p)) && steps_pay(p, total, ranges, (int)bg.groups.size());
+        fused = !captured && (batch || ranges > 1 || bg.wgs[0] >= fused_min_workgroups(p)) && steps_pay(p, opt.kscale != nullptr, n_tiles * p.tile_keys, ranges, (int)bg.groups.size());
     if (fused && big)           // no exchange area of their own: see fused_big
         for (size_t g = 0; g < bg.groups.size(); ++g)
             fused = fused && sp_fused::workspace_bytes(p.rows_pad, bg.wgs[g], bg.groups[g].n) <= w.split - w.part;

@@ -462,7 +462,7 @@ STAND_IN_SHAPES = [
     ("paged_pair", "paged", 2, 4, 1, 64, 8, [131072 + 500]),
     ("fp8_ranges", "fp8", 16, 32, 8, 64, 8, [30000]),
     ("fp8_direct_d128", "fp8", 28, 16, 8, 128, 8, [1700]),
-    ("fp8_pair", "fp8", 2, 4, 1, 64, 8, [131073]),
+    ("fp8_pair", "fp8", 2, 4, 1, 64, 8, [147457]),
 ]
 
 

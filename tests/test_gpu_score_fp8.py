@@ -51,6 +51,8 @@ FP8_SHAPES = [
     ("fp8_pair", 2, 4, 1, 64, 8, 131073),
     ("fp8_pair_two_gblocks", 1, 16, 2, 64, 5, 140000),
     ("fp8_pair_d128", 1, 4, 2, 128, 8, 65536 + 300),
+    ("fp8_pair_first_length", 2, 4, 1, 64, 8, 147457),
+    ("fp8_pair_two_gblocks_full_grid", 1, 16, 2, 64, 5, 262144),
 ]
 
 
