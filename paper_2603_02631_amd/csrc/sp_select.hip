@@ -203,7 +203,9 @@ struct Threshold {
 // that holds the k-th, and clears the histogram for the next pass: two barriers per pass. The search ends as
 // soon as the bin holds exactly the keys still needed (one of distinct scores: three passes, seldom four).
 // Scores share a handful of exponents, so in the first pass a wave adds up its keys of one bin before it
-// touches the counter: one by one, 64 keys of a bin take 64 turns at it.
+// touches the counter: one by one, 64 keys of a bin take 64 turns at it. Two bins so; what is left is spread, and goes
+// one by one (8000 lognormal chunk scores: 15.9 us, with three turns 18.8, with as many as there are bins 19.1; spread
+// over 200 powers of two 14.8, 17.9 and 69.0).
 // count(f) calls f(key, live) for each of this thread's keys, the same number of times in every thread of a wave.
 template <class Count>
 __device__ __forceinline__ Threshold radix_select(int64_t k, const Count &count)
@@ -221,12 +223,15 @@ __device__ __forceinline__ Threshold radix_select(int64_t k, const Count &count)
             count([&](uint32_t key, bool live) {
                 const uint32_t bin = key >> 24;
                 uint64_t left = __ballot(live);
-                while (left != 0) {                    // uniform: one turn per bin the wave's keys fall into
+#pragma unroll
+                for (int turn = 0; turn < 2; ++turn) {
+                    if (left == 0) return;             // uniform
                     const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)bin, __ffsll((unsigned long long)left) - 1);
                     const uint64_t same = __ballot(live && bin == b) & left;
                     if ((tid & 63) == 0) atomicAdd(&hist[b], __popcll(same));
                     left &= ~same;
                 }
+                if ((left >> (tid & 63)) & 1) atomicAdd(&hist[bin], 1);
             });
         } else {
             count([&](uint32_t key, bool live) {
