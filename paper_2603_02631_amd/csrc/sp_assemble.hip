@@ -6,7 +6,7 @@
 // consecutive ranges. Range r occupies one block of the output: its delimiter
 // (for r > 0) followed by its tokens.
 //
-// Buffers of up to 2048 ranges take one launch, sp_assemble_one_kernel: every
+// Buffers of up to 2048 ranges and 2^19 output entries take one launch, sp_assemble_one_kernel: every
 // workgroup prefix-sums the block lengths for itself (a few KB out of the caches)
 // into LDS, then one thread per output entry binary-searches the block starts
 // there and copies a delimiter id or a token id. More take two launches:
@@ -122,6 +122,7 @@ __global__ __launch_bounds__(kThreads) void sp_assemble_gather_kernel(const int3
 // launch: 5.9 us for the two on 163 ranges and 16384 tokens.
 constexpr int kOneThreads = 1024;
 constexpr int kOneSpans = 2048;
+constexpr int64_t kOneEntries = 1 << 19;        // as many workgroups as are resident at once, each with a scan of its own first
 __global__ __launch_bounds__(kOneThreads) void sp_assemble_one_kernel(const int32_t *__restrict__ target_ids, int64_t M,
                                                                       const int64_t *__restrict__ tspans,
                                                                       const int32_t *__restrict__ n_tspans_p,
@@ -182,7 +183,7 @@ extern "C" sp_status sp_assemble(const int32_t *target_ids_dev, int64_t M, const
     // the output cannot be longer than every target token plus a delimiter per range
     int64_t bound = M + (int64_t)(max_spans - 1) * n_delim;
     if (bound > out_capacity) bound = out_capacity;
-    if (max_spans <= kOneSpans) {
+    if (max_spans <= kOneSpans && bound <= kOneEntries) {
         hipLaunchKernelGGL(sp_assemble_one_kernel, dim3((unsigned)sp::ceil_div(bound, kOneThreads)), dim3(kOneThreads), 0, st,
                            target_ids_dev, M, tspans_dev, n_tspans_dev, (int)max_spans, delim_ids_dev, (int)n_delim,
                            out_capacity, out_ids_dev, out_pos_dev, out_src_dev, out_len_dev);

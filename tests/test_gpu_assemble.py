@@ -140,3 +140,22 @@ def test_assemble_after_projection_on_workloads(name):
     np.testing.assert_array_equal(op.cpu().numpy()[:n], want_pos)
     np.testing.assert_array_equal(os_.cpu().numpy()[:n], want_src)
     say(f"[assemble] {name}: ok, {n} ids ({ts.shape[0]} ranges) from {M} target tokens")
+
+
+@pytest.mark.parametrize("max_spans,capacity", [(2047, 4000), (2048, 1 << 19), (2048, (1 << 19) + 1), (2049, 4000), (2049, 600000)])
+def test_assemble_on_both_sides_of_the_one_launch_limits(max_spans, capacity):
+    """Up to 2048 ranges and 2^19 output entries take one launch, more take two; as many ranges as there may be."""
+    say(f"[assemble] {max_spans} ranges, capacity {capacity}")
+    rng = np.random.default_rng(max_spans)
+    M = 530000
+    ids = rng.integers(0, 150000, size=M).astype(np.int32)
+    bounds = np.concatenate([[0], np.sort(rng.choice(np.arange(1, M), size=2 * max_spans - 1, replace=False))]).reshape(-1, 2)
+    delim = rng.integers(150000, 150010, size=3).astype(np.int32)
+    want_ids, want_pos, want_src = oracle.assemble(ids, bounds, delim)
+    n = min(capacity, want_ids.size)
+    got_ids, got_pos, got_src, length = gpu_assemble(ids, bounds, delim, out_capacity=capacity)
+    assert length == want_ids.size
+    np.testing.assert_array_equal(got_ids[:n], want_ids[:n])
+    np.testing.assert_array_equal(got_pos[:n], want_pos[:n])
+    np.testing.assert_array_equal(got_src[:n], want_src[:n])
+    assert (got_ids[n:] == -1).all()
