@@ -112,7 +112,8 @@ sp_status sp_score_workspace(const sp_score_desc *desc, int64_t total_tokens,
  *    computes the scores without it (tens of milliseconds to a second).
  * Calls of one process on several streams take turns on the device with it (the
  * first ones after a change of stream may not be able to: they never fail either).
- * Calls recorded into a graph do not: such a call uses the single-launch kernel
+ * On a stream with a compute-unit mask no call fails.
+ * Calls recorded into a graph take no turns: such a call uses the single-launch kernel
  * only where sp_score_is_fused answers 1, and its replays must then not overlap
  * another such call or replay. (Elsewhere the recorded call takes the
  * three-kernel path, so its scores may differ from the eager call's by rounding.)

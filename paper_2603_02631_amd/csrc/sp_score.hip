@@ -1183,6 +1183,20 @@ bool capturing(hipStream_t st)
     return status != hipStreamCaptureStatusNone;
 }
 
+// Compute units that work on this stream may use: fewer than the device has where the stream was made with a mask.
+// 0.2 us for a stream of the program's own.
+int stream_compute_units(hipStream_t st)
+{
+    const int cus = device_compute_units();
+    if (special_stream(st) || cus < 1) return cus;
+    uint32_t mask[32] = {};
+    const int words = std::min(32, (cus + 31) / 32);
+    if (hipExtStreamGetCUMask(st, (uint32_t)words, mask) != hipSuccess) { (void)hipGetLastError(); return cus; }
+    int n = 0;
+    for (int i = 0; i < words; ++i) n += __builtin_popcount(mask[i]);
+    return n < 1 ? cus : std::min(n, cus);
+}
+
 // What the variants of sp_score add to the plain call.
 struct ScoreOptions {
     const void *k_look = nullptr;            // lookahead keys in the normaliser
@@ -1315,7 +1329,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     // What sp_score_is_fused and sp_score_batch_is_fused announce may fail. Every other call on the single-launch kernel,
     // and one that could not be ordered behind its neighbours, gives up early (see kYieldSpins) and is finished by a
     // launch that can do without that kernel.
-    const bool pair = may_fuse && !captured && !batch && pair_applies(p, opt.kscale != nullptr, total, desc->k_stride_token);
+    bool pair = may_fuse && !captured && !batch && pair_applies(p, opt.kscale != nullptr, total, desc->k_stride_token);
     bool fused = may_fuse && !pair && (batch ? plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg)
                                              : plan_fused_prompt(p, total, desc->k_stride_token, bg));
     int ranges = 1;
@@ -1330,8 +1344,17 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     if (fused && big)           // no exchange area of their own: see fused_big
         for (size_t g = 0; g < bg.groups.size(); ++g)
             fused = fused && sp_fused::workspace_bytes(p.rows_pad, bg.wgs[g], bg.groups[g].n) <= w.split - w.part;
+    // On part of the device the ranges that would fill it only wait for each other. What is announced keeps its kernel
+    // where that has a compute unit for every workgroup, but they are spread over the XCDs without regard to the mask.
+    const int cus = captured ? device_compute_units() : stream_compute_units(st);
+    const bool masked = cus < device_compute_units();
+    if (masked) {
+        pair = false;
+        ranges = 1;
+        fused = fused && announced && *std::max_element(bg.wgs.begin(), bg.wgs.end()) <= cus;
+    }
     if (fused || pair) {
-        bool stand_in = !announced;
+        bool stand_in = !announced || masked;
         {
             const Turn turn(st, !captured);
             stand_in = stand_in || turn.unordered();

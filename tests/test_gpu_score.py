@@ -667,6 +667,34 @@ def test_calls_that_cannot_be_ordered_never_fail():
             assert_scores_close(c[4].cpu().numpy(), c[6])
 
 
+@pytest.mark.parametrize("shape", [("short", 16, 32, 8, 64, 8, 6200), ("two_tiles", 1, 4, 1, 64, 8, 150000), ("announced", 2, 8, 2, 64, 8, 40000)],
+                         ids=lambda s: s[0])
+def test_scores_on_a_stream_with_a_compute_unit_mask(shape):
+    """128 of the device's compute units: nothing is launched whose workgroups would have to wait for others to end."""
+    import ctypes
+    import torch
+    import paper_2603_02631_amd as sp
+    from gpu_util import DEV, assert_scores_close, dev_bits, last_call_gave_up, make_desc, status_word, workspace
+    name, Lyr, H, Hkv, d, n_q, L = shape
+    say(f"[score-mask] {name} L={L}")
+    w = small_workload(name, Lyr, H, Hkv, d, n_q, L, cfg_id=292, hh=(1, 1000))
+    inp = synth.make_score_inputs(w)
+    desc = make_desc(Lyr, H, Hkv, d, n_q, w.scale, 0, "HND", L)
+    qd, kd = dev_bits(inp["q"][0]), [dev_bits(k) for k in inp["k"]]
+    scores, ws = torch.zeros(L, dtype=torch.float32, device=DEV), workspace(sp.sp_score_workspace(desc, L, 1))
+    torch.cuda.synchronize()
+    hip, stream = ctypes.CDLL("libamdhip64.so.7"), ctypes.c_void_p()
+    mask = (ctypes.c_uint32 * 8)(*[0xFFFFFFFF] * 4, *[0] * 4)
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), 8, mask) == 0
+    try:
+        sp.sp_score(desc, qd, kd, L, scores, ws, stream=stream.value)
+        assert hip.hipStreamSynchronize(stream) == 0
+    finally:
+        assert hip.hipStreamDestroy(stream) == 0
+    assert status_word(ws) == 0 and not last_call_gave_up()
+    assert_scores_close(scores.cpu().numpy(), oracle.score(inp["q"][0], inp["k"], w.scale, 0))
+
+
 def test_captured_score_of_a_short_prompt():
     """A captured call takes the general path; every replay agrees with the eager call."""
     import torch
