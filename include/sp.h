@@ -438,6 +438,12 @@ sp_status sp_hbm_read_probe(const void *buf_dev, size_t bytes, uint64_t *sink_de
  * in the launches that hold prompt b of their call only. Process-wide. */
 void sp_debug_fused_giveup(uint32_t spin_limit, int32_t force_miss);
 
+/* Test hook: how the calling thread's last score call (of more than no tokens)
+ * was launched. 0 = the three-kernel path; otherwise the single-launch kernel:
+ * bits 0-7 tiles of keys a workgroup owns, bits 8-15 layer ranges side by side,
+ * bits 16-23 launches, bit 24 set if the call's last launch can stand in for it. */
+int32_t sp_debug_score_path(void);
+
 /* Description of the last error raised on the calling thread ("" if none).
  * The string lives in thread-local storage owned by the library. */
 const char *sp_last_error(void);

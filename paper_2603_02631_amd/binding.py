@@ -23,7 +23,7 @@ EXPORTS = (
     "sp_score_workspace", "sp_score", "sp_score_look", "sp_score_paged", "sp_score_fp8", "sp_score_is_fused", "sp_score_fp8_is_fused", "sp_score_batch", "sp_score_batch_is_fused", "sp_keep_count", "sp_select_workspace",
     "sp_select", "sp_select_static", "sp_select_batch_workspace", "sp_select_batch", "sp_select_budget_workspace", "sp_select_budget", "sp_project", "sp_project_batch",
     "sp_assemble_workspace", "sp_assemble", "sp_last_error", "sp_version",
-    "sp_debug_fused_giveup", "sp_hbm_read_probe",
+    "sp_debug_fused_giveup", "sp_debug_score_path", "sp_hbm_read_probe",
 )
 
 
@@ -100,6 +100,8 @@ def load_library():
     lib.sp_hbm_read_probe.restype = c.c_int
     lib.sp_debug_fused_giveup.argtypes = [c.c_uint32, c.c_int32]
     lib.sp_debug_fused_giveup.restype = None
+    lib.sp_debug_score_path.argtypes = []
+    lib.sp_debug_score_path.restype = c.c_int32
     lib.sp_last_error.restype = c.c_char_p
     lib.sp_version.restype = c.c_char_p
     for name in ("sp_score_workspace", "sp_score", "sp_score_look", "sp_score_paged", "sp_score_fp8", "sp_score_is_fused", "sp_score_batch", "sp_select_workspace", "sp_select",
@@ -179,6 +181,11 @@ def sp_version() -> str:
 def sp_debug_fused_giveup(spin_limit: int = 1 << 20, force_miss: int = 0) -> None:
     """Test hook: see ``sp_debug_fused_giveup`` in ``include/sp.h``."""
     load_library().sp_debug_fused_giveup(int(spin_limit), int(force_miss))
+
+
+def sp_debug_score_path() -> int:
+    """Test hook: see ``sp_debug_score_path`` in ``include/sp.h``."""
+    return int(load_library().sp_debug_score_path())
 
 
 def sp_hbm_read_probe(buf, nbytes: int, sink, stream=None) -> None:

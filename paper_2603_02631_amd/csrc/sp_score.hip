@@ -1206,6 +1206,8 @@ struct ScoreOptions {
     const float *kscale = nullptr;           // 8-bit keys with these scales
 };
 
+thread_local int32_t t_path = 0;         // see sp_debug_score_path
+
 sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *const *k_layers_host,
                      const int64_t *offsets_host, const int64_t *offsets_dev, int32_t B, int64_t L_single,
                      const ScoreOptions &opt, float *scores_dev, void *ws_dev, size_t ws_bytes, void *hip_stream)
@@ -1382,6 +1384,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
             }
             if (rs != SP_OK) return rs;
         }
+        t_path = (pair ? 2 : 1) | ranges << 8 | (pair ? 1 : (int32_t)std::min<size_t>(bg.groups.size(), 255)) << 16 | (int32_t)stand_in << 24;
         if (stand_in) return launch_finish(p, a, kp, batch ? offsets_dev : nullptr, a.status + 1, ranges, st);
         if (ranges > 1) return launch_reduce(a, ranges, st);
         if (bg.groups.size() > 1) {
@@ -1391,6 +1394,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
         }
         return SP_OK;
     }
+    t_path = 0;
     if (batch) {
         TileInfo *tiles = reinterpret_cast<TileInfo *>(ws + w.tiles);
         int32_t *pt = reinterpret_cast<int32_t *>(ws + w.prompt_tiles);
@@ -1425,6 +1429,8 @@ extern "C" void sp_debug_fused_giveup(uint32_t spin_limit, int32_t force_miss)
 {
     sp_fused::set_giveup(spin_limit, force_miss);
 }
+
+extern "C" int32_t sp_debug_score_path(void) { return t_path; }
 
 extern "C" int32_t sp_score_is_fused(const sp_score_desc *desc, int64_t L)
 {

@@ -49,6 +49,13 @@ def status_word(ws: torch.Tensor) -> int:
     return int(ws[:4].cpu().numpy().view(np.uint32)[0])
 
 
+def score_path():
+    """How the last score call was launched: "general" (three kernels), or (tiles a workgroup, layer ranges, launches)
+    of the single-launch kernel, with a fourth entry "stand-in" where the call's last launch can replace it."""
+    p = sp.sp_debug_score_path()
+    return "general" if p == 0 else (p & 255, p >> 8 & 255, p >> 16 & 255) + (("stand-in",) if p >> 24 else ())
+
+
 def gpu_score(q_bits: np.ndarray, k_layers: Sequence[np.ndarray], scale: float, layer_agg: int = 0,
               layout: str = "HND", k_dev: Optional[List[torch.Tensor]] = None) -> np.ndarray:
     """q_bits: uint16 [Lyr][H][n_q][d]; k_layers: uint16 [Hkv][L][d] (HND) or [L][Hkv][d] (NHD)."""

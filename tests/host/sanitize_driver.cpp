@@ -141,6 +141,7 @@ int main()
     }
     sp_debug_fused_giveup(4, 1);
     sp_debug_fused_giveup(1u << 20, 0);
+    EXPECT(sp_debug_score_path() == 0);
     std::printf(g_fail ? "sanitize driver: %d check(s) failed\n" : "sanitize driver: all checks passed\n", g_fail);
     return g_fail ? 1 : 0;
 }

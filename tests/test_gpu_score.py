@@ -294,12 +294,29 @@ RANGE_SHAPES = [
     ("ranges_d128_g5_padding", 24, 20, 4, 128, 5, [6200]),
     ("whole_d128_g8", 12, 8, 1, 128, 8, [45000]),                    # 176 workgroups, one range
     ("ranges_batch_d128_g8", 24, 32, 4, 128, 8, [6000, 300, 2000]),
+    # further from the lines between the kernels
+    ("ranges_6_rows64", 16, 32, 8, 64, 16, [17001]),
+    ("ranges_16_rows64", 16, 32, 8, 64, 16, [8190]),
+    ("ranges_4_two_gblocks", 16, 32, 4, 64, 8, [26000]),
+    ("ranges_7_d128_padding", 14, 8, 4, 128, 5, [6145]),
+    ("whole_d128_g8_long", 16, 8, 1, 128, 8, [57000]),
 ]
+# The kernels these take: (tiles a workgroup, layer ranges, launches, "stand-in") of the single-launch kernel.
+RANGE_PATHS = {
+    "ranges_16_of_1_layer": (1, 16, 1, "stand-in"), "ranges_8_of_2_layers_rows64": "general", "ranges_two_gblocks": "general",
+    "ranges_uneven_d128": (1, 4, 1, "stand-in"), "ranges_d128_padding": "general", "ranges_batch": (1, 6, 1, "stand-in"),
+    "ranges_batch_d128": (1, 3, 1, "stand-in"), "ranges_short_prompts": (1, 8, 1, "stand-in"),
+    "ranges_short_prompts_rows64": (1, 7, 1, "stand-in"), "ranges_short_prompts_d128": (1, 7, 1, "stand-in"),
+    "ranges_d128_g8": (1, 8, 1, "stand-in"), "ranges_d128_g5_padding": (1, 8, 1, "stand-in"), "whole_d128_g8": (1, 1, 1, "stand-in"),
+    "ranges_batch_d128_g8": (1, 6, 1, "stand-in"), "ranges_6_rows64": (1, 6, 1, "stand-in"), "ranges_16_rows64": (1, 16, 1, "stand-in"),
+    "ranges_4_two_gblocks": (1, 4, 1, "stand-in"), "ranges_7_d128_padding": (1, 7, 1, "stand-in"),
+    "whole_d128_g8_long": (1, 1, 1, "stand-in"),
+}
 
 
 @pytest.mark.parametrize("shape", RANGE_SHAPES, ids=[s[0] for s in RANGE_SHAPES])
 def test_score_in_layer_ranges_matches_oracle(shape):
-    from gpu_util import assert_scores_close, gpu_score, gpu_score_batch
+    from gpu_util import assert_scores_close, gpu_score, gpu_score_batch, score_path
     name, Lyr, H, Hkv, d, n_q, lens = shape
     lengths = np.array(lens, dtype=np.int64)
     say(f"[score-ranges] {name} Lyr={Lyr} H={H} Hkv={Hkv} d={d} n_q={n_q} lengths={lens}")
@@ -312,6 +329,7 @@ def test_score_in_layer_ranges_matches_oracle(shape):
           (lambda mode, k, lay: gpu_score_batch(q, k, offsets, w.scale, mode, layout=lay))
     for mode in (0, 1):
         got = run(mode, ks, "HND")
+        assert score_path() == RANGE_PATHS[name]
         for b, Lb in enumerate(lengths):
             if Lb:
                 sl = slice(int(offsets[b]), int(offsets[b + 1]))
@@ -338,7 +356,7 @@ PAIR_SHAPES = [
 
 @pytest.mark.parametrize("shape", PAIR_SHAPES, ids=[s[0] for s in PAIR_SHAPES])
 def test_score_with_two_tiles_a_workgroup_matches_oracle(shape):
-    from gpu_util import assert_scores_close, gpu_score, gpu_score_look, gpu_score_paged, make_paged
+    from gpu_util import assert_scores_close, gpu_score, gpu_score_look, gpu_score_paged, make_paged, score_path
     name, Lyr, H, Hkv, d, n_q, L, page = shape
     say(f"[score-pair] {name} Lyr={Lyr} H={H} Hkv={Hkv} d={d} n_q={n_q} L={L} page={page}")
     w = small_workload(name, Lyr, H, Hkv, d, n_q, L, cfg_id=600 + PAIR_SHAPES.index(shape), hh=(1, 1000))
@@ -351,6 +369,7 @@ def test_score_with_two_tiles_a_workgroup_matches_oracle(shape):
         run = lambda mode: gpu_score(q, k, w.scale, mode)
     for mode in ((0,) if Lyr > 4 else (0, 1)):
         got = run(mode)
+        assert score_path() == (2, 1, 1, "stand-in")
         assert_scores_close(got, oracle.score(q, k, w.scale, mode))
         assert run(mode).tobytes() == got.tobytes()
     if not page and Lyr <= 4:
@@ -362,7 +381,7 @@ def test_score_with_two_tiles_a_workgroup_matches_oracle(shape):
 
 def test_wide_query_groups_with_lookahead_and_paged_keys():
     """head_dim 128 with eight heads a kv head on the single-launch kernel: lookahead keys in the normaliser, paged keys."""
-    from gpu_util import assert_scores_close, gpu_score_look, gpu_score_paged, make_paged
+    from gpu_util import assert_scores_close, gpu_score_look, gpu_score_paged, make_paged, score_path
     Lyr, H, Hkv, d, n_q, L, page = 24, 32, 4, 128, 8, 6001, 512
     say(f"[score-wide] L={L}")
     w = small_workload("wide_group", Lyr, H, Hkv, d, n_q, L, cfg_id=650, hh=(1, 1000))
@@ -371,8 +390,10 @@ def test_wide_query_groups_with_lookahead_and_paged_keys():
     kl = synth.gen_look_keys(w, inp["q"])
     for mode in (0, 1):
         assert_scores_close(gpu_score_look(q, k, kl, 1, w.scale, mode), oracle.score_look(q, k, kl, 1, w.scale, mode))
+        assert score_path() == (1, 8, 1, "stand-in")
     pools, table = make_paged(k, page, "HND", seed=w.cfg_id)
     assert_scores_close(gpu_score_paged(q, pools, table, page, L, w.scale, 0, "HND"), oracle.score(q, k, w.scale, 0))
+    assert score_path() == (1, 8, 1, "stand-in")
 
 
 def test_fused_score_gives_up_as_a_whole():
@@ -499,7 +520,7 @@ def test_calls_that_are_not_announced_as_fused_never_fail(shape):
         try:
             sp.sp_debug_fused_giveup(4, 1)
             got = run()
-            assert u.last_call_gave_up()
+            assert u.last_call_gave_up() and u.score_path()[3] == "stand-in"
         finally:
             sp.sp_debug_fused_giveup(1 << 20, 0)
         plain = run()
@@ -592,11 +613,14 @@ def test_score_over_paged_keys_matches_oracle(shape):
         got = gpu_score_paged(q, pools, table, P, L, w.scale, mode, layout)
         assert_scores_close(got, want)
         say(f"  mode {mode}: max rel err {np.max(np.abs(got - want) / want):.2e}")
+
+
 @pytest.mark.parametrize("n_streams", [2, 4])
 def test_scores_on_several_streams_at_once(n_streams):
     """Single-launch kernels on different streams take turns: every call ends with the scores it has alone."""
     import torch
     import paper_2603_02631_amd as sp
+    from gpu_util import score_path
     dev = "cuda:0"
     say(f"[score-streams] {n_streams} streams")
     calls = []
@@ -608,6 +632,7 @@ def test_scores_on_several_streams_at_once(n_streams):
         ws = torch.empty(sp.sp_score_workspace(desc, L, 1), dtype=torch.uint8, device=dev)
         out = torch.zeros(L, dtype=torch.float32, device=dev)
         sp.sp_score(desc, q, k, L, out, ws)
+        assert score_path()[1] > 1
         calls.append((desc, q, k, L, out, ws, out.clone(), torch.cuda.Stream()))
     torch.cuda.synchronize()
     for _ in range(20):
@@ -699,6 +724,7 @@ def test_captured_score_of_a_short_prompt():
     """A captured call takes the general path; every replay agrees with the eager call."""
     import torch
     import paper_2603_02631_amd as sp
+    from gpu_util import score_path
     dev, L = "cuda:0", 8200
     say("[score-capture]")
     g = torch.Generator(device=dev).manual_seed(3)
@@ -708,10 +734,12 @@ def test_captured_score_of_a_short_prompt():
     ws = torch.empty(sp.sp_score_workspace(desc, L, 1), dtype=torch.uint8, device=dev)
     eager, out = torch.zeros(L, device=dev), torch.zeros(L, device=dev)
     sp.sp_score(desc, q, k, L, eager, ws)
+    assert score_path()[1] > 1
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         sp.sp_score(desc, q, k, L, out, ws)
+    assert score_path() == "general"
     for _ in range(3):
         out.fill_(-1.0)
         graph.replay()

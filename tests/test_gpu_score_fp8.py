@@ -53,13 +53,26 @@ FP8_SHAPES = [
     ("fp8_pair_d128", 1, 4, 2, 128, 8, 65536 + 300),
     ("fp8_pair_first_length", 2, 4, 1, 64, 8, 147457),
     ("fp8_pair_two_gblocks_full_grid", 1, 16, 2, 64, 5, 262144),
+    ("fp8_ranges_16_rows64", 16, 32, 8, 64, 16, 8190),
+    ("fp8_ranges_4_rows64", 16, 32, 8, 64, 16, 30000),
+    ("fp8_ranges_4_two_gblocks", 16, 32, 4, 64, 8, 30000),
 ]
+
+# The kernels the shapes of layer ranges and of two tiles a workgroup take (see gpu_util.score_path); three kernels below the
+# lines of their variants.
+FP8_PATHS = {
+    "fp8_ranges_draft_model_nq8": (1, 16, 1, "stand-in"), "fp8_ranges_rows64": "general", "fp8_ranges_two_gblocks": "general",
+    "fp8_ranges_d128_uneven": (1, 4, 1, "stand-in"), "fp8_ranges_d128_direct": (1, 28, 1, "stand-in"), "fp8_pair": "general",
+    "fp8_pair_two_gblocks": "general", "fp8_pair_d128": (2, 1, 1, "stand-in"), "fp8_pair_first_length": (2, 1, 1, "stand-in"),
+    "fp8_pair_two_gblocks_full_grid": (2, 1, 1, "stand-in"), "fp8_ranges_16_rows64": (1, 16, 1, "stand-in"),
+    "fp8_ranges_4_rows64": (1, 4, 1, "stand-in"), "fp8_ranges_4_two_gblocks": (1, 4, 1, "stand-in"),
+}
 
 
 @pytest.mark.parametrize("shape", FP8_SHAPES, ids=[s[0] for s in FP8_SHAPES])
 def test_score_fp8_matches_oracle(shape):
     import paper_2603_02631_amd as sp
-    from gpu_util import assert_scores_close, gpu_score_fp8, make_desc
+    from gpu_util import assert_scores_close, gpu_score_fp8, make_desc, score_path
     name, Lyr, H, Hkv, d, n_q, L = shape
     fused = sp.sp_score_fp8_is_fused(make_desc(Lyr, H, Hkv, d, n_q, 0.125, 0, "HND", L), L)
     assert fused == (1 if ("fused" in name or name == "fp8_g4_nq8_d64_long") else 0)
@@ -72,6 +85,7 @@ def test_score_fp8_matches_oracle(shape):
     for mode in (oracle.LAYER_MEAN, oracle.LAYER_MAX):
         want = oracle.score_fp8(inp["q"][0], k8, ksc.astype(np.float64), w.scale, mode)
         got = gpu_score_fp8(inp["q"][0], k8, ksc, w.scale, mode)
+        assert name not in FP8_PATHS or score_path() == FP8_PATHS[name]
         assert_scores_close(got, want)
         say(f"  mode {mode}: max rel err {np.max(np.abs(got - want) / want):.2e}")
     nhd = [np.ascontiguousarray(k.transpose(1, 0, 2)) for k in k8]
