@@ -258,7 +258,7 @@ sp_status sp_select(const float *scores_dev, int64_t L, int32_t pool_w,
                     void *hip_stream);
 
 /*
- * sp_select for a ragged batch of B prompts in two launches (Algorithm 1, the
+ * sp_select for a ragged batch of B prompts in one or two launches (Algorithm 1, the
  * same four steps, each prompt on its own: pooling windows and chunks never
  * cross a prompt's end). scores_dev is packed as sp_score_batch leaves it:
  * prompt b owns [offsets[b], offsets[b+1]). kept_off holds the prefix sums of the

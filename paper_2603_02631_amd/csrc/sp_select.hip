@@ -2,12 +2,12 @@
 // (paper: Algorithm 1 "AvgPool1D", "PartitionIntoChunks", "TopKChunks",
 // "MergeAdjacentChunks"; Appendix A.1.2; Appendix A.3).
 //
-// Two kernels:
+// Two kernels (prompts of a few chunks take both in one launch, sp_select_one_kernel):
 //   sp_chunk_kernel  one wavefront per chunk: the mean of the chunk's window
 //                    sums as one weighted sum, reduced by a fixed-order shuffle
 //                    tree. The pooled vector is never written out.
-//   sp_topk_kernel   one workgroup. MSB-first radix select (4 passes of 8 bits)
-//                    on order-preserving integer images of the fp32 chunk
+//   sp_topk_kernel   one workgroup. MSB-first radix select (up to 4 passes of 8
+//                    bits) on order-preserving integer images of the fp32 chunk
 //                    scores finds the k-th largest score exactly; chunks above
 //                    it are kept, chunks equal to it are kept in index order
 //                    until k is reached (lower index wins a tie); the kept
@@ -291,7 +291,7 @@ __device__ __forceinline__ void emit_kept(const bool (&gt)[R], const bool (&eq)[
                                           int32_t *__restrict__ sel, int64_t *__restrict__ spans, int32_t *__restrict__ n_spans)
 {
     constexpr int kWords = R * kTopkThreads / 64;
-    static_assert(kWords <= 128, "two words a lane");
+    static_assert(kWords % 2 == 0 && kWords <= 128, "two words a lane");
     __shared__ uint64_t s_gt[kWords], s_eq[kWords], s_start[kWords], s_end[kWords];
     __shared__ int32_t s_pos[kWords], s_id[kWords];       // kept chunks and spans before the word
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -462,27 +462,25 @@ __global__ __launch_bounds__(kTopkThreads) void sp_topk_kernel(const float *__re
     topk_body<R>(cs, n_chunks, k, k_dev, chunk, L, sel, spans, n_spans);
 }
 
-// Short prompts: chunk scores and selection by one workgroup, the scores through LDS.
-constexpr int kOneChunks = 2 * kTopkThreads;
+// Short prompts: chunk scores and selection by one workgroup, the scores through LDS. At most four chunks a wave.
+constexpr int kOneLoads = 4;
+constexpr int kOneChunks = kOneLoads * (kTopkThreads / 64);
 
 __device__ __forceinline__ void select_one_body(const float *__restrict__ scores, int64_t L, int pool_w, int chunk,
                                                 int64_t n_chunks, int64_t k, float *__restrict__ cs_out, int32_t *__restrict__ sel,
                                                 int64_t *__restrict__ spans, int32_t *__restrict__ n_spans)
 {
-    constexpr int kWaves = kTopkThreads / 64, kUnroll = 4;       // chunks of a wave in flight
+    constexpr int kWaves = kTopkThreads / 64;
     __shared__ float cs[kOneChunks];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int64_t c0 = wave; c0 < n_chunks; c0 += kWaves * kUnroll) {
-        float v[kUnroll];
-        chunk_means<kUnroll>(scores, L, pool_w, chunk, n_chunks, c0, kWaves, v);
+    float v[kOneLoads];
+    chunk_means<kOneLoads>(scores, L, pool_w, chunk, n_chunks, wave, kWaves, v);
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
-            if (lane == u && c0 + u * kWaves < n_chunks) cs[c0 + u * kWaves] = v[u];
-    }
+    for (int u = 0; u < kOneLoads; ++u)
+        if (lane == u && wave + u * kWaves < n_chunks) cs[wave + u * kWaves] = v[u];
     __syncthreads();
-    if (cs_out)
-        for (int64_t i = threadIdx.x; i < n_chunks; i += kTopkThreads) cs_out[i] = cs[i];
-    topk_words<kOneChunks / kTopkThreads>([&](int64_t i) { return cs[i]; }, n_chunks, k, chunk, L, sel, spans, n_spans);
+    if (cs_out && threadIdx.x < n_chunks) cs_out[threadIdx.x] = cs[threadIdx.x];
+    topk_words<1>([&](int64_t i) { return cs[i]; }, n_chunks, k, chunk, L, sel, spans, n_spans);
 }
 
 __global__ __launch_bounds__(kTopkThreads) void sp_select_one_kernel(const float *__restrict__ scores, int64_t L, int pool_w,
@@ -519,7 +517,8 @@ __global__ __launch_bounds__(kTopkThreads) void sp_select_one_batch_kernel(const
 // tokens: 6.2 against 6.4 us, called back to back 9.7 against 12.2); sixteen (8192 tokens) take 12.7 against 7.3 us.
 bool one_workgroup(int64_t n_chunks, int chunk, int pool_w)
 {
-    return n_chunks <= kOneChunks && sp::ceil_div(n_chunks, kTopkThreads / 64) * sp::ceil_div((int64_t)chunk + pool_w - 1, 64) <= 4;
+    // a chunk is one load at least, so this many loads are kOneChunks chunks at most
+    return n_chunks <= kOneChunks && sp::ceil_div(n_chunks, kTopkThreads / 64) * sp::ceil_div((int64_t)chunk + pool_w - 1, 64) <= kOneLoads;
 }
 
 // Ragged batch: one workgroup per prompt; prompt b keeps k_b = kept_off[b+1] - kept_off[b] chunks and
@@ -772,7 +771,7 @@ extern "C" sp_status sp_select_workspace(int64_t L, int32_t chunk, size_t *bytes
 
 namespace {
 
-// Validation shared by the two selection entry points, then the two launches; `cs` receives the chunk scores.
+// Validation shared by the two selection entry points, then the launches; `cs` receives the chunk scores.
 sp_status select_check(const float *scores_dev, int64_t L, int32_t pool_w, int32_t chunk, int64_t k,
                        const int32_t *sel_chunks_dev, const int64_t *spans_dev, const int32_t *n_spans_dev, int64_t &C)
 {
@@ -827,7 +826,7 @@ extern "C" sp_status sp_select(const float *scores_dev, int64_t L, int32_t pool_
 }
 
 // ---------------------------------------------------------------------------
-// sp_select for a ragged batch: two launches for all prompts.
+// sp_select for a ragged batch: one launch for prompts of a few chunks, two otherwise.
 // ---------------------------------------------------------------------------
 namespace {
 constexpr int kMaxBatchPrompts = 4096;
