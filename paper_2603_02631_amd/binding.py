@@ -154,17 +154,26 @@ def _k_bytes(desc: "ScoreDesc", tokens: int) -> int:
     return ((desc.n_kv_heads - 1) * desc.k_stride_head + (tokens - 1) * desc.k_stride_token + desc.head_dim) * 2
 
 
-_raw_stream = None      # (device index -> raw stream, -> current device index) of torch, resolved at the first use
+_current_stream = None      # () -> handle of torch's current stream, resolved at the first use
+
+
+def _resolve_current_stream():
+    import torch
+    torch.cuda.init()
+    try:        # 1.5 us a call less than through a Stream object; not public, so a torch without them takes the other
+        raw, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+        raw(device())
+    except (AttributeError, TypeError):
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
 
 
 def _stream(stream) -> Optional[int]:
-    global _raw_stream
+    global _current_stream
     if stream is None:
-        if _raw_stream is None:
-            import torch
-            torch.cuda.init()
-            _raw_stream = (torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
-        return _raw_stream[0](_raw_stream[1]()) or None
+        if _current_stream is None:
+            _current_stream = _resolve_current_stream()
+        return _current_stream() or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None

@@ -331,3 +331,22 @@ def test_score_fp8_argument_errors():
     with pytest.raises(sp.SpError) as e:
         sp.sp_score_fp8(d, fake, [fake, fake], fake, 1024, fake, fake, 256, stream=0)
     assert e.value.status == 3
+
+
+@pytest.mark.parametrize("private", [True, False])
+def test_current_stream_with_and_without_torchs_private_functions(monkeypatch, private):
+    """The binding takes torch's current stream through two functions that torch does not promise; without them it asks
+    the public interface."""
+    import types
+    import torch
+    monkeypatch.setattr(binding, "_current_stream", None)
+    monkeypatch.setattr(torch.cuda, "init", lambda: None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x50))
+    if private:
+        monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x40 + device, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert binding._stream(None) == (0x43 if private else 0x50)
+    assert binding._stream(7) == 7 and binding._stream(0) is None
+    assert binding._stream(types.SimpleNamespace(cuda_stream=9)) == 9
