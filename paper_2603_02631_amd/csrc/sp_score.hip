@@ -696,8 +696,9 @@ __global__ __launch_bounds__(kThreads) void sp_finish_kernel(ScoreArgs a, LayerP
     }
 }
 
-// Last launch of a batch of several launches: a call fails as a whole, and a launch that gave up may follow one that
-// has left valid scores.
+// Last launch of a batch of several prompts: a call fails as a whole, and a prompt whose waits gave up may follow one that
+// has left valid scores, in an earlier launch or in the same one (a prompt whose duties all sit in workgroups that
+// are there does not wait for the others' at its end).
 __global__ __launch_bounds__(256) void sp_fail_all_kernel(const uint32_t *__restrict__ status, int64_t total, float *__restrict__ scores)
 {
     if (*status == 0u) return;
@@ -1387,7 +1388,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
         t_path = (pair ? 2 : 1) | ranges << 8 | (pair ? 1 : (int32_t)std::min<size_t>(bg.groups.size(), 255)) << 16 | (int32_t)stand_in << 24;
         if (stand_in) return launch_finish(p, a, kp, batch ? offsets_dev : nullptr, a.status + 1, ranges, st);
         if (ranges > 1) return launch_reduce(a, ranges, st);
-        if (bg.groups.size() > 1) {
+        if (bg.groups.size() > 1 || bg.groups[0].n > 1) {
             hipLaunchKernelGGL(sp_fail_all_kernel, dim3((unsigned)std::min<int64_t>(sp::ceil_div(total, 1024), 64)), dim3(256), 0, st,
                                (const uint32_t *)a.status, total, scores_dev);
             SP_HIP_CHECK(hipGetLastError());

@@ -40,15 +40,17 @@
 // A wait that gives up makes the whole call fail: the workgroup raises the
 // call's status word at once, a duty that could not be completed publishes a
 // poison entry that fails every workgroup reading it, and every workgroup
-// reads the status word before it stores its scores (once any workgroup has
-// passed that point all exchanged data is out, so none can fail after it).
+// reads the status word before it stores its scores (once any workgroup of a
+// prompt has passed that point all exchanged data of the prompt is out, so none
+// of them can fail after it; the entries of a table can, one after another has
+// stored its scores, so the caller looks at the word once more in a later launch).
 //
 // Variants of the same loop: head_dim 128 (256 keys per workgroup, a wave's two
 // sub-tiles are the two halves of its 32 keys' rows: see the kernel's template
 // flag W; with two blocks of query rows Q takes twice the LDS and the transit
-// ring has two slots), two tiles a workgroup (flag PAIR), paged keys and lookahead keys in the normaliser (flag EXTRA), and
-// launches that carry a table of (prompt, layer range) entries (also under
-// EXTRA: each entry has its own workgroups, duty blocks and row of normalisers).
+// ring has two slots), two tiles a workgroup (flag PAIR), paged keys and lookahead keys in the normaliser, and
+// launches that carry a table of (prompt, layer range) entries (see Kind: each
+// entry has its own workgroups, duty blocks and row of normalisers).
 // Entries are the prompts of a ragged batch, and the layer ranges of prompts
 // that fill only part of the device: a step takes about as long whether 64 or
 // 256 compute units take part (the exchange and a wave's chain of dependent
@@ -1056,7 +1058,9 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
                 const uint64_t *src = a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad + duty_blk * kDutyRows;
                 // fast path: the partials requested at the start of this step are all there; otherwise poll (bounded)
                 DutyBlock de = read_duty_staging(lds0 + MP::kXduty, lane);
-                bool ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && a.force_miss == 0;
+                // test hook: every duty, or (whole prompts of a batch) those of one entry, see set_giveup
+                const bool miss = a.force_miss != 0 && (KIND != kExtra || a.force_miss == 1 || a.force_miss == 2 + lse_idx);
+                bool ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && !miss;
                 if (!ready && *fail == 0) {
                     unsigned spins = 0;
                     do {
@@ -1066,7 +1070,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
 #pragma unroll
                             for (int q = 0; q < 4; ++q)
                                 de.e[r][q] = ld64(src + (size_t)min(lane + 64 * q, src_n - 1) * a.rows_pad + r);
-                        ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && a.force_miss == 0;
+                        ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && !miss;
                     } while (!ready);
                 }
                 // per row: maximum first, then one exponential per partial (short dependency chains, fixed order)
@@ -1226,8 +1230,7 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     // caller guarantees L >= 512): every workgroup loads 512 real keys; rows below r_lo belong to the
     // previous workgroup. Paged keys: pages are allocated whole and hold a multiple of 512 keys, so the
     // last tile stays where it is and rows from r_hi on (allocated, never written) are ignored.
-    // Several entries in one launch (a prompt's layer range each; prompts are packed back to back, every
-    // one at least one tile long): entry p owns workgroups gt.w0[p] .. gt.w0[p+1]-1 and is a call of its
+    // Several entries in one launch (a prompt's layer range each; prompts are packed back to back): entry p owns workgroups gt.w0[p] .. gt.w0[p+1]-1 and is a call of its
     // own in everything below: tile positions count from its prompt's first key, its queries and layers
     // are its own, partials are combined among its workgroups only and its normalisers have their own row.
     const bool paged = EXTRA && a.block_table != nullptr;
@@ -1421,7 +1424,8 @@ __global__ void sp_fused_clear_kernel(uint64_t *p, size_t n, uint32_t *err)
 }
 
 // Test hook (see sp_debug_fused_giveup): polls before a wait gives up, and the launches whose duty waves
-// treat their partials as never arriving (0: none, 1: all, 2 + b: those that hold prompt b).
+// treat their partials as never arriving (0: none, 1: all, 2 + b: those that hold prompt b, where duties are
+// shared between prompts only those of that prompt).
 std::atomic<uint32_t> g_spin_max{1u << 20};     // about a second
 std::atomic<int32_t> g_force_miss{0};
 
@@ -1489,7 +1493,8 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
     a.spin_max = std::min(a.spin_max, g_spin_max.load(std::memory_order_relaxed));
     const int32_t miss = g_force_miss.load(std::memory_order_relaxed);
     a.force_miss = miss == 1 || (miss == 2 && gt.n == 0);
-    for (int i = 0; i < gt.n && miss >= 2; ++i) a.force_miss |= gt.prompt[i] == miss - 2;
+    for (int i = 0; i < gt.n && miss >= 2; ++i)
+        if (gt.prompt[i] == miss - 2) a.force_miss = shared ? 2 + i : 1;
     const size_t n_clear = n_part + n_lse;
     hipLaunchKernelGGL(sp_fused_clear_kernel, dim3((unsigned)((n_clear + 255) / 256 > 1024 ? 1024 : (n_clear + 255) / 256)),
                        dim3(256), 0, st, base, n_clear, clear_status ? status_word : (uint32_t *)nullptr);

@@ -7,7 +7,7 @@
 namespace sp_fused {
 
 constexpr int kTileKeys = 512;   // keys owned by one workgroup at head_dim 64; 256 at head_dim 128
-constexpr int kMaxRowsWide = 32; // head_dim 128: padded query rows per kv head
+constexpr int kMaxRowsWide = 32; // head_dim 128, one block of query rows (bf16 keys take two as well: fused_big)
 constexpr int kMaxRows = 64;     // padded query rows per kv head the kernel holds on chip
 constexpr int kSlots = 8;        // depth of the exchange ring
 constexpr int kDutyRows = 4;     // consecutive query rows one workgroup's duty covers
@@ -17,8 +17,8 @@ constexpr int kMaxGroup = 64;          // entries of a launch's table
 
 // The (prompt, layer range) pairs that share a launch. Entry i scores layers layer0[i] .. layer0[i] +
 // layers[i] - 1 of prompt `prompt[i]` of the batch (its queries), whose keys are [start[i], start[i] +
-// len[i]) of the packed key arrays (len >= one tile), on workgroups w0[i] .. w0[i+1]-1. An entry is on
-// its own in everything: its partials are combined among its workgroups and it has its own row of
+// len[i]) of the packed key arrays (shorter than a tile only where duties are not shared), on workgroups
+// w0[i] .. w0[i+1]-1. An entry is on its own in everything: its partials are combined among its workgroups and it has its own row of
 // normalisers. n == 0: all layers of a single prompt described by FusedArgs::L.
 // An entry has at least as many workgroups as duty blocks (rows_pad / kDutyRows) or few enough for
 // every one to combine all partials by itself (direct_max), so any number does.
@@ -45,7 +45,7 @@ struct FusedArgs {
     uint64_t *lse;               // [kSlots][rows_pad]        (-lse, phase + 1)
     uint32_t *err;               // the call's status word: raised by any workgroup whose bounded wait gave up
     uint32_t spin_max;           // polls before a wait gives up
-    int32_t force_miss;          // test hook: duty waves treat their partials as never arriving
+    int32_t force_miss;          // test hook: duty waves treat partials as never arriving (1: all, 2 + i: entry i's)
     const float *kscale;         // 8-bit keys (E4M3 codes): [n_phases] scale of each (layer, kv head); null: bf16 keys
     const float *look;           // [n_phases][rows_pad] log-sum-exp of each row over its visible lookahead keys
                                  // (raw-logit units, -inf for none), or null: prompt keys only

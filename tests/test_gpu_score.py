@@ -463,6 +463,43 @@ def test_batch_of_several_launches_gives_up_as_a_whole(prompt):
         assert bool(torch.isfinite(s).all()) and 0.99 < float(s.double().sum()) < H
 
 
+def test_batch_of_one_launch_gives_up_as_a_whole():
+    """Two prompts of 64 workgroups each and a single (layer, kv head), whose 16 duty blocks all sit in workgroups of the first
+    prompt: those of the second prompt's are not held up when the first prompt's wait for some milliseconds and give up,
+    so it is finished by then, and loses its scores all the same."""
+    import torch
+    import paper_2603_02631_amd as sp
+    from gpu_util import DEV, score_path, status_word, workspace
+    Lyr, H, Hkv, d, n_q = 1, 4, 1, 64, 8
+    off = [0, 32768, 65536]
+    say("[score-batch] give-up of one prompt of a launch")
+    g = torch.Generator(device=DEV).manual_seed(6)
+    q = torch.randn((2, Lyr, H, n_q, d), device=DEV, generator=g).to(torch.bfloat16)
+    k = [torch.randn((Hkv, off[-1], d), device=DEV, generator=g).to(torch.bfloat16) for _ in range(Lyr)]
+    desc = sp.ScoreDesc(Lyr, H, Hkv, d, n_q, 0.125, sp.SP_LAYER_MEAN, d, off[-1] * d)
+    assert sp.sp_score_batch_is_fused(desc, off) == 1
+    ws = workspace(sp.sp_score_workspace(desc, off[-1], 2))
+    od = torch.tensor(off, dtype=torch.int64, device=DEV)
+    scores = torch.zeros(off[-1], dtype=torch.float32, device=DEV)
+    for _ in range(600):                        # calls of one stream, whatever ran before: no stand-in
+        sp.sp_score_batch(desc, q, k, off, od, scores, ws)
+    assert score_path() == (1, 1, 1)
+    try:
+        sp.sp_debug_fused_giveup(1 << 12, 2)
+        sp.sp_score_batch(desc, q, k, off, od, scores, ws)
+        torch.cuda.synchronize()
+    finally:
+        sp.sp_debug_fused_giveup(1 << 20, 0)
+    assert status_word(ws) == 1
+    assert bool(torch.isnan(scores).all())
+    sp.sp_score_batch(desc, q, k, off, od, scores, ws)
+    torch.cuda.synchronize()
+    assert status_word(ws) == 0
+    for b in range(2):
+        s = scores[off[b]:off[b + 1]]
+        assert bool(torch.isfinite(s).all()) and 0.99 < float(s.double().sum()) < H
+
+
 # Calls that take the single-launch kernel although sp_score_is_fused does not say so.
 STAND_IN_SHAPES = [
     # name, entry, Lyr, H, Hkv, d, n_q, lengths
