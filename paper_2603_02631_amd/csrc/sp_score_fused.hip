@@ -1058,9 +1058,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
                 const uint64_t *src = a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad + duty_blk * kDutyRows;
                 // fast path: the partials requested at the start of this step are all there; otherwise poll (bounded)
                 DutyBlock de = read_duty_staging(lds0 + MP::kXduty, lane);
-                // test hook: every duty, or (whole prompts of a batch) those of one entry, see set_giveup
-                const bool miss = a.force_miss != 0 && (KIND != kExtra || a.force_miss == 1 || a.force_miss == 2 + lse_idx);
-                bool ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && !miss;
+                bool ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && a.force_miss == 0;
                 if (!ready && *fail == 0) {
                     unsigned spins = 0;
                     do {
@@ -1070,6 +1068,8 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
 #pragma unroll
                             for (int q = 0; q < 4; ++q)
                                 de.e[r][q] = ld64(src + (size_t)min(lane + 64 * q, src_n - 1) * a.rows_pad + r);
+                        // test hook: every duty, or (whole prompts of a batch) those of one entry, see set_giveup
+                        const bool miss = KIND == kExtra ? a.force_miss == 1 || a.force_miss == 2 + lse_idx : a.force_miss != 0;
                         ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && !miss;
                     } while (!ready);
                 }
