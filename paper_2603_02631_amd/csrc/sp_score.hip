@@ -961,21 +961,22 @@ bool whole_groups_pay(const BatchGroups &bg)
 // launches counts. Measured (tokens: three kernels / single launch, us; 16 layers x 8 kv heads unless noted):
 //   32 rows                      4600 40 / 40, 6000 45 / 37, 9000 58 / 53, 12000 69 / 54; 28 layers, head_dim 128: 1500 46 / 33;
 //                                4 x 4 heads, head_dim 128: 12000 31 / 31; 30 prompts of 1100 .. 1500 271 / 189
-//   64 rows, 9+ lookahead rows   4600 48 / 47, 6200 54 / 48, 9000 66 / 77, 10500 74 / 77, 12000 80 / 77, 16384 115 / 77;
+//   64 rows, 9+ lookahead rows   4500 50 / 49, 5000 52 / 49, 6200 54 / 48, 9000 73 / 77, 10100 78 / 78, 12000 80 / 77, 16384 115 / 77;
 //                                24 prompts of 60 .. 4000 282 / 292, 30 of 1100 .. 1500 352 / 292
 //   64 rows, 5+ heads a kv head  4600 48 / 51, 6200 53 / 51, 9000 66 / 82, 12000 80 / 83, 16384 116 / 83
 //   64 rows, head_dim 128        24 x 4 heads: 3000 45 / 49, 3600 49 / 47, 4500 66 / 48; 24 prompts of 60 .. 4000 457 / 418
-//   8-bit keys, 32 rows          6000 40 / 41, 8192 46 / 38, 10000 51 / 59, 12000 58 / 58, 16384 80 / 57; 25000 124 / 95;
+//   8-bit keys, 32 rows          6000 40 / 41, 8192 46 / 38, 10000 55 / 60, 12000 60 / 60, 16400 84 / 80, 18000 92 / 79, 22000 102 / 100;
 //                                28 layers, head_dim 128 (32 rows): 1500 43 / 35, as with bf16 keys
-//   8-bit keys, 64 rows          6200 53 / 51, 9000 63 / 83, 12000 74 / 82, 16384 101 / 80, 24000 127 / 138, 25000 161 / 146, 30000 176 / 136
+//   8-bit keys, 64 rows          6200 53 / 51, 9000 67 / 83, 12100 78 / 83, 13000 95 / 83, 16384 101 / 80, 18000 118 / 112, 19000 122 / 112,
+//                                22000 132 / 144, 24500 140 / 145, 30000 176 / 136 (no line has the crossing at 17600 as well)
 bool steps_pay(const Plan &p, bool fp8, int64_t keys, int ranges, int launches)
 {
     struct Line { double per_step, steep, base; };
     const bool wide = p.rows_pad > 32;
     const Line line = p.D == 128 ? (wide ? Line{8.0, 8.0, 0} : Line{6.3, 6.3, 0})
-                    : fp8        ? (wide ? Line{11.0, 14.9, 94} : Line{10.5, 13.2, 77})
+                    : fp8        ? (wide ? Line{11.0, 12.4, 59} : Line{9.35, 13.2, 77})
                     : !wide      ? Line{6.3, 6.3, 0}
-                    : p.NB == 2  ? Line{8.5, 12.5, 75}
+                    : p.NB == 2  ? Line{8.0, 11.25, 68}
                                  : Line{9.4, 14.0, 91};
     const double steps = (double)launches * (sp::ceil_div(p.n_layers, ranges) * (p.n_phases / p.n_layers) + 5);
     return (double)keys * p.n_phases * p.D * 2e-6 >= std::min(line.per_step * steps, line.steep * steps - line.base * launches);
