@@ -35,8 +35,8 @@ ROTATE_BYTES = 2 << 30          # K buffers are rotated over at least this much 
 # It is reported only while the kernel sources are the ones the counters were taken on.
 TRAFFIC = {
     "workload": "long-128k",
-    "sources_sha256": "3552e443f6ca870fc175fbc14b3ea1dee1b5e4004fb8521ac00800a02ef72406",
-    "fetch_bytes": 1090813.7 * 2048,      # FETCH_SIZE 1090813.7 per dispatch; the 1 GiB copy reads 524306 -> 2 KiB per count
+    "sources_sha256": "32d54f50d2a8de79c10022c09436fc2b84120b441e0c794b1da7b2666486f890",
+    "fetch_bytes": 1090758.7 * 2048,      # FETCH_SIZE 1090758.7 per dispatch; the 1 GiB copy reads 524319 -> 2 KiB per count
     "write_bytes": 16960.0 * 1024,        # WRITE_SIZE 16960.0 per dispatch; the 1 GiB copy writes 1048576 -> 1 KiB per count
 }
 KERNEL_SOURCES = ["sp_score_fused.hip", "sp_score_fused.hpp", "sp_score_dev.hpp"]     # the dominant kernel and its headers

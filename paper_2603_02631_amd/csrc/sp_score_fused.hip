@@ -1521,7 +1521,9 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
         return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, head_dim %d: %d x %d row blocks", a.head_dim, a.n_nblk, a.n_gblk);
     if (a.kscale != nullptr && extra && !(ranges && a.look == nullptr && a.block_table == nullptr))
         return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, 8-bit keys: one prompt, contiguous keys only");
-    // the fixed-model instantiations apply when every folded constant equals the call's value
+    // The fixed-model instantiations apply when every folded constant equals the call's value. Against the generic ones
+    // (whole passes): 128K tokens 4 %; in layer ranges 8192 tokens 60.8 -> 58.8 us, paged 50021 tokens 241.4 -> 233.1; two
+    // tiles a workgroup, 256K tokens 946.8 -> 932.3.
     const bool draft = a.head_dim == kD && a.n_layers == 16 && a.n_q_heads == 32 && a.n_kv_heads == 8 && a.k_stride_token == kD &&
                        a.c == kScaleEighthLog2e && a.inv_c == 1.0f / kScaleEighthLog2e;
     if (pair) {
