@@ -35,7 +35,7 @@ ROTATE_BYTES = 2 << 30          # K buffers are rotated over at least this much 
 # It is reported only while the kernel sources are the ones the counters were taken on.
 TRAFFIC = {
     "workload": "long-128k",
-    "sources_sha256": "32d54f50d2a8de79c10022c09436fc2b84120b441e0c794b1da7b2666486f890",
+    "sources_sha256": "e01eb6307fcdbeaf67aebf48b1c9472ac773458e7fa310b9129f3ef8d3595b40",
     "fetch_bytes": 1090758.7 * 2048,      # FETCH_SIZE 1090758.7 per dispatch; the 1 GiB copy reads 524319 -> 2 KiB per count
     "write_bytes": 16960.0 * 1024,        # WRITE_SIZE 16960.0 per dispatch; the 1 GiB copy writes 1048576 -> 1 KiB per count
 }

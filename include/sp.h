@@ -435,9 +435,9 @@ sp_status sp_hbm_read_probe(const void *buf_dev, size_t bytes, uint64_t *sink_de
  * (default 1 << 20), and with force_miss == 1 the waves that combine partial
  * results treat them as never arriving, so that the bounded waits give up on an
  * idle device and every kernel still runs to its end; force_miss == 2 + b does so
- * in the launches that hold prompt b of their call only, and in the calls that
- * sp_score_batch_is_fused announces to the partial results of that prompt only.
- * Process-wide. */
+ * in the launches that hold prompt b of their call only. force_miss == -1 leaves
+ * out the last workgroup of a launch instead, as if it had found no compute unit:
+ * only what waits for it gives up. Process-wide. */
 void sp_debug_fused_giveup(uint32_t spin_limit, int32_t force_miss);
 
 /* Test hook: how the calling thread's last score call (of more than no tokens)

@@ -45,7 +45,7 @@ struct FusedArgs {
     uint64_t *lse;               // [kSlots][rows_pad]        (-lse, phase + 1)
     uint32_t *err;               // the call's status word: raised by any workgroup whose bounded wait gave up
     uint32_t spin_max;           // polls before a wait gives up
-    int32_t force_miss;          // test hook: duty waves treat partials as never arriving (1: all, 2 + i: entry i's)
+    int32_t force_miss;          // test hook: duty waves treat partials as never arriving
     const float *kscale;         // 8-bit keys (E4M3 codes): [n_phases] scale of each (layer, kv head); null: bf16 keys
     const float *look;           // [n_phases][rows_pad] log-sum-exp of each row over its visible lookahead keys
                                  // (raw-logit units, -inf for none), or null: prompt keys only
@@ -90,7 +90,7 @@ sp_status launch(FusedArgs a, const sp_dev::LayerPtrs &kp, const GroupTable *gro
 constexpr uint32_t kYieldSpins = 1u << 15;
 
 // Test hook: polls before a bounded wait gives up (default 2^20) and whether duty waves treat their
-// partials as never arriving; applies to launches that follow.
+// partials as never arriving or launches lack a workgroup; applies to launches that follow.
 void set_giveup(uint32_t spin_max, int32_t force_miss);
 
 }  // namespace sp_fused

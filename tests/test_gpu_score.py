@@ -464,9 +464,9 @@ def test_batch_of_several_launches_gives_up_as_a_whole(prompt):
 
 
 def test_batch_of_one_launch_gives_up_as_a_whole():
-    """Two prompts of 64 workgroups each and a single (layer, kv head), whose 16 duty blocks all sit in workgroups of the first
-    prompt: those of the second prompt's are not held up when the first prompt's wait for some milliseconds and give up,
-    so it is finished by then, and loses its scores all the same."""
+    """Two prompts of 64 workgroups each and a single (layer, kv head); the last workgroup of the second prompt is missing.
+    What waits for its partial results gives up after some milliseconds, when workgroups of the first prompt are
+    finished; the first prompt loses its scores all the same."""
     import torch
     import paper_2603_02631_amd as sp
     from gpu_util import DEV, score_path, status_word, workspace
@@ -485,7 +485,7 @@ def test_batch_of_one_launch_gives_up_as_a_whole():
         sp.sp_score_batch(desc, q, k, off, od, scores, ws)
     assert score_path() == (1, 1, 1)
     try:
-        sp.sp_debug_fused_giveup(1 << 12, 2)
+        sp.sp_debug_fused_giveup(1 << 12, -1)
         sp.sp_score_batch(desc, q, k, off, od, scores, ws)
         torch.cuda.synchronize()
     finally:
