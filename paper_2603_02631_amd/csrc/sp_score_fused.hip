@@ -81,7 +81,7 @@ constexpr int kRing = kLag + 1;           // fragment ring: four phases
 constexpr int kSlots = sp_fused::kSlots;  // exchange ring depth
 constexpr int kMaxRowsF = sp_fused::kMaxRows;   // 64 padded query rows per kv head
 constexpr int kPubWave = 0;                // the wave that publishes this workgroup's partials
-constexpr int kDutyWave = 1;               // the wave that combines this workgroup's duty rows
+constexpr int kDutyWave = 1;               // the wave that combines this workgroup's duty rows, or with kDutyWave + 2 two of them each
 constexpr int kDutyRows = sp_fused::kDutyRows;   // 4: 32 bytes per source workgroup
 constexpr int kLseWave = 2;                // the wave that fetches the normalisers
 constexpr uint32_t kPoisonTag = 0xffffffffu;   // normaliser entry of a duty that gave up
@@ -716,36 +716,32 @@ __device__ __forceinline__ void read_wave_stats(uint32_t buf, int lane, float (&
 // Exchange data requested with direct-to-LDS loads lands in two small staging areas, each private
 // to one wave. Partials are stored workgroup-major, part[slot][workgroup][row], so that a workgroup
 // publishes all its rows with one contiguous store; a duty covers kDutyRows consecutive rows, i.e.
-// one 32-byte piece of every workgroup's line. xduty receives them as 16-byte pairs of rows:
-// chunk (2q + h) * 64 + lane holds rows 2h and 2h+1 of the block from workgroup lane + 64q.
-struct DutyBlock { uint64_t e[kDutyRows][4]; };     // [row of the block][workgroup lane + 64q]
+// one 32-byte piece of every workgroup's line. A wave that combines R of them fetches 16-byte pairs of rows:
+// its chunk (q * R / 2 + h) * 64 + lane of xduty holds its rows 2h and 2h+1 from workgroup lane + 64q.
+template <int R>
+struct DutyRows { uint64_t e[R][4]; };     // [row][workgroup lane + 64q]
 
-__device__ __forceinline__ DutyBlock read_duty_staging(uint32_t xduty, int lane)
+template <int R>
+__device__ __forceinline__ DutyRows<R> read_duty_staging(uint32_t staging, int lane)
 {
-    static_assert(kDutyRows == 4, "layout of the asm block");
+    static_assert(R == 2 || R == 4, "layout of the asm blocks");
     typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
-    const uint32_t ad = xduty + 16u * (uint32_t)lane;
-    u64x2 r[8];
-    __asm__ volatile(
-        "ds_read_b128 %0, %8\n\t"
-        "ds_read_b128 %1, %8 offset:1024\n\t"
-        "ds_read_b128 %2, %8 offset:2048\n\t"
-        "ds_read_b128 %3, %8 offset:3072\n\t"
-        "ds_read_b128 %4, %8 offset:4096\n\t"
-        "ds_read_b128 %5, %8 offset:5120\n\t"
-        "ds_read_b128 %6, %8 offset:6144\n\t"
-        "ds_read_b128 %7, %8 offset:7168\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
-        : "v"(ad)
-        : "memory");
-    DutyBlock d;
+    const uint32_t ad = staging + 16u * (uint32_t)lane;
+    u64x2 r[2 * R];
+#define SP_READ4(I, WAIT)                                                                                     \
+    __asm__ volatile("ds_read_b128 %0, %4 offset:" #I "*4096\n\tds_read_b128 %1, %4 offset:" #I "*4096+1024\n\t" \
+                     "ds_read_b128 %2, %4 offset:" #I "*4096+2048\n\tds_read_b128 %3, %4 offset:" #I "*4096+3072" WAIT \
+                     : "=&v"(r[4 * I]), "=&v"(r[4 * I + 1]), "=&v"(r[4 * I + 2]), "=&v"(r[4 * I + 3]) : "v"(ad) : "memory")
+    SP_READ4(0, "\n\ts_waitcnt lgkmcnt(0)");
+    if constexpr (R == 4) SP_READ4(1, "\n\ts_waitcnt lgkmcnt(0)");
+#undef SP_READ4
+    DutyRows<R> d;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            d.e[2 * h][q] = r[2 * q + h].x;
-            d.e[2 * h + 1][q] = r[2 * q + h].y;
+        for (int h = 0; h < R / 2; ++h) {
+            d.e[2 * h][q] = r[q * (R / 2) + h].x;
+            d.e[2 * h + 1][q] = r[q * (R / 2) + h].y;
         }
     return d;
 }
@@ -775,27 +771,28 @@ __device__ __forceinline__ void stage_direct(uint32_t xduty, const uint64_t *slo
         if (128 * i < entries) dma_v_device(slot_base + min(128 * i + 2 * lane, entries - 2), xduty + i * 1024);      // uniform
 }
 
-// The partials of rows row0 .. row0+3 of one exchange slot from every workgroup: eight loads, or (SKIP) two for
-// every 64 workgroups there are.
-template <bool SKIP>
-__device__ __forceinline__ void stage_duty_block(uint32_t xduty, const uint64_t *slot_base, int rows_pad, int n_wg,
-                                                 int row0, int lane)
+// The partials of rows row0 .. row0+R-1 of one exchange slot from every workgroup: R/2 loads for every 64 workgroups,
+// of 256 or (SKIP) of those there are.
+template <int R, bool SKIP>
+__device__ __forceinline__ void stage_duty_rows(uint32_t staging, const uint64_t *slot_base, int rows_pad, int n_wg,
+                                                int row0, int lane)
 {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-            if (!SKIP || 64 * q < n_wg) dma_v_device(slot_base + (size_t)min(lane + 64 * q, n_wg - 1) * rows_pad + row0 + 2 * h,
-                         xduty + (2 * q + h) * 1024);
+        for (int h = 0; h < R / 2; ++h)
+            if (!SKIP || 64 * q < n_wg)
+                dma_v_device(slot_base + (size_t)min(lane + 64 * q, n_wg - 1) * rows_pad + row0 + 2 * h, staging + (q * (R / 2) + h) * 1024);
 }
 
 // A partial is ready when it carries the parity of this use of its slot and a non-zero sum.
 // Entries beyond the last workgroup do not exist, rows outside the mask are padding: both count as ready.
-__device__ __forceinline__ bool duty_ready(const DutyBlock &d, uint32_t par, int lane, int n_wg, uint32_t row_mask)
+template <int R>
+__device__ __forceinline__ bool duty_ready(const DutyRows<R> &d, uint32_t par, int lane, int n_wg, uint32_t row_mask)
 {
-    uint32_t ok = 1u;           // branch-free: one straight-line test of the sixteen entries
+    uint32_t ok = 1u;           // branch-free: one straight-line test of all entries
 #pragma unroll
-    for (int r = 0; r < kDutyRows; ++r)
+    for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             ok &= (uint32_t)(lane + 64 * q >= n_wg) | (((row_mask >> r) & 1u) ^ 1u) |
@@ -873,15 +870,15 @@ struct Walk {
 
 // One step `s` of the software pipeline: everything between two workgroup barriers. Per wave, in
 // program order (phase numbers in brackets are skipped when out of range):
-//   mid     one wave publishes this workgroup's partials of phase s-1; the duty wave requests the
-//           partials of its duty rows of phase s-2; every wave requests its slices of Q(s+1) for
+//   mid     one wave publishes this workgroup's partials of phase s-1; the duty waves request the
+//           partials of their duty rows of phase s-2; every wave requests its slices of Q(s+1) for
 //           the next statistics pass and of Q(s-3) for the next probability pass
 //   prob    probability pass of phase s-4 from ring slot s%4; loads of sub-tile 0 of K(s+1)
-//   lift    wait for sub-tile 1 of K(s); lift K(s) into ring slot s%4
+//   lift    wait for sub-tile 1 of K(s); duty waves: combine the duty rows of phase s-2 and publish their
+//           normalisers (kDutyAtLift; otherwise at pre); lift K(s) into ring slot s%4
 //   stats   statistics pass of phase s; loads of sub-tile 1 of K(s+1); after its first step the
 //           normaliser wave requests the normalisers of phase s-3
-//   pre     wait for the Q slices (and the exchange data); duty wave: combine the duty rows of phase
-//           s-2 and publish their normalisers; normaliser wave: seeds of the probability pass of phase s-3
+//   pre     wait for the Q slices (and the exchange data); normaliser wave: seeds of the probability pass of phase s-3
 //   barrier
 // Vector-memory operations per wave and step, oldest first: [publish store] [8 duty loads] [Q] [Q]
 // 4 K loads (prob), [normaliser load], 4 K loads (stats); the bracketed ones exist on some waves or
@@ -940,10 +937,79 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         src_n = gt.w0[lse_idx + 1] - src_w0;
     }
 
+    // When the duty rows are combined, and by how many waves. With one block of query rows a step is short (some 4500
+    // cycles of work), and two trips through memory that the compute units share with the K stream take three such
+    // steps: combined at the end of the step by one wave (2900 cycles for four rows), the normalisers came too late in
+    // nine steps of ten, and everybody waited 3000 cycles. Two waves before the statistics pass have them out in time.
+    // Whole passes: 32K tokens of head_dim 128 366 -> 332 us, 128K tokens and 8 lookahead rows 465 -> 413, sixteen
+    // prompts 1119 -> 1025. With two blocks the pass itself bounds the step: 128K tokens and 16 lookahead rows
+    // 494 (one wave, end), 494 (one wave, here), 492 (two, end), 495 (two, here); 8-bit keys 465, 464, 470, 469.
+    constexpr bool kTwoBlocks = NB * GB == 2;
+    constexpr bool kDutyAtLift = !PAIR && (!kTwoBlocks || F8);
+    constexpr int kDutyWaves = kTwoBlocks && F8 ? 1 : 2, kWaveRows = kDutyRows / kDutyWaves;
+    // the duty of this wave: kWaveRows rows of the block from duty_row on
+    const bool duty_wave = (wave == kDutyWave || (kDutyWaves == 2 && wave == kDutyWave + 2)) && duty_blk >= 0;
+    const int duty_half = kDutyWaves == 2 && wave != kDutyWave ? 1 : 0;
+    const int duty_row = duty_blk * kDutyRows + duty_half * kWaveRows;
+    const uint32_t staging = lds0 + MP::kXduty + duty_half * (8192 / kDutyWaves);
+    int *fail = reinterpret_cast<int *>(lds + MP::kFail);
     auto request_duty = [&]() {
-        if (duty_blk >= 0)
-            stage_duty_block<EXTRA>(lds0 + MP::kXduty, a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad, a.rows_pad,
-                                    src_n, duty_blk * kDutyRows, lane);
+        if (duty_wave)
+            stage_duty_rows<kWaveRows, EXTRA>(staging, a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad, a.rows_pad,
+                                              src_n, duty_row, lane);
+    };
+    auto combine_duty = [&]() {
+        uint32_t row_mask = 0;
+#pragma unroll
+        for (int r = 0; r < kWaveRows; ++r) {
+            int g, n;
+            if (row_valid<NB>(a, duty_row + r, g, n)) row_mask |= 1u << r;
+        }
+        if (row_mask == 0) return;
+        const uint32_t par = (uint32_t)(pd / kSlots) & 1u;
+        const uint64_t *src = a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad + duty_row;
+        // fast path: the partials requested before are all there; otherwise poll (bounded)
+        DutyRows<kWaveRows> de = read_duty_staging<kWaveRows>(staging, lane);
+        bool ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && a.force_miss == 0;
+        if (!ready && *fail == 0) {
+            unsigned spins = 0;
+            do {
+                if (++spins > a.spin_max) { raise_failure(a, fail); break; }
+#pragma unroll
+                for (int r = 0; r < kWaveRows; ++r)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        de.e[r][q] = ld64(src + (size_t)min(lane + 64 * q, src_n - 1) * a.rows_pad + r);
+                ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && a.force_miss == 0;
+            } while (!ready);
+        }
+        // per row: maximum first, then one exponential per partial (short dependency chains, fixed order)
+        float mine = 0.f;       // lane r keeps the normaliser of row r of the wave's
+#pragma unroll
+        for (int r = 0; r < kWaveRows; ++r) {
+            float pm[4], pl4[4], m = neg_inf();
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const bool valid = lane + 64 * q < src_n;
+                pm[q] = valid ? __uint_as_float((uint32_t)de.e[r][q]) : neg_inf();
+                pl4[q] = valid ? __uint_as_float((uint32_t)(de.e[r][q] >> 32) & 0x7fffffffu) : 0.f;
+                m = fmaxf(m, pm[q]);
+            }
+            m = wave_max(m);
+            float l = 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (!EXTRA || 64 * q < src_n) l += pl4[q] * fast_exp2((pm[q] - m) * c_duty);      // uniform
+            l = wave_sum(l);
+            const float v = -(m + fast_log2(l) * (F8 ? 1.0f / c_duty : a.inv_c));
+            if (lane == r) mine = v;
+        }
+        // a duty that could not be completed (now or because the workgroup has failed before)
+        // publishes poison: whoever reads it fails too instead of using a wrong normaliser
+        const uint32_t tag = (ready && *fail == 0) ? (uint32_t)(pd + 1) : kPoisonTag;
+        if (lane < kWaveRows && ((row_mask >> lane) & 1u))
+            st64(a.lse + ((size_t)(pd % kSlots) * a.n_gp + lse_idx) * a.rows_pad + duty_row + lane,
+                 (uint64_t)__float_as_uint(mine) | ((uint64_t)tag << 32));
     };
 
     // ---- mid ----
@@ -971,7 +1037,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
                 st64(a.part + ((size_t)(pp % kSlots) * a.n_wg + w) * a.rows_pad + lane, bits);
             }
         }
-    } else if (!PAIR && wave == kDutyWave) {
+    } else if (!PAIR && duty_wave) {
         request_duty();
     } else if (RANGES && wave == kLseWave && direct && pl >= 0 && pl < n_phases) {
         stage_direct(lds0 + MP::kXduty, a.part + ((size_t)(pl % kSlots) * a.n_wg + a.ent_w0) * kRowsPad, a.ent_n * kRowsPad, lane);
@@ -1012,6 +1078,8 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     // ---- lift K(s), statistics pass of phase s; sub-tile 1 of K(s+1) ----
     // behind sub-tile 1 of K(s): at least the loads of sub-tile 0 of K(s+1); BIG: nothing that is certain
     if (BIG) vm_wait<0>(); else vm_wait<kSI>();
+    // The duty's partials were requested before the loads counted here, so they have landed as well.
+    if (kDutyAtLift && duty_wave) combine_duty();
     {
         KIssue ki;
         ki.lds_dst = lds0 + sub_slot_off<BIG>(wave, slot_next, 1);
@@ -1024,7 +1092,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         // this very step (their normalisers are due at the next one's end)
         auto late = [&]() {
             stage_exchange_rows(lds0 + MP::kXlse, lse_row, look_row, a.rows_pad, lane);
-            if (PAIR && PAR == 0 && wave == kDutyWave) request_duty();
+            if (PAIR && PAR == 0) request_duty();
         };
         // r_range = r_lo | r_hi << 16 (r_hi = 512 without EXTRA): this wave's share of it
         constexpr int kWaveKeys = W ? 32 : kNS * 32;
@@ -1042,64 +1110,10 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     }
 
     // ---- pre-barrier: exchange data in, seeds out ----
-    if ((wave == kLseWave && !(RANGES && direct && a.look == nullptr)) || (PAIR && PAR == 0 && wave == kDutyWave)) vm_wait<kLoadsBehindLse<NB * GB, F8, BIG>>();
+    if ((wave == kLseWave && !(RANGES && direct && a.look == nullptr)) || (PAIR && PAR == 0 && duty_wave)) vm_wait<kLoadsBehindLse<NB * GB, F8, BIG>>();
     else vm_wait<2 * kSI>();
-    int *fail = reinterpret_cast<int *>(lds + MP::kFail);
-    if (wave == kDutyWave) {
-        if (duty_blk >= 0) {
-            uint32_t row_mask = 0;
-#pragma unroll
-            for (int r = 0; r < kDutyRows; ++r) {
-                int g, n;
-                if (row_valid<NB>(a, duty_blk * kDutyRows + r, g, n)) row_mask |= 1u << r;
-            }
-            if (row_mask != 0) {
-                const uint32_t par = (uint32_t)(pd / kSlots) & 1u;
-                const uint64_t *src = a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad + duty_blk * kDutyRows;
-                // fast path: the partials requested at the start of this step are all there; otherwise poll (bounded)
-                DutyBlock de = read_duty_staging(lds0 + MP::kXduty, lane);
-                bool ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && a.force_miss == 0;
-                if (!ready && *fail == 0) {
-                    unsigned spins = 0;
-                    do {
-                        if (++spins > a.spin_max) { raise_failure(a, fail); break; }
-#pragma unroll
-                        for (int r = 0; r < kDutyRows; ++r)
-#pragma unroll
-                            for (int q = 0; q < 4; ++q)
-                                de.e[r][q] = ld64(src + (size_t)min(lane + 64 * q, src_n - 1) * a.rows_pad + r);
-                        ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && a.force_miss == 0;
-                    } while (!ready);
-                }
-                // per row: maximum first, then one exponential per partial (short dependency chains, fixed order)
-                float mine = 0.f;       // lane r keeps the normaliser of row r of the block
-#pragma unroll
-                for (int r = 0; r < kDutyRows; ++r) {
-                    float pm[4], pl4[4], m = neg_inf();
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const bool valid = lane + 64 * q < src_n;
-                        pm[q] = valid ? __uint_as_float((uint32_t)de.e[r][q]) : neg_inf();
-                        pl4[q] = valid ? __uint_as_float((uint32_t)(de.e[r][q] >> 32) & 0x7fffffffu) : 0.f;
-                        m = fmaxf(m, pm[q]);
-                    }
-                    m = wave_max(m);
-                    float l = 0.f;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        if (!EXTRA || 64 * q < src_n) l += pl4[q] * fast_exp2((pm[q] - m) * c_duty);      // uniform
-                    l = wave_sum(l);
-                    const float v = -(m + fast_log2(l) * (F8 ? 1.0f / c_duty : a.inv_c));
-                    if (lane == r) mine = v;
-                }
-                // a duty that could not be completed (now or because the workgroup has failed before)
-                // publishes poison: whoever reads it fails too instead of using a wrong normaliser
-                const uint32_t tag = (ready && *fail == 0) ? (uint32_t)(pd + 1) : kPoisonTag;
-                if (lane < kDutyRows && ((row_mask >> lane) & 1u))
-                    st64(a.lse + ((size_t)(pd % kSlots) * a.n_gp + lse_idx) * a.rows_pad + duty_blk * kDutyRows + lane,
-                         (uint64_t)__float_as_uint(mine) | ((uint64_t)tag << 32));
-            }
-        }
+    if (duty_wave) {
+        if (!kDutyAtLift) combine_duty();
     } else if (wave == kLseWave) {
         float direct_v = 0.f;
         if (RANGES && direct && pl >= 0 && pl < n_phases)
