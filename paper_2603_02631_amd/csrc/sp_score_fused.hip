@@ -341,6 +341,18 @@ constexpr int kDppXor2 = 0x4E;          // quad_perm [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141;   // lane i <- lane 7 - i within groups of 8
 constexpr int kDppMirror = 0x140;       // lane i <- lane 15 - i within rows of 16
 
+// Maximum and sum over a lane and the one 32 away, the same bits in both (no trip through LDS as shuffles make).
+__device__ __forceinline__ float halves_max(float v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float halves_sum(float v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 __device__ __forceinline__ float lane_value(float v, int lane)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
@@ -559,21 +571,24 @@ __device__ __forceinline__ f32x16 logits32(const bf16x8 (&kf)[kKS], const bf16x8
     return d;
 }
 
-// Folds the 16 logits of a lane into its running (max, sum exp); only keys lo <= key < hi of the
-// sub-tile are this workgroup's (all 32 except in the prompt's last tile).
+// Folds the 16 logits of a lane into its running (max, sum exp), which they start if FIRST (m = -inf, l = 0); only
+// keys lo <= key < hi of the sub-tile are this workgroup's (all 32 except in the prompt's last tile).
+template <bool FIRST>
 __device__ __forceinline__ void fold_logits(const f32x16 &d, float &m, float &l, float c, int lo, int hi, int hf)
 {
     if (lo <= 0 && hi >= 32) {
-        float mn = max3(m, d[0], d[1]);      // running maximum including these 16 logits
-#pragma unroll
-        for (int r = 2; r < 16; r += 2) mn = max3(mn, d[r], d[r + 1]);
-        l *= fast_exp2((m - mn) * c);
+        // running maximum including these 16 logits, as a tree: a chain of eight waits for every one of them
+        const float m0 = max3(d[0], d[1], d[2]), m1 = max3(d[3], d[4], d[5]), m2 = max3(d[6], d[7], d[8]);
+        const float m3 = max3(d[9], d[10], d[11]), m4 = max3(d[12], d[13], d[14]);
+        const float a0 = max3(m0, m1, m2), a1 = max3(m3, m4, d[15]);
+        const float mn = FIRST ? fmaxf(a0, a1) : max3(a0, a1, m);
+        if (!FIRST) l *= fast_exp2((m - mn) * c);
         m = mn;
         const float mc = mn * c;
-        float sum = 0.f;
+        float sum = fast_exp2(fmaf(d[0], c, -mc));
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sum += fast_exp2(fmaf(d[r], c, -mc));
-        l += sum;
+        for (int r = 1; r < 16; ++r) sum += fast_exp2(fmaf(d[r], c, -mc));
+        l = FIRST ? sum : l + sum;
     } else if (lo < 32 && hi > 0) {
         float tm = neg_inf();
 #pragma unroll
@@ -597,9 +612,9 @@ __device__ __forceinline__ void fold_logits(const f32x16 &d, float &m, float &l,
 
 __device__ __forceinline__ void store_row_stats(uint32_t ad, float m, float l, float c, int hf)
 {
-    const float m2 = __shfl_xor(m, 32), l2 = __shfl_xor(l, 32);
-    lse_merge(m, l, m2, l2, c);
-    if (hf == 0) lds_store_f2(ad, make_float2(m, l));
+    const float mm = halves_max(m);
+    l = halves_sum(mm > neg_inf() ? l * fast_exp2((m - mm) * c) : 0.f);
+    if (hf == 0) lds_store_f2(ad, make_float2(mm, l));
 }
 
 // Lifts the K tile of the phase into kf, then runs the MFMA steps one ahead of the arithmetic on
@@ -638,7 +653,7 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
             lift_at<MP::kQ1 + PAR * MP::kQTileBytes + MP::kQBlock>(lc, q0);
             lift_at<MP::kQ1 + PAR * MP::kQTileBytes + MP::kQBlock + kWideHalf>(lc, q1);
             f32x16 d1 = logits32(kf[0], q0);
-            fold_logits(d, m, l, c, lo0, hi0, hf);
+            fold_logits<true>(d, m, l, c, lo0, hi0, hf);
             store_row_stats(wstats_ad, m, l, c, hf);
             k_issue<2>(ki0, voff, 2);
             __builtin_amdgcn_sched_barrier(0);
@@ -646,11 +661,11 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
             for (int t = 0; t < kKS; ++t) d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][t], q1[t], d1, 0, 0, 0);
             k_issue<2>(ki, voff, 0);
             m = neg_inf(); l = 0.f;
-            fold_logits(d1, m, l, c, lo0, hi0, hf);
+            fold_logits<true>(d1, m, l, c, lo0, hi0, hf);
             store_row_stats(wstats_ad + 256, m, l, c, hf);
             k_issue<2>(ki, voff, 2);
         } else {
-            fold_logits(d, m, l, c, lo0, hi0, hf);
+            fold_logits<true>(d, m, l, c, lo0, hi0, hf);
             store_row_stats(wstats_ad, m, l, c, hf);
             k_issue<kPerStep>(ki, voff, kPerStep);
         }
@@ -664,7 +679,7 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
     f32x16 da = logits32(kf[0], qf);
     f32x16 db = logits32(kf[1], qf);
     float m = neg_inf(), l = 0.f;
-    fold_logits(da, m, l, c, lo0, hi0, hf);
+    fold_logits<true>(da, m, l, c, lo0, hi0, hf);
     k_issue<kPerStep>(ki, voff, 0);
     late();
     __builtin_amdgcn_sched_barrier(0);
@@ -672,17 +687,17 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
         lift_at<MP::kQ1 + PAR * MP::kQTileBytes + MP::kQBlock>(lc, qf);
         da = logits32(kf[0], qf);
     }
-    fold_logits(db, m, l, c, lo1, hi1, hf);
+    fold_logits<false>(db, m, l, c, lo1, hi1, hf);
     store_row_stats(wstats_ad, m, l, c, hf);
     k_issue<kPerStep>(ki, voff, kPerStep);
     __builtin_amdgcn_sched_barrier(0);
     if (NBLK == 2) {
         db = logits32(kf[1], qf);
         m = neg_inf(); l = 0.f;
-        fold_logits(da, m, l, c, lo0, hi0, hf);
+        fold_logits<true>(da, m, l, c, lo0, hi0, hf);
         k_issue<kLate>(ki, voff, 2 * kPerStep);
         __builtin_amdgcn_sched_barrier(0);
-        fold_logits(db, m, l, c, lo1, hi1, hf);
+        fold_logits<false>(db, m, l, c, lo1, hi1, hf);
         store_row_stats(wstats_ad + 256, m, l, c, hf);
         k_issue<kLate>(ki, voff, 3 * kPerStep);
         __builtin_amdgcn_sched_barrier(0);
@@ -848,13 +863,13 @@ __device__ __forceinline__ float direct_combine(const FusedArgs &a, const uint64
     float m = neg_inf(), l = 0.f;
 #pragma unroll
     for (int i = 0; i < kMaxE; ++i) m = i < mine ? fmaxf(m, __uint_as_float((uint32_t)e[i])) : m;
-    if (kRowsPad == 32) m = fmaxf(m, __shfl_xor(m, 32));
+    if (kRowsPad == 32) m = halves_max(m);
 #pragma unroll
     for (int i = 0; i < kMaxE; ++i) {
         const float p = __uint_as_float((uint32_t)(e[i] >> 32) & 0x7fffffffu) * fast_exp2((__uint_as_float((uint32_t)e[i]) - m) * c);
         l += i < mine ? p : 0.f;
     }
-    if (kRowsPad == 32) l += __shfl_xor(l, 32);
+    if (kRowsPad == 32) l = halves_sum(l);
     return -(m + fast_log2(l) * inv_c);
 }
 
