@@ -7,7 +7,8 @@
 //           head's whole query group against 256 keys, per-row running
 //           (max, sum of exp) kept per lane, one partial per (row, tile);
 //   merge   log-sum-exp combination of the partials of each row in a fixed
-//           order (deterministic), giving the row's normaliser;
+//           order (deterministic), giving the row's normaliser (short prompts:
+//           at the start of prob, see prob_merges);
 //   prob    one workgroup per (key tile, layer range), looping over its layers
 //           and the kv heads:
 //           logits again with the normaliser folded into the MFMA's C operand,
@@ -63,7 +64,7 @@ struct ScoreArgs {
     const int32_t *prompt_tiles;  // [B+1] first tile of each prompt (batch only)
     int64_t L;                // tokens of the call (single prompt: its length)
     float2 *part;             // [n_phases][n_tiles][rows_pad]
-    float *lse_neg;           // [B][n_phases][rows_pad]  (-lse in raw-logit units, permuted)
+    float *lse_neg;           // [B][n_phases][rows_pad]  (-lse in raw-logit units, permuted), or null: the prob pass merges
     float *scores;
     uint32_t *status;         // the call's status word (cleared here: this path cannot give up)
     const int32_t *block_table;   // paged keys (single prompt): token j lives in page block_table[j / page_tokens]
@@ -452,6 +453,33 @@ __device__ __forceinline__ float close_rows(float (&mx)[NB][4], float c)
     return sum;
 }
 
+// The merge of a short prompt, by every workgroup of the prob pass for the phases of its own layers: one thread per
+// (phase, row) walks the prompt's tiles, eight partials in flight. `out`: [phases][rows_pad], permuted as in lse_neg.
+__device__ __forceinline__ void merge_rows(const ScoreArgs &a, const TileInfo &ti, int phase0, int phases, float *out, int tid)
+{
+    const int t0 = a.prompt_tiles ? a.prompt_tiles[ti.prompt] : 0, t1 = a.prompt_tiles ? a.prompt_tiles[ti.prompt + 1] : a.n_tiles;
+    for (int i = tid; i < phases * a.rows_pad; i += kThreads) {
+        const int ph = i / a.rows_pad, row = i - ph * a.rows_pad, phase = phase0 + ph;
+        const float c = a.kscale ? a.c * a.kscale[phase] : a.c;
+        const float2 *src = a.part + (int64_t)phase * a.n_tiles * a.rows_pad + row;
+        float m = neg_inf(), l = 0.f;
+        for (int t = t0; t < t1; t += 8) {
+            float2 p[8];
+            float mm = m;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) p[u] = t + u < t1 ? src[(int64_t)(t + u) * a.rows_pad] : make_float2(neg_inf(), 0.f);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) mm = fmaxf(mm, p[u].x);
+            if (mm == neg_inf()) continue;
+            l *= fast_exp2((m - mm) * c);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) l += p[u].y * fast_exp2((p[u].x - mm) * c);
+            m = mm;
+        }
+        out[ph * a.rows_pad + (row & ~31) + seed_pos(row & 31)] = row_normaliser(a, phase, row, m, l, c, a.kscale ? 1.0f / c : a.inv_c);
+    }
+}
+
 template <int D, int NS, int NB, bool FP8>
 __global__ __launch_bounds__(kThreads, 3) void sp_prob_kernel(ScoreArgs a, LayerPtrs kp)
 {
@@ -460,7 +488,7 @@ __global__ __launch_bounds__(kThreads, 3) void sp_prob_kernel(ScoreArgs a, Layer
     extern __shared__ u32x4 lds[];
     u32x4 *ks = lds;
     u32x4 *qs = lds + TILE * (D / 8);
-    float *ci = reinterpret_cast<float *>(qs + a.rows_pad * (D / 8));   // rows_pad floats
+    float *ci0 = reinterpret_cast<float *>(qs + a.rows_pad * (D / 8));   // rows_pad floats, or as many for every phase
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, hf = lane >> 5, col = lane & 31;
     const int tile = blockIdx.x, split = blockIdx.y;
     const TileInfo ti = get_tile(a, tile, TILE);
@@ -481,9 +509,12 @@ __global__ __launch_bounds__(kThreads, 3) void sp_prob_kernel(ScoreArgs a, Layer
             for (int e = 0; e < 4; ++e) mx[s][b][e] = neg_inf();
     }
 
+    const bool merge = a.lse_neg == nullptr;
+    if (merge) merge_rows(a, ti, layer_lo * a.n_kv_heads, (layer_hi - layer_lo) * a.n_kv_heads, ci0, tid);
     for (int layer = layer_lo; layer < layer_hi; ++layer) {
         for (int kv = 0; kv < a.n_kv_heads; ++kv) {
             const int phase = layer * a.n_kv_heads + kv;
+            float *ci = ci0 + (merge ? (phase - layer_lo * a.n_kv_heads) * a.rows_pad : 0);
             __syncthreads();
             stage_q<D>(qs, a, ti.prompt, layer, kv, tid);
             if (FP8) stage_k_fp8<D, NS>(ks, key_base_fp8(a, kp, layer, kv), a.k_stride_token, ti.j0, ti.end, tid);
@@ -491,8 +522,9 @@ __global__ __launch_bounds__(kThreads, 3) void sp_prob_kernel(ScoreArgs a, Layer
             // 8-bit keys: logit differences of this (layer, kv head) are in units of its stored keys; its scale
             // brings them to the common unit before they meet those of other heads and layers
             const float ksc = FP8 ? a.kscale[phase] : 1.0f;
-            for (int i = tid; i < a.rows_pad; i += kThreads)
-                ci[i] = a.lse_neg[((int64_t)ti.prompt * n_phases + phase) * a.rows_pad + i];
+            if (!merge)
+                for (int i = tid; i < a.rows_pad; i += kThreads)
+                    ci[i] = a.lse_neg[((int64_t)ti.prompt * n_phases + phase) * a.rows_pad + i];
             __syncthreads();
 
             bf16x8 kf[NS][KS];
@@ -1069,19 +1101,36 @@ sp_status launch_finish(const Plan &p, const ScoreArgs &a, const LayerPtrs &kp, 
                      : launch_finish_as<128, 1, false>(p, a, kp, offsets, gave_up, n_ranges, st);
 }
 
+// Whether the prob pass merges the tiles' statistics itself (`longest`: tokens of the longest prompt): a launch less
+// (3.5 us in a chain of launches, 2.5 us of the host) for up to 20 partials a thread and workgroup. Whole passes with the
+// merge kernel and without, 16 layers x 8 kv heads, 32 rows: 1000 tokens 40.9 / 37.3 us, 3000 48.5 / 46.3, 4500 (18 partials)
+// 53.7 / 51.9, 8-bit keys 6000 (24) 52.9 / 53.8; 64 rows: 2000 (16) 51.6 / 49.0, 4500 (36) 62.7 / 63.3; 2 layers x 2 kv
+// heads, 1024 tokens 30.3 / 26.7.
+bool prob_merges(const Plan &p, const ScoreArgs &a, int64_t longest)
+{
+    const int64_t rows = (int64_t)a.layers_per_split * a.n_kv_heads * p.rows_pad;        // of a workgroup, over all its phases
+    return p.lds_bytes + sizeof(float) * (size_t)(rows - p.rows_pad) <= kLdsBudget && rows * sp::ceil_div(longest, p.tile_keys) <= 20 * kThreads;
+}
+
 template <int D, int NS, bool FP8 = false>
-sp_status launch_all(const Plan &p, const ScoreArgs &a, const LayerPtrs &kp, hipStream_t st)
+sp_status launch_all(const Plan &p, ScoreArgs a, const LayerPtrs &kp, int64_t longest, hipStream_t st)
 {
     const dim3 block(kThreads);
     hipLaunchKernelGGL((sp_stats_kernel<D, NS, FP8>), dim3(a.n_tiles, p.n_phases), block, p.lds_bytes, st, a, kp);
     SP_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(sp_merge_kernel, dim3(p.rows_pad / 32, p.n_phases, a.n_prompts), dim3(kMergeThreads), 0, st, a);
-    SP_HIP_CHECK(hipGetLastError());
+    size_t prob_lds = p.lds_bytes;
+    if (prob_merges(p, a, longest)) {
+        a.lse_neg = nullptr;
+        prob_lds += sizeof(float) * (size_t)p.rows_pad * (a.layers_per_split * a.n_kv_heads - 1);
+    } else {
+        hipLaunchKernelGGL(sp_merge_kernel, dim3(p.rows_pad / 32, p.n_phases, a.n_prompts), dim3(kMergeThreads), 0, st, a);
+        SP_HIP_CHECK(hipGetLastError());
+    }
     const dim3 grid(a.n_tiles, a.n_splits);
     if (p.NB == 1)
-        hipLaunchKernelGGL((sp_prob_kernel<D, NS, 1, FP8>), grid, block, p.lds_bytes, st, a, kp);
+        hipLaunchKernelGGL((sp_prob_kernel<D, NS, 1, FP8>), grid, block, prob_lds, st, a, kp);
     else
-        hipLaunchKernelGGL((sp_prob_kernel<D, NS, 2, FP8>), grid, block, p.lds_bytes, st, a, kp);
+        hipLaunchKernelGGL((sp_prob_kernel<D, NS, 2, FP8>), grid, block, prob_lds, st, a, kp);
     SP_HIP_CHECK(hipGetLastError());
     if (a.n_splits > 1) return launch_reduce(a, a.n_splits, st);
     return SP_OK;
@@ -1244,7 +1293,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
                             (long long)opt.page_stride);
     }
 
-    int64_t total = 0, n_tiles = 0;
+    int64_t total = 0, n_tiles = 0, longest = 0;
     const bool batch = offsets_host != nullptr;
     if (batch) {
         if (!offsets_dev) return sp::fail(SP_ERR_INVALID_ARG, "offsets_dev is null");
@@ -1254,12 +1303,14 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
             const int64_t len = offsets_host[b + 1] - offsets_host[b];
             if (len < 0) return sp::fail(SP_ERR_INVALID_ARG, "offsets_host decreases at prompt %d", b);
             n_tiles += sp::ceil_div(len, p.tile_keys);
+            longest = std::max(longest, len);
         }
         total = offsets_host[B];
     } else {
         if (L_single < 0) return sp::fail(SP_ERR_INVALID_ARG, "L = %lld is negative", (long long)L_single);
         total = L_single;
         n_tiles = sp::ceil_div(total, p.tile_keys);
+        longest = total;
         B = 1;
     }
     if (total == 0) return SP_OK;
@@ -1410,9 +1461,9 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
         a.tiles = tiles;
         a.prompt_tiles = pt;
     }
-    if (opt.kscale) return p.D == 64 ? launch_all<64, 2, true>(p, a, kp, st) : launch_all<128, 1, true>(p, a, kp, st);
-    if (p.D == 64) return launch_all<64, 2>(p, a, kp, st);
-    return launch_all<128, 1>(p, a, kp, st);
+    if (opt.kscale) return p.D == 64 ? launch_all<64, 2, true>(p, a, kp, longest, st) : launch_all<128, 1, true>(p, a, kp, longest, st);
+    if (p.D == 64) return launch_all<64, 2>(p, a, kp, longest, st);
+    return launch_all<128, 1>(p, a, kp, longest, st);
 }
 
 }  // namespace
