@@ -23,11 +23,14 @@
 //   mask groups   stage the spans' character intervals in LDS; since they are
 //                 sorted, token [ts, te) is kept iff the first span that ends
 //                 after ts begins before te: one LDS binary search per token.
-// More spans take three launches:
+// Long texts take two launches: the chain of workgroup 0 above costs more than a second launch, so its searches go to
+// the mask groups, which look at every token and its neighbourhood anyway:
+//   sp_project_mark_kernel   one thread per target token: mask, and the first tokens of the spans that begin or end in it;
+//   sp_project_spans_kernel  one workgroup: scans, merged target ranges, their count and the kept-token total.
+// More spans than fit LDS take three:
 //   sp_project_search_kernel one wave per (span, end): 64-ary search of the
 //                            target offsets, three rounds of memory latency.
-//   sp_project_spans_kernel  one workgroup: scans, merged target ranges,
-//                            their count and the kept-token total.
+//   sp_project_spans_kernel  as above.
 //   sp_project_mask_kernel   one thread per target token: binary search of the
 //                            merged ranges, writes the 0/1 keep mask.
 #include "sp_common.hpp"
@@ -66,38 +69,6 @@ __device__ __forceinline__ int64_t wave_search(const int64_t *a, int64_t n, int6
     return lo;
 }
 
-struct ScanSmem {
-    int64_t wave_max[kWavesPerBlock];
-    int wave_sum[kWavesPerBlock];
-};
-
-// Inclusive block scans: running maximum of an int64 and running sum of an int.
-__device__ __forceinline__ void block_scan(int64_t &mx, int &sum, ScanSmem &sm, int64_t &tot_max, int &tot_sum)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int64_t m2 = __shfl_up(mx, off);
-        const int s2 = __shfl_up(sum, off);
-        if (lane >= off) { mx = mx > m2 ? mx : m2; sum += s2; }
-    }
-    __syncthreads();
-    if (lane == 63) { sm.wave_max[wave] = mx; sm.wave_sum[wave] = sum; }
-    __syncthreads();
-    int64_t bm = -1; int bs = 0;
-    tot_max = -1; tot_sum = 0;
-#pragma unroll
-    for (int w = 0; w < kWavesPerBlock; ++w) {
-        const int64_t wm = sm.wave_max[w];
-        const int ws = sm.wave_sum[w];
-        if (w < wave) { bm = bm > wm ? bm : wm; bs += ws; }
-        tot_max = tot_max > wm ? tot_max : wm;
-        tot_sum += ws;
-    }
-    mx = mx > bm ? mx : bm;
-    sum += bs;
-}
-
 // Raw target range of every span: tspans[2s] = first t with target_off[t+1] > cs,
 // tspans[2s+1] = first t with target_off[t] >= ce (M if none).
 __global__ __launch_bounds__(kThreads) void sp_project_search_kernel(
@@ -117,67 +88,96 @@ __global__ __launch_bounds__(kThreads) void sp_project_search_kernel(
     if (lane == 0) tspans[2 * s + end] = r;
 }
 
-__global__ __launch_bounds__(kThreads) void sp_project_spans_kernel(
-    const int32_t *__restrict__ n_spans_p, int max_spans, int64_t *tspans, int32_t *n_tspans, int64_t *n_kept)
-{
-    __shared__ ScanSmem sm;
-    __shared__ int64_t red[kWavesPerBlock];
-    const int tid = threadIdx.x;
-    int n_spans = *n_spans_p;
-    if (n_spans > max_spans) n_spans = max_spans;
-    if (n_spans < 0) n_spans = 0;
+constexpr int kSpanThreads = 1024;
+constexpr int kSpanWaves = kSpanThreads / 64;
 
+struct SpanSmem {
+    int64_t wave_max[kSpanWaves];
+    int64_t red[kSpanWaves];
+    int wave_sum[kSpanWaves];
+};
+
+// Merges the raw ranges in tspans (see the file header) in place, kSpanThreads spans at a time.
+// Bound by its chain of round trips: one load of the ranges (not waiting for the count), two scans, one store.
+__device__ __forceinline__ void merge_spans_body(int n_spans, int max_spans, int64_t *tspans, int32_t *n_tspans, int64_t *n_kept)
+{
+    __shared__ SpanSmem sm;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int64_t carry_hi = -1;      // largest range end seen in earlier segments (-1: none)
+    int64_t kept = 0;
     int carry_n = 0;            // merged ranges opened in earlier segments
-    for (int base = 0; base < n_spans; base += kThreads) {
+    for (int base = 0; base == 0 || base < n_spans; base += kSpanThreads) {
         const int s = base + tid;
         int64_t lo = 0, hi = 0;
-        bool nonempty = false;
-        if (s < n_spans) {          // raw range from the search kernel; merged ranges are written back in place
-            lo = tspans[2 * s];     // (an entry is overwritten only after its segment has been read: r <= s)
+        if (s < max_spans) {        // merged ranges are written back in place (an entry is overwritten only after
+            lo = tspans[2 * s];     // its segment has been read: r <= s)
             hi = tspans[2 * s + 1];
-            nonempty = lo < hi;
         }
+        const bool nonempty = s < n_spans && lo < hi;
         // exclusive running maximum of the ends of earlier non-empty ranges
-        int64_t incl_max = nonempty ? hi : -1;
-        int dummy = 0;
-        int64_t tot_max; int tot_dummy;
-        block_scan(incl_max, dummy, sm, tot_max, tot_dummy);
-        int64_t prev_hi = __shfl_up(incl_max, 1);
-        if ((tid & 63) == 0) {
-            prev_hi = -1;
-            for (int w = 0; w < (tid >> 6); ++w) prev_hi = prev_hi > sm.wave_max[w] ? prev_hi : sm.wave_max[w];
+        int64_t incl = nonempty ? hi : -1;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int64_t other = __shfl_up(incl, off);
+            if (lane >= off) incl = incl > other ? incl : other;
         }
-        prev_hi = prev_hi > carry_hi ? prev_hi : carry_hi;
-        const int start = nonempty && (prev_hi < 0 || lo > prev_hi);
-        int id = start;
-        int64_t dm = -1; int64_t tm; int tot_start;
-        block_scan(dm, id, sm, tm, tot_start);
+        if (lane == 63) sm.wave_max[wave] = incl;
+        __syncthreads();
+        int64_t prev_hi = __shfl_up(incl, 1), all_hi = carry_hi;
+        if (lane == 0) prev_hi = -1;
+        int64_t before = carry_hi;
+#pragma unroll
+        for (int w = 0; w < kSpanWaves; ++w) {
+            const int64_t wm = sm.wave_max[w];
+            if (w < wave) before = before > wm ? before : wm;
+            all_hi = all_hi > wm ? all_hi : wm;
+        }
+        prev_hi = prev_hi > before ? prev_hi : before;
+        const bool start = nonempty && (prev_hi < 0 || lo > prev_hi);
+        if (nonempty) {             // the range's part beyond every earlier end
+            const int64_t from = lo > prev_hi ? lo : prev_hi;
+            kept += hi > from ? hi - from : 0;
+        }
+        const uint64_t starts = __ballot(start);
+        if (lane == 0) sm.wave_sum[wave] = __popcll(starts);
+        __syncthreads();
+        int r = carry_n + __popcll(starts & ((1ull << lane) - 1)), total = 0;
+#pragma unroll
+        for (int w = 0; w < kSpanWaves; ++w) {
+            const int ws = sm.wave_sum[w];
+            if (w < wave) r += ws;
+            total += ws;
+        }
         if (start) {
-            const int r = carry_n + id - 1;
             tspans[2 * r] = lo;
             if (r > 0) tspans[2 * (r - 1) + 1] = prev_hi;   // closes the previous merged range
         }
-        carry_hi = carry_hi > tot_max ? carry_hi : tot_max;
-        carry_n += tot_start;
+        carry_hi = all_hi;
+        carry_n += total;
     }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) kept += __shfl_xor(kept, off);
+    if (lane == 0) sm.red[wave] = kept;
+    __syncthreads();
     if (tid == 0) {
         if (carry_n > 0) tspans[2 * (carry_n - 1) + 1] = carry_hi;
         *n_tspans = carry_n;
-    }
-    __syncthreads();
-    // kept-token total = sum of merged range lengths
-    int64_t part = 0;
-    for (int r = tid; r < carry_n; r += kThreads) part += tspans[2 * r + 1] - tspans[2 * r];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) part += __shfl_xor(part, off);
-    if ((tid & 63) == 0) red[tid >> 6] = part;
-    __syncthreads();
-    if (tid == 0) {
         int64_t t = 0;
-        for (int w = 0; w < kWavesPerBlock; ++w) t += red[w];
+        for (int w = 0; w < kSpanWaves; ++w) t += sm.red[w];
         *n_kept = t;
     }
+}
+
+__device__ __forceinline__ int span_count(const int32_t *n_spans_p, int max_spans)
+{
+    const int n = *n_spans_p;
+    return n > max_spans ? max_spans : (n < 0 ? 0 : n);
+}
+
+__global__ __launch_bounds__(kSpanThreads) void sp_project_spans_kernel(const int32_t *__restrict__ n_spans_p, int max_spans,
+                                                                        int64_t *tspans, int32_t *n_tspans, int64_t *n_kept)
+{
+    merge_spans_body(span_count(n_spans_p, max_spans), max_spans, tspans, n_tspans, n_kept);
 }
 
 __global__ __launch_bounds__(kThreads) void sp_project_mask_kernel(const int64_t *__restrict__ tspans,
@@ -423,6 +423,79 @@ __global__ __launch_bounds__(kOneThreads) void sp_project_one_kernel(
                                      n_tspans, n_kept, mask);
 }
 
+// ---------------------------------------------------------------------------
+// two launches
+// ---------------------------------------------------------------------------
+constexpr int kMarkThreads = 1024;
+constexpr int kMarkSpans = 4096;             // spans whose character intervals fit the LDS of two workgroups a unit (64 KB)
+constexpr int kMarkPerThread = 2;
+// Target tokens from which two launches are faster than one, whose workgroup 0 stages more of the text the longer it is
+// (tokens / spans: one launch and two, us: 9400 / 40 8.4 and 9.1, 18000 / 80 9.0 and 9.5, 23000 / 107 9.9 and 9.6,
+// 57000 / 197 13.9 and 10.1, 57000 / 383 17.9 and 11.0, 150000 / 182 14.6 and 9.9; three launches, 300000 / 181 12.4 and 9.9).
+constexpr int64_t kMarkLine = 22 * 1024;
+
+// Target token [ts, te) is kept iff the first span j that ends after ts begins before te. Raw range of span s, from
+// the token that its interval [cs, ce) begins or ends in (offsets do not decrease, so that is one token):
+//   begin: t if ts <= cs < te (t = 0: cs < te), M if cs >= te of the last token
+//   end:   t + 1 if ts < ce <= te (the last token: ts < ce), 0 if ce <= ts of token 0
+// Spans are sorted and disjoint, so those of a token are neighbours of j (one of them as a rule). Spans without
+// characters that sit on ts come before j.
+__device__ __forceinline__ void mark_body(const int64_t *__restrict__ draft_off, int64_t L, const int64_t *__restrict__ target_off,
+                                          int64_t M, const int64_t *__restrict__ spans, const int32_t *__restrict__ n_spans_p,
+                                          int max_spans, int64_t *__restrict__ tspans, uint8_t *__restrict__ mask)
+{
+    extern __shared__ int64_t mark_ch[];     // [2 * max_spans] character position of every (span, end)
+    const int tid = threadIdx.x;
+    const int64_t base = (int64_t)blockIdx.x * (kMarkThreads * kMarkPerThread);
+    int64_t ts[kMarkPerThread], te[kMarkPerThread];
+#pragma unroll
+    for (int k = 0; k < kMarkPerThread; ++k) {
+        const int64_t t = base + k * kMarkThreads + tid;
+        ts[k] = target_off[t < M ? t : M];
+        te[k] = target_off[t < M ? t + 1 : M];
+    }
+    // all max_spans entries are read, so that this does not wait for the count; those past it are not used
+    for (int i = tid; i < 2 * max_spans; i += kMarkThreads) {
+        int64_t tok = spans[i];
+        tok = tok < 0 ? 0 : (tok > L ? L : tok);
+        mark_ch[i] = draft_off[tok];
+    }
+    const int n = span_count(n_spans_p, max_spans);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kMarkPerThread; ++k) {
+        const int64_t t = base + k * kMarkThreads + tid;
+        if (t >= M) break;
+        const bool first = t == 0, last = t == M - 1;
+        int j = 0, hi = n;                   // first span whose end lies after ts
+        while (j < hi) {
+            const int mid = j + ((hi - j) >> 1);
+            if (mark_ch[2 * mid + 1] > ts[k]) hi = mid; else j = mid + 1;
+        }
+        if (mask) mask[t] = j < n && mark_ch[2 * j] < te[k];
+        for (int s = j; s < n; ++s) {
+            const int64_t cs = mark_ch[2 * s], ce = mark_ch[2 * s + 1];
+            const bool begins = cs < te[k] && (first || cs >= ts[k]), ends = ce <= te[k] || last;
+            if (begins || (last && cs >= te[k])) tspans[2 * s] = begins ? t : M;
+            if (ends) tspans[2 * s + 1] = t + 1;
+            if (!last && !ends) break;       // later spans begin behind this one's end
+        }
+        for (int s = j - 1; s >= 0 && (first || mark_ch[2 * s] >= ts[k]); --s) {
+            if (mark_ch[2 * s] < te[k]) tspans[2 * s] = t;
+            else if (last) tspans[2 * s] = M;
+            if (first) tspans[2 * s + 1] = 0;
+        }
+    }
+}
+
+__global__ __launch_bounds__(kMarkThreads) void sp_project_mark_kernel(
+    const int64_t *__restrict__ draft_off, int64_t L, const int64_t *__restrict__ target_off, int64_t M,
+    const int64_t *__restrict__ spans, const int32_t *__restrict__ n_spans_p, int max_spans, int64_t *__restrict__ tspans,
+    uint8_t *__restrict__ mask)
+{
+    mark_body(draft_off, L, target_off, M, spans, n_spans_p, max_spans, tspans, mask);
+}
+
 // Ragged batch: prompt b = blockIdx.y. Its L_b + 1 draft offsets start at off[b] + b of the packed array,
 // its M_b + 1 target offsets at moff[b] + b, its spans and target ranges (k_b of each at most) at
 // kept_off[b], its mask bytes at moff[b]. Workgroup 0 of a prompt finds its ranges, the others its mask.
@@ -467,6 +540,16 @@ extern "C" sp_status sp_project(const int64_t *draft_off_dev, int64_t L, const i
     if (max_spans < 1 || max_spans > (1 << 24))
         return sp::fail(SP_ERR_INVALID_ARG, "max_spans = %d outside 1..2^24", max_spans);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    if (max_spans <= kMarkSpans && (M >= kMarkLine || max_spans > kOneSpans)) {
+        hipLaunchKernelGGL(sp_project_mark_kernel, dim3((unsigned)sp::ceil_div(M, (int64_t)kMarkThreads * kMarkPerThread)), dim3(kMarkThreads),
+                           sizeof(int64_t) * 2 * (size_t)max_spans, st, draft_off_dev, L, target_off_dev, M, spans_dev, n_spans_dev,
+                           (int)max_spans, tspans_dev, keep_mask_dev);
+        SP_HIP_CHECK(hipGetLastError());
+        hipLaunchKernelGGL(sp_project_spans_kernel, dim3(1), dim3(kSpanThreads), 0, st, n_spans_dev, (int)max_spans, tspans_dev,
+                           n_tspans_dev, n_kept_dev);
+        SP_HIP_CHECK(hipGetLastError());
+        return SP_OK;
+    }
     // one launch when the spans fit its LDS and one stride of the coarse index fits a wave-wide probe
     const int64_t stride = M / kCoarse + 1;          // ceil((M + 1) / kCoarse)
     if (max_spans <= kOneSpans && stride <= 63) {
@@ -482,7 +565,7 @@ extern "C" sp_status sp_project(const int64_t *draft_off_dev, int64_t L, const i
     hipLaunchKernelGGL(sp_project_search_kernel, dim3(search_grid), dim3(kThreads), 0, st, draft_off_dev, L,
                        target_off_dev, M, spans_dev, n_spans_dev, (int)max_spans, tspans_dev);
     SP_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(sp_project_spans_kernel, dim3(1), dim3(kThreads), 0, st, n_spans_dev, (int)max_spans,
+    hipLaunchKernelGGL(sp_project_spans_kernel, dim3(1), dim3(kSpanThreads), 0, st, n_spans_dev, (int)max_spans,
                        tspans_dev, n_tspans_dev, n_kept_dev);
     SP_HIP_CHECK(hipGetLastError());
     if (keep_mask_dev) {

@@ -143,7 +143,7 @@ def check_project(doff, toff, spans):
     ts2, m2, n2 = gpu_project(doff, toff, spans, want_mask=False, max_spans=max(1, spans.shape[0]) + 3)
     np.testing.assert_array_equal(ts2, o_ts)
     assert m2 is None and n2 == o_n
-    # a capacity beyond what the one-launch kernel holds in LDS takes the three-launch path
+    # a capacity beyond what the one-launch kernel holds in LDS takes two launches
     ts3, m3, n3 = gpu_project(doff, toff, spans, max_spans=1500)
     np.testing.assert_array_equal(ts3, o_ts)
     np.testing.assert_array_equal(m3, o_mask)
@@ -204,6 +204,33 @@ def test_project_long_prompt_coarse_index_strides():
         say(f"  L={L} M={toff.size - 1} spans={spans.shape[0]}")
         check_project(doff, toff, spans)
         check_project(doff, toff, np.array([[0, 1], [L - 1, L]], dtype=np.int64))   # first and last token
+
+
+@pytest.mark.parametrize("tokens", [22 * 1024 - 1, 22 * 1024, 24 * 1024 + 1])
+def test_project_around_the_line_to_two_launches(tokens):
+    """One launch, two (a mark per target token) and three (more spans than the mark kernel's LDS holds) on the same
+    text: zero-length tokens on both sides, spans without characters, target tokens that hold several spans, spans at
+    both ends of the text."""
+    from gpu_util import gpu_project
+    say(f"[project] M={tokens}")
+    rng = np.random.default_rng(tokens)
+    lens = rng.integers(0, 4, size=tokens)
+    lens[rng.choice(tokens, size=40, replace=False)] = 300          # long target tokens
+    lens[:2], lens[-2:] = 0, 0
+    toff = offsets_from_lengths(lens)
+    total = int(toff[-1])
+    draft = np.sort(rng.integers(0, total + 1, size=total // 4))    # repeated offsets: tokens without characters
+    doff = np.concatenate([[0, 0], draft, [total, total]]).astype(np.int64)
+    L = doff.size - 1
+    pts = np.sort(rng.choice(np.arange(1, L), size=1400, replace=False)).reshape(-1, 2)
+    spans = np.concatenate([[[0, 1]], pts[pts[:, 0] > 1], [[L - 1, L]]]).astype(np.int64)
+    for sel in (spans, spans[::7], spans[:1], spans[-1:]):
+        want = oracle.project(doff, toff, sel)
+        for cap in (sel.shape[0], 1024, 1025, 4096, 4097):
+            ts, mask, n = gpu_project(doff, toff, sel, max_spans=cap)
+            np.testing.assert_array_equal(ts, want[0])
+            np.testing.assert_array_equal(mask, want[1])
+            assert n == want[2]
 
 
 def test_project_workload_char_models():
