@@ -61,6 +61,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
+#include <type_traits>
 
 namespace {
 
@@ -109,6 +110,28 @@ struct Map {
     static constexpr int kSlotsPerWave = BIG ? 2 : kSubSlots;
     static constexpr int kBytes = kKring + kFWaves * kSlotsPerWave * kSubBytes;
     static_assert(kQ2 + 2 * kQTileBytes <= 65536 && kBytes <= 160 * 1024, "offset fields hold 16 bits; 160 KB a compute unit");
+};
+
+// The probability pass at the end of a step (see step_late): K stays in the transit ring for the whole step, so a wave
+// has four slots (two tiles of two sub-tiles); everything else is sized for 32 rows.
+struct LateMap {
+    static constexpr int kRows = 32, kWaveStats = kRows * 8;                   // (max, sum) of one wave
+    static constexpr int kQTileBytes = kRows * kD * 2;
+    static constexpr int kQBlock = kQTileBytes;
+    static constexpr int kQ1 = 0;                                  // [2] by step parity
+    static constexpr int kQ2 = kQ1 + 2 * kQTileBytes;              // [2]
+    static constexpr int kWstats = kQ2 + 2 * kQTileBytes;          // first tile of a phase: [2] by phase parity; second tile
+    static constexpr int kCinit = kWstats + 3 * kFWaves * kWaveStats;
+    static constexpr int kXduty = kCinit + kRows * 4;              // two waves x 4 KB
+    static constexpr int kXlse = kXduty + 8192;                    // normaliser entries
+    static constexpr int kXlook = kXlse + kRows * 8;
+    static constexpr int kFail = kXlook + kRows * 4;
+    static constexpr int kSeeded = kFail + 4;                      // phase whose seeds are in kCinit, plus one
+    static constexpr int kKring = (kFail + 16 + 1023) / 1024 * 1024;
+    static constexpr int kBytes = kKring + kFWaves * 4 * kSubBytes;
+    static_assert(kBytes <= 160 * 1024, "160 KB a compute unit");
+    // sub-tile s2 of the tile of a step of parity par
+    static __device__ __forceinline__ uint32_t slot(int wave, int par, int s2) { return (uint32_t)(kKring + ((wave * 2 + par) * 2 + s2) * kSubBytes); }
 };
 
 #define SP_LPTR(p) ((__attribute__((address_space(3))) void *)(p))
@@ -252,6 +275,50 @@ __device__ __forceinline__ void lift_k_and_q(const LaneConst &lc, uint32_t koff0
     }
 }
 
+// One 32-key sub-tile at a run-time offset, both of a tile, and one with a 32-row Q block: one round trip to LDS each.
+__device__ __forceinline__ void lift_sub(const LaneConst &lc, uint32_t koff, bf16x8 (&kf)[kKS])
+{
+    static_assert(kKS == 4, "layout of the asm block");
+    u32x4 r[4];
+    __asm__ volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+                     : "v"(lc.ld[0] + koff), "v"(lc.ld[1] + koff), "v"(lc.ld[2] + koff), "v"(lc.ld[3] + koff) : "memory");
+#pragma unroll
+    for (int t = 0; t < kKS; ++t) kf[t] = __builtin_bit_cast(bf16x8, r[t]);
+}
+__device__ __forceinline__ void lift_tile(const LaneConst &lc, uint32_t koff, bf16x8 (&kf)[kNS][kKS])
+{
+    static_assert(kKS == 4 && kNS == 2 && kSubBytes == 4096, "layout of the asm block");
+    u32x4 r[8];
+    __asm__ volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+                     "ds_read_b128 %4, %8 offset:4096\n\tds_read_b128 %5, %9 offset:4096\n\t"
+                     "ds_read_b128 %6, %10 offset:4096\n\tds_read_b128 %7, %11 offset:4096\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
+                     : "v"(lc.ld[0] + koff), "v"(lc.ld[1] + koff), "v"(lc.ld[2] + koff), "v"(lc.ld[3] + koff) : "memory");
+#pragma unroll
+    for (int t = 0; t < kKS; ++t) {
+        kf[0][t] = __builtin_bit_cast(bf16x8, r[t]);
+        kf[1][t] = __builtin_bit_cast(bf16x8, r[4 + t]);
+    }
+}
+template <int QOFF>
+__device__ __forceinline__ void lift_sub_and_q(const LaneConst &lc, uint32_t koff, bf16x8 (&kf)[kKS], bf16x8 (&qf)[kKS])
+{
+    static_assert(kKS == 4 && QOFF >= 0 && QOFF < 65536, "layout of the asm block");
+    u32x4 r[8];
+    __asm__ volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+                     "ds_read_b128 %4, %12 offset:%16\n\tds_read_b128 %5, %13 offset:%16\n\t"
+                     "ds_read_b128 %6, %14 offset:%16\n\tds_read_b128 %7, %15 offset:%16\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
+                     : "v"(lc.ld[0] + koff), "v"(lc.ld[1] + koff), "v"(lc.ld[2] + koff), "v"(lc.ld[3] + koff),
+                       "v"(lc.ld[0]), "v"(lc.ld[1]), "v"(lc.ld[2]), "v"(lc.ld[3]), "i"(QOFF) : "memory");
+#pragma unroll
+    for (int t = 0; t < kKS; ++t) {
+        kf[t] = __builtin_bit_cast(bf16x8, r[t]);
+        qf[t] = __builtin_bit_cast(bf16x8, r[4 + t]);
+    }
+}
+
 // 8-bit keys: both 32-key sub-tiles of a K tile (rows of 64 codes; this lane's eight codes of k-step t
 // are one 8-byte read) and one 32-row Q block in one round trip to LDS, the codes widened to bf16.
 template <int QOFF>
@@ -323,6 +390,16 @@ __device__ __forceinline__ void lift_q_and_seed(const LaneConst &lc, uint32_t se
 __device__ __forceinline__ void lds_store_f32(uint32_t ad, float v)
 {
     __asm__ volatile("ds_write_b32 %0, %1" : : "v"(ad), "v"(v) : "memory");
+}
+__device__ __forceinline__ void lds_store_u32(uint32_t ad, uint32_t v)
+{
+    __asm__ volatile("ds_write_b32 %0, %1" : : "v"(ad), "v"(v) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_load_u32(uint32_t ad)
+{
+    uint32_t v;
+    __asm__ volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v) : "v"(ad) : "memory");
+    return uniform32(v);
 }
 __device__ __forceinline__ void lds_store_f2(uint32_t ad, float2 v)
 {
@@ -704,25 +781,26 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
     }
 }
 
-// The eight per-wave statistics of row `lane` of one buffer, one round trip to LDS.
+// The eight per-wave statistics of row `lane` of one buffer, STRIDE bytes apart, one round trip to LDS.
+template <int STRIDE>
 __device__ __forceinline__ void read_wave_stats(uint32_t buf, int lane, float (&m)[kFWaves], float (&l)[kFWaves])
 {
     typedef __attribute__((ext_vector_type(2))) float f32x2;
     const uint32_t ad = buf + 8u * (uint32_t)lane;
     f32x2 r[kFWaves];
-    static_assert(kFWaves == 8 && kMaxRowsF * 8 == 512, "layout of the asm block");
+    static_assert(kFWaves == 8, "layout of the asm block");
     __asm__ volatile(
         "ds_read_b64 %0, %8\n\t"
-        "ds_read_b64 %1, %8 offset:512\n\t"
-        "ds_read_b64 %2, %8 offset:1024\n\t"
-        "ds_read_b64 %3, %8 offset:1536\n\t"
-        "ds_read_b64 %4, %8 offset:2048\n\t"
-        "ds_read_b64 %5, %8 offset:2560\n\t"
-        "ds_read_b64 %6, %8 offset:3072\n\t"
-        "ds_read_b64 %7, %8 offset:3584\n\t"
+        "ds_read_b64 %1, %8 offset:%9\n\t"
+        "ds_read_b64 %2, %8 offset:%9*2\n\t"
+        "ds_read_b64 %3, %8 offset:%9*3\n\t"
+        "ds_read_b64 %4, %8 offset:%9*4\n\t"
+        "ds_read_b64 %5, %8 offset:%9*5\n\t"
+        "ds_read_b64 %6, %8 offset:%9*6\n\t"
+        "ds_read_b64 %7, %8 offset:%9*7\n\t"
         "s_waitcnt lgkmcnt(0)"
         : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
-        : "v"(ad)
+        : "v"(ad), "i"(STRIDE)
         : "memory");
 #pragma unroll
     for (int i = 0; i < kFWaves; ++i) { m[i] = r[i].x; l[i] = r[i].y; }
@@ -769,9 +847,9 @@ __device__ __forceinline__ uint64_t read_lse_staging(uint32_t xlse, int lane)
     return v;
 }
 
-__device__ __forceinline__ float read_look_staging(uint32_t xlse, int lane)
+__device__ __forceinline__ float read_look_staging(uint32_t xlook, int lane)
 {
-    const uint32_t ad = xlse + kOffXlook + 4u * (uint32_t)lane;
+    const uint32_t ad = xlook + 4u * (uint32_t)lane;
     float v;
     __asm__ volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v) : "v"(ad) : "memory");
     return v;
@@ -871,6 +949,65 @@ __device__ __forceinline__ float direct_combine(const FusedArgs &a, const uint64
     }
     if (kRowsPad == 32) l = halves_sum(l);
     return -(m + fast_log2(l) * inv_c);
+}
+
+// One duty wave's rows duty_row .. duty_row + R - 1 of phase pd, whose partials from workgroups src_w0 .. src_w0 + src_n - 1
+// have been staged: publishes their normalisers in row lse_idx.
+template <int NB, int R, bool EXTRA, bool F8>
+__device__ __forceinline__ void combine_rows(const FusedArgs &a, uint32_t staging, int pd, int duty_row, int src_w0, int src_n,
+                                             int lse_idx, float c_duty, int *fail, int lane)
+{
+    uint32_t row_mask = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        int g, n;
+        if (row_valid<NB>(a, duty_row + r, g, n)) row_mask |= 1u << r;
+    }
+    if (row_mask == 0) return;
+    const uint32_t par = (uint32_t)(pd / kSlots) & 1u;
+    const uint64_t *src = a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad + duty_row;
+    // fast path: the partials requested before are all there; otherwise poll (bounded)
+    DutyRows<R> de = read_duty_staging<R>(staging, lane);
+    bool ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && a.force_miss == 0;
+    if (!ready && *fail == 0) {
+        unsigned spins = 0;
+        do {
+            if (++spins > a.spin_max) { raise_failure(a, fail); break; }
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    de.e[r][q] = ld64(src + (size_t)min(lane + 64 * q, src_n - 1) * a.rows_pad + r);
+            ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && a.force_miss == 0;
+        } while (!ready);
+    }
+    // per row: maximum first, then one exponential per partial (short dependency chains, fixed order)
+    float mine = 0.f;       // lane r keeps the normaliser of row r of the wave's
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        float pm[4], pl4[4], m = neg_inf();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool valid = lane + 64 * q < src_n;
+            pm[q] = valid ? __uint_as_float((uint32_t)de.e[r][q]) : neg_inf();
+            pl4[q] = valid ? __uint_as_float((uint32_t)(de.e[r][q] >> 32) & 0x7fffffffu) : 0.f;
+            m = fmaxf(m, pm[q]);
+        }
+        m = wave_max(m);
+        float l = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (!EXTRA || 64 * q < src_n) l += pl4[q] * fast_exp2((pm[q] - m) * c_duty);      // uniform
+        l = wave_sum(l);
+        const float v = -(m + fast_log2(l) * (F8 ? 1.0f / c_duty : a.inv_c));
+        if (lane == r) mine = v;
+    }
+    // a duty that could not be completed (now or because the workgroup has failed before)
+    // publishes poison: whoever reads it fails too instead of using a wrong normaliser
+    const uint32_t tag = (ready && *fail == 0) ? (uint32_t)(pd + 1) : kPoisonTag;
+    if (lane < R && ((row_mask >> lane) & 1u))
+        st64(a.lse + ((size_t)(pd % kSlots) * a.n_gp + lse_idx) * a.rows_pad + duty_row + lane,
+             (uint64_t)__float_as_uint(mine) | ((uint64_t)tag << 32));
 }
 
 // Uniform state that walks along with the steps.
@@ -974,57 +1111,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
                                               src_n, duty_row, lane);
     };
     auto combine_duty = [&]() {
-        uint32_t row_mask = 0;
-#pragma unroll
-        for (int r = 0; r < kWaveRows; ++r) {
-            int g, n;
-            if (row_valid<NB>(a, duty_row + r, g, n)) row_mask |= 1u << r;
-        }
-        if (row_mask == 0) return;
-        const uint32_t par = (uint32_t)(pd / kSlots) & 1u;
-        const uint64_t *src = a.part + ((size_t)(pd % kSlots) * a.n_wg + src_w0) * a.rows_pad + duty_row;
-        // fast path: the partials requested before are all there; otherwise poll (bounded)
-        DutyRows<kWaveRows> de = read_duty_staging<kWaveRows>(staging, lane);
-        bool ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && a.force_miss == 0;
-        if (!ready && *fail == 0) {
-            unsigned spins = 0;
-            do {
-                if (++spins > a.spin_max) { raise_failure(a, fail); break; }
-#pragma unroll
-                for (int r = 0; r < kWaveRows; ++r)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        de.e[r][q] = ld64(src + (size_t)min(lane + 64 * q, src_n - 1) * a.rows_pad + r);
-                ready = !__any(!duty_ready(de, par, lane, src_n, row_mask)) && a.force_miss == 0;
-            } while (!ready);
-        }
-        // per row: maximum first, then one exponential per partial (short dependency chains, fixed order)
-        float mine = 0.f;       // lane r keeps the normaliser of row r of the wave's
-#pragma unroll
-        for (int r = 0; r < kWaveRows; ++r) {
-            float pm[4], pl4[4], m = neg_inf();
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const bool valid = lane + 64 * q < src_n;
-                pm[q] = valid ? __uint_as_float((uint32_t)de.e[r][q]) : neg_inf();
-                pl4[q] = valid ? __uint_as_float((uint32_t)(de.e[r][q] >> 32) & 0x7fffffffu) : 0.f;
-                m = fmaxf(m, pm[q]);
-            }
-            m = wave_max(m);
-            float l = 0.f;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (!EXTRA || 64 * q < src_n) l += pl4[q] * fast_exp2((pm[q] - m) * c_duty);      // uniform
-            l = wave_sum(l);
-            const float v = -(m + fast_log2(l) * (F8 ? 1.0f / c_duty : a.inv_c));
-            if (lane == r) mine = v;
-        }
-        // a duty that could not be completed (now or because the workgroup has failed before)
-        // publishes poison: whoever reads it fails too instead of using a wrong normaliser
-        const uint32_t tag = (ready && *fail == 0) ? (uint32_t)(pd + 1) : kPoisonTag;
-        if (lane < kWaveRows && ((row_mask >> lane) & 1u))
-            st64(a.lse + ((size_t)(pd % kSlots) * a.n_gp + lse_idx) * a.rows_pad + duty_row + lane,
-                 (uint64_t)__float_as_uint(mine) | ((uint64_t)tag << 32));
+        combine_rows<NB, kWaveRows, EXTRA, F8>(a, staging, pd, duty_row, src_w0, src_n, lse_idx, c_duty, fail, lane);
     };
 
     // ---- mid ----
@@ -1034,8 +1121,8 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
             // then one exponential per source, and publishes the rows with one contiguous store
             constexpr int kSets = PAIR ? 2 : 1;          // of eight per-wave statistics
             float pm[kSets][kFWaves], pl8[kSets][kFWaves];
-            read_wave_stats(lds0 + MP::kWstats + (PAIR ? (SLOT ^ 2) : 1 - PAR) * kWstatsBytes, lane, pm[0], pl8[0]);
-            if constexpr (PAIR) read_wave_stats(lds0 + MP::kWstats + ((SLOT ^ 2) + 1) % 4 * kWstatsBytes, lane, pm[1], pl8[1]);
+            read_wave_stats<kMaxRowsF * 8>(lds0 + MP::kWstats + (PAIR ? (SLOT ^ 2) : 1 - PAR) * kWstatsBytes, lane, pm[0], pl8[0]);
+            if constexpr (PAIR) read_wave_stats<kMaxRowsF * 8>(lds0 + MP::kWstats + ((SLOT ^ 2) + 1) % 4 * kWstatsBytes, lane, pm[1], pl8[1]);
             float m = neg_inf();
 #pragma unroll
             for (int h = 0; h < kSets; ++h)
@@ -1154,7 +1241,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
                 if (EXTRA && a.look != nullptr) {
                     // the row's softmax also runs over its visible lookahead keys: log-sum-exp of the
                     // prompt's normaliser and theirs (-inf when the row sees none), in raw-logit units
-                    const float lp = -v, lk = read_look_staging(lds0 + MP::kXlse, lane), top = fmaxf(lp, lk);
+                    const float lp = -v, lk = read_look_staging(lds0 + MP::kXlse + kOffXlook, lane), top = fmaxf(lp, lk);
                     v = -(top + fast_log2(fast_exp2((lp - top) * a.c) + fast_exp2((lk - top) * a.c)) * a.inv_c);
                 }
             }
@@ -1180,6 +1267,184 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         wk.dfirst += duty_blocks;
         if (wk.dfirst >= duty_n) wk.dfirst -= duty_n;
     }
+    lds_barrier();
+}
+
+// The step of two tiles a workgroup, one block of query rows, head_dim 64, bf16 keys. Half as many phases are in flight
+// as with one tile, and the exchange's two trips through memory, each behind what the compute units have requested of K,
+// take some 16000 cycles: with the order of `step` odd steps waited 5500 of their 9600 cycles for the normalisers. Here
+// the probability pass comes last, so that they have most of a step more, and what is exchanged is requested and
+// consumed while no tile loads are in flight (loads return in order, and a load issued behind a burst of
+// tile loads takes as long as they do):
+//   top     even steps: the normaliser wave requests the normalisers of phase P-2; wait for K(s); even steps: publish both
+//           tiles' partials of phase P-1, seeds of phase P-2; odd steps: combine the duty rows of phase P-1; requests of Q
+//   stats   statistics pass of K(s) from the transit ring; loads of K(s+1), the first sub-tile right after the lift
+//   prob    probability pass of this tile of phase P-2 from ring slot s%4, once its seeds are there (even steps wait
+//           for the normaliser wave, without a barrier)
+//   lift    K(s) into ring slot s%4; even steps: request of the duty rows
+//   barrier
+// Whole passes of 256K tokens: 924 us before, 980 with the loads and requests where `step` has them, 875 with the duty
+// rows requested last, 833 with the tile loads behind the consumption, 802 with the normalisers requested at the top.
+// Duty rows requested at the top as well: 898; behind the statistics: 985; combined in even steps: 840 .. 894.
+template <int SLOT, int PAR, Kind KIND>
+__device__ __forceinline__ void step_late(const FusedArgs &a, const LayerPtrs &kp, int s, int n_phases, Ring &ring, Acc<1> (&accs)[2],
+                                          const LaneConst &lc, Walk &wk, unsigned char *lds, uint32_t lds0, uint64_t wave_off,
+                                          const int (&r_ranges)[2])
+{
+    constexpr bool EXTRA = KIND != kPlain;
+    using MP = LateMap;
+    int tid = threadIdx.x;
+    __asm__ volatile("" : "+v"(tid));
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int w = blockIdx.x;
+    const int ps = s >> 1, pf = (s + 1) >> 1, pd = (s - 2) >> 1, pc = (s - 4) >> 1;       // pd: published, combined; pc: probability pass
+    const uint32_t stride_bytes = (uint32_t)a.k_stride_token * 2u;
+    int *fail = reinterpret_cast<int *>(lds + MP::kFail);
+    constexpr int kBlocks = MP::kRows / kDutyRows, kWaveRows = kDutyRows / 2;
+    int duty_blk = wk.dfirst <= w ? w - wk.dfirst : w - wk.dfirst + a.n_wg;
+    if (pd < 0 || pd >= n_phases || duty_blk >= kBlocks) duty_blk = -1;
+    const bool duty_wave = (wave == kDutyWave || wave == kDutyWave + 2) && duty_blk >= 0;
+    const int duty_half = wave != kDutyWave ? 1 : 0;
+
+    // ---- top ----
+    const bool publishes = PAR == 0 && wave == kPubWave && pd >= 0 && pd < n_phases;
+    uint64_t partial = 0;
+    if (publishes) {
+        // the first tile's statistics in one half of the wave, the second's in the other
+        float pm[kFWaves], pl8[kFWaves];
+        const uint32_t buf = lds0 + MP::kWstats + (lane < 32 ? (1 - (SLOT >> 1)) * kFWaves * MP::kWaveStats : 2 * kFWaves * MP::kWaveStats - MP::kWaveStats);
+        read_wave_stats<MP::kWaveStats>(buf, lane, pm, pl8);
+        float m = neg_inf(), l = 0.f;
+#pragma unroll
+        for (int i = 0; i < kFWaves; ++i) m = fmaxf(m, pm[i]);
+        m = halves_max(m);
+#pragma unroll
+        for (int i = 0; i < kFWaves; ++i) l += pl8[i] * fast_exp2((pm[i] - m) * a.c);
+        l = halves_sum(l);
+        partial = (uint64_t)__float_as_uint(m) | ((uint64_t)__float_as_uint(l) << 32) | ((uint64_t)((pd / kSlots) & 1) << 63);
+    }
+    const char *kbase = wk.kptr + (PAR == 0 ? wk.pair_off : 0);      // the second tile is fetched in even steps
+    const uint32_t live = pf < n_phases ? 0xffffffffu : 0u;          // past the last phase one 16-byte piece per instruction
+    const uint32_t voff[2] = {lc.koff[0] & live, lc.koff[1] & live};
+    KIssue k0, k1;
+    k0.lds_dst = lds0 + MP::slot(wave, 1 - PAR, 0);
+    k0.base = kbase;
+    k0.step_bytes = 8u * stride_bytes;
+    k1.lds_dst = lds0 + MP::slot(wave, 1 - PAR, 1);
+    k1.base = kbase + (int64_t)32 * stride_bytes;
+    k1.step_bytes = k0.step_bytes;
+    const bool do_prob = pc >= 0 && pc < n_phases;
+    const bool consumes = PAR == 0 ? wave == kLseWave && do_prob : duty_wave;
+    if (PAR == 0 && consumes) {
+        if (EXTRA && a.look != nullptr && lane < MP::kRows / 4) dma_v_device(a.look + (size_t)pc * MP::kRows + 4 * lane, lds0 + MP::kXlook);
+        if (lane < MP::kRows / 2) dma_v_device(a.lse + (size_t)(pc % kSlots) * MP::kRows + 2 * lane, lds0 + MP::kXlse);
+    }
+    vm_wait<0>();                    // K(s), and what was requested behind it
+    if (publishes && lane < MP::kRows)      // only now: the wait would be for this store as well
+        st64(a.part + ((size_t)(pd % kSlots) * a.n_wg + w) * MP::kRows + lane, partial);
+    if (PAR == 0 && consumes) {
+        if (lane < MP::kRows) {
+            int g, n;
+            float v = neg_inf();
+            if (row_valid<1>(a, lane, g, n)) {
+                const uint64_t *src = a.lse + (size_t)(pc % kSlots) * MP::kRows + lane;
+                uint64_t entry = read_lse_staging(lds0 + MP::kXlse, lane);
+                if ((uint32_t)(entry >> 32) != (uint32_t)(pc + 1) && *fail == 0) {
+                    unsigned spins = 0;
+                    while ((uint32_t)(entry >> 32) != (uint32_t)(pc + 1)) {
+                        if ((uint32_t)(entry >> 32) == kPoisonTag || ++spins > a.spin_max) { raise_failure(a, fail); break; }
+                        entry = ld64(src);
+                    }
+                }
+                v = __uint_as_float((uint32_t)entry);
+                if (EXTRA && a.look != nullptr) {
+                    const float lp = -v, lk = read_look_staging(lds0 + MP::kXlook, lane), top = fmaxf(lp, lk);
+                    v = -(top + fast_log2(fast_exp2((lp - top) * a.c) + fast_exp2((lk - top) * a.c)) * a.inv_c);
+                }
+            }
+            lds_store_f32(lds0 + MP::kCinit + 4u * (uint32_t)(((lane >> 2) & 1) * 16 + 4 * (lane >> 3) + (lane & 3)), v);
+        }
+        __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        lds_store_u32(lds0 + MP::kSeeded, (uint32_t)(pc + 1));
+    }
+    if (PAR == 1 && consumes)
+        combine_rows<1, kWaveRows, false, false>(a, lds0 + MP::kXduty + duty_half * 4096, pd, duty_blk * kDutyRows + duty_half * kWaveRows, 0,
+                                                 a.n_wg, 0, a.c, fail, lane);
+    if (lc.qoff[0] >= 0) {
+        const uint32_t qblock = (uint32_t)(a.group * a.n_q * kD * 2);
+        const char *q1src = reinterpret_cast<const char *>(a.q) + (uint32_t)min(pf, n_phases - 1) * qblock;
+        const char *q2src = reinterpret_cast<const char *>(a.q) + (uint32_t)clampi((s - 3) >> 1, 0, n_phases - 1) * qblock;
+        dma_u<MP::kQ1 + (1 - PAR) * MP::kQTileBytes>((uint32_t)lc.qoff[0], q1src, lds0 + wave * 1024);
+        dma_u<MP::kQ2 + (1 - PAR) * MP::kQTileBytes>((uint32_t)lc.qoff[0], q2src, lds0 + wave * 1024);
+    }
+
+    // ---- statistics pass ----
+    if (ps < n_phases) {
+        const int r_range = r_ranges[PAR];
+        const int lo0 = (r_range & 0xffff) - wave * (kNS * 32), hi0 = EXTRA ? (r_range >> 16) - wave * (kNS * 32) : kNS * 32;
+        const int hf = lane >> 5;
+        const uint32_t wstats_ad = lds0 + MP::kWstats + ((PAR ? 2 : SLOT >> 1) * kFWaves + wave) * MP::kWaveStats + ((uint32_t)(lane & 31) << 3);
+        bf16x8 kf[kKS], qf[kKS];
+        float m = neg_inf(), l = 0.f;
+        lift_sub_and_q<MP::kQ1 + PAR * MP::kQTileBytes>(lc, MP::slot(wave, PAR, 0), kf, qf);
+        k_issue<kSubInstr>(k0, voff, 0);
+        const f32x16 da = logits32(kf, qf);
+        lift_sub(lc, MP::slot(wave, PAR, 1), kf);
+        const f32x16 db = logits32(kf, qf);
+        fold_logits<true>(da, m, l, a.c, lo0, hi0, hf);
+        k_issue<2>(k1, voff, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        fold_logits<false>(db, m, l, a.c, lo0 - 32, hi0 - 32, hf);
+        store_row_stats(wstats_ad, m, l, a.c, hf);
+        k_issue<2>(k1, voff, 2);
+    } else {
+        k_issue<kSubInstr>(k0, voff, 0);
+        k_issue<kSubInstr>(k1, voff, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- probability pass ----
+    if (do_prob) {
+        if (PAR == 0)       // set in this step, whatever the waits came to
+            while (lds_load_u32(lds0 + MP::kSeeded) != (uint32_t)(pc + 1)) __builtin_amdgcn_s_sleep(1);
+        Acc<1> &acc = accs[PAR];
+        bf16x8 qf[kKS];
+        f32x16 seed;
+        lift_q_and_seed<MP::kQ2 + PAR * MP::kQTileBytes>(lc, lds0 + MP::kCinit + ((uint32_t)(lane & 32) << 1), qf, seed);
+#pragma unroll
+        for (int s2 = 0; s2 < kNS; ++s2) {
+            f32x16 d = seed;
+#pragma unroll
+            for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[t], ring.kf[SLOT][s2][t], d, 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc.mx[s2][0][e] = max3(max3(d[e], d[4 + e], d[8 + e]), d[12 + e], acc.mx[s2][0][e]);
+        }
+        if (wk.c.kv == a.n_kv_heads - 1 && (a.layer_agg == SP_LAYER_MEAN || wk.c.layer == a.n_layers - 1)) close_layer<1, kNS>(acc, a.c);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    lift_tile(lc, MP::slot(wave, PAR, 0), ring.kf[SLOT]);
+    if (PAR == 0 && duty_wave)
+        stage_duty_rows<kWaveRows, false>(lds0 + MP::kXduty + duty_half * 4096, a.part + (size_t)(pd % kSlots) * a.n_wg * MP::kRows, MP::kRows,
+                                          a.n_wg, duty_blk * kDutyRows + duty_half * kWaveRows, lane);
+
+    // ---- walk on ----
+    if (PAR == 0 && pf + 1 < n_phases) {               // K pointer of the next phase to fetch
+        if (++wk.k.kv == a.n_kv_heads) {
+            wk.k.kv = 0;
+            ++wk.k.layer;
+            wk.kptr = reinterpret_cast<const char *>(kp.p[wk.k.layer]) + wave_off;
+        } else {
+            wk.kptr += (uint64_t)a.k_stride_head * 2u;
+        }
+    }
+    if (PAR == 1) phase_advance(wk.c, pc + 1, n_phases, a.n_kv_heads);
+    if (PAR == 1 && pd + 1 > 0 && pd + 1 < n_phases) {
+        wk.dfirst += kBlocks;
+        if (wk.dfirst >= a.n_wg) wk.dfirst -= a.n_wg;
+    }
+    // Q(s+1): K(s+1) was requested behind it, and on the duty waves their rows
+    if (PAR == 0 && duty_wave) vm_wait<2 * kSubInstr + 4>();
+    else vm_wait<2 * kSubInstr>();
     lds_barrier();
 }
 
@@ -1238,7 +1503,8 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     static_assert(!W || (NB == 1 && !M::kFixed), "head_dim 128: one block of lookahead rows");
     constexpr bool BIG = W && NB * GB == 2;
     static_assert(!BIG || (!PAIR && !F8), "head_dim 128, two blocks of query rows: bf16 keys, one tile a workgroup");
-    using MP = Map<BIG>;
+    constexpr bool LATE = PAIR && !W && !F8 && NB * GB == 1;
+    using MP = typename std::conditional<LATE, LateMap, Map<BIG>>::type;
     static_assert(!F8 || KIND != kExtra, "8-bit keys: contiguous keys of one prompt");
     static_assert(!PAIR || (NB == 1 && KIND != kRanges), "pairs of tiles: whole prompts, one block of lookahead rows");
     constexpr bool EXTRA = KIND != kPlain, RANGES = KIND == kRanges;
@@ -1312,8 +1578,8 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
         const u32x4 zero = {0u, 0u, 0u, 0u};
         for (int i = tid; i < 4 * MP::kQTileBytes / 16; i += kFThreads) z[i] = zero;
         float *ci = reinterpret_cast<float *>(lds + MP::kCinit);
-        if (tid < 2 * kMaxRowsF) ci[tid] = neg_inf();
-        if (tid == 0) *reinterpret_cast<int *>(lds + MP::kFail) = 0;
+        if (tid < (LATE ? 32 : 2 * kMaxRowsF)) ci[tid] = neg_inf();
+        if (tid < (LATE ? 2 : 1)) reinterpret_cast<int *>(lds + MP::kFail)[tid] = 0;       // LATE: and kSeeded
     }
     __syncthreads();
 
@@ -1377,7 +1643,7 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
 #pragma unroll
     for (int s2 = 0; s2 < kNS; ++s2) {
         KIssue ki;
-        ki.lds_dst = lds0 + sub_slot_off<BIG>(wave_u, 0, s2);
+        ki.lds_dst = lds0 + (LATE ? LateMap::slot(wave_u, 0, s2) : sub_slot_off<BIG>(wave_u, 0, s2));
         ki.base = reinterpret_cast<const char *>(kp.p[layer0]) + wave_off + (W ? (uint64_t)(s2 * kD * kElem) : (uint64_t)(s2 * 32) * stride_bytes);
         ki.step_bytes = (F8 ? 16u : 8u) * stride_bytes;
         k_issue<kSI>(ki, lc.koff, 0);
@@ -1400,11 +1666,20 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     // (s % 2) are compile-time; the trip count is rounded up, surplus steps do no work but keep the
     // instruction stream uniform. The last probability pass (phase n_phases - 1) runs in step n_phases + 3.
     const int n_steps = ((PAIR ? 2 * n_phases : n_phases) + kLag + 1 + 3) / 4 * 4;
-    for (int s0 = 0; s0 < n_steps; s0 += 4) {
-        step<NB, GB, 0, 0, KIND, W, F8, PAIR>(a, kp, gt, s0 + 0, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
-        step<NB, GB, 1, 1, KIND, W, F8, PAIR>(a, kp, gt, s0 + 1, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
-        step<NB, GB, 2, 0, KIND, W, F8, PAIR>(a, kp, gt, s0 + 2, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
-        step<NB, GB, 3, 1, KIND, W, F8, PAIR>(a, kp, gt, s0 + 3, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+    if constexpr (LATE) {
+        for (int s0 = 0; s0 < n_steps; s0 += 4) {
+            step_late<0, 0, KIND>(a, kp, s0 + 0, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+            step_late<1, 1, KIND>(a, kp, s0 + 1, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+            step_late<2, 0, KIND>(a, kp, s0 + 2, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+            step_late<3, 1, KIND>(a, kp, s0 + 3, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+        }
+    } else {
+        for (int s0 = 0; s0 < n_steps; s0 += 4) {
+            step<NB, GB, 0, 0, KIND, W, F8, PAIR>(a, kp, gt, s0 + 0, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+            step<NB, GB, 1, 1, KIND, W, F8, PAIR>(a, kp, gt, s0 + 1, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+            step<NB, GB, 2, 0, KIND, W, F8, PAIR>(a, kp, gt, s0 + 2, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+            step<NB, GB, 3, 1, KIND, W, F8, PAIR>(a, kp, gt, s0 + 3, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+        }
     }
     vm_wait<0>();               // no direct-to-LDS load may outlive the workgroup
     lds_barrier();
