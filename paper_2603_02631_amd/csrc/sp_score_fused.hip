@@ -702,10 +702,11 @@ __device__ __forceinline__ void store_row_stats(uint32_t ad, float m, float l, f
 template <int NBLK, bool F8, bool BIG>
 constexpr int kLoadsBehindLse = BIG ? 6 : F8 ? 1 : kSubInstr - kSubInstr / (NBLK * kNS);
 
-template <int NBLK, int PAR, bool W, bool F8, class Late>
+template <int NBLK, int PAR, bool W, bool F8, class Late, class Advance>
 __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], const LaneConst &lc, uint32_t koff0,
                                            uint32_t koff1, uint32_t wstats_ad, int lo0, int hi0, int lane,
-                                           const KIssue &ki0, const KIssue &ki, const uint32_t (&voff)[2], const Late &late)
+                                           const KIssue &ki0, const KIssue &ki, const uint32_t (&voff)[2], const Late &late,
+                                           const Advance &advance)
 {
     // tile-load instructions issued after each MFMA step (8-bit keys: two in all, after the first two steps)
     constexpr int kPerStep = F8 ? 1 : kSubInstr / (NBLK * kNS);
@@ -721,6 +722,7 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
         f32x16 d = logits32(kf[0], q0);
 #pragma unroll
         for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][t], q1[t], d, 0, 0, 0);
+        advance();
         k_issue<NBLK == 2 ? 2 : kPerStep>(NBLK == 2 ? ki0 : ki, voff, 0);
         late();
         __builtin_amdgcn_sched_barrier(0);
@@ -755,6 +757,7 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
     else lift_k_and_q<MP::kQ1 + PAR * MP::kQTileBytes>(lc, koff0, koff1, kf, qf);
     f32x16 da = logits32(kf[0], qf);
     f32x16 db = logits32(kf[1], qf);
+    advance();
     float m = neg_inf(), l = 0.f;
     fold_logits<true>(da, m, l, c, lo0, hi0, hf);
     k_issue<kPerStep>(ki, voff, 0);
@@ -1017,6 +1020,7 @@ struct Walk {
     PhaseCtr c;       // phase s - 4: this step's probability pass
     int slot0;        // transit slot of sub-tile 0 of phase s: 2s mod 3
     uint64_t pair_off;    // PAIR: bytes from a wave's first key in the first tile to its first key in the second
+    int duty_blk;     // this workgroup's block of phase s - 2, or -1
     int dfirst;       // workgroup (of those that share the duties) that combines block 0 of phase s - 2
 };
 
@@ -1028,8 +1032,8 @@ struct Walk {
 //   prob    probability pass of phase s-4 from ring slot s%4; loads of sub-tile 0 of K(s+1)
 //   lift    wait for sub-tile 1 of K(s); duty waves: combine the duty rows of phase s-2 and publish their
 //           normalisers (kDutyAtLift; otherwise at pre); lift K(s) into ring slot s%4
-//   stats   statistics pass of phase s; loads of sub-tile 1 of K(s+1); after its first step the
-//           normaliser wave requests the normalisers of phase s-3
+//   stats   statistics pass of phase s; loads of sub-tile 1 of K(s+1); scalar state of step s+1 under the first MFMA steps;
+//           after the first of them the normaliser wave requests the normalisers of phase s-3
 //   pre     wait for the Q slices (and the exchange data); normaliser wave: seeds of the probability pass of phase s-3
 //   barrier
 // Vector-memory operations per wave and step, oldest first: [publish store] [8 duty loads] [Q] [Q]
@@ -1079,8 +1083,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     constexpr int kRowsPad = 32 * NB * GB, kBlocks = kRowsPad / kDutyRows;
     const bool direct = RANGES && a.ent_n <= sp_fused::direct_max(kRowsPad);
     const int duty_w0 = RANGES ? a.ent_w0 : 0, duty_n = RANGES ? a.ent_n : a.n_wg, duty_blocks = RANGES ? kBlocks : kBlocks * a.n_gp;
-    int duty_blk = wk.dfirst <= w - duty_w0 ? w - duty_w0 - wk.dfirst : w - duty_w0 - wk.dfirst + duty_n;
-    if (pd < 0 || pd >= n_phases || duty_blk >= duty_blocks || direct) duty_blk = -1;
+    int duty_blk = wk.duty_blk;
     int src_w0 = duty_w0, src_n = duty_n, lse_idx = RANGES ? a.p_idx : 0;
     if (KIND == kExtra && a.n_gp > 1 && duty_blk >= 0) {
         lse_idx = duty_blk / kBlocks;
@@ -1196,15 +1199,40 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
             stage_exchange_rows(lds0 + MP::kXlse, lse_row, look_row, a.rows_pad, lane);
             if (PAIR && PAR == 0) request_duty();
         };
+        // Scalar state of the next step. A chain of some thirty scalar instructions: at the end of the step it took 400 to
+        // 500 cycles of the waves that everybody waits for; here it runs while the first MFMA steps are under way (whole
+        // passes: 8192 tokens 56.4 -> 55.5 us, paged 50021 tokens 205 -> 201.5, 20001 tokens 146 -> 143).
+        const int slot0 = wk.slot0;
+        auto advance = [&]() {
+            if (PAIR ? PAR == 0 && pf + 1 < n_phases : s + 2 < n_phases) {               // K pointer of the next phase to fetch
+                wk.kptr += (uint64_t)a.k_stride_head * kElem;
+                if (__builtin_expect(++wk.k.kv == a.n_kv_heads, 0)) {
+                    wk.k.kv = 0;
+                    ++wk.k.layer;
+                    wk.kptr = reinterpret_cast<const char *>(kp.p[wk.k.layer]) + wave_off;
+                }
+            }
+            if (!PAIR || PAR == 1) phase_advance(wk.c, pc + 1, n_phases, a.n_kv_heads);
+            wk.slot0 = slot_next;
+            const int pd_next = PAIR ? (PAR == 1 ? (s - 1) >> 1 : -1) : pd + 1;
+            if (pd + 1 > 0 && pd + 1 < n_phases && (!PAIR || PAR == 0)) {
+                wk.dfirst += duty_blocks;
+                if (wk.dfirst >= duty_n) wk.dfirst -= duty_n;
+            }
+            const int blk = w - duty_w0 - wk.dfirst;
+            wk.duty_blk = blk < 0 ? blk + duty_n : blk;
+            if (pd_next < 0 || pd_next >= n_phases || wk.duty_blk >= duty_blocks || direct) wk.duty_blk = -1;
+        };
         // r_range = r_lo | r_hi << 16 (r_hi = 512 without EXTRA): this wave's share of it
         constexpr int kWaveKeys = W ? 32 : kNS * 32;
         const int lo0 = (r_range & 0xffff) - wave * kWaveKeys;
         const int hi0 = EXTRA ? (r_range >> 16) - wave * kWaveKeys : kWaveKeys;
         if (do_stats) {
             const uint32_t wstats_ad = lds0 + MP::kWstats + (PAIR ? SLOT : PAR) * kWstatsBytes + wave * (kMaxRowsF * 8) + ((uint32_t)(lane & 31) << 3);
-            stats_pass<NB * GB, PAR, W, F8>(c_stats, ring.kf[SLOT], lc, sub_slot_off<BIG>(wave, wk.slot0, 0),
-                                     sub_slot_off<BIG>(wave, wk.slot0, 1), wstats_ad, lo0, hi0, lane, ki0, ki, voff, late);
+            stats_pass<NB * GB, PAR, W, F8>(c_stats, ring.kf[SLOT], lc, sub_slot_off<BIG>(wave, slot0, 0),
+                                     sub_slot_off<BIG>(wave, slot0, 1), wstats_ad, lo0, hi0, lane, ki0, ki, voff, late, advance);
         } else {
+            advance();
             late();
             if (BIG) k_issue<kSI>(ki0, voff, 0);
             k_issue<kSI>(ki, voff, 0);
@@ -1251,22 +1279,6 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         }
     }
 
-    // ---- walk on ----
-    if (PAIR ? PAR == 0 && pf + 1 < n_phases : s + 2 < n_phases) {               // K pointer of the next phase to fetch
-        if (++wk.k.kv == a.n_kv_heads) {
-            wk.k.kv = 0;
-            ++wk.k.layer;
-            wk.kptr = reinterpret_cast<const char *>(kp.p[wk.k.layer]) + wave_off;
-        } else {
-            wk.kptr += (uint64_t)a.k_stride_head * kElem;
-        }
-    }
-    if (!PAIR || PAR == 1) phase_advance(wk.c, pc + 1, n_phases, a.n_kv_heads);
-    wk.slot0 = slot_next;
-    if (pd + 1 > 0 && pd + 1 < n_phases && (!PAIR || PAR == 0)) {
-        wk.dfirst += duty_blocks;
-        if (wk.dfirst >= duty_n) wk.dfirst -= duty_n;
-    }
     lds_barrier();
 }
 
@@ -1301,10 +1313,31 @@ __device__ __forceinline__ void step_late(const FusedArgs &a, const LayerPtrs &k
     const uint32_t stride_bytes = (uint32_t)a.k_stride_token * 2u;
     int *fail = reinterpret_cast<int *>(lds + MP::kFail);
     constexpr int kBlocks = MP::kRows / kDutyRows, kWaveRows = kDutyRows / 2;
-    int duty_blk = wk.dfirst <= w ? w - wk.dfirst : w - wk.dfirst + a.n_wg;
-    if (pd < 0 || pd >= n_phases || duty_blk >= kBlocks) duty_blk = -1;
+    const int duty_blk = wk.duty_blk;
     const bool duty_wave = (wave == kDutyWave || wave == kDutyWave + 2) && duty_blk >= 0;
     const int duty_half = wave != kDutyWave ? 1 : 0;
+    const PhaseCtr c_now = wk.c;
+    // scalar state of the next step, as in `step`
+    auto advance = [&]() {
+        if (PAR == 0 && pf + 1 < n_phases) {               // K pointer of the next phase to fetch
+            wk.kptr += (uint64_t)a.k_stride_head * 2u;
+            if (__builtin_expect(++wk.k.kv == a.n_kv_heads, 0)) {
+                wk.k.kv = 0;
+                ++wk.k.layer;
+                wk.kptr = reinterpret_cast<const char *>(kp.p[wk.k.layer]) + wave_off;
+            }
+        }
+        if (PAR == 1) {
+            phase_advance(wk.c, pc + 1, n_phases, a.n_kv_heads);
+            if (pd + 1 > 0 && pd + 1 < n_phases) {
+                wk.dfirst += kBlocks;
+                if (wk.dfirst >= a.n_wg) wk.dfirst -= a.n_wg;
+            }
+            const int blk = w - wk.dfirst;
+            wk.duty_blk = blk < 0 ? blk + a.n_wg : blk;
+            if (pd + 1 < 0 || pd + 1 >= n_phases || wk.duty_blk >= kBlocks) wk.duty_blk = -1;
+        }
+    };
 
     // ---- top ----
     const bool publishes = PAR == 0 && wave == kPubWave && pd >= 0 && pd < n_phases;
@@ -1391,6 +1424,7 @@ __device__ __forceinline__ void step_late(const FusedArgs &a, const LayerPtrs &k
         const f32x16 da = logits32(kf, qf);
         lift_sub(lc, MP::slot(wave, PAR, 1), kf);
         const f32x16 db = logits32(kf, qf);
+        advance();
         fold_logits<true>(da, m, l, a.c, lo0, hi0, hf);
         k_issue<2>(k1, voff, 0);
         __builtin_amdgcn_sched_barrier(0);
@@ -1398,6 +1432,7 @@ __device__ __forceinline__ void step_late(const FusedArgs &a, const LayerPtrs &k
         store_row_stats(wstats_ad, m, l, a.c, hf);
         k_issue<2>(k1, voff, 2);
     } else {
+        advance();
         k_issue<kSubInstr>(k0, voff, 0);
         k_issue<kSubInstr>(k1, voff, 0);
     }
@@ -1419,7 +1454,7 @@ __device__ __forceinline__ void step_late(const FusedArgs &a, const LayerPtrs &k
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc.mx[s2][0][e] = max3(max3(d[e], d[4 + e], d[8 + e]), d[12 + e], acc.mx[s2][0][e]);
         }
-        if (wk.c.kv == a.n_kv_heads - 1 && (a.layer_agg == SP_LAYER_MEAN || wk.c.layer == a.n_layers - 1)) close_layer<1, kNS>(acc, a.c);
+        if (c_now.kv == a.n_kv_heads - 1 && (a.layer_agg == SP_LAYER_MEAN || c_now.layer == a.n_layers - 1)) close_layer<1, kNS>(acc, a.c);
         __builtin_amdgcn_sched_barrier(0);
     }
     lift_tile(lc, MP::slot(wave, PAR, 0), ring.kf[SLOT]);
@@ -1427,21 +1462,6 @@ __device__ __forceinline__ void step_late(const FusedArgs &a, const LayerPtrs &k
         stage_duty_rows<kWaveRows, false>(lds0 + MP::kXduty + duty_half * 4096, a.part + (size_t)(pd % kSlots) * a.n_wg * MP::kRows, MP::kRows,
                                           a.n_wg, duty_blk * kDutyRows + duty_half * kWaveRows, lane);
 
-    // ---- walk on ----
-    if (PAR == 0 && pf + 1 < n_phases) {               // K pointer of the next phase to fetch
-        if (++wk.k.kv == a.n_kv_heads) {
-            wk.k.kv = 0;
-            ++wk.k.layer;
-            wk.kptr = reinterpret_cast<const char *>(kp.p[wk.k.layer]) + wave_off;
-        } else {
-            wk.kptr += (uint64_t)a.k_stride_head * 2u;
-        }
-    }
-    if (PAR == 1) phase_advance(wk.c, pc + 1, n_phases, a.n_kv_heads);
-    if (PAR == 1 && pd + 1 > 0 && pd + 1 < n_phases) {
-        wk.dfirst += kBlocks;
-        if (wk.dfirst >= a.n_wg) wk.dfirst -= a.n_wg;
-    }
     // Q(s+1): K(s+1) was requested behind it, and on the duty waves their rows
     if (PAR == 0 && duty_wave) vm_wait<2 * kSubInstr + 4>();
     else vm_wait<2 * kSubInstr>();
@@ -1660,6 +1680,7 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     wk.c.layer += layer0;
     wk.slot0 = 0;
     wk.dfirst = 0;
+    wk.duty_blk = -1;
     if (!EXTRA) { a.p_idx = 0; a.n_gp = 1; }
 
     // The body is unrolled four times so that the fragment ring slot (s % 4) and the buffer parity
