@@ -533,8 +533,9 @@ struct Acc {
 };
 
 // ---- probability pass of one phase from the fragment ring; tile loads are issued between the MFMA steps ----
-// Of the four loads of sub-tile 0 two are issued right after the barrier and two between the MFMA steps of
-// the probability pass (8-bit keys: two loads a sub-tile, one and one).
+// The four loads of sub-tile 0 (8-bit keys: two) are issued between the MFMA steps of the probability pass. With half of
+// them right after the barrier, where every wave also requests its slices of Q, eight waves stood behind each other at
+// the unit's memory pipe: sixteen prompts 1017 -> 1002 us.
 
 // F8: logits are in units of the phase's key scale `ks`; a phase's head maximum is brought to common
 // units before it meets other phases'. One tile load instead of two (half the bytes per sub-tile).
@@ -544,7 +545,7 @@ __device__ __forceinline__ void prob_pass(const bf16x8 (&kf)[kNS][kKS], const La
 {
     static_assert(NB * GB == 1 || NB * GB == 2, "one load per row block, or one per step");
     using MP = Map<W && NB * GB == 2>;
-    constexpr int kMid = F8 ? 1 : 2;
+    constexpr int kHalf = F8 ? 1 : 2;
     if constexpr (W) {
         // head_dim 128: one chain of eight MFMA steps over both halves of the 32 keys' rows
         static_assert(NB == 1, "one block of lookahead rows");
@@ -561,7 +562,7 @@ __device__ __forceinline__ void prob_pass(const bf16x8 (&kf)[kNS][kKS], const La
             }
 #pragma unroll
             for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q0[t], kf[0][t], d, 0, 0, 0);
-            if (GB == 1) k_issue<1>(ki, voff, kMid);
+            if (GB == 1) k_issue<kHalf>(ki, voff, 0);
 #pragma unroll
             for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q1[t], kf[1][t], d, 0, 0, 0);
 #pragma unroll
@@ -569,7 +570,7 @@ __device__ __forceinline__ void prob_pass(const bf16x8 (&kf)[kNS][kKS], const La
                 if (F8) acc.mx[0][0][e] = fmaxf(acc.mx[0][0][e], fmaxf(max3(d[e], d[4 + e], d[8 + e]), d[12 + e]) * ks);
                 else acc.mx[0][0][e] = max3(max3(d[e], d[4 + e], d[8 + e]), d[12 + e], acc.mx[0][0][e]);
             }
-            if (GB == 1 && !F8) k_issue<1>(ki, voff, kMid + 1);
+            if (GB == 1) k_issue<kHalf>(ki, voff, kHalf);
         }
         __builtin_amdgcn_sched_barrier(0);
         return;
@@ -594,9 +595,8 @@ __device__ __forceinline__ void prob_pass(const bf16x8 (&kf)[kNS][kKS], const La
                     if (F8) acc.mx[s][nb][e] = fmaxf(acc.mx[s][nb][e], fmaxf(max3(d[e], d[4 + e], d[8 + e]), d[12 + e]) * ks);
                     else acc.mx[s][nb][e] = max3(max3(d[e], d[4 + e], d[8 + e]), d[12 + e], acc.mx[s][nb][e]);
                 }
-                if (F8) { if (blk == 0 && s == 0) k_issue<1>(ki, voff, kMid); }
-                else if (NB * GB == 1) k_issue<1>(ki, voff, kMid + s);
-                else if (s == kNS - 1) k_issue<1>(ki, voff, kMid + blk);
+                if (NB * GB == 1) k_issue<kHalf>(ki, voff, kHalf * s);
+                else if (!F8 || blk == 0) k_issue<1>(ki, voff, kNS * blk + s);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -1066,7 +1066,6 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     Acc<NB> &acc = accs[PAIR ? PAR : 0];
     const int r_range = r_ranges[PAIR ? PAR : 0];
     constexpr int kSI = F8 ? kSubInstr / 2 : kSubInstr;     // tile-load instructions per sub-tile
-    constexpr int kMid = F8 ? 1 : 2;                        // of them, for sub-tile 0: issued right after the barrier
     constexpr uint32_t kElem = F8 ? 1u : 2u;                // bytes per key element
     const uint32_t stride_bytes = (uint32_t)a.k_stride_token * kElem;
     // 8-bit keys: the exponent's scale of a phase is c times that phase's key scale
@@ -1166,7 +1165,6 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         dma_u<MP::kQ1 + (1 - PAR) * MP::kQTileBytes>((uint32_t)lc.qoff[blk], q1src, dst);
         dma_u<MP::kQ2 + PAR * MP::kQTileBytes>((uint32_t)lc.qoff[blk], q2src, dst);
     }
-    if (!BIG) k_issue<kMid>(ki0, voff, 0);
 
     // ---- probability pass of phase pc; sub-tile 0 of K(s+1) ----
     {
@@ -1176,7 +1174,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
             if (wk.c.kv == a.n_kv_heads - 1 && (a.layer_agg == SP_LAYER_MEAN || wk.c.layer == (RANGES ? a.last_layer : a.n_layers - 1)))
                 close_layer<NB, W ? 1 : kNS>(acc, a.c);
         } else if (!BIG) {
-            k_issue<kSI - kMid>(ki0, voff, kMid);
+            k_issue<kSI>(ki0, voff, 0);
         }
     }
 
