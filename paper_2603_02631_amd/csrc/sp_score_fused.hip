@@ -1031,13 +1031,13 @@ struct Walk {
 //           the next statistics pass and of Q(s-3) for the next probability pass
 //   prob    probability pass of phase s-4 from ring slot s%4; loads of sub-tile 0 of K(s+1)
 //   lift    wait for sub-tile 1 of K(s); duty waves: combine the duty rows of phase s-2 and publish their
-//           normalisers (kDutyAtLift; otherwise at pre); lift K(s) into ring slot s%4
-//   stats   statistics pass of phase s; loads of sub-tile 1 of K(s+1); scalar state of step s+1 under the first MFMA steps;
-//           after the first of them the normaliser wave requests the normalisers of phase s-3
+//           normalisers (kDutyAtLift; otherwise at pre); normaliser wave: request of the normalisers of phase s-3
+//           (kEarlyLse; otherwise after the first step of stats); lift K(s) into ring slot s%4
+//   stats   statistics pass of phase s; loads of sub-tile 1 of K(s+1); scalar state of step s+1 under the first MFMA steps
 //   pre     wait for the Q slices (and the exchange data); normaliser wave: seeds of the probability pass of phase s-3
 //   barrier
 // Vector-memory operations per wave and step, oldest first: [publish store] [8 duty loads] [Q] [Q]
-// 4 K loads (prob), [normaliser load], 4 K loads (stats); the bracketed ones exist on some waves or
+// 4 K loads (prob), [normaliser load], 4 K loads (stats; kEarlyLse false: it comes between them); the bracketed ones exist on some waves or
 // in some steps only, so every wait counts only operations that are certainly issued behind the
 // ones it needs.
 // KIND (see there): the plain variant carries none of the others' code or registers.
@@ -1099,6 +1099,12 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     // prompts 1119 -> 1025. With two blocks the pass itself bounds the step: 128K tokens and 16 lookahead rows
     // 494 (one wave, end), 494 (one wave, here), 492 (two, end), 495 (two, here); 8-bit keys 465, 464, 470, 469.
     constexpr bool kTwoBlocks = NB * GB == 2;
+    // When the normaliser wave requests the normalisers of phase s-3. After the first MFMA step of the statistics pass it
+    // waits for them at the end of a short step (500 to 1100 cycles, everybody else for it); at the top of the step they
+    // are often not out yet, and every miss is a trip of its own. Before the lift, against the former: 24 short prompts
+    // 329 -> 293 us, 12007 tokens 83.7 -> 79.5, 32K tokens of head_dim 128 326.3 -> 321.5, sixteen prompts 1002 -> 997; at the
+    // top 291, 79.8, 349 and 1018. With two blocks the pass is long enough: 20001 tokens 145 -> 148.
+    constexpr bool kEarlyLse = !PAIR && !kTwoBlocks;
     constexpr bool kDutyAtLift = !PAIR && (!kTwoBlocks || F8);
     constexpr int kDutyWaves = kTwoBlocks && F8 ? 1 : 2, kWaveRows = kDutyRows / kDutyWaves;
     // the duty of this wave: kWaveRows rows of the block from duty_row on
@@ -1194,9 +1200,10 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         // requests after the first MFMA step: the normalisers; PAIR: also the duty rows, published at the start of
         // this very step (their normalisers are due at the next one's end)
         auto late = [&]() {
-            stage_exchange_rows(lds0 + MP::kXlse, lse_row, look_row, a.rows_pad, lane);
+            if (!kEarlyLse) stage_exchange_rows(lds0 + MP::kXlse, lse_row, look_row, a.rows_pad, lane);
             if (PAIR && PAR == 0) request_duty();
         };
+        if (kEarlyLse) stage_exchange_rows(lds0 + MP::kXlse, lse_row, look_row, a.rows_pad, lane);
         // Scalar state of the next step. A chain of some thirty scalar instructions: at the end of the step it took 400 to
         // 500 cycles of the waves that everybody waits for; here it runs while the first MFMA steps are under way (whole
         // passes: 8192 tokens 56.4 -> 55.5 us, paged 50021 tokens 205 -> 201.5, 20001 tokens 146 -> 143).
@@ -1238,7 +1245,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     }
 
     // ---- pre-barrier: exchange data in, seeds out ----
-    if ((wave == kLseWave && !(RANGES && direct && a.look == nullptr)) || (PAIR && PAR == 0 && duty_wave)) vm_wait<kLoadsBehindLse<NB * GB, F8, BIG>>();
+    if ((wave == kLseWave && !(RANGES && direct && a.look == nullptr)) || (PAIR && PAR == 0 && duty_wave)) vm_wait<kEarlyLse ? kSI : kLoadsBehindLse<NB * GB, F8, BIG>>();
     else vm_wait<2 * kSI>();
     if (duty_wave) {
         if (!kDutyAtLift) combine_duty();
