@@ -1768,9 +1768,11 @@ void set_giveup(uint32_t spin_max, int32_t force_miss)
     g_force_miss.store(force_miss, std::memory_order_relaxed);
 }
 
+size_t exchange_words(int rows_pad, int n_wg, int n_entries) { return (size_t)kSlots * rows_pad * (n_wg + n_entries); }
+
 size_t workspace_bytes(int rows_pad, int n_wg, int n_prompts)
 {
-    return sp::align_up(sizeof(uint64_t) * ((size_t)kSlots * rows_pad * n_wg + (size_t)kSlots * rows_pad * n_prompts), 256);
+    return sp::align_up(sizeof(uint64_t) * exchange_words(rows_pad, n_wg, n_prompts), 256);
 }
 
 bool fits_one_per_cu()
@@ -1781,7 +1783,7 @@ bool fits_one_per_cu()
     return n1 >= 1 && n2 >= 1;
 }
 
-sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool shared, bool clear_status, void *ws,
+sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool shared, Clear clear, void *ws,
                  uint32_t *status_word, hipStream_t st)
 {
     GroupTable gt;
@@ -1815,19 +1817,20 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
             return sp::fail(SP_ERR_INVALID_ARG, "fused score kernel: %d entries of %d rows share %d workgroups", gt.n, a.rows_pad, a.n_wg);
     }
     uint64_t *base = static_cast<uint64_t *>(ws);
-    const size_t n_part = (size_t)kSlots * a.rows_pad * a.n_wg, n_lse = (size_t)kSlots * a.rows_pad * (gt.n > 0 ? gt.n : 1);
     a.part = base;
-    a.lse = base + n_part;
+    a.lse = base + exchange_words(a.rows_pad, a.n_wg, 0);
     a.err = status_word;
     a.spin_max = std::min(a.spin_max, g_spin_max.load(std::memory_order_relaxed));
     const int32_t miss = g_force_miss.load(std::memory_order_relaxed);
     a.force_miss = miss == 1 || (miss == 2 && gt.n == 0);
     for (int i = 0; i < gt.n && miss >= 2; ++i)
         a.force_miss |= gt.prompt[i] == miss - 2;
-    const size_t n_clear = n_part + n_lse;
-    hipLaunchKernelGGL(sp_fused_clear_kernel, dim3((unsigned)((n_clear + 255) / 256 > 1024 ? 1024 : (n_clear + 255) / 256)),
-                       dim3(256), 0, st, base, n_clear, clear_status ? status_word : (uint32_t *)nullptr);
-    SP_HIP_CHECK(hipGetLastError());
+    if (clear != Clear::kDone) {
+        const size_t n_clear = exchange_words(a.rows_pad, a.n_wg, gt.n > 0 ? gt.n : 1);
+        hipLaunchKernelGGL(sp_fused_clear_kernel, dim3((unsigned)((n_clear + 255) / 256 > 1024 ? 1024 : (n_clear + 255) / 256)),
+                           dim3(256), 0, st, base, n_clear, clear == Clear::kAll ? status_word : (uint32_t *)nullptr);
+        SP_HIP_CHECK(hipGetLastError());
+    }
     // Every workgroup must be resident for the exchange to make progress: one workgroup fits per
     // compute unit (LDS), so the grid may not exceed the number of compute units. All waits in the
     // kernel are bounded; should residency fail (the device shared with other work), the call ends

@@ -65,7 +65,13 @@ struct FusedArgs {
     float c, inv_c, out_scale;
 };
 
+// 8-byte words of the exchange area of a launch of n_wg workgroups and n_entries entries (one prompt: 1).
+size_t exchange_words(int rows_pad, int n_wg, int n_entries);
 size_t workspace_bytes(int rows_pad, int n_wg, int n_prompts);
+
+// What the launch has to clear first: the exchange area and the status word (the first launch of a call), the area
+// only, or nothing, when an earlier launch on the stream has cleared both.
+enum class Clear { kAll, kExchange, kDone };
 
 // Entries of fewer workgroups than duty blocks exchange directly: every workgroup combines all partials of
 // its entry by itself. Only those: at 16 or 32 workgroups an entry the extra loads (8 KB a workgroup and phase
@@ -76,13 +82,12 @@ constexpr int direct_max(int rows_pad) { return rows_pad / kDutyRows - 1; }
 // True when the device can hold one workgroup of the fused kernel per compute unit.
 bool fits_one_per_cu();
 
-// Enqueues the clear kernel and the fused kernel. `ws` must hold workspace_bytes(); `status_word`
-// (device) is cleared first and raised if the call gives up, after at most `a.spin_max` polls in a wait.
-// `group` (or null for one prompt) describes the entries of the launch; the status word is cleared only
-// when clear_status is set (the first launch of a call).
+// Enqueues the clear kernel, as far as `clear` asks for it, and the fused kernel. `ws` must hold workspace_bytes();
+// `status_word` (device) is raised if the call gives up, after at most `a.spin_max` polls in a wait.
+// `group` (or null for one prompt) describes the entries of the launch.
 // `shared`: the duties rotate over all workgroups of the launch (whole prompts of at least a tile only, at
 // least as many workgroups as duty blocks); otherwise every entry keeps to itself.
-sp_status launch(FusedArgs a, const sp_dev::LayerPtrs &kp, const GroupTable *group, bool shared, bool clear_status, void *ws,
+sp_status launch(FusedArgs a, const sp_dev::LayerPtrs &kp, const GroupTable *group, bool shared, Clear clear, void *ws,
                  uint32_t *status_word, hipStream_t st);
 
 // Polls (about 30 ms) after which a launch gives up that a later launch can stand in for: early, so that it frees its
