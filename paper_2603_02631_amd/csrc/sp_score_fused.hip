@@ -722,7 +722,7 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
         f32x16 d = logits32(kf[0], q0);
 #pragma unroll
         for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][t], q1[t], d, 0, 0, 0);
-        advance();
+        if (NBLK == 1) advance();
         k_issue<NBLK == 2 ? 2 : kPerStep>(NBLK == 2 ? ki0 : ki, voff, 0);
         late();
         __builtin_amdgcn_sched_barrier(0);
@@ -743,6 +743,7 @@ __device__ __forceinline__ void stats_pass(float c, bf16x8 (&kf)[kNS][kKS], cons
             fold_logits<true>(d1, m, l, c, lo0, hi0, hf);
             store_row_stats(wstats_ad + 256, m, l, c, hf);
             k_issue<2>(ki, voff, 2);
+            advance();          // 15503 tokens: 119.2 us, up there 119.9; 20001: 146.3 and 146.2
         } else {
             fold_logits<true>(d, m, l, c, lo0, hi0, hf);
             store_row_stats(wstats_ad, m, l, c, hf);
@@ -1206,7 +1207,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
         if (kEarlyLse) stage_exchange_rows(lds0 + MP::kXlse, lse_row, look_row, a.rows_pad, lane);
         // Scalar state of the next step. A chain of some thirty scalar instructions: at the end of the step it took 400 to
         // 500 cycles of the waves that everybody waits for; here it runs while the first MFMA steps are under way (whole
-        // passes: 8192 tokens 56.4 -> 55.5 us, paged 50021 tokens 205 -> 201.5, 20001 tokens 146 -> 143).
+        // passes: 8192 tokens 56.4 -> 55.5 us, paged 50021 tokens 205 -> 201.5; BIG: at the end of the pass).
         const int slot0 = wk.slot0;
         auto advance = [&]() {
             if (PAIR ? PAR == 0 && pf + 1 < n_phases : s + 2 < n_phases) {               // K pointer of the next phase to fetch
