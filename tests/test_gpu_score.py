@@ -629,6 +629,43 @@ def test_score_with_lookahead_keys_matches_oracle(shape):
     assert_scores_close(gpu_score(q, inp["k"], w.scale, 0), plain)
 
 
+@pytest.mark.parametrize("Lyr,H,Hkv,n_q,L,tiles,in_ranges", [
+    (2, 8, 2, 16, 33000, 1, False),         # all layers in one launch entry, fewer threads than words to clear
+    (16, 32, 8, 8, 6200, 1, True),          # layer ranges: the area lies elsewhere
+    (2, 4, 1, 8, 140001, 2, False),         # two tiles a workgroup
+])
+def test_lookahead_call_on_a_workspace_that_holds_an_earlier_call(Lyr, H, Hkv, n_q, L, tiles, in_ranges):
+    """What an earlier call exchanged is well-formed data of the same phases: a call that finds any of it takes wrong
+    normalisers. Same bits as on a fresh workspace (the reductions have a fixed order)."""
+    import torch
+    import paper_2603_02631_amd as sp
+    from gpu_util import DEV, make_desc, score_path, workspace
+    say(f"[look-stale] Lyr={Lyr} H={H} Hkv={Hkv} n_q={n_q} L={L}")
+    desc = make_desc(Lyr, H, Hkv, 64, n_q, 0.125, 0, "HND", L)
+    g = torch.Generator(device=DEV).manual_seed(L)
+
+    def inputs(spread):
+        make = lambda *shape: torch.randn(shape, device=DEV, generator=g).mul_(spread).to(torch.bfloat16)
+        return make(Lyr, H, n_q, 64), [make(Hkv, L, 64) for _ in range(Lyr)], make(Lyr, Hkv, n_q, 64)
+
+    def call(ws, q, k, kl):
+        scores = torch.full((L,), float("nan"), device=DEV)
+        sp.sp_score_look(desc, q, k, L, kl, 1, scores, ws)
+        torch.cuda.synchronize()
+        return scores.cpu()
+
+    first, second = inputs(1.5), inputs(1.0)
+    size = sp.sp_score_workspace(desc, L, 1)
+    used = workspace(size)
+    stale = call(used, *first)
+    got = call(used, *second)
+    path = score_path()
+    assert path[0] == tiles and (path[1] > 1) == in_ranges, path
+    want = call(workspace(size), *second)
+    assert torch.isfinite(want).all() and not torch.equal(stale, want)
+    assert torch.equal(got, want)
+
+
 PAGED_SHAPES = [
     # name, Lyr, H, Hkv, d, n_q, L, page_tokens, layout
     ("paged_general_d64", 3, 8, 2, 64, 16, 1500, 512, "HND"),
