@@ -350,8 +350,9 @@ sp_status sp_select_budget(const float *scores_dev, int64_t L, int32_t pool_w,
  * must be readable device memory) and do not use what they hold.
  *  - tspans_dev[max_spans][2]: kept target tokens as maximal ranges
  *    [begin, end), ascending, disjoint and non-adjacent (ranges that overlap or
- *    touch are merged); *n_tspans_dev of them are written (entries behind them, as
- *    many as there are spans, may hold intermediate values);
+ *    touch are merged); *n_tspans_dev of them are written (with max_spans > 1024
+ *    or M >= 258048, entries behind them, as many as there are spans, may hold
+ *    intermediate values);
  *  - keep_mask_dev: optional uint8[M], 1 for kept target tokens (may be NULL);
  *  - *n_kept_dev: number of kept target tokens.
  * Requires L >= 1, M >= 1, 1 <= max_spans <= 2^24.

@@ -11,7 +11,7 @@
 // so ranges that overlap or touch are merged with an exclusive running maximum
 // of the range ends and a prefix sum of "starts a new range" flags.
 //
-// Up to 1024 spans (the usual case: a few hundred kept chunks) take ONE launch,
+// Up to 1024 spans (the usual case: a few hundred kept chunks) of fewer than 258048 target tokens take ONE launch,
 // sp_project_one_kernel: workgroup 0 finds and merges the ranges, the other
 // workgroups write the mask, each for itself and straight from the spans:
 //   workgroup 0   stages a coarse index of the target offsets (every stride-th
@@ -23,8 +23,7 @@
 //   mask groups   stage the spans' character intervals in LDS; since they are
 //                 sorted, token [ts, te) is kept iff the first span that ends
 //                 after ts begins before te: one LDS binary search per token.
-// Long texts take two launches: the chain of workgroup 0 above costs more than a second launch, so its searches go to
-// the mask groups, which look at every token and its neighbourhood anyway:
+// More spans or tokens take two launches, which leave raw ranges in tspans between them:
 //   sp_project_mark_kernel   one thread per target token: mask, and the first tokens of the spans that begin or end in it;
 //   sp_project_spans_kernel  one workgroup: scans, merged target ranges, their count and the kept-token total.
 // More spans than fit LDS take three:
@@ -429,11 +428,6 @@ __global__ __launch_bounds__(kOneThreads) void sp_project_one_kernel(
 constexpr int kMarkThreads = 1024;
 constexpr int kMarkSpans = 4096;             // spans whose character intervals fit the LDS of two workgroups a unit (64 KB)
 constexpr int kMarkPerThread = 2;
-// Target tokens from which two launches are faster than one, whose workgroup 0 stages more of the text the longer it is
-// (tokens / spans: one launch and two, us: 9400 / 40 8.4 and 9.1, 18000 / 80 9.0 and 9.5, 23000 / 107 9.9 and 9.6,
-// 57000 / 197 13.9 and 10.1, 57000 / 383 17.9 and 11.0, 150000 / 182 14.6 and 9.9; three launches, 300000 / 181 12.4 and 9.9).
-constexpr int64_t kMarkLine = 22 * 1024;
-
 // Target token [ts, te) is kept iff the first span j that ends after ts begins before te. Raw range of span s, from
 // the token that its interval [cs, ce) begins or ends in (offsets do not decrease, so that is one token):
 //   begin: t if ts <= cs < te (t = 0: cs < te), M if cs >= te of the last token
@@ -540,16 +534,6 @@ extern "C" sp_status sp_project(const int64_t *draft_off_dev, int64_t L, const i
     if (max_spans < 1 || max_spans > (1 << 24))
         return sp::fail(SP_ERR_INVALID_ARG, "max_spans = %d outside 1..2^24", max_spans);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    if (max_spans <= kMarkSpans && (M >= kMarkLine || max_spans > kOneSpans)) {
-        hipLaunchKernelGGL(sp_project_mark_kernel, dim3((unsigned)sp::ceil_div(M, (int64_t)kMarkThreads * kMarkPerThread)), dim3(kMarkThreads),
-                           sizeof(int64_t) * 2 * (size_t)max_spans, st, draft_off_dev, L, target_off_dev, M, spans_dev, n_spans_dev,
-                           (int)max_spans, tspans_dev, keep_mask_dev);
-        SP_HIP_CHECK(hipGetLastError());
-        hipLaunchKernelGGL(sp_project_spans_kernel, dim3(1), dim3(kSpanThreads), 0, st, n_spans_dev, (int)max_spans, tspans_dev,
-                           n_tspans_dev, n_kept_dev);
-        SP_HIP_CHECK(hipGetLastError());
-        return SP_OK;
-    }
     // one launch when the spans fit its LDS and one stride of the coarse index fits a wave-wide probe
     const int64_t stride = M / kCoarse + 1;          // ceil((M + 1) / kCoarse)
     if (max_spans <= kOneSpans && stride <= 63) {
@@ -558,6 +542,16 @@ extern "C" sp_status sp_project(const int64_t *draft_off_dev, int64_t L, const i
         hipLaunchKernelGGL(sp_project_one_kernel, dim3((unsigned)(1 + mask_groups)), dim3(kOneThreads), 0, st, draft_off_dev, L,
                            target_off_dev, (int)M, spans_dev, n_spans_dev, (int)max_spans, (int)stride, n_coarse, tspans_dev,
                            n_tspans_dev, n_kept_dev, keep_mask_dev);
+        SP_HIP_CHECK(hipGetLastError());
+        return SP_OK;
+    }
+    if (max_spans <= kMarkSpans) {
+        hipLaunchKernelGGL(sp_project_mark_kernel, dim3((unsigned)sp::ceil_div(M, (int64_t)kMarkThreads * kMarkPerThread)), dim3(kMarkThreads),
+                           sizeof(int64_t) * 2 * (size_t)max_spans, st, draft_off_dev, L, target_off_dev, M, spans_dev, n_spans_dev,
+                           (int)max_spans, tspans_dev, keep_mask_dev);
+        SP_HIP_CHECK(hipGetLastError());
+        hipLaunchKernelGGL(sp_project_spans_kernel, dim3(1), dim3(kSpanThreads), 0, st, n_spans_dev, (int)max_spans, tspans_dev,
+                           n_tspans_dev, n_kept_dev);
         SP_HIP_CHECK(hipGetLastError());
         return SP_OK;
     }

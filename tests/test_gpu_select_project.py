@@ -206,14 +206,9 @@ def test_project_long_prompt_coarse_index_strides():
         check_project(doff, toff, np.array([[0, 1], [L - 1, L]], dtype=np.int64))   # first and last token
 
 
-@pytest.mark.parametrize("tokens", [22 * 1024 - 1, 22 * 1024, 24 * 1024 + 1])
-def test_project_around_the_line_to_two_launches(tokens):
-    """One launch, two (a mark per target token) and three (more spans than the mark kernel's LDS holds) on the same
-    text: zero-length tokens on both sides, spans without characters, target tokens that hold several spans, spans at
-    both ends of the text."""
-    from gpu_util import gpu_project
-    say(f"[project] M={tokens}")
-    rng = np.random.default_rng(tokens)
+def ragged_text(rng, tokens):
+    """(draft offsets, target offsets, spans) of a text with zero-length tokens on both sides, spans without characters,
+    target tokens that hold several spans, spans at both ends of the text."""
     lens = rng.integers(0, 4, size=tokens)
     lens[rng.choice(tokens, size=40, replace=False)] = 300          # long target tokens
     lens[:2], lens[-2:] = 0, 0
@@ -224,6 +219,16 @@ def test_project_around_the_line_to_two_launches(tokens):
     L = doff.size - 1
     pts = np.sort(rng.choice(np.arange(1, L), size=1400, replace=False)).reshape(-1, 2)
     spans = np.concatenate([[[0, 1]], pts[pts[:, 0] > 1], [[L - 1, L]]]).astype(np.int64)
+    return doff, toff, spans
+
+
+@pytest.mark.parametrize("tokens", [22 * 1024, 63 * 4096 - 1, 63 * 4096, 63 * 4096 + 4097])
+def test_project_around_the_line_to_two_launches(tokens):
+    """One launch (up to 1024 spans of fewer than 63 * 4096 target tokens), two, and three (more spans than the mask
+    workgroups' LDS holds) on the same text."""
+    from gpu_util import gpu_project
+    say(f"[project] M={tokens}")
+    doff, toff, spans = ragged_text(np.random.default_rng(tokens), tokens)
     for sel in (spans, spans[::7], spans[:1], spans[-1:]):
         want = oracle.project(doff, toff, sel)
         for cap in (sel.shape[0], 1024, 1025, 4096, 4097):
@@ -231,6 +236,30 @@ def test_project_around_the_line_to_two_launches(tokens):
             np.testing.assert_array_equal(ts, want[0])
             np.testing.assert_array_equal(mask, want[1])
             assert n == want[2]
+
+
+@pytest.mark.parametrize("tokens", [22 * 1024, 100003, 63 * 4096 - 1])
+@pytest.mark.parametrize("want_mask", [True, False])
+def test_project_leaves_the_entries_behind_its_ranges_alone(tokens, want_mask):
+    """Up to 1024 spans of fewer than 258048 target tokens: entries of tspans behind the ranges keep what they held."""
+    import torch
+    import paper_2603_02631_amd as sp
+    from gpu_util import DEV
+    say(f"[project] entries behind the ranges, M={tokens}")
+    doff, toff, spans = ragged_text(np.random.default_rng(tokens + 1), tokens)
+    o_ts = oracle.project(doff, toff, spans)[0]
+    assert o_ts.shape[0] < spans.shape[0] <= 1024           # some spans share a range
+    dd, td, sd = (torch.from_numpy(a).to(DEV) for a in (doff, toff, spans))
+    tsp = torch.full((spans.shape[0], 2), -77, dtype=torch.int64, device=DEV)
+    n_sp = torch.tensor([spans.shape[0]], dtype=torch.int32, device=DEV)
+    n_t = torch.zeros(1, dtype=torch.int32, device=DEV)
+    n_kept = torch.zeros(1, dtype=torch.int64, device=DEV)
+    mask = torch.empty(tokens, dtype=torch.uint8, device=DEV) if want_mask else None
+    sp.sp_project(dd, doff.size - 1, td, tokens, sd, n_sp, spans.shape[0], tsp, n_t, mask, n_kept)
+    torch.cuda.synchronize()
+    n = int(n_t.item())
+    np.testing.assert_array_equal(tsp[:n].cpu().numpy(), o_ts)
+    assert (tsp[n:] == -77).all()
 
 
 def test_project_workload_char_models():
