@@ -23,12 +23,13 @@
 //   mask groups   stage the spans' character intervals in LDS; since they are
 //                 sorted, token [ts, te) is kept iff the first span that ends
 //                 after ts begins before te: one LDS binary search per token.
-// More spans or tokens take two launches, which leave raw ranges in tspans between them:
-//   sp_project_mark_kernel   one thread per target token: mask, and the first tokens of the spans that begin or end in it;
-//   sp_project_spans_kernel  one workgroup: scans, merged target ranges, their count and the kept-token total.
-// More spans than fit LDS take three:
-//   sp_project_search_kernel one wave per (span, end): 64-ary search of the
-//                            target offsets, three rounds of memory latency.
+// More spans or tokens take two launches and leave raw ranges in tspans between them:
+//   sp_project_mark_kernel   search groups: one wave per (span, end), a 64-ary search of the target
+//                            offsets, three rounds of memory latency; mask groups as above.
+//   sp_project_spans_kernel  one workgroup: scans, merged target ranges,
+//                            their count and the kept-token total.
+// Without a mask, and for more spans than the mask groups' LDS holds, the searches are a launch of their own:
+//   sp_project_search_kernel the searches of the mark kernel.
 //   sp_project_spans_kernel  as above.
 //   sp_project_mask_kernel   one thread per target token: binary search of the
 //                            merged ranges, writes the 0/1 keep mask.
@@ -68,23 +69,36 @@ __device__ __forceinline__ int64_t wave_search(const int64_t *a, int64_t n, int6
     return lo;
 }
 
-// Raw target range of every span: tspans[2s] = first t with target_off[t+1] > cs,
-// tspans[2s+1] = first t with target_off[t] >= ce (M if none).
+// Number of spans; character position of a draft token.
+__device__ __forceinline__ int span_count(const int32_t *n_spans_p, int max_spans)
+{
+    const int n = *n_spans_p;
+    return n > max_spans ? max_spans : (n < 0 ? 0 : n);
+}
+
+__device__ __forceinline__ int64_t draft_char(const int64_t *__restrict__ draft_off, int64_t L, int64_t tok)
+{
+    return draft_off[tok < 0 ? 0 : (tok > L ? L : tok)];
+}
+
+// Bound q = 2s (begin) or 2s + 1 (end) of the raw target range of span s, found by one wave: first t with
+// target_off[t+1] > cs, first t with target_off[t] >= ce (M if none).
+__device__ __forceinline__ int64_t raw_bound(const int64_t *__restrict__ draft_off, int64_t L, const int64_t *__restrict__ target_off,
+                                             int64_t M, const int64_t *__restrict__ spans, int q, int lane)
+{
+    const int64_t ch = draft_char(draft_off, L, spans[q]);
+    return (q & 1) == 0 ? wave_search<true>(target_off + 1, M, ch, lane) : wave_search<false>(target_off, M, ch, lane);
+}
+
 __global__ __launch_bounds__(kThreads) void sp_project_search_kernel(
     const int64_t *__restrict__ draft_off, int64_t L, const int64_t *__restrict__ target_off, int64_t M,
     const int64_t *__restrict__ spans, const int32_t *__restrict__ n_spans_p, int max_spans, int64_t *tspans)
 {
     const int lane = threadIdx.x & 63;
-    const int gw = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    const int s = gw >> 1, end = gw & 1;
-    int n_spans = *n_spans_p;
-    if (n_spans > max_spans) n_spans = max_spans;
-    if (s >= n_spans) return;
-    int64_t tok = spans[2 * s + end];
-    tok = tok < 0 ? 0 : (tok > L ? L : tok);
-    const int64_t ch = draft_off[tok];
-    const int64_t r = end == 0 ? wave_search<true>(target_off + 1, M, ch, lane) : wave_search<false>(target_off, M, ch, lane);
-    if (lane == 0) tspans[2 * s + end] = r;
+    const int q = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+    if (q >= 2 * span_count(n_spans_p, max_spans)) return;
+    const int64_t r = raw_bound(draft_off, L, target_off, M, spans, q, lane);
+    if (lane == 0) tspans[q] = r;
 }
 
 constexpr int kSpanThreads = 1024;
@@ -165,12 +179,6 @@ __device__ __forceinline__ void merge_spans_body(int n_spans, int max_spans, int
         for (int w = 0; w < kSpanWaves; ++w) t += sm.red[w];
         *n_kept = t;
     }
-}
-
-__device__ __forceinline__ int span_count(const int32_t *n_spans_p, int max_spans)
-{
-    const int n = *n_spans_p;
-    return n > max_spans ? max_spans : (n < 0 ? 0 : n);
 }
 
 __global__ __launch_bounds__(kSpanThreads) void sp_project_spans_kernel(const int32_t *__restrict__ n_spans_p, int max_spans,
@@ -426,21 +434,35 @@ __global__ __launch_bounds__(kOneThreads) void sp_project_one_kernel(
 // two launches
 // ---------------------------------------------------------------------------
 constexpr int kMarkThreads = 1024;
+constexpr int kMarkWaves = kMarkThreads / 64;
 constexpr int kMarkSpans = 4096;             // spans whose character intervals fit the LDS of two workgroups a unit (64 KB)
 constexpr int kMarkPerThread = 2;
-// Target token [ts, te) is kept iff the first span j that ends after ts begins before te. Raw range of span s, from
-// the token that its interval [cs, ce) begins or ends in (offsets do not decrease, so that is one token):
-//   begin: t if ts <= cs < te (t = 0: cs < te), M if cs >= te of the last token
-//   end:   t + 1 if ts < ce <= te (the last token: ts < ce), 0 if ce <= ts of token 0
-// Spans are sorted and disjoint, so those of a token are neighbours of j (one of them as a rule). Spans without
-// characters that sit on ts come before j.
-__device__ __forceinline__ void mark_body(const int64_t *__restrict__ draft_off, int64_t L, const int64_t *__restrict__ target_off,
-                                          int64_t M, const int64_t *__restrict__ spans, const int32_t *__restrict__ n_spans_p,
-                                          int max_spans, int64_t *__restrict__ tspans, uint8_t *__restrict__ mask)
+constexpr int kSearchGroups = 128;           // search workgroups: a wave for every (span, end) of up to 1024 spans
+
+// The first `search_groups` workgroups find the raw range of every span, a wave a search (as sp_project_search_kernel),
+// the others write the mask straight from the spans, as those of the single launch do. Bound by the search's chain of
+// round trips (count, span, character, three probes), beside which the mask is free. Neither looks at spans past the
+// count: a gather for all max_spans entries takes longer than waiting for the count on inputs that no cache holds.
+// Both launches, in a row / alone on inputs in no cache, us (tokens / spans / max_spans), against search, merge and mask
+// launches: 1500 / 8 / 2048 10.0 / 11.6 against 12.4 / 12.1, 149796 / 213 / 2048 9.9 / 12.3 against 12.5 / 14.4,
+// 149796 / 748 / 4096 10.6 / 13.9 against 14.4 / 18.8, 299593 / 427 / 427 10.0 / 12.8 against 13.1 / 17.1.
+__global__ __launch_bounds__(kMarkThreads) void sp_project_mark_kernel(
+    const int64_t *__restrict__ draft_off, int64_t L, const int64_t *__restrict__ target_off, int64_t M,
+    const int64_t *__restrict__ spans, const int32_t *__restrict__ n_spans_p, int max_spans, int search_groups,
+    int64_t *__restrict__ tspans, uint8_t *__restrict__ mask)
 {
     extern __shared__ int64_t mark_ch[];     // [2 * max_spans] character position of every (span, end)
     const int tid = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * (kMarkThreads * kMarkPerThread);
+    const int n = span_count(n_spans_p, max_spans);
+    if ((int)blockIdx.x < search_groups) {
+        const int lane = tid & 63;
+        for (int q = blockIdx.x * kMarkWaves + (tid >> 6); q < 2 * n; q += search_groups * kMarkWaves) {
+            const int64_t r = raw_bound(draft_off, L, target_off, M, spans, q, lane);
+            if (lane == 0) tspans[q] = r;
+        }
+        return;
+    }
+    const int64_t base = ((int64_t)blockIdx.x - search_groups) * (kMarkThreads * kMarkPerThread);
     int64_t ts[kMarkPerThread], te[kMarkPerThread];
 #pragma unroll
     for (int k = 0; k < kMarkPerThread; ++k) {
@@ -448,46 +470,19 @@ __device__ __forceinline__ void mark_body(const int64_t *__restrict__ draft_off,
         ts[k] = target_off[t < M ? t : M];
         te[k] = target_off[t < M ? t + 1 : M];
     }
-    // all max_spans entries are read, so that this does not wait for the count; those past it are not used
-    for (int i = tid; i < 2 * max_spans; i += kMarkThreads) {
-        int64_t tok = spans[i];
-        tok = tok < 0 ? 0 : (tok > L ? L : tok);
-        mark_ch[i] = draft_off[tok];
-    }
-    const int n = span_count(n_spans_p, max_spans);
+    for (int i = tid; i < 2 * n; i += kMarkThreads) mark_ch[i] = draft_char(draft_off, L, spans[i]);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kMarkPerThread; ++k) {
         const int64_t t = base + k * kMarkThreads + tid;
         if (t >= M) break;
-        const bool first = t == 0, last = t == M - 1;
         int j = 0, hi = n;                   // first span whose end lies after ts
         while (j < hi) {
             const int mid = j + ((hi - j) >> 1);
             if (mark_ch[2 * mid + 1] > ts[k]) hi = mid; else j = mid + 1;
         }
-        if (mask) mask[t] = j < n && mark_ch[2 * j] < te[k];
-        for (int s = j; s < n; ++s) {
-            const int64_t cs = mark_ch[2 * s], ce = mark_ch[2 * s + 1];
-            const bool begins = cs < te[k] && (first || cs >= ts[k]), ends = ce <= te[k] || last;
-            if (begins || (last && cs >= te[k])) tspans[2 * s] = begins ? t : M;
-            if (ends) tspans[2 * s + 1] = t + 1;
-            if (!last && !ends) break;       // later spans begin behind this one's end
-        }
-        for (int s = j - 1; s >= 0 && (first || mark_ch[2 * s] >= ts[k]); --s) {
-            if (mark_ch[2 * s] < te[k]) tspans[2 * s] = t;
-            else if (last) tspans[2 * s] = M;
-            if (first) tspans[2 * s + 1] = 0;
-        }
+        mask[t] = j < n && mark_ch[2 * j] < te[k];
     }
-}
-
-__global__ __launch_bounds__(kMarkThreads) void sp_project_mark_kernel(
-    const int64_t *__restrict__ draft_off, int64_t L, const int64_t *__restrict__ target_off, int64_t M,
-    const int64_t *__restrict__ spans, const int32_t *__restrict__ n_spans_p, int max_spans, int64_t *__restrict__ tspans,
-    uint8_t *__restrict__ mask)
-{
-    mark_body(draft_off, L, target_off, M, spans, n_spans_p, max_spans, tspans, mask);
 }
 
 // Ragged batch: prompt b = blockIdx.y. Its L_b + 1 draft offsets start at off[b] + b of the packed array,
@@ -545,10 +540,13 @@ extern "C" sp_status sp_project(const int64_t *draft_off_dev, int64_t L, const i
         SP_HIP_CHECK(hipGetLastError());
         return SP_OK;
     }
-    if (max_spans <= kMarkSpans) {
-        hipLaunchKernelGGL(sp_project_mark_kernel, dim3((unsigned)sp::ceil_div(M, (int64_t)kMarkThreads * kMarkPerThread)), dim3(kMarkThreads),
-                           sizeof(int64_t) * 2 * (size_t)max_spans, st, draft_off_dev, L, target_off_dev, M, spans_dev, n_spans_dev,
-                           (int)max_spans, tspans_dev, keep_mask_dev);
+    // two launches when the spans fit the LDS of the mask's workgroups; without a mask its search workgroups alone would be
+    // slower than the smaller ones below (alone, inputs in no cache: 149796 tokens, 200 of 2048 spans 12.5 us against 10.5)
+    if (max_spans <= kMarkSpans && keep_mask_dev) {
+        const int search_groups = std::min(kSearchGroups, (int)sp::ceil_div(2 * (int64_t)max_spans, (int64_t)kMarkWaves));
+        hipLaunchKernelGGL(sp_project_mark_kernel, dim3((unsigned)(search_groups + sp::ceil_div(M, (int64_t)kMarkThreads * kMarkPerThread))),
+                           dim3(kMarkThreads), sizeof(int64_t) * 2 * (size_t)max_spans, st, draft_off_dev, L, target_off_dev, M, spans_dev,
+                           n_spans_dev, (int)max_spans, search_groups, tspans_dev, keep_mask_dev);
         SP_HIP_CHECK(hipGetLastError());
         hipLaunchKernelGGL(sp_project_spans_kernel, dim3(1), dim3(kSpanThreads), 0, st, n_spans_dev, (int)max_spans, tspans_dev,
                            n_tspans_dev, n_kept_dev);
