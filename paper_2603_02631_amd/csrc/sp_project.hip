@@ -101,7 +101,9 @@ __global__ __launch_bounds__(kThreads) void sp_project_search_kernel(
     if (lane == 0) tspans[q] = r;
 }
 
-constexpr int kSpanThreads = 1024;
+// Spans a turn of the merge. Searches and merge without a mask / with one, alone on inputs in no cache, us (spans): 256
+// threads 9.9 (200) / 13.8 (748) / 31.2 (4000), 512 10.1 / 13.4 / 25.8, 1024 11.7 / 13.8 / 26.5.
+constexpr int kSpanThreads = 512;
 constexpr int kSpanWaves = kSpanThreads / 64;
 
 struct SpanSmem {
@@ -111,22 +113,23 @@ struct SpanSmem {
 };
 
 // Merges the raw ranges in tspans (see the file header) in place, kSpanThreads spans at a time.
-// Bound by its chain of round trips: one load of the ranges (not waiting for the count), two scans, one store.
-__device__ __forceinline__ void merge_spans_body(int n_spans, int max_spans, int64_t *tspans, int32_t *n_tspans, int64_t *n_kept)
+// Bound by its chain of round trips: the count, the ranges, two scans, one store. Loads of ranges that do not wait for the
+// count read entries that nothing has written: 0.2 to 0.5 us more on inputs in no cache, no less on others.
+__device__ __forceinline__ void merge_spans_body(int n_spans, int64_t *tspans, int32_t *n_tspans, int64_t *n_kept)
 {
     __shared__ SpanSmem sm;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int64_t carry_hi = -1;      // largest range end seen in earlier segments (-1: none)
     int64_t kept = 0;
     int carry_n = 0;            // merged ranges opened in earlier segments
-    for (int base = 0; base == 0 || base < n_spans; base += kSpanThreads) {
+    for (int base = 0; base < n_spans; base += kSpanThreads) {
         const int s = base + tid;
         int64_t lo = 0, hi = 0;
-        if (s < max_spans) {        // merged ranges are written back in place (an entry is overwritten only after
+        if (s < n_spans) {          // merged ranges are written back in place (an entry is overwritten only after
             lo = tspans[2 * s];     // its segment has been read: r <= s)
             hi = tspans[2 * s + 1];
         }
-        const bool nonempty = s < n_spans && lo < hi;
+        const bool nonempty = lo < hi;
         // exclusive running maximum of the ends of earlier non-empty ranges
         int64_t incl = nonempty ? hi : -1;
 #pragma unroll
@@ -184,7 +187,7 @@ __device__ __forceinline__ void merge_spans_body(int n_spans, int max_spans, int
 __global__ __launch_bounds__(kSpanThreads) void sp_project_spans_kernel(const int32_t *__restrict__ n_spans_p, int max_spans,
                                                                         int64_t *tspans, int32_t *n_tspans, int64_t *n_kept)
 {
-    merge_spans_body(span_count(n_spans_p, max_spans), max_spans, tspans, n_tspans, n_kept);
+    merge_spans_body(span_count(n_spans_p, max_spans), tspans, n_tspans, n_kept);
 }
 
 __global__ __launch_bounds__(kThreads) void sp_project_mask_kernel(const int64_t *__restrict__ tspans,
@@ -444,8 +447,8 @@ constexpr int kSearchGroups = 128;           // search workgroups: a wave for ev
 // round trips (count, span, character, three probes), beside which the mask is free. Neither looks at spans past the
 // count: a gather for all max_spans entries takes longer than waiting for the count on inputs that no cache holds.
 // Both launches, in a row / alone on inputs in no cache, us (tokens / spans / max_spans), against search, merge and mask
-// launches: 1500 / 8 / 2048 10.0 / 11.6 against 12.4 / 12.1, 149796 / 213 / 2048 9.9 / 12.3 against 12.5 / 14.4,
-// 149796 / 748 / 4096 10.6 / 13.9 against 14.4 / 18.8, 299593 / 427 / 427 10.0 / 12.8 against 13.1 / 17.1.
+// launches: 1500 / 8 / 2048 10.0 / 9.9 against 12.4 / 12.6, 149796 / 213 / 2048 10.0 / 10.3 against 12.7 / 14.4,
+// 149796 / 748 / 4096 10.1 / 13.3 against 14.4 / 18.7, 299593 / 427 / 427 10.7 / 11.6 against 13.8 / 17.4.
 __global__ __launch_bounds__(kMarkThreads) void sp_project_mark_kernel(
     const int64_t *__restrict__ draft_off, int64_t L, const int64_t *__restrict__ target_off, int64_t M,
     const int64_t *__restrict__ spans, const int32_t *__restrict__ n_spans_p, int max_spans, int search_groups,
@@ -540,8 +543,8 @@ extern "C" sp_status sp_project(const int64_t *draft_off_dev, int64_t L, const i
         SP_HIP_CHECK(hipGetLastError());
         return SP_OK;
     }
-    // two launches when the spans fit the LDS of the mask's workgroups; without a mask its search workgroups alone would be
-    // slower than the smaller ones below (alone, inputs in no cache: 149796 tokens, 200 of 2048 spans 12.5 us against 10.5)
+    // two launches when the spans fit the LDS of the mask's workgroups; without a mask the searches alone are two launches
+    // as well, in smaller workgroups (inputs in no cache, 149796 tokens, 200 of 2048 spans: 12.0 us, in these 12.5)
     if (max_spans <= kMarkSpans && keep_mask_dev) {
         const int search_groups = std::min(kSearchGroups, (int)sp::ceil_div(2 * (int64_t)max_spans, (int64_t)kMarkWaves));
         hipLaunchKernelGGL(sp_project_mark_kernel, dim3((unsigned)(search_groups + sp::ceil_div(M, (int64_t)kMarkThreads * kMarkPerThread))),

@@ -173,7 +173,7 @@ def test_project_many_spans_and_special_tokenisations():
     doff = offsets_from_lengths(rng.geometric(0.25, size=L))
     toff = split_same_text(rng, int(doff[-1]), 9)
     C = L // 32
-    sel = np.sort(rng.choice(C, size=C // 3, replace=False)).astype(np.int64)      # ~ 300 spans: > one scan segment
+    sel = np.sort(rng.choice(C, size=C // 3, replace=False)).astype(np.int64)      # ~ 300 spans
     spans = oracle.merge(sel, 32, L)
     assert spans.shape[0] > 256
     check_project(doff, toff, spans)
@@ -260,6 +260,45 @@ def test_project_leaves_the_entries_behind_its_ranges_alone(tokens, want_mask):
     n = int(n_t.item())
     np.testing.assert_array_equal(tsp[:n].cpu().numpy(), o_ts)
     assert (tsp[n:] == -77).all()
+
+
+@pytest.mark.parametrize("n", [512, 513, 1025, 2049, 4096, 5000])
+@pytest.mark.parametrize("kind", ["apart", "overlapping", "touching", "empty_segment", "one_range"])
+def test_project_merges_ranges_across_turns_of_512_spans(n, kind):
+    """The merge takes 512 spans a turn and carries its last range and its count to the next: ranges that overlap or touch
+    across a turn's edge, a turn of empty ranges only, one range over all turns. With a mask (searches beside it, a launch
+    of their own beyond 4096 spans) and without."""
+    from gpu_util import gpu_project
+    say(f"[project] merge turns n={n} {kind}")
+    # span i: ten draft tokens of one character from 40 i on; target tokens of five characters
+    at = 40 * np.arange(n, dtype=np.int64)
+    spans = np.stack([at, at + 10], axis=1)
+    lens = np.ones(40 * n, dtype=np.int64)
+    toff = np.arange(0, 40 * n + 1, 5, dtype=np.int64)
+    edges = np.arange(512, n, 512)
+    if kind == "overlapping":               # one target token holds the spans on both sides of an edge
+        for e in edges:
+            toff = toff[(toff <= 40 * (e - 1)) | (toff >= 40 * e + 10)]
+    elif kind == "touching":                # the span before an edge reaches up to the one behind it
+        spans[edges - 1, 1] = spans[edges, 0]
+    elif kind == "empty_segment":           # no characters, at a target token's edge
+        lo, hi = 40 * 512, 40 * min(n, 1024)
+        lens[lo:hi] = 0
+        toff = np.unique(np.minimum(toff, toff[-1] - (hi - lo))) if hi > lo else toff
+    elif kind == "one_range":
+        toff = np.array([0, 40 * n], dtype=np.int64)
+    doff = offsets_from_lengths(lens)
+    assert doff[-1] == toff[-1]
+    want = oracle.project(doff, toff, spans)
+    expect = {"apart": n, "overlapping": n - edges.size, "touching": n - edges.size,
+              "empty_segment": n - max(0, min(n, 1024) - 512), "one_range": 1}[kind]
+    assert want[0].shape[0] == expect
+    for cap, want_mask in ((n, True), (n, False), (max(n, 1025), True), (5000, True)):
+        ts, mask, kept = gpu_project(doff, toff, spans, max_spans=cap, want_mask=want_mask)
+        np.testing.assert_array_equal(ts, want[0])
+        if want_mask:
+            np.testing.assert_array_equal(mask, want[1])
+        assert kept == want[2]
 
 
 @pytest.mark.parametrize("where", ["in_the_last_token", "behind_the_last_token", "in_the_first_token"])
