@@ -1098,7 +1098,9 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     // nine steps of ten, and everybody waited 3000 cycles. Two waves before the statistics pass have them out in time.
     // Whole passes: 32K tokens of head_dim 128 366 -> 332 us, 128K tokens and 8 lookahead rows 465 -> 413, sixteen
     // prompts 1119 -> 1025. With two blocks the pass itself bounds the step: 128K tokens and 16 lookahead rows
-    // 494 (one wave, end), 494 (one wave, here), 492 (two, end), 495 (two, here); 8-bit keys 465, 464, 470, 469.
+    // 494 (one wave, end), 494 (one wave, here), 492 (two, end), 495 (two, here); 8-bit keys 465, 464, 470, 469. In layer
+    // ranges 8-bit keys and 16 lookahead rows are better off at the end: 65536 tokens 261 -> 257, 33000 204.5 -> 201.5
+    // (all layers in one range, 100000 tokens: 403 here, 414 at the end).
     constexpr bool kTwoBlocks = NB * GB == 2;
     // When the normaliser wave requests the normalisers of phase s-3. After the first MFMA step of the statistics pass it
     // waits for them at the end of a short step (500 to 1100 cycles, everybody else for it); at the top of the step they
@@ -1106,7 +1108,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     // 329 -> 293 us, 12007 tokens 83.7 -> 79.5, 32K tokens of head_dim 128 326.3 -> 321.5, sixteen prompts 1002 -> 997; at the
     // top 291, 79.8, 349 and 1018. With two blocks the pass is long enough: 20001 tokens 145 -> 148.
     constexpr bool kEarlyLse = !PAIR && !kTwoBlocks;
-    constexpr bool kDutyAtLift = !PAIR && (!kTwoBlocks || F8);
+    constexpr bool kDutyAtLift = !PAIR && (!kTwoBlocks || (F8 && !RANGES));
     constexpr int kDutyWaves = kTwoBlocks && F8 ? 1 : 2, kWaveRows = kDutyRows / kDutyWaves;
     // the duty of this wave: kWaveRows rows of the block from duty_row on
     const bool duty_wave = (wave == kDutyWave || (kDutyWaves == 2 && wave == kDutyWave + 2)) && duty_blk >= 0;
