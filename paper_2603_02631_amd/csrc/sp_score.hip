@@ -365,6 +365,7 @@ __global__ __launch_bounds__(kThreads) void sp_look_kernel(ScoreArgs a, const ui
 {
     if (status != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *status = 0u;
     for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < clear_n; i += (size_t)gridDim.x * kThreads) clear[i] = 0;
+    if ((int)blockIdx.x >= a.n_layers * a.n_kv_heads) return;      // launched to clear only
     __shared__ float logit[kMaxLookRows][17];                    // [padded row][key], odd stride: no bank conflicts down a row
     const int phase = blockIdx.x;
     const int layer = phase / a.n_kv_heads, kv = phase - layer * a.n_kv_heads;
@@ -1363,7 +1364,10 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     a.look = look;
     auto launch_look = [&](void *clear, size_t clear_n, uint32_t *status) -> sp_status {
         const auto kernel = p.D == 64 ? sp_look_kernel<64> : sp_look_kernel<128>;
-        hipLaunchKernelGGL(kernel, dim3(p.n_phases), dim3(kThreads), 0, st, a, static_cast<const uint16_t *>(opt.k_look),
+        // Workgroups beyond the phases clear only: with few phases the area, up to 1 MB, would be left to as few workgroups
+        // (one phase, 131072 tokens, 16 lookahead rows: 38.1 us a call against 23.9; 26.4 with a clear launch).
+        const int groups = std::max(p.n_phases, (int)std::min<size_t>(sp::ceil_div(clear_n, (size_t)kThreads), 256));
+        hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), 0, st, a, static_cast<const uint16_t *>(opt.k_look),
                            (int)opt.look_self, look, static_cast<uint64_t *>(clear), clear_n, status);
         SP_HIP_CHECK(hipGetLastError());
         return SP_OK;

@@ -630,7 +630,8 @@ def test_score_with_lookahead_keys_matches_oracle(shape):
 
 
 @pytest.mark.parametrize("Lyr,H,Hkv,n_q,L,tiles,in_ranges", [
-    (2, 8, 2, 16, 33000, 1, False),         # all layers in one launch entry, fewer threads than words to clear
+    (2, 8, 2, 16, 33000, 1, False),         # all layers in one launch entry, most workgroups only clear
+    (1, 4, 1, 16, 131072, 1, False),        # one phase, the largest area: more words than threads that clear
     (16, 32, 8, 8, 6200, 1, True),          # layer ranges: the area lies elsewhere
     (2, 4, 1, 8, 140001, 2, False),         # two tiles a workgroup
 ])
