@@ -1107,14 +1107,17 @@ sp_status launch_finish(const Plan &p, const ScoreArgs &a, const LayerPtrs &kp, 
 }
 
 // Whether the prob pass merges the tiles' statistics itself (`longest`: tokens of the longest prompt): a launch less
-// (3.5 us in a chain of launches, 2.5 us of the host) for up to 20 partials a thread and workgroup. Whole passes with the
-// merge kernel and without, 16 layers x 8 kv heads, 32 rows: 1000 tokens 40.9 / 37.3 us, 3000 48.5 / 46.3, 4500 (18 partials)
-// 53.7 / 51.9, 8-bit keys 6000 (24) 52.9 / 53.8; 64 rows: 2000 (16) 51.6 / 49.0, 4500 (36) 62.7 / 63.3; 2 layers x 2 kv
-// heads, 1024 tokens 30.3 / 26.7.
+// (3.5 us in a chain of launches, 2.5 us of the host) for up to 20 partials a thread of a workgroup on average, and up to 48
+// tiles, which one thread walks for its row. Whole passes with the merge kernel and without, 16 layers x 8 kv heads, 32
+// rows: 1000 tokens 40.9 / 37.3 us, 3000 48.5 / 46.3, 4500 (18 partials) 53.7 / 51.9, 8-bit keys 6000 (24) 52.9 / 53.8; 64
+// rows: 2000 (16) 51.6 / 49.0, 4500 (36) 62.7 / 63.3; 2 layers x 2 kv heads, 1024 tokens 30.3 / 26.7. Score calls of few
+// phases (fewer rows than threads): 2 x 2, 48 tiles 17.7 / 16.7, 80 19.7 / 19.9; 1 x 1, 64 rows, 48 15.2 / 14.5, 56 14.7 /
+// 15.0, 80 15.4 / 16.3; 2 x 1, head_dim 128, 48 18.8 / 17.2, 80 18.9 / 19.4.
 bool prob_merges(const Plan &p, const ScoreArgs &a, int64_t longest)
 {
     const int64_t rows = (int64_t)a.layers_per_split * a.n_kv_heads * p.rows_pad;        // of a workgroup, over all its phases
-    return p.lds_bytes + sizeof(float) * (size_t)(rows - p.rows_pad) <= kLdsBudget && rows * sp::ceil_div(longest, p.tile_keys) <= 20 * kThreads;
+    const int64_t tiles = sp::ceil_div(longest, p.tile_keys);
+    return p.lds_bytes + sizeof(float) * (size_t)(rows - p.rows_pad) <= kLdsBudget && tiles <= 48 && rows * tiles <= 20 * kThreads;
 }
 
 template <int D, int NS, bool FP8 = false>

@@ -58,14 +58,14 @@ def test_score_matches_oracle(shape, mode):
     assert_scores_close(got, want)
 
 
-@pytest.mark.parametrize("tokens", [8 * 256, 8 * 256 + 1, 80 * 256, 80 * 256 + 1])
+@pytest.mark.parametrize("tokens", [8 * 256, 8 * 256 + 1, 48 * 256, 48 * 256 + 1])
 @pytest.mark.parametrize("n_q", [8, 16])
 def test_score_around_the_merge_in_the_prob_pass(tokens, n_q):
     """Three-kernel path: eight partials a turn of the merge loop, and the last length the prob pass merges itself
-    (two phases of 32 rows a workgroup: 80 tiles; of 64 rows: 40) against the first that takes the merge kernel."""
+    (two phases of 32 rows a workgroup: 48 tiles; of 64 rows: 40) against the first that takes the merge kernel."""
     from gpu_util import assert_scores_close, gpu_score, score_path
     if n_q == 16 and tokens > 40 * 256:
-        tokens -= 40 * 256
+        tokens -= 8 * 256
     say(f"[score] merge n_q={n_q} L={tokens}")
     w = small_workload("merge", 2, 8, 2, 64, n_q, tokens, cfg_id=180, hh=(1, 200))
     inp = synth.make_score_inputs(w)
