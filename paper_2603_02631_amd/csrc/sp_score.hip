@@ -64,7 +64,7 @@ struct ScoreArgs {
     const int32_t *prompt_tiles;  // [B+1] first tile of each prompt (batch only)
     int64_t L;                // tokens of the call (single prompt: its length)
     float2 *part;             // [n_phases][n_tiles][rows_pad]
-    float *lse_neg;           // [B][n_phases][rows_pad]  (-lse in raw-logit units, permuted), or null: the prob pass merges
+    float *lse_neg;           // [B][n_phases][rows_pad]  (-lse in raw-logit units, permuted); not used where the prob pass merges
     float *scores;
     uint32_t *status;         // the call's status word (cleared here: this path cannot give up)
     const int32_t *block_table;   // paged keys (single prompt): token j lives in page block_table[j / page_tokens]
@@ -485,7 +485,9 @@ __device__ __forceinline__ void merge_rows(const ScoreArgs &a, const TileInfo &t
     }
 }
 
-template <int D, int NS, int NB, bool FP8>
+// MERGE: see prob_merges. A template argument: as a run-time branch it cost the long prompts, which never take it, 1.5 %
+// (170000 paged tokens, 16 lookahead rows 1174 -> 1191 us; spilled scalar registers in the loop).
+template <int D, int NS, int NB, bool FP8, bool MERGE>
 __global__ __launch_bounds__(kThreads, 3) void sp_prob_kernel(ScoreArgs a, LayerPtrs kp)
 {
     constexpr int KS = D / 16;
@@ -514,12 +516,11 @@ __global__ __launch_bounds__(kThreads, 3) void sp_prob_kernel(ScoreArgs a, Layer
             for (int e = 0; e < 4; ++e) mx[s][b][e] = neg_inf();
     }
 
-    const bool merge = a.lse_neg == nullptr;
-    if (merge) merge_rows(a, ti, layer_lo * a.n_kv_heads, (layer_hi - layer_lo) * a.n_kv_heads, ci0, tid);
+    if (MERGE) merge_rows(a, ti, layer_lo * a.n_kv_heads, (layer_hi - layer_lo) * a.n_kv_heads, ci0, tid);
     for (int layer = layer_lo; layer < layer_hi; ++layer) {
         for (int kv = 0; kv < a.n_kv_heads; ++kv) {
             const int phase = layer * a.n_kv_heads + kv;
-            float *ci = ci0 + (merge ? (phase - layer_lo * a.n_kv_heads) * a.rows_pad : 0);
+            float *ci = ci0 + (MERGE ? (phase - layer_lo * a.n_kv_heads) * a.rows_pad : 0);
             __syncthreads();
             stage_q<D>(qs, a, ti.prompt, layer, kv, tid);
             if (FP8) stage_k_fp8<D, NS>(ks, key_base_fp8(a, kp, layer, kv), a.k_stride_token, ti.j0, ti.end, tid);
@@ -527,7 +528,7 @@ __global__ __launch_bounds__(kThreads, 3) void sp_prob_kernel(ScoreArgs a, Layer
             // 8-bit keys: logit differences of this (layer, kv head) are in units of its stored keys; its scale
             // brings them to the common unit before they meet those of other heads and layers
             const float ksc = FP8 ? a.kscale[phase] : 1.0f;
-            if (!merge)
+            if (!MERGE)
                 for (int i = tid; i < a.rows_pad; i += kThreads)
                     ci[i] = a.lse_neg[((int64_t)ti.prompt * n_phases + phase) * a.rows_pad + i];
             __syncthreads();
@@ -1121,24 +1122,20 @@ bool prob_merges(const Plan &p, const ScoreArgs &a, int64_t longest)
 }
 
 template <int D, int NS, bool FP8 = false>
-sp_status launch_all(const Plan &p, ScoreArgs a, const LayerPtrs &kp, int64_t longest, hipStream_t st)
+sp_status launch_all(const Plan &p, const ScoreArgs &a, const LayerPtrs &kp, int64_t longest, hipStream_t st)
 {
     const dim3 block(kThreads);
     hipLaunchKernelGGL((sp_stats_kernel<D, NS, FP8>), dim3(a.n_tiles, p.n_phases), block, p.lds_bytes, st, a, kp);
     SP_HIP_CHECK(hipGetLastError());
-    size_t prob_lds = p.lds_bytes;
+    const dim3 grid(a.n_tiles, a.n_splits);
     if (prob_merges(p, a, longest)) {
-        a.lse_neg = nullptr;
-        prob_lds += sizeof(float) * (size_t)p.rows_pad * (a.layers_per_split * a.n_kv_heads - 1);
+        const size_t lds = p.lds_bytes + sizeof(float) * (size_t)p.rows_pad * (a.layers_per_split * a.n_kv_heads - 1);
+        hipLaunchKernelGGL(p.NB == 1 ? (sp_prob_kernel<D, NS, 1, FP8, true>) : (sp_prob_kernel<D, NS, 2, FP8, true>), grid, block, lds, st, a, kp);
     } else {
         hipLaunchKernelGGL(sp_merge_kernel, dim3(p.rows_pad / 32, p.n_phases, a.n_prompts), dim3(kMergeThreads), 0, st, a);
         SP_HIP_CHECK(hipGetLastError());
+        hipLaunchKernelGGL(p.NB == 1 ? (sp_prob_kernel<D, NS, 1, FP8, false>) : (sp_prob_kernel<D, NS, 2, FP8, false>), grid, block, p.lds_bytes, st, a, kp);
     }
-    const dim3 grid(a.n_tiles, a.n_splits);
-    if (p.NB == 1)
-        hipLaunchKernelGGL((sp_prob_kernel<D, NS, 1, FP8>), grid, block, prob_lds, st, a, kp);
-    else
-        hipLaunchKernelGGL((sp_prob_kernel<D, NS, 2, FP8>), grid, block, prob_lds, st, a, kp);
     SP_HIP_CHECK(hipGetLastError());
     if (a.n_splits > 1) return launch_reduce(a, a.n_splits, st);
     return SP_OK;
