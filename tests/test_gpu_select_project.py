@@ -143,11 +143,13 @@ def check_project(doff, toff, spans):
     ts2, m2, n2 = gpu_project(doff, toff, spans, want_mask=False, max_spans=max(1, spans.shape[0]) + 3)
     np.testing.assert_array_equal(ts2, o_ts)
     assert m2 is None and n2 == o_n
-    # a capacity beyond what the one-launch kernel holds in LDS takes two launches
-    ts3, m3, n3 = gpu_project(doff, toff, spans, max_spans=1500)
-    np.testing.assert_array_equal(ts3, o_ts)
-    np.testing.assert_array_equal(m3, o_mask)
-    assert n3 == o_n
+    # a capacity beyond what the one-launch kernel holds in LDS takes two launches, beyond 4096 spans three
+    for cap, want_mask in ((1500, True), (1500, False), (4097, True)):
+        ts3, m3, n3 = gpu_project(doff, toff, spans, max_spans=cap, want_mask=want_mask)
+        np.testing.assert_array_equal(ts3, o_ts)
+        if want_mask:
+            np.testing.assert_array_equal(m3, o_mask)
+        assert n3 == o_n
 
 
 def random_spans(rng, L, n_max):
@@ -454,3 +456,44 @@ def test_select_and_project_batch_match_the_per_prompt_calls_and_the_oracle(case
     torch.cuda.synchronize()
     assert sel2.cpu().numpy().tobytes() == sel.tobytes() and spans2.cpu().numpy().tobytes() == spans.tobytes()
     assert tsp2.cpu().numpy().tobytes() == tsp.tobytes() and n_kept2.cpu().numpy().tobytes() == n_kept.tobytes()
+
+
+def test_project_batch_at_every_scale_of_the_coarse_index():
+    """sp_project_batch keeps one launch up to its limit of 258047 target tokens, strides of the coarse index 1 .. 63:
+    prompts on both sides of a stride's edge, odd strides, the limit itself, with as many as 1024 spans."""
+    import torch
+    import paper_2603_02631_amd as sp
+    from gpu_util import DEV
+    Ms = [63 * 4096 - 1, 5000, 21 * 4096 - 1, 21 * 4096, 100003, 47 * 4096 - 1, 47 * 4096, 62 * 4096 - 1, 62 * 4096]
+    say(f"[project batch] M={Ms}")
+    rng = np.random.default_rng(91)
+    texts = [ragged_text(rng, M) for M in Ms]
+    doff, toff, _ = texts[0]                       # the limit of both: 1024 spans, some without characters
+    pts = np.sort(rng.choice(doff.size, size=2048, replace=False)).reshape(-1, 2).astype(np.int64)
+    texts[0] = (doff, toff, pts)
+
+    def packed(arrays, dt):
+        return torch.from_numpy(np.ascontiguousarray(np.concatenate(arrays), dtype=dt)).to(DEV)
+
+    def prefix(sizes):
+        p = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+        return [int(v) for v in p], torch.from_numpy(p).to(DEV)
+
+    B = len(Ms)
+    off, off_d = prefix([t[0].size - 1 for t in texts])
+    moff, moff_d = prefix(Ms)
+    kept, kept_d = prefix([t[2].shape[0] for t in texts])
+    n_sp = torch.tensor([t[2].shape[0] for t in texts], dtype=torch.int32, device=DEV)
+    for want_mask in (True, False):
+        tsp = torch.full((kept[-1], 2), -1, dtype=torch.int64, device=DEV)
+        n_t, n_kept = torch.full((B,), -1, dtype=torch.int32, device=DEV), torch.full((B,), -1, dtype=torch.int64, device=DEV)
+        mask = torch.full((moff[-1],), 7, dtype=torch.uint8, device=DEV) if want_mask else None
+        sp.sp_project_batch(packed([t[0] for t in texts], np.int64), off, off_d, packed([t[1] for t in texts], np.int64), moff, moff_d,
+                            packed([t[2] for t in texts], np.int64), n_sp, kept, kept_d, tsp, n_t, mask, n_kept)
+        torch.cuda.synchronize()
+        for b, (d, t, spans) in enumerate(texts):
+            want, n = oracle.project(d, t, spans), int(n_t[b])
+            np.testing.assert_array_equal(tsp[kept[b]:kept[b] + n].cpu().numpy(), want[0])
+            assert (tsp[kept[b] + n:kept[b + 1]] == -1).all() and int(n_kept[b]) == want[2]
+            if want_mask:
+                np.testing.assert_array_equal(mask[moff[b]:moff[b + 1]].cpu().numpy(), want[1])
