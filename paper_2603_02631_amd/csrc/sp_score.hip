@@ -893,9 +893,11 @@ bool fused_applies(const Plan &p, int64_t L, int64_t k_stride_token)
 }
 
 // Prompts that need more than one tile per compute unit, and no more than two: K is still read once (16 layers
-// x 8 kv heads, head_dim 64: 256K tokens 904 us against 1552 on the three-kernel path, one token beyond 128K 686 against
-// 783). 8-bit keys at head_dim 64 leave the three kernels half the bytes and cross an eighth later (140000 tokens 672 /
-// 658, 200000 690 / 940; 64 rows 140000 818 / 829). Up to eight lookahead rows: there is no variant for more.
+// x 8 kv heads, head_dim 64: 256K tokens 781 us against 1514 on the three-kernel path, one token beyond 128K 523 against
+// 756; 64 rows, 140000 744 against 940). 8-bit keys at head_dim 64 leave the three kernels half the bytes; their line lies
+// an eighth later, where the kernels crossed when it was drawn (140000 tokens 621 / 676, 200000 651 / 935; 64 rows
+// 140000 802 / 850: the present kernel is ahead from the first token beyond a tile a unit on). Up to eight lookahead rows:
+// there is no variant for more.
 bool pair_applies(const Plan &p, bool fp8, int64_t L, int64_t k_stride_token)
 {
     if (!fused_base_shape(p) || p.NB != 1 || k_stride_token > (int64_t(1) << 20)) return false;
@@ -974,9 +976,10 @@ bool plan_fused_batch(const Plan &p, const int64_t *offsets, int B, int64_t k_st
 
 // How many layer ranges a launch over all of `n_prompts` prompts is cut into: as many as its `tiles`
 // workgroups fit the device, so that the ranges run side by side. `room`: bytes for their exchange area.
-// A step of the kernel takes 2.1 us on 64 workgroups and 2.9 us on 256 (head_dim 64, 32 rows), so every
-// range more is time saved (16 layers, 8 kv heads, head_dim 64: 32K tokens 276 -> 111 us with four
-// ranges, 64K tokens 305 -> 211 us with two; 28 layers, head_dim 128: 32K tokens 542 -> 363 us).
+// A step of the kernel takes 1.8 us on 64 workgroups and 2.9 us on 256 (head_dim 64, 32 rows), so every
+// range more is time saved (16 layers, 8 kv heads, head_dim 64: 32K tokens 245 -> 101 us with four
+// ranges, 64K tokens 267 -> 188 us with two; 28 layers, head_dim 128: 32K tokens 445 -> 305 us, 16K tokens 398 -> 165
+// with four).
 int fused_ranges(const Plan &p, int tiles, int n_prompts, size_t room)
 {
     int n = std::min({std::min(256, device_compute_units()) / tiles, p.n_layers, sp_fused::kMaxGroup / n_prompts});
@@ -996,17 +999,21 @@ bool whole_groups_pay(const BatchGroups &bg)
 // three-kernel path. A launch costs its steps (a range's phases and five more to fill and drain the pipeline); the three
 // kernels take the longer the more keys their tiles hold, `keys` with the empty places. Each variant has its line,
 // in MB of bf16 keys: `per_step` for each step, or `steep` for each step less `base` where the fixed cost of the three
-// launches counts. Measured (tokens: three kernels / single launch, us; 16 layers x 8 kv heads unless noted):
-//   32 rows                      4600 40 / 40, 6000 45 / 37, 9000 58 / 53, 12000 69 / 54; 28 layers, head_dim 128: 1500 46 / 33;
-//                                4 x 4 heads, head_dim 128: 12000 31 / 31; 30 prompts of 1100 .. 1500 271 / 189
-//   64 rows, 9+ lookahead rows   4500 50 / 49, 5000 52 / 49, 6200 54 / 48, 9000 73 / 77, 10100 78 / 78, 12000 80 / 77, 16384 115 / 77;
-//                                24 prompts of 60 .. 4000 282 / 292, 30 of 1100 .. 1500 352 / 292
-//   64 rows, 5+ heads a kv head  4600 48 / 51, 6200 53 / 51, 9000 66 / 82, 12000 80 / 83, 16384 116 / 83
-//   64 rows, head_dim 128        24 x 4 heads: 3000 45 / 49, 3600 49 / 47, 4500 66 / 48; 24 prompts of 60 .. 4000 457 / 418
-//   8-bit keys, 32 rows          6000 40 / 41, 8192 46 / 38, 10000 55 / 60, 12000 60 / 60, 16400 84 / 80, 18000 92 / 79, 22000 102 / 100;
-//                                28 layers, head_dim 128 (32 rows): 1500 43 / 35, as with bf16 keys
-//   8-bit keys, 64 rows          6200 53 / 51, 9000 67 / 83, 12100 78 / 83, 13000 95 / 83, 16384 101 / 80, 18000 118 / 112, 19000 122 / 112,
-//                                22000 132 / 144, 24500 140 / 145, 30000 176 / 136 (no line has the crossing at 17600 as well)
+// launches counts. The lines were drawn where the kernels crossed before the single launch's steps became 5 to 25 %
+// shorter and short prompts lost their merge launch; the present kernels cross at or a little before them. Measured on
+// these (tokens: three kernels / single launch, us; * = the line still takes the slower one; 16 layers x 8 kv heads unless
+// noted):
+//   32 rows                      3000 32 / 34, 3600 36 / 36, 4600* 41 / 36, 6000 48 / 37, 9000 63 / 53, 12000 75 / 54; 28 layers,
+//                                head_dim 128: 700 33 / 34, 1000* 38 / 36, 1500 46 / 37; 4 x 4 heads, head_dim 128: 9000 29 / 29,
+//                                12000* 32 / 31; 30 prompts of 1100 .. 1500 271 / 175, 24 of 60 .. 4000 364 / 189
+//   64 rows, 9+ lookahead rows   3600 47 / 47, 4500* 51 / 48, 5000 53 / 49, 6200 58 / 51, 9000 75 / 79, 10100* 79 / 73, 12000 88 / 73,
+//                                16384 121 / 76; 24 prompts of 60 .. 4000 460 / 293, 30 of 1100 .. 1500 359 / 291
+//   64 rows, 5+ heads a kv head  4600 51 / 51, 6200 58 / 52, 9000 73 / 80, 12000* 86 / 74, 16384 117 / 78
+//   64 rows, head_dim 128        24 x 4 heads: 3000 50 / 52, 3600* 54 / 50, 4500 70 / 50; 24 prompts of 60 .. 4000 671 / 429
+//   8-bit keys, 32 rows          4500 35 / 38, 6000 43 / 38, 8192 49 / 38, 10000 56 / 56, 12000 62 / 55, 16400 86 / 73, 18000 95 / 74,
+//                                22000 105 / 94; 28 layers, head_dim 128 (32 rows): 1000 34 / 35, 1500 40 / 36, as with bf16 keys
+//   8-bit keys, 64 rows          6200 56 / 53, 9000 69 / 86, 12100 80 / 85, 13000 97 / 84, 16384 108 / 86, 18000* 122 / 113, 19000 124 / 113,
+//                                22000 137 / 142, 24500* 145 / 147, 30000 189 / 141 (no line has the crossing at 17600 as well)
 bool steps_pay(const Plan &p, bool fp8, int64_t keys, int ranges, int launches)
 {
     struct Line { double per_step, steep, base; };

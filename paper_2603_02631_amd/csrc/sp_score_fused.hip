@@ -16,13 +16,14 @@
 //    phases live in registers (a ring of 4 x 32 VGPRs);
 //  * a vector-memory instruction blocks its wave while the compute unit's memory
 //    pipe is full, and the pipe drains at the unit's share of HBM bandwidth, so
-//    the eight tile loads of an iteration are issued one by one between the
-//    MFMA steps: while one wave waits for a slot the other waves compute;
+//    the eight tile loads of an iteration are spread over its MFMA steps, one
+//    or two at a time (two tiles a workgroup: four, behind what the step waits
+//    for): while one wave waits for a slot the other waves compute;
 //  * phase p: the statistics pass computes the partial (max, sum exp) of every
 //    query row over the workgroup's keys and publishes it to global memory;
-//  * one wave of some workgroup (rotating "duty") combines the partials of four
-//    consecutive rows over all workgroups in a fixed order and publishes their
-//    normalisers;
+//  * some workgroup (rotating "duty") combines the partials of four consecutive
+//    rows over all workgroups in a fixed order and publishes their normalisers:
+//    one wave, or two with two rows each (see kDutyWaves);
 //  * three phases later the workgroup picks the normalisers up and runs the
 //    probability pass of phase p from the fragments still in its registers:
 //    logits again with -lse folded into the MFMA accumulator, maximum over
@@ -1037,10 +1038,11 @@ struct Walk {
 //   stats   statistics pass of phase s; loads of sub-tile 1 of K(s+1); scalar state of step s+1 under the first MFMA steps
 //   pre     wait for the Q slices (and the exchange data); normaliser wave: seeds of the probability pass of phase s-3
 //   barrier
-// Vector-memory operations per wave and step, oldest first: [publish store] [8 duty loads] [Q] [Q]
-// 4 K loads (prob), [normaliser load], 4 K loads (stats; kEarlyLse false: it comes between them); the bracketed ones exist on some waves or
-// in some steps only, so every wait counts only operations that are certainly issued behind the
-// ones it needs.
+// Vector-memory operations per wave and step, oldest first: [publish store] [4 duty loads on each of two waves, or 8 on
+// one] [Q] [Q] 4 K loads (prob), [normalisers' duty stores (kDutyAtLift)], [normaliser load], 4 K loads (stats; kEarlyLse
+// false: the normaliser load comes between them, PAIR: the duty loads as well; 8-bit keys: 2 and 2 K loads; BIG: none in
+// prob, 8 in stats); the bracketed ones exist on some waves or in some steps only, so every wait counts only operations
+// that are certainly issued behind the ones it needs.
 // KIND (see there): the plain variant carries none of the others' code or registers.
 template <int NB, int GB, int SLOT, int PAR, Kind KIND, bool W, bool F8, bool PAIR>
 __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, const GroupTable &gt, int s, int n_phases, Ring &ring,
@@ -1522,9 +1524,9 @@ __device__ __forceinline__ void fold_model_constants(FusedArgs &a)
 // widened to bf16 at the lift; every phase has its own key scale.
 // PAIR: prompts of up to two tiles per compute unit (head_dim 64: 256K tokens, 128: 128K). A workgroup owns two
 // tiles and a phase takes two steps, one a tile, on the same fragment ring: two phases instead of four are in
-// flight, so the normalisers have to come back within four steps less the two of their own phase. Duties are therefore
-// combined in the step in which the partials are published, which has twice a tile's time (5.5 us of HBM time)
-// to go around. One read of K instead of the general path's two.
+// flight, so the normalisers have to come back within four steps less the two of their own phase. In `step` duties are
+// therefore combined in the step in which the partials are published; step_late gives them the next one and takes the
+// probability pass last. One read of K instead of the general path's two.
 template <int NB, int GB, Kind KIND, class M, bool W = false, bool F8 = false, bool PAIR = false>
 __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, LayerPtrs kp, GroupTable gt)
 {

@@ -11,8 +11,11 @@ constexpr int kMaxRowsWide = 32; // head_dim 128, one block of query rows (bf16 
 constexpr int kMaxRows = 64;     // padded query rows per kv head the kernel holds on chip
 constexpr int kSlots = 8;        // depth of the exchange ring
 constexpr int kDutyRows = 4;     // consecutive query rows one workgroup's duty covers
-constexpr int kMinWorkgroups = 64;       // head_dim 64: with all layers in one range, shorter prompts are faster on the two-pass path
-constexpr int kMinWorkgroupsWide = 96;   // head_dim 128 (measured crossover near 24K tokens)
+// Fewest workgroups with all layers in one range; shorter prompts (of captured calls, for instance) take the three kernels.
+// Three kernels / single launch, us: 16 x 8 heads of 64, 16384 tokens 100 / 243, 28672 184 / 241, 32768 (64 workgroups) 202 /
+// 239; 28 x 8 heads of 128, 12288 tokens 296 / 386, 16384 387 / 385, 24576 (96 workgroups) 537 / 400.
+constexpr int kMinWorkgroups = 64;       // head_dim 64
+constexpr int kMinWorkgroupsWide = 96;   // head_dim 128
 constexpr int kMaxGroup = 64;          // entries of a launch's table
 
 // The (prompt, layer range) pairs that share a launch. Entry i scores layers layer0[i] .. layer0[i] +
