@@ -11,8 +11,8 @@
 // so ranges that overlap or touch are merged with an exclusive running maximum
 // of the range ends and a prefix sum of "starts a new range" flags.
 //
-// Up to 1024 spans (the usual case: a few hundred kept chunks) of fewer than 258048 target tokens take ONE launch,
-// sp_project_one_kernel: workgroup 0 finds and merges the ranges, the other
+// Up to 1024 spans (the usual case: a few hundred kept chunks) of fewer than 22528 target tokens, or without a mask of
+// fewer than 258048, take ONE launch, sp_project_one_kernel: workgroup 0 finds and merges the ranges, the other
 // workgroups write the mask, each for itself and straight from the spans:
 //   workgroup 0   stages a coarse index of the target offsets (every stride-th
 //                 one, at most 4096) and the spans' character positions in LDS,
@@ -23,11 +23,12 @@
 //   mask groups   stage the spans' character intervals in LDS; since they are
 //                 sorted, token [ts, te) is kept iff the first span that ends
 //                 after ts begins before te: one LDS binary search per token.
-// More spans or tokens take two launches and leave raw ranges in tspans between them:
+// Otherwise, with a mask, two launches:
 //   sp_project_mark_kernel   search groups: one wave per (span, end), a 64-ary search of the target
 //                            offsets, three rounds of memory latency; mask groups as above.
-//   sp_project_spans_kernel  one workgroup: scans, merged target ranges,
-//                            their count and the kept-token total.
+//   sp_project_parked_kernel, sp_project_spans_kernel  one workgroup: scans, merged target ranges,
+//                            their count and the kept-token total. Between the launches the raw ranges lie in the mask's
+//                            first bytes, or for more than 1024 spans or 258047 tokens in tspans.
 // Without a mask, and for more spans than the mask groups' LDS holds, the searches are a launch of their own:
 //   sp_project_search_kernel the searches of the mark kernel.
 //   sp_project_spans_kernel  as above.
@@ -112,10 +113,11 @@ struct SpanSmem {
     int wave_sum[kSpanWaves];
 };
 
-// Merges the raw ranges in tspans (see the file header) in place, kSpanThreads spans at a time.
+// Merges the raw ranges (see the file header) into tspans, which may be where they lie, kSpanThreads spans at a time.
 // Bound by its chain of round trips: the count, the ranges, two scans, one store. Loads of ranges that do not wait for the
 // count read entries that nothing has written: 0.2 to 0.5 us more on inputs in no cache, no less on others.
-__device__ __forceinline__ void merge_spans_body(int n_spans, int64_t *tspans, int32_t *n_tspans, int64_t *n_kept)
+template <class T>
+__device__ __forceinline__ void merge_spans_body(int n_spans, const T *raw, int64_t *tspans, int32_t *n_tspans, int64_t *n_kept)
 {
     __shared__ SpanSmem sm;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -125,9 +127,9 @@ __device__ __forceinline__ void merge_spans_body(int n_spans, int64_t *tspans, i
     for (int base = 0; base < n_spans; base += kSpanThreads) {
         const int s = base + tid;
         int64_t lo = 0, hi = 0;
-        if (s < n_spans) {          // merged ranges are written back in place (an entry is overwritten only after
-            lo = tspans[2 * s];     // its segment has been read: r <= s)
-            hi = tspans[2 * s + 1];
+        if (s < n_spans) {          // in place: an entry is overwritten only after its segment has been read (r <= s)
+            lo = raw[2 * s];
+            hi = raw[2 * s + 1];
         }
         const bool nonempty = lo < hi;
         // exclusive running maximum of the ends of earlier non-empty ranges
@@ -187,7 +189,7 @@ __device__ __forceinline__ void merge_spans_body(int n_spans, int64_t *tspans, i
 __global__ __launch_bounds__(kSpanThreads) void sp_project_spans_kernel(const int32_t *__restrict__ n_spans_p, int max_spans,
                                                                         int64_t *tspans, int32_t *n_tspans, int64_t *n_kept)
 {
-    merge_spans_body(span_count(n_spans_p, max_spans), tspans, n_tspans, n_kept);
+    merge_spans_body(span_count(n_spans_p, max_spans), tspans, tspans, n_tspans, n_kept);
 }
 
 __global__ __launch_bounds__(kThreads) void sp_project_mask_kernel(const int64_t *__restrict__ tspans,
@@ -442,6 +444,19 @@ constexpr int kMarkSpans = 4096;             // spans whose character intervals 
 constexpr int kMarkPerThread = 2;
 constexpr int kSearchGroups = 128;           // search workgroups: a wave for every (span, end) of up to 1024 spans
 
+// Calls that one launch can do leave the entries of tspans behind the merged ranges alone. On two launches their raw ranges
+// lie in the mask's own first bytes in between (PARKED), eight a span from the first multiple of 8 on; the second launch
+// marks the tokens of these bytes.
+constexpr int64_t parked_bytes(int64_t n) { return 8 * n + 7; }
+__device__ __forceinline__ int32_t *parked_ranges(uint8_t *mask) { return reinterpret_cast<int32_t *>(((uintptr_t)mask + 7) & ~(uintptr_t)7); }
+// Target tokens from which two launches are taken where one would do, whose workgroup 0 has a chain that grows with tokens
+// and spans. One launch / two, alone on inputs in no cache, as a serving program's always are, us (tokens / spans): 17000 /
+// 42 11.6 / 10.1, 23000 / 32 11.8 / 10.2, 37449 / 187 15.9 / 11.2, 57166 / 81 15.2 / 10.7, 149796 / 213 18.9 / 12.3, 748 30.5 /
+// 15.3, 257000 / 367 22.3 / 13.1. Call after call on the same inputs they cross later: 17000 / 42 7.2 / 8.6, 23000 / 32 7.8 /
+// 10.0, 37449 / 187 10.4 / 9.8, 57166 / 81 9.3 / 9.8, 149796 / 213 11.6 / 9.8, 748 21.9 / 11.5, 257000 / 367 14.6 / 10.2.
+constexpr int64_t kParkedLine = 22 * 1024;
+static_assert(kParkedLine >= parked_bytes(kOneSpans), "the parked ranges lie within the mask");
+
 // The first `search_groups` workgroups find the raw range of every span, a wave a search (as sp_project_search_kernel),
 // the others write the mask straight from the spans, as those of the single launch do. Bound by the search's chain of
 // round trips (count, span, character, three probes), beside which the mask is free. Neither looks at spans past the
@@ -449,10 +464,11 @@ constexpr int kSearchGroups = 128;           // search workgroups: a wave for ev
 // Both launches, in a row / alone on inputs in no cache, us (tokens / spans / max_spans), against search, merge and mask
 // launches: 1500 / 8 / 2048 10.0 / 9.9 against 12.4 / 12.6, 149796 / 213 / 2048 10.0 / 10.3 against 12.7 / 14.4,
 // 149796 / 748 / 4096 10.1 / 13.3 against 14.4 / 18.7, 299593 / 427 / 427 10.7 / 11.6 against 13.8 / 17.4.
+template <bool PARKED>
 __global__ __launch_bounds__(kMarkThreads) void sp_project_mark_kernel(
     const int64_t *__restrict__ draft_off, int64_t L, const int64_t *__restrict__ target_off, int64_t M,
     const int64_t *__restrict__ spans, const int32_t *__restrict__ n_spans_p, int max_spans, int search_groups,
-    int64_t *__restrict__ tspans, uint8_t *__restrict__ mask)
+    int64_t *__restrict__ tspans, uint8_t *mask)
 {
     extern __shared__ int64_t mark_ch[];     // [2 * max_spans] character position of every (span, end)
     const int tid = threadIdx.x;
@@ -461,7 +477,10 @@ __global__ __launch_bounds__(kMarkThreads) void sp_project_mark_kernel(
         const int lane = tid & 63;
         for (int q = blockIdx.x * kMarkWaves + (tid >> 6); q < 2 * n; q += search_groups * kMarkWaves) {
             const int64_t r = raw_bound(draft_off, L, target_off, M, spans, q, lane);
-            if (lane == 0) tspans[q] = r;
+            if (lane == 0) {
+                if (PARKED) parked_ranges(mask)[q] = (int32_t)r;
+                else tspans[q] = r;
+            }
         }
         return;
     }
@@ -479,6 +498,7 @@ __global__ __launch_bounds__(kMarkThreads) void sp_project_mark_kernel(
     for (int k = 0; k < kMarkPerThread; ++k) {
         const int64_t t = base + k * kMarkThreads + tid;
         if (t >= M) break;
+        if (PARKED && t < parked_bytes(n)) continue;
         int j = 0, hi = n;                   // first span whose end lies after ts
         while (j < hi) {
             const int mid = j + ((hi - j) >> 1);
@@ -486,6 +506,32 @@ __global__ __launch_bounds__(kMarkThreads) void sp_project_mark_kernel(
         }
         mask[t] = j < n && mark_ch[2 * j] < te[k];
     }
+}
+
+// The merge of parked ranges, and the mask of the tokens whose bytes they took: each span sets its tokens' bits in LDS (a
+// search of the ranges for every token took 4 us for each 2048 of them).
+__global__ __launch_bounds__(kSpanThreads) void sp_project_parked_kernel(const int32_t *__restrict__ n_spans_p, int max_spans,
+                                                                         int64_t *__restrict__ tspans, int32_t *__restrict__ n_tspans,
+                                                                         int64_t *__restrict__ n_kept, uint8_t *mask)
+{
+    constexpr int kWords = (int)(parked_bytes(kOneSpans) + 31) / 32;
+    __shared__ int32_t bound[2 * kOneSpans];
+    __shared__ uint32_t kept[kWords];
+    const int n = span_count(n_spans_p, max_spans), end = (int)parked_bytes(n), tid = threadIdx.x;
+    const int32_t *raw = parked_ranges(mask);
+    for (int i = tid; i < kWords; i += kSpanThreads) kept[i] = 0;
+    for (int i = tid; i < 2 * n; i += kSpanThreads) bound[i] = raw[i];
+    __syncthreads();                         // every parked range has been read
+    for (int s = tid; s < n; s += kSpanThreads) {
+        const int hi = bound[2 * s + 1] < end ? bound[2 * s + 1] : end;
+        for (int t = bound[2 * s]; t < hi; t = (t | 31) + 1) {
+            const int last = (t | 31) < hi ? 31 : (hi - 1) & 31;
+            atomicOr(&kept[t >> 5], (0xffffffffu >> (31 - last)) & (0xffffffffu << (t & 31)));
+        }
+    }
+    merge_spans_body(n, bound, tspans, n_tspans, n_kept);
+    __syncthreads();
+    for (int t = tid; t < end; t += kSpanThreads) mask[t] = kept[t >> 5] >> (t & 31) & 1u;
 }
 
 // Ragged batch: prompt b = blockIdx.y. Its L_b + 1 draft offsets start at off[b] + b of the packed array,
@@ -534,7 +580,8 @@ extern "C" sp_status sp_project(const int64_t *draft_off_dev, int64_t L, const i
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     // one launch when the spans fit its LDS and one stride of the coarse index fits a wave-wide probe
     const int64_t stride = M / kCoarse + 1;          // ceil((M + 1) / kCoarse)
-    if (max_spans <= kOneSpans && stride <= 63) {
+    const bool one = max_spans <= kOneSpans && stride <= 63;
+    if (one && !(keep_mask_dev && M >= kParkedLine)) {
         const int n_coarse = (int)sp::ceil_div(M + 1, stride);
         const int64_t mask_groups = keep_mask_dev ? sp::ceil_div(M, (int64_t)kOneThreads * kMaskPerThread) : 0;
         hipLaunchKernelGGL(sp_project_one_kernel, dim3((unsigned)(1 + mask_groups)), dim3(kOneThreads), 0, st, draft_off_dev, L,
@@ -547,12 +594,17 @@ extern "C" sp_status sp_project(const int64_t *draft_off_dev, int64_t L, const i
     // as well, in smaller workgroups (inputs in no cache, 149796 tokens, 200 of 2048 spans: 12.0 us, in these 12.5)
     if (max_spans <= kMarkSpans && keep_mask_dev) {
         const int search_groups = std::min(kSearchGroups, (int)sp::ceil_div(2 * (int64_t)max_spans, (int64_t)kMarkWaves));
-        hipLaunchKernelGGL(sp_project_mark_kernel, dim3((unsigned)(search_groups + sp::ceil_div(M, (int64_t)kMarkThreads * kMarkPerThread))),
+        hipLaunchKernelGGL(one ? sp_project_mark_kernel<true> : sp_project_mark_kernel<false>,
+                           dim3((unsigned)(search_groups + sp::ceil_div(M, (int64_t)kMarkThreads * kMarkPerThread))),
                            dim3(kMarkThreads), sizeof(int64_t) * 2 * (size_t)max_spans, st, draft_off_dev, L, target_off_dev, M, spans_dev,
                            n_spans_dev, (int)max_spans, search_groups, tspans_dev, keep_mask_dev);
         SP_HIP_CHECK(hipGetLastError());
-        hipLaunchKernelGGL(sp_project_spans_kernel, dim3(1), dim3(kSpanThreads), 0, st, n_spans_dev, (int)max_spans, tspans_dev,
-                           n_tspans_dev, n_kept_dev);
+        if (one)
+            hipLaunchKernelGGL(sp_project_parked_kernel, dim3(1), dim3(kSpanThreads), 0, st, n_spans_dev, (int)max_spans, tspans_dev,
+                               n_tspans_dev, n_kept_dev, keep_mask_dev);
+        else
+            hipLaunchKernelGGL(sp_project_spans_kernel, dim3(1), dim3(kSpanThreads), 0, st, n_spans_dev, (int)max_spans, tspans_dev,
+                               n_tspans_dev, n_kept_dev);
         SP_HIP_CHECK(hipGetLastError());
         return SP_OK;
     }

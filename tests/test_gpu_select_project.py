@@ -224,10 +224,10 @@ def ragged_text(rng, tokens):
     return doff, toff, spans
 
 
-@pytest.mark.parametrize("tokens", [22 * 1024, 63 * 4096 - 1, 63 * 4096, 63 * 4096 + 4097])
+@pytest.mark.parametrize("tokens", [22 * 1024 - 1, 22 * 1024, 63 * 4096 - 1, 63 * 4096, 63 * 4096 + 4097])
 def test_project_around_the_line_to_two_launches(tokens):
-    """One launch (up to 1024 spans of fewer than 63 * 4096 target tokens), two, and three (more spans than the mask
-    workgroups' LDS holds) on the same text."""
+    """One launch, two with the raw ranges in the mask (up to 1024 spans of fewer than 63 * 4096 target tokens) or in tspans,
+    and three (more spans than the mask workgroups' LDS holds) on the same text."""
     from gpu_util import gpu_project
     say(f"[project] M={tokens}")
     doff, toff, spans = ragged_text(np.random.default_rng(tokens), tokens)
@@ -241,27 +241,38 @@ def test_project_around_the_line_to_two_launches(tokens):
 
 
 @pytest.mark.parametrize("tokens", [22 * 1024, 100003, 63 * 4096 - 1])
-@pytest.mark.parametrize("want_mask", [True, False])
-def test_project_leaves_the_entries_behind_its_ranges_alone(tokens, want_mask):
-    """Up to 1024 spans of fewer than 258048 target tokens: entries of tspans behind the ranges keep what they held."""
+@pytest.mark.parametrize("mask_at", [0, 1, 4, 7, None])
+@pytest.mark.parametrize("keep", [1, 250, 1024])
+def test_project_leaves_the_entries_behind_its_ranges_alone(tokens, mask_at, keep):
+    """Up to 1024 spans of fewer than 258048 target tokens: entries of tspans behind the ranges keep what they held, and so
+    do the bytes around the mask, whatever its alignment (raw ranges lie in it between two launches)."""
     import torch
     import paper_2603_02631_amd as sp
     from gpu_util import DEV
     say(f"[project] entries behind the ranges, M={tokens}")
-    doff, toff, spans = ragged_text(np.random.default_rng(tokens + 1), tokens)
-    o_ts = oracle.project(doff, toff, spans)[0]
-    assert o_ts.shape[0] < spans.shape[0] <= 1024           # some spans share a range
+    rng = np.random.default_rng(tokens + 1)
+    doff, toff, spans = ragged_text(rng, tokens)
+    if keep == 1024:
+        spans = np.sort(rng.choice(doff.size, size=2048, replace=False)).reshape(-1, 2).astype(np.int64)
+    else:                                                   # the first tokens of the text among them
+        spans = np.concatenate([[[0, 60]], spans[spans[:, 0] >= 60]])[:keep]
+    o_ts, o_mask, o_n = oracle.project(doff, toff, spans)
+    assert o_ts.shape[0] < spans.shape[0] <= 1024 or keep < 1024           # some spans share a range
     dd, td, sd = (torch.from_numpy(a).to(DEV) for a in (doff, toff, spans))
-    tsp = torch.full((spans.shape[0], 2), -77, dtype=torch.int64, device=DEV)
+    tsp = torch.full((spans.shape[0] + 5, 2), -77, dtype=torch.int64, device=DEV)
     n_sp = torch.tensor([spans.shape[0]], dtype=torch.int32, device=DEV)
     n_t = torch.zeros(1, dtype=torch.int32, device=DEV)
     n_kept = torch.zeros(1, dtype=torch.int64, device=DEV)
-    mask = torch.empty(tokens, dtype=torch.uint8, device=DEV) if want_mask else None
+    around = torch.full((tokens + 24,), 7, dtype=torch.uint8, device=DEV)
+    mask = around[8 + mask_at:8 + mask_at + tokens] if mask_at is not None else None
     sp.sp_project(dd, doff.size - 1, td, tokens, sd, n_sp, spans.shape[0], tsp, n_t, mask, n_kept)
     torch.cuda.synchronize()
     n = int(n_t.item())
     np.testing.assert_array_equal(tsp[:n].cpu().numpy(), o_ts)
-    assert (tsp[n:] == -77).all()
+    assert (tsp[n:] == -77).all() and int(n_kept.item()) == o_n
+    if mask is not None:
+        np.testing.assert_array_equal(mask.cpu().numpy(), o_mask)
+        assert (around[:8 + mask_at] == 7).all() and (around[8 + mask_at + tokens:] == 7).all()
 
 
 @pytest.mark.parametrize("n", [512, 513, 1025, 2049, 4096, 5000])
@@ -304,15 +315,17 @@ def test_project_merges_ranges_across_turns_of_512_spans(n, kind):
 
 
 @pytest.mark.parametrize("where", ["in_the_last_token", "behind_the_last_token", "in_the_first_token"])
-def test_project_spans_that_share_a_token_or_lie_behind_the_text(where):
+@pytest.mark.parametrize("n", [1000, 4000])
+def test_project_spans_that_share_a_token_or_lie_behind_the_text(where, n):
     """Thousands of spans that begin and end in one target token: exact, and no serial walk over them by whoever has the
-    token. Such a walk took 625 us against 13 for the same spans spread over the text; the searches 20. Bound: 8 times."""
+    token. Such a walk took 625 us (1000 spans: 160) against 13 for the same spans spread over the text; the searches 20
+    (18). Bound: 8 times."""
     import torch
     import paper_2603_02631_amd as sp
     from gpu_util import DEV
-    say(f"[project] 4000 spans {where}")
+    say(f"[project] {n} spans {where}")
     rng = np.random.default_rng(77)
-    M, L, n = 150000, 130000, 4000
+    M, L = 150000, 130000
     doff = offsets_from_lengths(rng.geometric(0.25, size=L))
     total = int(doff[-1])
     even = np.linspace(0, total, M + 1).astype(np.int64)
