@@ -177,6 +177,20 @@ enum Kind {
     kRanges     // + paged keys, lookahead keys, and a table of entries that keep to themselves: layer ranges, short prompts
 };
 
+// A workgroup's index, which says which tile it owns and where its partials go. Blocks are handed to the eight dies in
+// turn. Where a prompt has the launch to itself (contiguous bf16 keys of head_dim 64) consecutive tiles go to one die,
+// since with every eighth tile a die asks for the same few address bits all the time when a kv head's keys are a power of two
+// apart: whole passes of 131072 tokens and 8 lookahead rows 407 -> 391 us, token-major 488 -> 463, 16 rows 482 -> 478, 262144
+// tokens 797 -> 794, 100000 tokens 325 -> 322. Not elsewhere: 8-bit keys 458 -> 460, head_dim 128 two tiles a workgroup 1103 ->
+// 1110, sixteen prompts 999 -> 1001; layer ranges 8192 tokens 55.9 -> 59.3 (a range's workgroups on one die). Duties go by
+// block, so that the workgroups of a phase's duties sit on all dies (with them by tile 262144 tokens took 841).
+template <Kind KIND, bool W, bool F8>
+__device__ __forceinline__ int workgroup_index(int n_wg)
+{
+    const int b = (int)blockIdx.x, die = b & 7;
+    return KIND == kPlain && !W && !F8 ? die * (n_wg >> 3) + min(die, n_wg & 7) + (b >> 3) : b;
+}
+
 struct Ring {
     bf16x8 kf[kRing][kNS][kKS];           // K fragments of the phases in flight
 };
@@ -1056,7 +1070,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
     int tid = threadIdx.x;
     __asm__ volatile("" : "+v"(tid));
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int w = blockIdx.x;
+    const int w = workgroup_index<KIND, W, F8>(a.n_wg);
     // Phases this step works on; < 0 or >= n_phases: nothing to do. PAIR: step s handles tile s % 2 (= PAR) of
     // phase s / 2; publishing and duties happen in even steps, when both tiles of a phase have been seen.
     const int ps = PAIR ? s >> 1 : s;                             // statistics pass
@@ -1229,7 +1243,7 @@ __device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, co
                 wk.dfirst += duty_blocks;
                 if (wk.dfirst >= duty_n) wk.dfirst -= duty_n;
             }
-            const int blk = w - duty_w0 - wk.dfirst;
+            const int blk = (int)blockIdx.x - duty_w0 - wk.dfirst;
             wk.duty_blk = blk < 0 ? blk + duty_n : blk;
             if (pd_next < 0 || pd_next >= n_phases || wk.duty_blk >= duty_blocks || direct) wk.duty_blk = -1;
         };
@@ -1318,7 +1332,7 @@ __device__ __forceinline__ void step_late(const FusedArgs &a, const LayerPtrs &k
     int tid = threadIdx.x;
     __asm__ volatile("" : "+v"(tid));
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int w = blockIdx.x;
+    const int w = workgroup_index<KIND, false, false>(a.n_wg);
     const int ps = s >> 1, pf = (s + 1) >> 1, pd = (s - 2) >> 1, pc = (s - 4) >> 1;       // pd: published, combined; pc: probability pass
     const uint32_t stride_bytes = (uint32_t)a.k_stride_token * 2u;
     int *fail = reinterpret_cast<int *>(lds + MP::kFail);
@@ -1343,7 +1357,7 @@ __device__ __forceinline__ void step_late(const FusedArgs &a, const LayerPtrs &k
                 wk.dfirst += kBlocks;
                 if (wk.dfirst >= a.n_wg) wk.dfirst -= a.n_wg;
             }
-            const int blk = w - wk.dfirst;
+            const int blk = (int)blockIdx.x - wk.dfirst;
             wk.duty_blk = blk < 0 ? blk + a.n_wg : blk;
             if (pd + 1 < 0 || pd + 1 >= n_phases || wk.duty_blk >= kBlocks) wk.duty_blk = -1;
         }
@@ -1547,7 +1561,7 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     fold_model_constants<M>(a);
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, hf = lane >> 5, col = lane & 31;
-    const int w = blockIdx.x;
+    const int w = workgroup_index<KIND, W, F8>(a.n_wg);
     int n_phases = a.n_layers * a.n_kv_heads;
     // Contiguous keys: the last workgroup's tile is shifted back so that it ends with the prompt (the
     // caller guarantees L >= 512): every workgroup loads 512 real keys; rows below r_lo belong to the

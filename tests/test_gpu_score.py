@@ -292,6 +292,15 @@ def test_fused_score_matches_oracle(shape):
     assert got_nhd.tobytes() == got.tobytes()        # same keys through token-major strides
 
 
+@pytest.mark.parametrize("workgroups", [64, 65, 66, 67, 68, 69, 70, 71])
+def test_tiles_of_a_prompt_on_its_dies(workgroups):
+    """Workgroups of a whole prompt take tiles by die: every remainder of the workgroup count by eight."""
+    from gpu_util import assert_scores_close, gpu_score
+    w = small_workload("dies", 1, 4, 1, 64, 8, workgroups * 512 - 77, cfg_id=240 + workgroups, hh=(1, 1000))
+    inp = synth.make_score_inputs(w)
+    assert_scores_close(gpu_score(inp["q"][0], inp["k"], w.scale, 0), oracle.score(inp["q"][0], inp["k"], w.scale, 0))
+
+
 # Prompts that fill only part of the device: the layers run in ranges side by side and a last launch adds them up.
 RANGE_SHAPES = [
     # name, Lyr, H, Hkv, d, n_q, lengths  (one: sp_score; several: sp_score_batch)
