@@ -774,9 +774,15 @@ struct Plan {
     size_t lds_bytes;
 };
 
-// Layers per workgroup of the prob pass: all of them once the tiles alone fill the device.
+// Layers per workgroup of the prob pass: all of them once the tiles alone fill the device, and where a workgroup gets through
+// all phases of a short prompt in less time than the launch that adds up the ranges takes. Whole passes with ranges and
+// without: 2 layers x 2 kv heads of 64, 1024 tokens 26.2 / 23.8 us, 6000 (24 tiles) 29.4 / 28.9; of 128, 2500 (20 tiles) 28.8 / 28.7,
+// 6000 (47) 30.5 / 32.0; 4 x 2, 1024 tokens 25.9 / 28.1; 2 x 8 32.1 / 37.3.
+constexpr int kWholePhases = 4, kWholeTiles = 24;
+
 int prob_layers_per_split(const Plan &p, int64_t n_tiles)
 {
+    if (p.n_phases <= kWholePhases && n_tiles <= kWholeTiles) return p.n_layers;
     int64_t want = (kProbTargetWgs + n_tiles - 1) / n_tiles;
     if (want < 1) want = 1;
     if (want > p.n_layers) want = p.n_layers;

@@ -218,6 +218,21 @@ def test_score_mid_size_config():
         say(f"  mode {mode}: max rel err {np.max(np.abs(got - want) / want):.2e}")
 
 
+@pytest.mark.parametrize("Lyr,Hkv,tiles", [(2, 2, 1), (2, 2, 24), (2, 2, 25), (4, 1, 24), (5, 1, 24), (1, 4, 24)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_score_of_few_phases_in_one_range(Lyr, Hkv, tiles, d):
+    """Three-kernel path: up to four phases and 24 tiles the prob pass takes all layers in one workgroup, beyond in ranges."""
+    from gpu_util import assert_scores_close, gpu_score, score_path
+    L = tiles * (256 if d == 64 else 128) - 19
+    say(f"[score] few phases Lyr={Lyr} Hkv={Hkv} d={d} L={L}")
+    w = small_workload("few", Lyr, 2 * Hkv, Hkv, d, 8, L, cfg_id=190, hh=(1, 100))
+    inp = synth.make_score_inputs(w)
+    for mode in (0, 1):
+        got = gpu_score(inp["q"][0], inp["k"], w.scale, mode)
+        assert score_path() == "general"
+        assert_scores_close(got, oracle.score(inp["q"][0], inp["k"], w.scale, mode))
+
+
 # Long single prompts take the single-launch kernel that keeps K on chip (head_dim 64: up to 64 padded
 # query rows and 128K tokens; head_dim 128: up to 32 rows and 64K tokens).
 FUSED_SHAPES = [
