@@ -902,11 +902,12 @@ bool fused_applies(const Plan &p, int64_t L, int64_t k_stride_token)
 // x 8 kv heads, head_dim 64: 256K tokens 781 us against 1514 on the three-kernel path, one token beyond 128K 523 against
 // 756; 64 rows, 140000 744 against 940). 8-bit keys at head_dim 64 leave the three kernels half the bytes; their line lies
 // an eighth later, where the kernels crossed when it was drawn (140000 tokens 621 / 676, 200000 651 / 935; 64 rows
-// 140000 802 / 850: the present kernel is ahead from the first token beyond a tile a unit on). Up to eight lookahead rows:
-// there is no variant for more.
+// 140000 802 / 850: the present kernel is ahead from the first token beyond a tile a unit on). With 64 padded rows (whole passes, three
+// kernels / this one): 16 lookahead rows 131600 901 / 758, 200000 1368 / 853, 262144 1800 / 1033, paged 200000 1515 / 1001, 8-bit keys
+// 150000 878 / 805, 262144 1591 / 884; 24 x 4 heads of 128, eight query heads each, 66000 812 / 600, 131072 1587 / 905.
 bool pair_applies(const Plan &p, bool fp8, int64_t L, int64_t k_stride_token)
 {
-    if (!fused_base_shape(p) || p.NB != 1 || k_stride_token > (int64_t(1) << 20)) return false;
+    if (!fused_shape_ok(p) || k_stride_token > (int64_t(1) << 20)) return false;
     const int cus = std::min(256, device_compute_units());
     const int64_t tiles = sp::ceil_div(L, fused_tile(p));
     return cus >= 128 && tiles > (fp8 && p.D == 64 ? cus + cus / 8 : cus) && tiles <= 2 * (int64_t)cus;
@@ -1415,6 +1416,8 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
                                              : plan_fused_prompt(p, total, desc->k_stride_token, bg));
     int ranges = 1;
     const bool big = fused_big(p);
+    if (pair && big)            // no exchange area of their own: see fused_big
+        pair = sp_fused::workspace_bytes(p.rows_pad, (int)sp::ceil_div(total, 2 * fused_tile(p)), 1) <= w.split - w.part;
     if (fused && !captured && bg.groups.size() == 1) {
         // the exchange area of a launch in layer ranges takes the place of the general path's buffers
         ranges = fused_ranges(p, bg.wgs[0], bg.groups[0].n, w.split - w.part);
@@ -1452,8 +1455,9 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
             if (pair) {
                 f.tile_keys = 2 * fused_tile(p);
                 f.n_wg = (int)sp::ceil_div(total, f.tile_keys);
-                rs = clear_and_look(1, ws + w.fused);
-                if (rs == SP_OK) rs = sp_fused::launch(f, kp, nullptr, true, clear, ws + w.fused, err, st);
+                char *const area = ws + (big ? w.part : w.fused);
+                rs = clear_and_look(1, area);
+                if (rs == SP_OK) rs = sp_fused::launch(f, kp, nullptr, true, clear, area, err, st);
             } else if (ranges > 1) {
                 const sp_fused::GroupTable t = split_layers(bg.groups[0], p.n_layers, ranges);
                 f.n_wg = bg.wgs[0] * ranges;

@@ -1546,11 +1546,11 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
 {
     static_assert(!W || (NB == 1 && !M::kFixed), "head_dim 128: one block of lookahead rows");
     constexpr bool BIG = W && NB * GB == 2;
-    static_assert(!BIG || (!PAIR && !F8), "head_dim 128, two blocks of query rows: bf16 keys, one tile a workgroup");
+    static_assert(!BIG || !F8, "head_dim 128, two blocks of query rows: bf16 keys");
     constexpr bool LATE = PAIR && !W && !F8 && NB * GB == 1;
     using MP = typename std::conditional<LATE, LateMap, Map<BIG>>::type;
     static_assert(!F8 || KIND != kExtra, "8-bit keys: contiguous keys of one prompt");
-    static_assert(!PAIR || (NB == 1 && KIND != kRanges), "pairs of tiles: whole prompts, one block of lookahead rows");
+    static_assert(!PAIR || KIND != kRanges, "pairs of tiles: whole prompts");
     constexpr bool EXTRA = KIND != kPlain, RANGES = KIND == kRanges;
     constexpr int kSI = F8 ? kSubInstr / 2 : kSubInstr;
     constexpr uint32_t kElem = F8 ? 1u : 2u;
@@ -1868,7 +1868,7 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
     using Draft16 = Draft16x32x8<16, 0>;
     using Draft8 = Draft16x32x8<8, 0>;
     const int blocks = a.n_nblk * 10 + a.n_gblk;
-    if (a.head_dim == 2 * kD ? blocks != 11 && (blocks != 12 || a.kscale || pair) : blocks != 11 && blocks != 12 && blocks != 21)
+    if (a.head_dim == 2 * kD ? blocks != 11 && (blocks != 12 || a.kscale) : blocks != 11 && blocks != 12 && blocks != 21)
         return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, head_dim %d: %d x %d row blocks", a.head_dim, a.n_nblk, a.n_gblk);
     if (a.kscale != nullptr && extra && !(ranges && a.look == nullptr && a.block_table == nullptr))
         return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, 8-bit keys: one prompt, contiguous keys only");
@@ -1878,17 +1878,24 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
     const bool draft = a.head_dim == kD && a.n_layers == 16 && a.n_q_heads == 32 && a.n_kv_heads == 8 && a.k_stride_token == kD &&
                        a.c == kScaleEighthLog2e && a.inv_c == 1.0f / kScaleEighthLog2e;
     if (pair) {
-        if (gt.n > 0 || a.n_nblk != 1)
-            return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, two tiles a workgroup: one prompt, up to 8 lookahead rows");
+        if (gt.n > 0)
+            return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, two tiles a workgroup: one prompt");
         if (a.kscale != nullptr) {
             if (a.head_dim == 2 * kD) SP_FUSED(1, 1, kPlain, AnyModel, true, true, true);
             else if (blocks == 12) SP_FUSED(1, 2, kPlain, AnyModel, false, true, true);
+            else if (blocks == 21 && draft && a.n_q == 16) SP_FUSED(2, 1, kPlain, Draft16, false, true, true);
+            else if (blocks == 21) SP_FUSED(2, 1, kPlain, AnyModel, false, true, true);
             else SP_FUSED(1, 1, kPlain, AnyModel, false, true, true);
         } else
-        if (a.head_dim == 2 * kD && extra) SP_FUSED(1, 1, kExtra, AnyModel, true, false, true);
+        if (a.head_dim == 2 * kD && blocks == 12 && extra) SP_FUSED(1, 2, kExtra, AnyModel, true, false, true);
+        else if (a.head_dim == 2 * kD && blocks == 12) SP_FUSED(1, 2, kPlain, AnyModel, true, false, true);
+        else if (a.head_dim == 2 * kD && extra) SP_FUSED(1, 1, kExtra, AnyModel, true, false, true);
         else if (a.head_dim == 2 * kD) SP_FUSED(1, 1, kPlain, AnyModel, true, false, true);
         else if (blocks == 12 && extra) SP_FUSED(1, 2, kExtra, AnyModel, false, false, true);
         else if (blocks == 12) SP_FUSED(1, 2, kPlain, AnyModel, false, false, true);
+        else if (blocks == 21 && extra) SP_FUSED(2, 1, kExtra, AnyModel, false, false, true);
+        else if (blocks == 21 && draft && a.n_q == 16) SP_FUSED(2, 1, kPlain, Draft16, false, false, true);
+        else if (blocks == 21) SP_FUSED(2, 1, kPlain, AnyModel, false, false, true);
         else if (extra) SP_FUSED(1, 1, kExtra, AnyModel, false, false, true);
         else if (draft && a.n_q == 8) SP_FUSED(1, 1, kPlain, Draft8, false, false, true);
         else SP_FUSED(1, 1, kPlain, AnyModel, false, false, true);

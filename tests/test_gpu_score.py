@@ -380,6 +380,16 @@ def test_score_in_layer_ranges_matches_oracle(shape):
         assert run(mode, nhd, "NHD").tobytes() == got.tobytes()
 
 
+def test_two_tiles_a_workgroup_want_room_for_the_exchange():
+    """Two blocks of query rows at head_dim 128 exchange in the general path's buffers, which are too small with one phase."""
+    from gpu_util import assert_scores_close, gpu_score, score_path
+    w = small_workload("pair_no_room", 1, 8, 1, 128, 8, 70000, cfg_id=690, hh=(1, 1000))
+    inp = synth.make_score_inputs(w)
+    got = gpu_score(inp["q"][0], inp["k"], w.scale, 0)
+    assert score_path() == "general"
+    assert_scores_close(got, oracle.score(inp["q"][0], inp["k"], w.scale, 0))
+
+
 # More than one tile per compute unit: a workgroup owns two.
 PAIR_SHAPES = [
     # name, Lyr, H, Hkv, d, n_q, L, page_tokens (0: contiguous keys, also with lookahead keys)
@@ -392,6 +402,15 @@ PAIR_SHAPES = [
     ("pair_paged_second_tile_empty", 2, 4, 1, 64, 8, 131072 + 500, 512),
     ("pair_paged_d128_tail", 1, 4, 2, 128, 8, 70000, 4096),
     ("pair_draft_model", 16, 32, 8, 64, 8, 131072 + 777, 0),
+    # two blocks of query rows: more than eight lookahead rows, five to eight heads a kv head of 128
+    ("pair_rows64", 2, 4, 1, 64, 16, 131073, 0),
+    ("pair_rows64_padding", 1, 3, 1, 64, 11, 200001, 0),
+    ("pair_rows64_paged", 2, 4, 1, 64, 9, 131072 + 500, 512),
+    ("pair_rows64_full_grid", 1, 4, 2, 64, 16, 262144, 0),
+    ("pair_rows64_draft_model", 16, 32, 8, 64, 16, 131072 + 777, 0),
+    ("pair_d128_g8", 3, 8, 1, 128, 8, 65537, 0),
+    ("pair_d128_g5_padding_full_grid", 4, 5, 1, 128, 5, 131072, 0),
+    ("pair_d128_g8_paged", 3, 8, 1, 128, 8, 70000, 4096),
 ]
 
 
@@ -562,6 +581,9 @@ STAND_IN_SHAPES = [
     ("fp8_ranges", "fp8", 16, 32, 8, 64, 8, [30000]),
     ("fp8_direct_d128", "fp8", 28, 16, 8, 128, 8, [1700]),
     ("fp8_pair", "fp8", 2, 4, 1, 64, 8, [147457]),
+    ("pair_rows64", "prompt", 2, 4, 1, 64, 16, [131073]),
+    ("pair_d128_g8", "prompt", 3, 8, 1, 128, 8, [70000]),
+    ("fp8_pair_rows64", "fp8", 2, 4, 1, 64, 16, [147457]),
 ]
 
 

@@ -56,6 +56,9 @@ FP8_SHAPES = [
     ("fp8_ranges_16_rows64", 16, 32, 8, 64, 16, 8190),
     ("fp8_ranges_4_rows64", 16, 32, 8, 64, 16, 30000),
     ("fp8_ranges_4_two_gblocks", 16, 32, 4, 64, 8, 30000),
+    ("fp8_pair_rows64", 2, 4, 1, 64, 16, 147457),
+    ("fp8_pair_rows64_padding_full_grid", 1, 3, 1, 64, 10, 262144),
+    ("fp8_pair_rows64_draft_model", 16, 32, 8, 64, 16, 147457 + 99),
 ]
 
 # The kernels the shapes of layer ranges and of two tiles a workgroup take (see gpu_util.score_path); three kernels below the
@@ -66,6 +69,8 @@ FP8_PATHS = {
     "fp8_pair_two_gblocks": "general", "fp8_pair_d128": (2, 1, 1, "stand-in"), "fp8_pair_first_length": (2, 1, 1, "stand-in"),
     "fp8_pair_two_gblocks_full_grid": (2, 1, 1, "stand-in"), "fp8_ranges_16_rows64": (1, 16, 1, "stand-in"),
     "fp8_ranges_4_rows64": (1, 4, 1, "stand-in"), "fp8_ranges_4_two_gblocks": (1, 4, 1, "stand-in"),
+    "fp8_pair_rows64": (2, 1, 1, "stand-in"), "fp8_pair_rows64_padding_full_grid": (2, 1, 1, "stand-in"),
+    "fp8_pair_rows64_draft_model": (2, 1, 1, "stand-in"),
 }
 
 
