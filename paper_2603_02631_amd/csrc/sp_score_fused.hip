@@ -1059,12 +1059,24 @@ struct Walk {
 // that are certainly issued behind the ones it needs.
 // KIND (see there): the plain variant carries none of the others' code or registers.
 template <int NB, int GB, int SLOT, int PAR, Kind KIND, bool W, bool F8, bool PAIR>
-__device__ __forceinline__ void step(const FusedArgs &a, const LayerPtrs &kp, const GroupTable &gt, int s, int n_phases, Ring &ring,
+__device__ __forceinline__ void step(const FusedArgs &args, const LayerPtrs &kp, const GroupTable &gt, int s, int n_phases, Ring &ring,
                                      Acc<NB> (&accs)[PAIR ? 2 : 1], const LaneConst &lc, Walk &wk, unsigned char *lds, uint32_t lds0,
                                      uint64_t wave_off, const int (&r_ranges)[PAIR ? 2 : 1])
 {
     constexpr bool EXTRA = KIND != kPlain, RANGES = KIND == kRanges, BIG = W && NB * GB == 2;
     using MP = Map<BIG>;
+    // Two blocks of query rows in layer ranges: the compiler keeps what the four unrolled steps compute from these values alive
+    // across the loop, 160 to 210 scalars in vector lanes, of which a step read some 250 back, each behind wait states before
+    // it can be an address. Opaque copies make every step compute them again (90 to 115 scalars; at head_dim 128 from the
+    // pointers and strides on). Whole passes: 20001 tokens of 24 x 4 heads of 128 142.0 -> 135.9 us, 30000 201.2 -> 195.0; 16 x 8
+    // heads of 64, 16 lookahead rows 40000 tokens 190.9 -> 184.1, token-major 20000 119.0 -> 114.8, 8-bit keys 20000 129.2 -> 124.8.
+    // With one block the step waits for memory, and the added instructions cost 1 %; pointers as well at head_dim 64: 1 %.
+    FusedArgs a = args;
+    if constexpr (RANGES && NB * GB == 2) {
+        __asm__ volatile("" : "+s"(a.n_wg), "+s"(a.ent_w0), "+s"(a.ent_n), "+s"(a.p_idx), "+s"(a.n_gp), "+s"(a.phase0));
+        if constexpr (BIG) __asm__ volatile("" : "+s"(a.part), "+s"(a.lse), "+s"(a.q), "+s"(a.k_stride_token), "+s"(a.k_stride_head),
+                                                 "+s"(a.group), "+s"(a.n_q), "+s"(a.rows_pad));
+    }
     // Other lane-derived values are recomputed every step instead of being kept in registers across
     // the whole loop (the opaque copy stops the compiler from hoisting them).
     int tid = threadIdx.x;
