@@ -26,15 +26,18 @@
 // inside one chunk or on a boundary whose chunks on both sides are all selected,
 // r(t) = the largest rank among them. Kept tokens at k = #{t : r(t) < k}: a
 // histogram of r and a prefix sum give the count for every k at once.
+// Up to 8192 chunks the tokens need not wait for the ranks: whether a token's number is the smallest or the largest
+// rank among some chunks, it is the rank of one of them, which their scores tell as well.
 //   sp_chunk_kernel       also leaves the chunk boundaries' character offsets in a
-//                         compact array and clears the counters of the next two;
-//   sp_rank_kernel        rank of every chunk by counting: tiles of 256 chunks
-//                         against tiles of 64 chunks, one workgroup per pair;
-//   sp_token_rank_kernel  one thread per target token: binary search of the
-//                         compact boundary array, r(t), histogram;
-//   sp_budget_select_kernel  one workgroup: prefix sum, largest k within the
-//                         budget, and the chunks of rank < k with their spans.
-// Beyond 8192 chunks the last one is two: sp_budget_kernel for k, and
+//                         compact array and clears the counters of the next one;
+//   sp_rank_tokens_kernel  some workgroups: rank of every chunk by counting, tiles of 1024
+//                         chunks against tiles of 64; the others: one thread per target token,
+//                         binary search of the compact boundary array, the chunk whose rank is
+//                         r(t), histogram by chunk;
+//   sp_budget_select_kernel  one workgroup: histogram by rank, prefix sum, largest k within
+//                         the budget, and the chunks of rank < k with their spans.
+// Beyond 8192 chunks ranks (sp_rank_kernel) and tokens (sp_token_rank_kernel, histogram by
+// rank) are two launches, and so is the last one: sp_budget_kernel for k, and
 // sp_topk_kernel as above, reading k from device memory.
 #include "sp_common.hpp"
 
@@ -550,16 +553,15 @@ constexpr int kRankThreads = 256;
 constexpr int kMaxBudgetChunks = 1 << 16;
 
 // rank[j] = number of chunks that come before chunk j in the order (score descending, index
-// ascending). Workgroup (x, y) counts, for the 256 chunks of tile x, the 64 chunks of tile y that come
-// before them and adds the counts to rank (cleared beforehand): C^2 comparisons over C^2 / 2^14
-// workgroups (2048 chunks: 256; with tiles of 256 x 256 they were 64, and 8.4 us).
+// ascending). A workgroup counts, for the THREADS chunks of tile x, the 64 chunks of tile y that come
+// before them and adds the counts to rank (cleared beforehand): C^2 comparisons over
+// C^2 / (64 THREADS) workgroups (2048 chunks; with square tiles of 256 it took 8.4 us).
 constexpr int kRankTile = 64;
-__global__ __launch_bounds__(kRankThreads) void sp_rank_kernel(const float *__restrict__ cs, int n_chunks,
-                                                               int32_t *__restrict__ rank)
+template <int THREADS>
+__device__ __forceinline__ void rank_tile(const float *__restrict__ cs, int n_chunks, int32_t *__restrict__ rank, int x, int y, uint4 *tile)
 {
-    __shared__ uint4 tile[kRankTile / 4];
-    const int j = blockIdx.x * kRankThreads + threadIdx.x;
-    const int base = blockIdx.y * kRankTile;
+    const int j = x * THREADS + threadIdx.x;
+    const int base = y * kRankTile;
     // entries past the last chunk get key 0, the image of no finite score: they never count
     if (threadIdx.x < kRankTile)
         reinterpret_cast<uint32_t *>(tile)[threadIdx.x] = base + (int)threadIdx.x < n_chunks ? order_key(cs[base + threadIdx.x]) : 0u;
@@ -579,6 +581,13 @@ __global__ __launch_bounds__(kRankThreads) void sp_rank_kernel(const float *__re
     if (before) atomicAdd(&rank[j], before);
 }
 
+__global__ __launch_bounds__(kRankThreads) void sp_rank_kernel(const float *__restrict__ cs, int n_chunks,
+                                                               int32_t *__restrict__ rank)
+{
+    __shared__ uint4 tile[kRankTile / 4];
+    rank_tile<kRankThreads>(cs, n_chunks, rank, blockIdx.x, blockIdx.y, tile);
+}
+
 // First boundary index in [lo, hi] whose offset is > x (STRICT) or >= x; hi + 1 if none.
 template <bool STRICT>
 __device__ __forceinline__ int first_boundary(const int64_t *bnd, int lo, int hi, int64_t x)
@@ -592,58 +601,92 @@ __device__ __forceinline__ int first_boundary(const int64_t *bnd, int lo, int hi
     return a;
 }
 
-// LDS: the boundaries' offsets (up to kLdsBounds of them) are staged, so that the searches do not go to memory for
-// every step (2048 chunks: a search is 11 dependent loads).
+// The chunks that decide about a target token of characters [a, b): any(j) is called for each of which one
+// has to be selected, or all(j) for each of those that have to be selected together, or neither (kept by no selection).
+template <class Any, class All>
+__device__ __forceinline__ void deciding_chunks(const int64_t *bnd, int C, int64_t a, int64_t b, const Any &any, const All &all)
+{
+    if (b > a) {
+        // chunks j with a < e[j+1] and b > e[j]: a contiguous range
+        for (int j = first_boundary<true>(bnd, 1, C, a) - 1; j < C && bnd[j] < b; ++j) any(j);
+        return;
+    }
+    const int m1 = first_boundary<false>(bnd, 0, C, a);                            // first boundary >= a
+    if (m1 > C || m1 < 1) return;
+    if (bnd[m1] != a) { any(m1 - 1); return; }                                      // strictly inside chunk m1 - 1
+    const int m2 = first_boundary<true>(bnd, m1, C, a) - 1;                         // last boundary == a
+    if (m2 < C)
+        for (int j = m1 - 1; j <= m2; ++j) all(j);
+}
+
+// Neighbouring tokens mostly share their bin: the first lane of every run of equal bins within the
+// wave adds the run's length (integer counts: the histogram is the same in any order). bin < 0: no token.
+__device__ __forceinline__ void count_runs(int32_t *__restrict__ hist, int bin)
+{
+    const int lane = threadIdx.x & 63;
+    const int prev = __shfl_up(bin, 1);
+    const bool leader = lane == 0 || prev != bin;
+    const uint64_t leaders = __ballot(leader);
+    if (leader && bin >= 0) {
+        const uint64_t later = lane == 63 ? 0 : leaders >> (lane + 1);
+        const int run = later ? __ffsll((unsigned long long)later) : 64 - lane;
+        atomicAdd(&hist[bin], run);
+    }
+}
+
 constexpr int kTokenThreads = 1024;
-constexpr int kLdsBounds = 4097;
-template <bool LDS>
-__global__ __launch_bounds__(kTokenThreads) void sp_token_rank_kernel(const int64_t *__restrict__ g_bnd, int n_chunks,
+__global__ __launch_bounds__(kTokenThreads) void sp_token_rank_kernel(const int64_t *__restrict__ bnd, int n_chunks,
                                                                       const int64_t *__restrict__ toff, int64_t M,
                                                                       const int32_t *__restrict__ rank,
                                                                       int32_t *__restrict__ hist)
 {
-    __shared__ int64_t s_bnd[LDS ? kLdsBounds : 1];
     const int64_t t = (int64_t)blockIdx.x * kTokenThreads + threadIdx.x;
+    int r = -1;
+    if (t < M) {
+        r = n_chunks;                            // kept by no selection
+        deciding_chunks(bnd, n_chunks, toff[t], toff[t + 1], [&](int j) { r = min(r, rank[j]); },
+                        [&](int j) { r = r == n_chunks ? rank[j] : max(r, rank[j]); });
+    }
+    count_runs(hist, r);
+}
+
+// Ranks and tokens in one launch, up to 8192 chunks: the first `rank_groups` workgroups count ranks, the others a
+// histogram of the tokens by the chunk whose rank decides about them. Bound by latency: with the tokens in a launch of
+// their own behind the ranks (4.2 and 4.5 us) a cut of 131072 tokens in 2048 chunks took 31.7 us with projection and
+// assembly, now 29.9.
+// LDS: the boundaries' offsets (up to kLdsBounds of them) are staged, so that the searches do not go to memory for
+// every step (2048 chunks: a search is 11 dependent loads).
+constexpr int kLdsBounds = 4097;
+template <bool LDS>
+__global__ __launch_bounds__(kTokenThreads) void sp_rank_tokens_kernel(const float *__restrict__ cs, const int64_t *__restrict__ g_bnd, int n_chunks,
+                                                                       const int64_t *__restrict__ toff, int64_t M, int rank_groups,
+                                                                       int32_t *__restrict__ rank, int32_t *__restrict__ hist)
+{
+    __shared__ int64_t s_bnd[LDS ? kLdsBounds : 1];
+    __shared__ uint4 tile[kRankTile / 4];
+    const int C = n_chunks;
+    if ((int)blockIdx.x < rank_groups) {
+        const int across = (C + kTokenThreads - 1) / kTokenThreads;
+        rank_tile<kTokenThreads>(cs, C, rank, blockIdx.x % across, blockIdx.x / across, tile);
+        return;
+    }
+    const int64_t t = (int64_t)(blockIdx.x - rank_groups) * kTokenThreads + threadIdx.x;
     const bool live = t < M;
     const int64_t a = live ? toff[t] : 0, b = live ? toff[t + 1] : 0;
-    const int C = n_chunks;
     if (LDS) {
         for (int i = threadIdx.x; i <= C; i += kTokenThreads) s_bnd[i] = g_bnd[i];
         __syncthreads();
     }
-    const int64_t *bnd = LDS ? s_bnd : g_bnd;
-    int r = C;                                   // bin C: kept by no selection
-    if (!live) {
-        r = -1;
-    } else if (b > a) {
-        // chunks j with a < e[j+1] and b > e[j]: a contiguous range
-        for (int j = first_boundary<true>(bnd, 1, C, a) - 1; j < C && bnd[j] < b; ++j) r = min(r, rank[j]);
-    } else {
-        const int m1 = first_boundary<false>(bnd, 0, C, a);                        // first boundary >= a
-        if (m1 <= C && m1 >= 1) {
-            if (bnd[m1] != a) {
-                r = rank[m1 - 1];                                                   // strictly inside chunk m1 - 1
-            } else {
-                const int m2 = first_boundary<true>(bnd, m1, C, a) - 1;             // last boundary == a
-                if (m2 < C) {                    // chunks m1-1 .. m2 all have to be selected
-                    int worst = 0;
-                    for (int j = m1 - 1; j <= m2; ++j) worst = max(worst, rank[j]);
-                    r = worst;
-                }
-            }
-        }
+    int bin = -1;
+    if (live) {
+        bin = C;
+        uint32_t key = 0;
+        // in ascending order of the chunks: of equal scores the first has the smallest rank and the last the largest
+        deciding_chunks(LDS ? s_bnd : g_bnd, C, a, b,
+                        [&](int j) { const uint32_t k = order_key(cs[j]); if (bin == C || k > key) { bin = j; key = k; } },
+                        [&](int j) { const uint32_t k = order_key(cs[j]); if (bin == C || k <= key) { bin = j; key = k; } });
     }
-    // Neighbouring tokens mostly share their bin: the first lane of every run of equal r within the
-    // wave adds the run's length (integer counts: the histogram is the same in any order).
-    const int lane = threadIdx.x & 63;
-    const int prev = __shfl_up(r, 1);
-    const bool leader = lane == 0 || prev != r;
-    const uint64_t leaders = __ballot(leader);
-    if (leader && r >= 0) {
-        const uint64_t later = lane == 63 ? 0 : leaders >> (lane + 1);
-        const int run = later ? __ffsll((unsigned long long)later) : 64 - lane;
-        atomicAdd(&hist[r], run);
-    }
+    count_runs(hist, bin);
 }
 
 // kept(k) = hist[0] + .. + hist[k-1]; writes the largest k in 1..C with kept(k) <= budget (1 if none)
@@ -687,8 +730,8 @@ __global__ __launch_bounds__(kTopkThreads) void sp_budget_kernel(const int32_t *
     }
 }
 
-// The same with the selection itself, for up to R * 1024 chunks: chunk i is kept iff rank[i] < k. A thread holds R
-// consecutive bins, so one block scan does for all of them.
+// The same with the selection itself, for up to R * 1024 chunks and a histogram by chunk: chunk i is kept iff
+// rank[i] < k. A thread holds the bins of R consecutive ranks, so one block scan does for all of them.
 template <int R>
 __global__ __launch_bounds__(kTopkThreads) void sp_budget_select_kernel(const int32_t *__restrict__ hist, const int32_t *__restrict__ rank,
                                                                         int n_chunks, int64_t budget, int chunk, int64_t L,
@@ -698,11 +741,21 @@ __global__ __launch_bounds__(kTopkThreads) void sp_budget_select_kernel(const in
 {
     __shared__ int wave_tot[kTopkThreads / 64], wave_ok[kTopkThreads / 64], wave_best[kTopkThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ int32_t by_rank[R * kTopkThreads];
     int h[R], mine[R], sum = 0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        h[r] = tid * R + r < n_chunks ? hist[tid * R + r] : 0;
-        mine[r] = r * kTopkThreads + tid < n_chunks ? rank[r * kTopkThreads + tid] : n_chunks;
+        const int i = r * kTopkThreads + tid;
+        h[r] = i < n_chunks ? hist[i] : 0;
+        mine[r] = i < n_chunks ? rank[i] : n_chunks;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (mine[r] < n_chunks) by_rank[mine[r]] = h[r];                  // ranks are a permutation of 0 .. n_chunks - 1
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        h[r] = tid * R + r < n_chunks ? by_rank[tid * R + r] : 0;
         sum += h[r];
     }
     int total;
@@ -1002,20 +1055,24 @@ extern "C" sp_status sp_select_budget(const float *scores_dev, int64_t L, int32_
                        dim3(kChunkThreads), 0, st, scores_dev, L, (int)pool_w, (int)chunk, C, cs, chunk_scores_dev,
                        draft_off_dev, bnd, rank, hist);
     SP_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(sp_rank_kernel, dim3((unsigned)sp::ceil_div(C, kRankThreads), (unsigned)sp::ceil_div(C, kRankTile)),
-                       dim3(kRankThreads), 0, st, (const float *)cs, (int)C, rank);
-    SP_HIP_CHECK(hipGetLastError());
-    const auto token_rank = C < kLdsBounds ? sp_token_rank_kernel<true> : sp_token_rank_kernel<false>;
-    hipLaunchKernelGGL(token_rank, dim3((unsigned)sp::ceil_div(M, kTokenThreads)), dim3(kTokenThreads), 0, st,
-                       (const int64_t *)bnd, (int)C, target_off_dev, M, (const int32_t *)rank, hist);
-    SP_HIP_CHECK(hipGetLastError());
     if (C <= 8 * kTopkThreads) {
+        const int64_t rank_groups = sp::ceil_div(C, kTokenThreads) * sp::ceil_div(C, kRankTile), token_groups = sp::ceil_div(M, kTokenThreads);
+        const auto rank_tokens = C < kLdsBounds ? sp_rank_tokens_kernel<true> : sp_rank_tokens_kernel<false>;
+        hipLaunchKernelGGL(rank_tokens, dim3((unsigned)(rank_groups + token_groups)), dim3(kTokenThreads), 0, st, (const float *)cs,
+                           (const int64_t *)bnd, (int)C, target_off_dev, M, (int)rank_groups, rank, hist);
+        SP_HIP_CHECK(hipGetLastError());
         const auto budget_select = C <= 2 * kTopkThreads ? sp_budget_select_kernel<2> : sp_budget_select_kernel<8>;
         hipLaunchKernelGGL(budget_select, dim3(1), dim3(kTopkThreads), 0, st, (const int32_t *)hist, (const int32_t *)rank, (int)C,
                            budget, (int)chunk, L, k_dev, n_kept_dev, sel_chunks_dev, spans_dev, n_spans_dev);
         SP_HIP_CHECK(hipGetLastError());
         return SP_OK;
     }
+    hipLaunchKernelGGL(sp_rank_kernel, dim3((unsigned)sp::ceil_div(C, kRankThreads), (unsigned)sp::ceil_div(C, kRankTile)),
+                       dim3(kRankThreads), 0, st, (const float *)cs, (int)C, rank);
+    SP_HIP_CHECK(hipGetLastError());
+    hipLaunchKernelGGL(sp_token_rank_kernel, dim3((unsigned)sp::ceil_div(M, kTokenThreads)), dim3(kTokenThreads), 0, st,
+                       (const int64_t *)bnd, (int)C, target_off_dev, M, (const int32_t *)rank, hist);
+    SP_HIP_CHECK(hipGetLastError());
     hipLaunchKernelGGL(sp_budget_kernel, dim3(1), dim3(kTopkThreads), 0, st, (const int32_t *)hist, (int)C, budget, k_dev,
                        n_kept_dev);
     SP_HIP_CHECK(hipGetLastError());

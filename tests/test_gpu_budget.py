@@ -120,3 +120,29 @@ def test_budget_full_size_benchmark_workload():
         more = oracle.project(doff, toff, oracle.merge(oracle.topk(cs64, k + 1), w.chunk, w.L))[2]
         assert more > budget
         say(f"[budget] {w.name}: budget {budget} of {M} -> k = {k} of {C}, kept {n_kept}; k + 1 keeps {more}")
+
+
+@pytest.mark.parametrize("C", [64, 65, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193])
+def test_budget_at_the_edges_of_its_kernels(C):
+    """Tiles of 1024 and 64 chunks, boundaries in LDS up to 4096 chunks, two or eight chunks a thread, ranks and tokens in
+    one launch up to 8192: few distinct scores, tokens and chunks without characters. Exact: the kept chunks are the top
+    k, they keep n_kept target tokens within the budget, and k + 1 would keep more than it."""
+    from gpu_util import gpu_select_budget
+    say(f"[budget] edges C={C}")
+    rng = np.random.default_rng(5300 + C)
+    chunk = 2
+    L = C * chunk - 1
+    lens = rng.integers(0, 4, size=L)
+    lens[L // 3:L // 3 + 4 * chunk] = 0                               # chunks without characters
+    doff = offsets_from_lengths(lens)
+    toff = split_same_text(rng, int(doff[-1]), 3, allow_zero=True)
+    M = toff.size - 1
+    scores = rng.integers(0, 6, size=L).astype(np.float32)
+    for budget in (M // 7, M // 2):
+        k, n_kept, sel, spans, cs = gpu_select_budget(scores, 1, chunk, doff, toff, budget)
+        cs = cs.astype(np.float64)
+        exact = oracle.topk(cs, k)
+        np.testing.assert_array_equal(sel.astype(np.int64), exact)
+        np.testing.assert_array_equal(spans, oracle.merge(exact, chunk, L))
+        assert oracle.project(doff, toff, spans)[2] == n_kept <= budget
+        assert oracle.project(doff, toff, oracle.merge(oracle.topk(cs, k + 1), chunk, L))[2] > budget
