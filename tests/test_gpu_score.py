@@ -523,6 +523,25 @@ def test_batch_of_several_launches_gives_up_as_a_whole(prompt):
         assert bool(torch.isfinite(s).all()) and 0.99 < float(s.double().sum()) < H
 
 
+@pytest.mark.parametrize("tiles", [[150, 106, 100, 100, 56], [200, 3, 60, 17, 2, 30]],
+                         ids=["only_first_fit_fits", "shared_out_evenly"])
+def test_batch_of_several_launches_matches_oracle(tiles):
+    """512 and 312 workgroups in two launches of at most 256: sharing them out evenly, longest prompt first, leaves no room
+    for the last prompt of the first batch."""
+    from gpu_util import assert_scores_close, gpu_score_batch, score_path
+    say(f"[score-batch] tiles {tiles}")
+    lengths = np.array([512 * t - 9 * i for i, t in enumerate(tiles)], dtype=np.int64)
+    w = dataclasses.replace(small_workload("launches", 1, 4, 1, 64, 8, 0, cfg_id=470 + len(tiles), hh=(1, 1000)), batch=len(tiles))
+    q = synth.gen_q(w, len(tiles))
+    ks = [synth.gen_k_layer(w, 0, q, lengths, synth.heavy_hitter_positions(w, lengths))]
+    offsets = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    got = gpu_score_batch(q, ks, offsets, w.scale, 0)
+    assert score_path()[:3] == (1, 1, 2)
+    for b in range(len(tiles)):
+        sl = slice(int(offsets[b]), int(offsets[b + 1]))
+        assert_scores_close(got[sl], oracle.score(q[b], [np.ascontiguousarray(ks[0][:, sl, :])], w.scale, 0))
+
+
 def test_batch_of_one_launch_gives_up_as_a_whole():
     """Two prompts of 64 workgroups each and a single (layer, kv head); the last workgroup of the second prompt is missing.
     What waits for its partial results gives up after some milliseconds, when workgroups of the first prompt are
