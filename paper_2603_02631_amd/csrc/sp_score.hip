@@ -930,7 +930,7 @@ struct BatchGroups {
     std::vector<int> wgs;
     int64_t tiles = 0;              // of all prompts
     bool short_prompt = false;      // one of them is shorter than a tile
-    bool shared = true;             // in every launch the duties can rotate over all prompts (see score_impl)
+    bool shared = true;             // in every launch of first fit the duties can rotate over all prompts (see score_impl)
 };
 
 bool duties_shared(const Plan &p, const BatchGroups &bg, size_t g)
@@ -938,11 +938,11 @@ bool duties_shared(const Plan &p, const BatchGroups &bg, size_t g)
     return !bg.short_prompt && bg.groups[g].n * (p.rows_pad / sp_fused::kDutyRows) <= bg.wgs[g];
 }
 
-bool plan_fused_batch(const Plan &p, const int64_t *offsets, int B, int64_t k_stride_token, BatchGroups &out)
+bool plan_fused_batch(const Plan &p, const int64_t *offsets, int B, int64_t k_stride_token, BatchGroups &out, int ranges = 1)
 {
     if (!fused_shape_ok(p) || k_stride_token > (int64_t(1) << 20)) return false;
-    const int cap = std::min(256, device_compute_units());
-    if (cap < sp_fused::kMinWorkgroups || offsets[B] < fused_tile(p)) return false;
+    const int units = std::min(256, device_compute_units()), cap = units / ranges, max_prompts = std::min(kMaxGroupPrompts, sp_fused::kMaxGroup / ranges);
+    if (units < sp_fused::kMinWorkgroups || offsets[B] < fused_tile(p)) return false;
     std::vector<std::pair<int, int>> order;        // (tiles, prompt)
     for (int b = 0; b < B; ++b) {
         const int64_t len = offsets[b + 1] - offsets[b];
@@ -954,7 +954,7 @@ bool plan_fused_batch(const Plan &p, const int64_t *offsets, int B, int64_t k_st
         out.tiles += (int)tiles;
     }
     std::stable_sort(order.begin(), order.end(), [](const std::pair<int, int> &x, const std::pair<int, int> &y) { return x.first > y.first; });
-    auto fits = [&](const BatchGroups &bg, size_t g, int tiles) { return bg.wgs[g] + tiles <= cap && bg.groups[g].n < kMaxGroupPrompts; };
+    auto fits = [&](const BatchGroups &bg, size_t g, int tiles) { return bg.wgs[g] + tiles <= cap && bg.groups[g].n < max_prompts; };
     auto add = [&](BatchGroups &bg, size_t g, const std::pair<int, int> &tp) {
         sp_fused::GroupTable &t = bg.groups[g];
         t.prompt[t.n] = tp.second;
@@ -1001,8 +1001,9 @@ bool plan_fused_batch(const Plan &p, const int64_t *offsets, int B, int64_t k_st
             if (to == even.groups.size()) return true;       // no room left for this one: as it was
             add(even, to, tp);
         }
-        even.shared = all_shared(even);
-        if (even.shared == out.shared) out = even;
+        if (out.shared && !all_shared(even)) return true;       // what is announced stays so
+        out.groups = even.groups;       // out.shared stays as well: it tells what is announced
+        out.wgs = even.wgs;
     }
     return true;
 }
@@ -1026,6 +1027,37 @@ int fused_ranges(const Plan &p, int tiles, int n_prompts, size_t room)
 bool whole_groups_pay(const BatchGroups &bg)
 {
     return bg.shared && bg.tiles >= sp_fused::kMinWorkgroups;
+}
+
+// A batch of several launches may do with fewer steps on more of them: launches of at most half the workgroups run their
+// layers as two ranges side by side, in half the steps. A launch costs the steps of a range and some nine more to
+// be launched, to fill and to drain; a step takes 2.05 us on up to 200 workgroups and 2.6 on 256, where HBM bounds it. Whole
+// passes, 16 x 8 phases of head_dim 64: 279 workgroups in nine prompts 606 -> 516 us, token-major 343 in fifteen 721 -> 585; 28 x 8 of head_dim
+// 128: 260 1028 -> 840, 298 in nine 1019 -> 790, in twelve 1073 -> 839.
+// Replaces `out` and tells the number of ranges; `w`: the call's workspace, which has to hold what a launch
+// exchanges and the ranges' results.
+int spread_batch(const Plan &p, const int64_t *offsets, int B, int64_t k_stride_token, const WsLayout &w, BatchGroups &out)
+{
+    if (out.groups.size() < 2) return 1;
+    const size_t result = sizeof(float) * (size_t)offsets[B] * (p.layer_agg == SP_LAYER_MAX ? 8 * p.NB : 1);      // of a range
+    auto time = [&](const BatchGroups &bg, int ranges) {
+        const int most = ranges * *std::max_element(bg.wgs.begin(), bg.wgs.end());
+        return (double)bg.groups.size() * (sp::ceil_div(p.n_layers, ranges) * (p.n_phases / p.n_layers) + 9) * std::max(0.8, most / 256.0);
+    };
+    int best = 1;
+    double least = 0.92 * time(out, 1);         // not for less than the model is worth
+    for (int ranges = 2; ranges <= std::min(4, p.n_layers) && ranges * result <= w.look - w.split; ++ranges) {
+        BatchGroups bg;
+        if (!plan_fused_batch(p, offsets, B, k_stride_token, bg, ranges) || bg.groups.size() < 2 || time(bg, ranges) >= least) continue;
+        bool room = true;
+        for (size_t g = 0; g < bg.groups.size(); ++g)
+            room &= sp_fused::workspace_bytes(p.rows_pad, bg.wgs[g] * ranges, bg.groups[g].n * ranges) <= w.split - w.part;
+        if (!room) continue;
+        least = time(bg, ranges);
+        best = ranges;
+        out = bg;
+    }
+    return best;
 }
 
 // Otherwise (few workgroups, or tiles that short prompts leave half empty): whether the single-launch kernel beats the
@@ -1448,7 +1480,9 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
         // the exchange area of a launch in layer ranges takes the place of the general path's buffers
         ranges = fused_ranges(p, bg.wgs[0], bg.groups[0].n, w.split - w.part);
     }
-    const bool announced = fused && !big && (batch ? whole_groups_pay(bg) : bg.wgs[0] >= fused_min_workgroups(p));
+    const bool announced_batch = fused && !big && batch && whole_groups_pay(bg);
+    if (fused && batch && !captured && bg.groups.size() > 1) ranges = spread_batch(p, offsets_host, B, desc->k_stride_token, w, bg);
+    const bool announced = fused && !big && (batch ? announced_batch : bg.wgs[0] >= fused_min_workgroups(p));
     if (fused && !announced)
         fused = !captured && (batch || ranges > 1 || bg.wgs[0] >= fused_min_workgroups(p)) && steps_pay(p, opt.kscale != nullptr, n_tiles * p.tile_keys, ranges, (int)bg.groups.size());
     if (fused && big)           // no exchange area of their own: see fused_big
@@ -1485,12 +1519,14 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
                 rs = clear_and_look(1, area);
                 if (rs == SP_OK) rs = sp_fused::launch(f, kp, nullptr, true, clear, area, err, st);
             } else if (ranges > 1) {
-                const sp_fused::GroupTable t = split_layers(bg.groups[0], p.n_layers, ranges);
-                f.n_wg = bg.wgs[0] * ranges;
                 f.split_out = a.split_buf;
                 f.split_stride = total;
-                rs = clear_and_look(t.n, ws + w.part);
-                if (rs == SP_OK) rs = sp_fused::launch(f, kp, &t, false, clear, ws + w.part, err, st);
+                for (size_t g = 0; g < bg.groups.size() && rs == SP_OK; ++g) {
+                    const sp_fused::GroupTable t = split_layers(bg.groups[g], p.n_layers, ranges);
+                    f.n_wg = bg.wgs[g] * ranges;
+                    rs = clear_and_look(t.n, ws + w.part);
+                    if (rs == SP_OK) rs = sp_fused::launch(f, kp, &t, false, g > 0 ? Clear::kExchange : clear, ws + w.part, err, st);
+                }
             } else {
                 for (size_t g = 0; g < bg.groups.size() && rs == SP_OK; ++g) {
                     f.n_wg = bg.wgs[g];
@@ -1577,7 +1613,11 @@ extern "C" int32_t sp_score_batch_is_fused(const sp_score_desc *desc, const int6
     for (int b = 0; b < B; ++b)
         if (offsets_host[b + 1] < offsets_host[b]) return -1;
     BatchGroups bg;
-    return fused_base_shape(p) && plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg) && whole_groups_pay(bg) ? (int32_t)bg.groups.size() : 0;
+    if (!fused_base_shape(p) || !plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg) || !whole_groups_pay(bg)) return 0;
+    int64_t n_tiles = 0;
+    for (int b = 0; b < B; ++b) n_tiles += sp::ceil_div(offsets_host[b + 1] - offsets_host[b], p.tile_keys);
+    (void)spread_batch(p, offsets_host, B, desc->k_stride_token, ws_layout(p, n_tiles, B), bg);
+    return (int32_t)bg.groups.size();
 }
 
 extern "C" sp_status sp_score(const sp_score_desc *desc, const void *q_dev, const void *const *k_layers_host,

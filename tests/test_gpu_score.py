@@ -542,6 +542,28 @@ def test_batch_of_several_launches_matches_oracle(tiles):
         assert_scores_close(got[sl], oracle.score(q[b], [np.ascontiguousarray(ks[0][:, sl, :])], w.scale, 0))
 
 
+@pytest.mark.parametrize("d,tiles,last,path", [(64, [90, 70, 50, 40, 12], 512, (1, 2, 3)),
+                                               (128, [80, 60, 0, 50, 40, 35], 100, (1, 2, 3, "stand-in"))], ids=["announced", "short_prompt_d128"])
+def test_batch_in_layer_ranges_on_several_launches(d, tiles, last, path):
+    """Batches of a little more than one launch: three launches of two layer ranges instead of two of one; the second batch
+    ends with a prompt shorter than a tile."""
+    from gpu_util import assert_scores_close, gpu_score_batch, score_path
+    say(f"[score-batch] ranges on several launches, d={d} tiles={tiles}")
+    tile, Lyr, Hkv = 32768 // d, 6, 8
+    lengths = np.array([tile * t - 5 * (t > 0) for t in tiles] + [last], dtype=np.int64)
+    w = dataclasses.replace(small_workload("spread", Lyr, 2 * Hkv, Hkv, d, 8, 0, cfg_id=480 + d, hh=(1, 1000)), batch=len(lengths))
+    q = synth.gen_q(w, len(lengths))
+    ks = [synth.gen_k_layer(w, l, q, lengths, synth.heavy_hitter_positions(w, lengths)) for l in range(Lyr)]
+    offsets = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    for mode in (0, 1):
+        got = gpu_score_batch(q, ks, offsets, w.scale, mode)
+        assert score_path() == path
+        for b in ((0, len(lengths) - 1) if mode else range(len(lengths))):
+            sl = slice(int(offsets[b]), int(offsets[b + 1]))
+            if lengths[b]:
+                assert_scores_close(got[sl], oracle.score(q[b], [np.ascontiguousarray(k[:, sl, :]) for k in ks], w.scale, mode))
+
+
 def test_batch_of_one_launch_gives_up_as_a_whole():
     """Two prompts of 64 workgroups each and a single (layer, kv head); the last workgroup of the second prompt is missing.
     What waits for its partial results gives up after some milliseconds, when workgroups of the first prompt are
