@@ -185,10 +185,12 @@ enum Kind {
 // 1110, sixteen prompts 999 -> 1001; layer ranges 8192 tokens 55.9 -> 59.3 (a range's workgroups on one die). Duties go by
 // block, so that the workgroups of a phase's duties sit on all dies (with them by tile 262144 tokens took 841).
 template <Kind KIND, bool W, bool F8>
+constexpr bool tiles_by_die = KIND == kPlain && !W && !F8;
+template <Kind KIND, bool W, bool F8>
 __device__ __forceinline__ int workgroup_index(int n_wg)
 {
     const int b = (int)blockIdx.x, die = b & 7;
-    return KIND == kPlain && !W && !F8 ? die * (n_wg >> 3) + min(die, n_wg & 7) + (b >> 3) : b;
+    return tiles_by_die<KIND, W, F8> ? die * (n_wg >> 3) + min(die, n_wg & 7) + (b >> 3) : b;
 }
 
 struct Ring {
@@ -1071,8 +1073,9 @@ __device__ __forceinline__ void step(const FusedArgs &args, const LayerPtrs &kp,
     // pointers and strides on). Whole passes: 20001 tokens of 24 x 4 heads of 128 142.0 -> 135.9 us, 30000 201.2 -> 195.0; 16 x 8
     // heads of 64, 16 lookahead rows 40000 tokens 190.9 -> 184.1, token-major 20000 119.0 -> 114.8, 8-bit keys 20000 129.2 -> 124.8.
     // With one block the step waits for memory, and the added instructions cost 1 %; pointers as well at head_dim 64: 1 %.
-    FusedArgs a = args;
-    if constexpr (RANGES && NB * GB == 2) {
+    constexpr bool kRecompute = RANGES && NB * GB == 2;
+    typename std::conditional<kRecompute, FusedArgs, const FusedArgs &>::type a = args;
+    if constexpr (kRecompute) {
         __asm__ volatile("" : "+s"(a.n_wg), "+s"(a.ent_w0), "+s"(a.ent_n), "+s"(a.p_idx), "+s"(a.n_gp), "+s"(a.phase0));
         if constexpr (BIG) __asm__ volatile("" : "+s"(a.part), "+s"(a.lse), "+s"(a.q), "+s"(a.k_stride_token), "+s"(a.k_stride_head),
                                                  "+s"(a.group), "+s"(a.n_q), "+s"(a.rows_pad));
@@ -1255,7 +1258,7 @@ __device__ __forceinline__ void step(const FusedArgs &args, const LayerPtrs &kp,
                 wk.dfirst += duty_blocks;
                 if (wk.dfirst >= duty_n) wk.dfirst -= duty_n;
             }
-            const int blk = (int)blockIdx.x - duty_w0 - wk.dfirst;
+            const int blk = (tiles_by_die<KIND, W, F8> ? (int)blockIdx.x : w) - duty_w0 - wk.dfirst;
             wk.duty_blk = blk < 0 ? blk + duty_n : blk;
             if (pd_next < 0 || pd_next >= n_phases || wk.duty_blk >= duty_blocks || direct) wk.duty_blk = -1;
         };
