@@ -107,6 +107,7 @@ struct Map {
     static constexpr int kXduty = kCinit + 2 * kMaxRowsF * 4;      // 8 KB: partials of the duty rows (direct exchange: of all rows)
     static constexpr int kXlse = kXduty + 8192;                    // 1 KB: normaliser entries of one phase, 1 KB: lookahead-key terms
     static constexpr int kFail = kXlse + 2048;
+    static constexpr int kSeeded = kFail + 4;                      // step_prob_last: phase whose seeds are in kCinit, plus one
     static constexpr int kKring = (kFail + 16 + 1023) / 1024 * 1024;   // [8 waves][slots][32 rows x 128 bytes]
     static constexpr int kSlotsPerWave = BIG ? 2 : kSubSlots;
     static constexpr int kBytes = kKring + kFWaves * kSlotsPerWave * kSubBytes;
@@ -289,6 +290,58 @@ __device__ __forceinline__ void lift_k_and_q(const LaneConst &lc, uint32_t koff0
         kf[0][t] = __builtin_bit_cast(bf16x8, r[t]);
         kf[1][t] = __builtin_bit_cast(bf16x8, r[4 + t]);
         qf[t] = __builtin_bit_cast(bf16x8, r[8 + t]);
+    }
+}
+
+// head_dim 128: both halves of a 32-row Q block in one round trip to LDS, with the seeds or the K tile that go with it.
+template <int QOFF>
+__device__ __forceinline__ void lift_q_wide_and_seed(const LaneConst &lc, uint32_t seed_ad, bf16x8 (&q0)[kKS], bf16x8 (&q1)[kKS], f32x16 &seed)
+{
+    typedef __attribute__((ext_vector_type(4))) float f32x4;
+    u32x4 r[8];
+    f32x4 c[4];
+    __asm__ volatile(
+        "ds_read_b128 %8, %16\n\tds_read_b128 %9, %16 offset:16\n\tds_read_b128 %10, %16 offset:32\n\tds_read_b128 %11, %16 offset:48\n\t"
+        "ds_read_b128 %0, %12 offset:%17\n\tds_read_b128 %1, %13 offset:%17\n\t"
+        "ds_read_b128 %2, %14 offset:%17\n\tds_read_b128 %3, %15 offset:%17\n\t"
+        "ds_read_b128 %4, %12 offset:%17+4096\n\tds_read_b128 %5, %13 offset:%17+4096\n\t"
+        "ds_read_b128 %6, %14 offset:%17+4096\n\tds_read_b128 %7, %15 offset:%17+4096\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7]),
+          "=&v"(c[0]), "=&v"(c[1]), "=&v"(c[2]), "=&v"(c[3])
+        : "v"(lc.ld[0]), "v"(lc.ld[1]), "v"(lc.ld[2]), "v"(lc.ld[3]), "v"(seed_ad), "i"(QOFF) : "memory");
+#pragma unroll
+    for (int t = 0; t < kKS; ++t) {
+        q0[t] = __builtin_bit_cast(bf16x8, r[t]);
+        q1[t] = __builtin_bit_cast(bf16x8, r[4 + t]);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) { seed[4 * v] = c[v].x; seed[4 * v + 1] = c[v].y; seed[4 * v + 2] = c[v].z; seed[4 * v + 3] = c[v].w; }
+}
+// The K tile's two halves (run-time slot offsets) and both halves of a Q block.
+template <int QOFF>
+__device__ __forceinline__ void lift_k_and_q_wide(const LaneConst &lc, uint32_t koff0, uint32_t koff1, bf16x8 (&kf)[kNS][kKS],
+                                                  bf16x8 (&q0)[kKS], bf16x8 (&q1)[kKS])
+{
+    u32x4 r[16];
+    uint32_t a0[kKS], a1[kKS];
+#pragma unroll
+    for (int t = 0; t < kKS; ++t) { a0[t] = lc.ld[t] + koff0; a1[t] = lc.ld[t] + koff1; }
+    __asm__ volatile(
+        "ds_read_b128 %0, %16\n\tds_read_b128 %1, %17\n\tds_read_b128 %2, %18\n\tds_read_b128 %3, %19\n\t"
+        "ds_read_b128 %8, %24 offset:%28\n\tds_read_b128 %9, %25 offset:%28\n\tds_read_b128 %10, %26 offset:%28\n\tds_read_b128 %11, %27 offset:%28\n\t"
+        "ds_read_b128 %4, %20\n\tds_read_b128 %5, %21\n\tds_read_b128 %6, %22\n\tds_read_b128 %7, %23\n\t"
+        "ds_read_b128 %12, %24 offset:%28+4096\n\tds_read_b128 %13, %25 offset:%28+4096\n\t"
+        "ds_read_b128 %14, %26 offset:%28+4096\n\tds_read_b128 %15, %27 offset:%28+4096\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7]),
+          "=&v"(r[8]), "=&v"(r[9]), "=&v"(r[10]), "=&v"(r[11]), "=&v"(r[12]), "=&v"(r[13]), "=&v"(r[14]), "=&v"(r[15])
+        : "v"(a0[0]), "v"(a0[1]), "v"(a0[2]), "v"(a0[3]), "v"(a1[0]), "v"(a1[1]), "v"(a1[2]), "v"(a1[3]),
+          "v"(lc.ld[0]), "v"(lc.ld[1]), "v"(lc.ld[2]), "v"(lc.ld[3]), "i"(QOFF) : "memory");
+#pragma unroll
+    for (int t = 0; t < kKS; ++t) {
+        kf[0][t] = __builtin_bit_cast(bf16x8, r[t]);
+        kf[1][t] = __builtin_bit_cast(bf16x8, r[4 + t]);
+        q0[t] = __builtin_bit_cast(bf16x8, r[8 + t]);
+        q1[t] = __builtin_bit_cast(bf16x8, r[12 + t]);
     }
 }
 
@@ -1321,6 +1374,192 @@ __device__ __forceinline__ void step(const FusedArgs &args, const LayerPtrs &kp,
     lds_barrier();
 }
 
+// The step of one prompt of head_dim 128, one tile a workgroup, one block of query rows, bf16 keys, where the prompt
+// fills the device (see launch): the probability pass comes last. The order of `step` has the normalisers back three steps
+// after their partials; with K streaming at the rate of HBM two trips through memory take about that long, and whoever
+// finds them missing polls behind its own tile loads. Here the tile of a step waits in registers of its own (head_dim 64
+// has none left for that: with spills 50021 tokens took 237 us against 176) until the probability pass of the phase
+// four steps earlier has freed its place in the ring, and the normalisers have two thirds of a step more:
+//   top     publish the partials of phase s-1; the normaliser wave requests the normalisers of phase s-4; wait for K(s)
+//   lift    K(s); requests of the duty rows of phase s-2 and of Q
+//   stats   statistics pass of phase s; loads of the rows' second halves of K(s+1)
+//   duties  duty rows of phase s-2 combined; seeds of phase s-4, handed over through LDS without a barrier
+//   prob    probability pass of phase s-4; loads of the first halves of K(s+2); K(s) into its place in the ring
+//   barrier
+// Loads return in order: every wait counts the loads certainly issued behind what it needs. Whole passes of 28 x 8
+// phases: 50000 tokens 539 -> 521 us, 54000 578 -> 545, 60000 632 -> 594, 65536 692 -> 649, token-major 779 -> 733, paged 50000
+// 620 -> 551, lookahead keys 58000 624 -> 579.
+template <int SLOT, int PAR, Kind KIND>
+__device__ __forceinline__ void step_prob_last(const FusedArgs &a, const LayerPtrs &kp, int s, int n_phases, Ring &ring, Acc<1> &acc,
+                                               const LaneConst &lc, Walk &wk, unsigned char *lds, uint32_t lds0, uint64_t wave_off, int r_range)
+{
+    constexpr bool EXTRA = KIND != kPlain;
+    using MP = Map<false>;
+    int tid = threadIdx.x;
+    __asm__ volatile("" : "+v"(tid));
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, hf = lane >> 5;
+    const int w = blockIdx.x;
+    // phases: fetched, published, combined, of the next step's probability pass, of this one's
+    const int pf = s + 1, pp = s - 1, pd = s - 2, pl = s - kLag, pc = s - 1 - kLag;
+    const bool do_stats = s < n_phases, do_prob = pc >= 0 && pc < n_phases;
+    constexpr int kBlocks = 32 / kDutyRows, kWaveRows = kDutyRows / 2, kHalf = kSubInstr / 2, kWaveKeys = 32;
+    const uint32_t stride_bytes = (uint32_t)a.k_stride_token * 2u;
+    const int duty_blk = wk.duty_blk;
+    const bool duty_wave = (wave == kDutyWave || wave == kDutyWave + 2) && duty_blk >= 0;
+    const int duty_half = wave != kDutyWave ? 1 : 0;
+    const int duty_row = duty_blk * kDutyRows + duty_half * kWaveRows;
+    const uint32_t staging = lds0 + MP::kXduty + duty_half * 4096;
+    int *fail = reinterpret_cast<int *>(lds + MP::kFail);
+    const PhaseCtr c_now = wk.c;
+
+    // ---- top ----
+    const bool publishes = wave == kPubWave && pp >= 0 && pp < n_phases;
+    if (publishes) {
+        float pm[kFWaves], pl8[kFWaves];
+        read_wave_stats<kMaxRowsF * 8>(lds0 + MP::kWstats + (1 - PAR) * kWstatsBytes, lane, pm, pl8);
+        float m = neg_inf(), l = 0.f;
+#pragma unroll
+        for (int i = 0; i < kFWaves; ++i) m = fmaxf(m, pm[i]);
+#pragma unroll
+        for (int i = 0; i < kFWaves; ++i) l += pl8[i] * fast_exp2((pm[i] - m) * a.c);
+        if (lane < a.rows_pad)
+            st64(a.part + ((size_t)(pp % kSlots) * a.n_wg + w) * a.rows_pad + lane,
+                 (uint64_t)__float_as_uint(m) | ((uint64_t)__float_as_uint(l) << 32) | ((uint64_t)((pp / kSlots) & 1) << 63));
+    }
+    const bool seeds = wave == kLseWave && do_prob;
+    if (seeds)
+        stage_exchange_rows(lds0 + MP::kXlse, a.lse + (size_t)(pc % kSlots) * a.rows_pad,
+                            EXTRA && a.look != nullptr ? a.look + (size_t)pc * a.rows_pad : nullptr, a.rows_pad, lane);
+    // the second halves of K(s): behind them the first halves of K(s+1), and the store or the request just issued
+    if (publishes || seeds) vm_wait<kSubInstr + 1>(); else vm_wait<kSubInstr>();
+
+    // ---- lift, statistics pass ----
+    const uint32_t live1 = pf < n_phases ? 0xffffffffu : 0u, live2 = s + 2 < n_phases ? 0xffffffffu : 0u;      // past the last phase 16 bytes a load
+    const uint32_t voff1[2] = {lc.koff[0] & live1, lc.koff[1] & live1}, voff2[2] = {lc.koff[0] & live2, lc.koff[1] & live2};
+    const int slot0 = wk.slot0;
+    int slot_next = slot0 + 2;
+    slot_next = slot_next >= kSubSlots ? slot_next - kSubSlots : slot_next;
+    KIssue k1, k0;
+    k1.lds_dst = lds0 + sub_slot_off<false>(wave, slot_next, 1);          // where the first halves of K(s) are
+    k1.base = wk.kptr + kD * 2;
+    k1.step_bytes = 8u * stride_bytes;
+    auto requests = [&]() {
+        if (duty_wave)
+            stage_duty_rows<kWaveRows, EXTRA>(staging, a.part + (size_t)(pd % kSlots) * a.n_wg * a.rows_pad, a.rows_pad, a.n_wg, duty_row, lane);
+        if (lc.qoff[0] >= 0) {
+            const uint32_t qblock = (uint32_t)(a.group * a.n_q * kD * 4);
+            const char *q1src = reinterpret_cast<const char *>(a.q) + (uint32_t)min(pf, n_phases - 1) * qblock;
+            const char *q2src = reinterpret_cast<const char *>(a.q) + (uint32_t)clampi(pl, 0, n_phases - 1) * qblock;
+            dma_u<MP::kQ1 + (1 - PAR) * MP::kQTileBytes>((uint32_t)lc.qoff[0], q1src, lds0 + wave * 1024);
+            dma_u<MP::kQ2 + PAR * MP::kQTileBytes>((uint32_t)lc.qoff[0], q2src, lds0 + wave * 1024);
+        }
+    };
+    auto advance = [&]() {               // scalar state of the next step, as in `step`
+        if (s + 2 < n_phases) {
+            wk.kptr += (uint64_t)a.k_stride_head * 2u;
+            if (__builtin_expect(++wk.k.kv == a.n_kv_heads, 0)) {
+                wk.k.kv = 0;
+                ++wk.k.layer;
+                wk.kptr = reinterpret_cast<const char *>(kp.p[wk.k.layer]) + wave_off;
+            }
+        }
+        phase_advance(wk.c, pc + 1, n_phases, a.n_kv_heads);
+        wk.slot0 = slot_next;
+        if (pd + 1 > 0 && pd + 1 < n_phases) {
+            wk.dfirst += kBlocks;
+            if (wk.dfirst >= a.n_wg) wk.dfirst -= a.n_wg;
+        }
+        const int blk = w - wk.dfirst;
+        wk.duty_blk = blk < 0 ? blk + a.n_wg : blk;
+        if (pd + 1 < 0 || pd + 1 >= n_phases || wk.duty_blk >= kBlocks) wk.duty_blk = -1;
+    };
+    bf16x8 kf[kNS][kKS];
+    if (do_stats) {
+        const int lo = (r_range & 0xffff) - wave * kWaveKeys, hi = EXTRA ? (r_range >> 16) - wave * kWaveKeys : kWaveKeys;
+        bf16x8 q0[kKS], q1[kKS];
+        lift_k_and_q_wide<MP::kQ1 + PAR * MP::kQTileBytes>(lc, sub_slot_off<false>(wave, slot0, 0), sub_slot_off<false>(wave, slot0, 1), kf, q0, q1);
+        requests();
+        f32x16 d = logits32(kf[0], q0);
+#pragma unroll
+        for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][t], q1[t], d, 0, 0, 0);
+        advance();
+        k_issue<kHalf>(k1, voff1, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        float m = neg_inf(), l = 0.f;
+        fold_logits<true>(d, m, l, a.c, lo, hi, hf);
+        store_row_stats(lds0 + MP::kWstats + PAR * kWstatsBytes + wave * (kMaxRowsF * 8) + ((uint32_t)(lane & 31) << 3), m, l, a.c, hf);
+        k_issue<kHalf>(k1, voff1, kHalf);
+    } else {
+        requests();
+        advance();
+        k_issue<kSubInstr>(k1, voff1, 0);
+#pragma unroll
+        for (int i = 0; i < kNS; ++i)
+#pragma unroll
+            for (int t = 0; t < kKS; ++t) kf[i][t] = ring.kf[SLOT][i][t];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- duties, seeds: their data was requested before the loads of the statistics pass ----
+    if (duty_wave) {
+        vm_wait<kSubInstr>();
+        combine_rows<1, kWaveRows, EXTRA, false>(a, staging, pd, duty_row, 0, a.n_wg, 0, a.c, fail, lane);
+    } else if (seeds) {
+        vm_wait<kSubInstr>();
+        if (lane < a.rows_pad) {
+            int g, n;
+            float v = neg_inf();
+            if (row_valid<1>(a, lane, g, n)) {
+                const uint64_t *src = a.lse + (size_t)(pc % kSlots) * a.rows_pad + lane;
+                uint64_t entry = read_lse_staging(lds0 + MP::kXlse, lane);
+                if ((uint32_t)(entry >> 32) != (uint32_t)(pc + 1) && *fail == 0) {
+                    unsigned spins = 0;
+                    while ((uint32_t)(entry >> 32) != (uint32_t)(pc + 1)) {
+                        if ((uint32_t)(entry >> 32) == kPoisonTag || ++spins > a.spin_max) { raise_failure(a, fail); break; }
+                        entry = ld64(src);
+                    }
+                }
+                v = __uint_as_float((uint32_t)entry);
+                if (EXTRA && a.look != nullptr) {
+                    const float lp = -v, lk = read_look_staging(lds0 + MP::kXlse + kOffXlook, lane), top = fmaxf(lp, lk);
+                    v = -(top + fast_log2(fast_exp2((lp - top) * a.c) + fast_exp2((lk - top) * a.c)) * a.inv_c);
+                }
+            }
+            lds_store_f32(lds0 + MP::kCinit + 4u * (uint32_t)(((lane >> 2) & 1) * 16 + 4 * (lane >> 3) + (lane & 3)), v);
+        }
+        __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        lds_store_u32(lds0 + MP::kSeeded, (uint32_t)(pc + 1));
+    }
+
+    // ---- probability pass ----
+    k0.lds_dst = lds0 + sub_slot_off<false>(wave, slot0, 1);              // where the second halves of K(s) were
+    k0.base = wk.kptr;
+    k0.step_bytes = k1.step_bytes;
+    if (do_prob) {
+        while (lds_load_u32(lds0 + MP::kSeeded) != (uint32_t)(pc + 1)) __builtin_amdgcn_s_sleep(1);      // set in this step, whatever the waits came to
+        bf16x8 q0[kKS], q1[kKS];
+        f32x16 d;
+        lift_q_wide_and_seed<MP::kQ2 + (1 - PAR) * MP::kQTileBytes>(lc, lds0 + MP::kCinit + ((uint32_t)(lane & 32) << 1), q0, q1, d);
+#pragma unroll
+        for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q0[t], ring.kf[SLOT][0][t], d, 0, 0, 0);
+        k_issue<kHalf>(k0, voff2, 0);
+#pragma unroll
+        for (int t = 0; t < kKS; ++t) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q1[t], ring.kf[SLOT][1][t], d, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc.mx[0][0][e] = max3(max3(d[e], d[4 + e], d[8 + e]), d[12 + e], acc.mx[0][0][e]);
+        k_issue<kHalf>(k0, voff2, kHalf);
+        if (c_now.kv == a.n_kv_heads - 1 && (a.layer_agg == SP_LAYER_MEAN || c_now.layer == a.n_layers - 1)) close_layer<1, 1>(acc, a.c);
+    } else {
+        k_issue<kSubInstr>(k0, voff2, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < kNS; ++i)
+#pragma unroll
+        for (int t = 0; t < kKS; ++t) ring.kf[SLOT][i][t] = kf[i][t];
+    vm_wait<2 * kSubInstr>();            // Q
+    lds_barrier();
+}
+
 // The step of two tiles a workgroup, one block of query rows, head_dim 64, bf16 keys. Half as many phases are in flight
 // as with one tile, and the exchange's two trips through memory, each behind what the compute units have requested of K,
 // take some 16000 cycles: with the order of `step` odd steps waited 5500 of their 9600 cycles for the normalisers. Here
@@ -1556,12 +1795,14 @@ __device__ __forceinline__ void fold_model_constants(FusedArgs &a)
 // flight, so the normalisers have to come back within four steps less the two of their own phase. In `step` duties are
 // therefore combined in the step in which the partials are published; step_late gives them the next one and takes the
 // probability pass last. One read of K instead of the general path's two.
-template <int NB, int GB, Kind KIND, class M, bool W = false, bool F8 = false, bool PAIR = false>
+// PROB_LAST: see step_prob_last.
+template <int NB, int GB, Kind KIND, class M, bool W = false, bool F8 = false, bool PAIR = false, bool PROB_LAST = false>
 __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, LayerPtrs kp, GroupTable gt)
 {
     static_assert(!W || (NB == 1 && !M::kFixed), "head_dim 128: one block of lookahead rows");
     constexpr bool BIG = W && NB * GB == 2;
     static_assert(!BIG || !F8, "head_dim 128, two blocks of query rows: bf16 keys");
+    static_assert(!PROB_LAST || (W && NB * GB == 1 && KIND != kRanges && !F8 && !PAIR), "head_dim 128, one block of query rows, whole prompts");
     constexpr bool LATE = PAIR && !W && !F8 && NB * GB == 1;
     using MP = typename std::conditional<LATE, LateMap, Map<BIG>>::type;
     static_assert(!F8 || KIND != kExtra, "8-bit keys: contiguous keys of one prompt");
@@ -1638,7 +1879,7 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
         for (int i = tid; i < 4 * MP::kQTileBytes / 16; i += kFThreads) z[i] = zero;
         float *ci = reinterpret_cast<float *>(lds + MP::kCinit);
         if (tid < (LATE ? 32 : 2 * kMaxRowsF)) ci[tid] = neg_inf();
-        if (tid < (LATE ? 2 : 1)) reinterpret_cast<int *>(lds + MP::kFail)[tid] = 0;       // LATE: and kSeeded
+        if (tid < (LATE || PROB_LAST ? 2 : 1)) reinterpret_cast<int *>(lds + MP::kFail)[tid] = 0;       // and kSeeded
     }
     __syncthreads();
 
@@ -1717,6 +1958,13 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     wk.kptr = reinterpret_cast<const char *>(kp.p[wk.k.layer]) + (uint64_t)wk.k.kv * (uint64_t)a.k_stride_head * kElem + wave_off;
     wk.c = phase_at(0, n_phases, a.n_kv_heads);
     wk.c.layer += layer0;
+    if constexpr (PROB_LAST) {           // the first halves of K(1)
+        KIssue ki;
+        ki.lds_dst = lds0 + sub_slot_off<BIG>(wave_u, 2, 0);
+        ki.base = wk.kptr;
+        ki.step_bytes = 8u * stride_bytes;
+        k_issue<kSubInstr>(ki, lc.koff, 0);
+    }
     wk.slot0 = 0;
     wk.dfirst = 0;
     wk.duty_blk = -1;
@@ -1732,6 +1980,13 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
             step_late<1, 1, KIND>(a, kp, s0 + 1, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
             step_late<2, 0, KIND>(a, kp, s0 + 2, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
             step_late<3, 1, KIND>(a, kp, s0 + 3, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+        }
+    } else if constexpr (PROB_LAST) {
+        for (int s0 = 0; s0 < n_steps; s0 += 4) {
+            step_prob_last<0, 0, KIND>(a, kp, s0 + 0, n_phases, ring, accs[0], lc, wk, lds, lds0, wave_off, r_ranges[0]);
+            step_prob_last<1, 1, KIND>(a, kp, s0 + 1, n_phases, ring, accs[0], lc, wk, lds, lds0, wave_off, r_ranges[0]);
+            step_prob_last<2, 0, KIND>(a, kp, s0 + 2, n_phases, ring, accs[0], lc, wk, lds, lds0, wave_off, r_ranges[0]);
+            step_prob_last<3, 1, KIND>(a, kp, s0 + 3, n_phases, ring, accs[0], lc, wk, lds, lds0, wave_off, r_ranges[0]);
         }
     } else {
         for (int s0 = 0; s0 < n_steps; s0 += 4) {
@@ -1927,6 +2182,11 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
         else if (blocks == 12) SP_FUSED(1, 2, kPlain, AnyModel, false, true);
         else SP_FUSED(1, 1, kPlain, AnyModel, false, true);
     } else if (a.head_dim == 2 * kD && blocks == 12) SP_FUSED_KINDS(1, 2, AnyModel, true);
+    // One prompt of head_dim 128 on most of the device. `step` / step_prob_last, 28 x 8 phases: 34000 tokens (133 workgroups) 461 /
+    // 463 us, 45000 (176) 492 / 494, 48000 (188) 507 / 510, 50000 (196) 539 / 521, 65536 (256) 692 / 649. Batches stay: 234
+    // workgroups of six prompts 558 / 568.
+    else if (a.head_dim == 2 * kD && gt.n == 0 && a.n_wg >= 192 && extra) SP_FUSED(1, 1, kExtra, AnyModel, true, false, false, true);
+    else if (a.head_dim == 2 * kD && gt.n == 0 && a.n_wg >= 192) SP_FUSED(1, 1, kPlain, AnyModel, true, false, false, true);
     else if (a.head_dim == 2 * kD) SP_FUSED_KINDS(1, 1, AnyModel, true);
     else if (draft && !extra && a.n_q == 16 && a.n_wg == 256) SP_FUSED(2, 1, kPlain, Draft16x32x8<16, 256>);
     else if (draft && !extra && a.n_q == 8 && a.n_wg == 256) SP_FUSED(1, 1, kPlain, Draft16x32x8<8, 256>);

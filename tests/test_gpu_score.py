@@ -456,6 +456,41 @@ def test_wide_query_groups_with_lookahead_and_paged_keys():
     assert score_path() == (1, 8, 1, "stand-in")
 
 
+@pytest.mark.parametrize("Lyr,H,Hkv,n_q,L", [(1, 4, 1, 8, 191 * 256 + 1), (1, 2, 2, 8, 50000), (3, 3, 1, 5, 60001), (5, 4, 2, 8, 49152 + 77),
+                                             (3, 8, 4, 8, 65536)])
+def test_long_prompt_of_head_dim_128_with_its_probabilities_last(Lyr, H, Hkv, n_q, L):
+    """From 192 workgroups on: fewer phases than are in flight, and several turns of the exchange ring; contiguous and paged
+    keys, lookahead keys, both aggregation modes; a call that gives up."""
+    import torch
+    import paper_2603_02631_amd as sp
+    from gpu_util import (DEV, assert_scores_close, dev_bits, gpu_score, gpu_score_look, gpu_score_paged, make_desc, make_paged, score_path,
+                          status_word, workspace)
+    say(f"[score-prob-last] Lyr={Lyr} H={H} Hkv={Hkv} n_q={n_q} L={L}")
+    w = small_workload("prob_last", Lyr, H, Hkv, 128, n_q, L, cfg_id=660 + Lyr, hh=(1, 1000))
+    inp = synth.make_score_inputs(w)
+    q, k = inp["q"][0], inp["k"]
+    pools, table = make_paged(k, 512, "HND", seed=w.cfg_id)
+    kl = synth.gen_look_keys(w, inp["q"])
+    for mode in (0, 1):
+        want = oracle.score(q, k, w.scale, mode)
+        got = gpu_score(q, k, w.scale, mode)
+        assert score_path()[:3] == (1, 1, 1)
+        assert_scores_close(got, want)
+        assert gpu_score(q, k, w.scale, mode).tobytes() == got.tobytes()
+        assert_scores_close(gpu_score_paged(q, pools, table, 512, L, w.scale, mode, "HND"), want)
+        assert_scores_close(gpu_score_look(q, k, kl, 1, w.scale, mode), oracle.score_look(q, k, kl, 1, w.scale, mode))
+    try:
+        sp.sp_debug_fused_giveup(4, 1)
+        desc = make_desc(Lyr, H, Hkv, 128, n_q, w.scale, 0, "HND", L)
+        ws, scores = workspace(sp.sp_score_workspace(desc, L, 1)), torch.zeros(L, device=DEV)
+        sp.sp_score(desc, dev_bits(q), [dev_bits(x) for x in k], L, scores, ws)
+        torch.cuda.synchronize()
+        assert status_word(ws) == 1 and bool(torch.isnan(scores).all())
+    finally:
+        sp.sp_debug_fused_giveup(1 << 20, 0)
+    assert_scores_close(gpu_score(q, k, w.scale, 1), want)
+
+
 def test_fused_score_gives_up_as_a_whole():
     """The bounded waits of the single-launch kernel, driven to give up from the host (the test hook
     makes the combining waves treat their partial results as never arriving, with a spin limit of a few
