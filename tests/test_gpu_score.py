@@ -660,6 +660,7 @@ STAND_IN_SHAPES = [
     ("pair_rows64", "prompt", 2, 4, 1, 64, 16, [131073]),
     ("pair_d128_g8", "prompt", 3, 8, 1, 128, 8, [70000]),
     ("fp8_pair_rows64", "fp8", 2, 4, 1, 64, 16, [147457]),
+    ("batch_ranges_on_several_launches", "batch", 6, 16, 8, 128, 8, [20480, 15360, 0, 12800, 10240, 8960, 100]),
 ]
 
 
