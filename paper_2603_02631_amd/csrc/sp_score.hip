@@ -1064,13 +1064,15 @@ int spread_batch(const Plan &p, const int64_t *offsets, int B, int64_t k_stride_
 // three-kernel path. A launch costs its steps (a range's phases and five more to fill and drain the pipeline); the three
 // kernels take the longer the more keys their tiles hold, `keys` with the empty places. Each variant has its line,
 // in MB of bf16 keys: `per_step` for each step, or `steep` for each step less `base` where the fixed cost of the three
-// launches counts. The lines were drawn where the kernels crossed before the single launch's steps became 5 to 25 %
-// shorter and short prompts lost their merge launch; the present kernels cross at or a little before them. Measured on
-// these (tokens: three kernels / single launch, us; * = the line still takes the slower one; 16 layers x 8 kv heads unless
-// noted):
-//   32 rows                      3000 32 / 34, 3600 36 / 36, 4600* 41 / 36, 6000 48 / 37, 9000 63 / 53, 12000 75 / 54; 28 layers,
+// launches counts. The lines of 32 rows lie where the present kernels cross (8-bit keys of head_dim 64 apart); the others
+// where they crossed before the single launch's steps became 5 to 25 % shorter and short prompts lost their merge launch;
+// the present kernels cross at or a little before them. Measured on these (tokens: three kernels / single launch, us; * =
+// the line still takes the slower one; 16 layers x 8 kv heads unless noted):
+//   32 rows                      3000 32 / 34, 3600 36 / 36, 4600 41 / 36, 6000 48 / 37, 9000 63 / 53, 12000 75 / 54; 28 layers,
 //                                head_dim 128: 700 33 / 34, 1000* 38 / 36, 1500 46 / 37; 4 x 4 heads, head_dim 128: 9000 29 / 29,
-//                                12000* 32 / 31; 30 prompts of 1100 .. 1500 271 / 175, 24 of 60 .. 4000 364 / 189
+//                                12000 32 / 31; 30 prompts of 1100 .. 1500 271 / 175, 24 of 60 .. 4000 364 / 189. Whole passes:
+//                                3900 51.1 / 51.4, 4200 54.0 / 50.3, 4850 56.5 / 50.6; 28 layers, 2800 57.2 / 52.2; 28 layers, head_dim
+//                                128: 1030 51.8 / 48.0, 1400 57.6 / 49.6; 16 layers, 2200 59.9 / 52.5
 //   64 rows, 9+ lookahead rows   3600 47 / 47, 4500* 51 / 48, 5000 53 / 49, 6200 58 / 51, 9000 75 / 79, 10100* 79 / 73, 12000 88 / 73,
 //                                16384 121 / 76; 24 prompts of 60 .. 4000 460 / 293, 30 of 1100 .. 1500 359 / 291
 //   64 rows, 5+ heads a kv head  4600 51 / 51, 6200 58 / 52, 9000 73 / 80, 12000* 86 / 74, 16384 117 / 78
@@ -1083,9 +1085,9 @@ bool steps_pay(const Plan &p, bool fp8, int64_t keys, int ranges, int launches)
 {
     struct Line { double per_step, steep, base; };
     const bool wide = p.rows_pad > 32;
-    const Line line = p.D == 128 ? (wide ? Line{8.0, 8.0, 0} : Line{6.3, 6.3, 0})
+    const Line line = p.D == 128 ? (wide ? Line{8.0, 8.0, 0} : fp8 ? Line{5.2, 5.2, 0} : Line{4.7, 4.7, 0})
                     : fp8        ? (wide ? Line{11.0, 12.4, 59} : Line{9.35, 13.2, 77})
-                    : !wide      ? Line{6.3, 6.3, 0}
+                    : !wide      ? Line{5.2, 5.2, 0}
                     : p.NB == 2  ? Line{8.0, 11.25, 68}
                                  : Line{9.4, 14.0, 91};
     const double steps = (double)launches * (sp::ceil_div(p.n_layers, ranges) * (p.n_phases / p.n_layers) + 5);

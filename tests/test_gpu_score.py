@@ -390,6 +390,28 @@ def test_two_tiles_a_workgroup_want_room_for_the_exchange():
     assert_scores_close(got, oracle.score(inp["q"][0], inp["k"], w.scale, 0))
 
 
+@pytest.mark.parametrize("d,Lyr,H,Hkv,lens,path", [
+    (64, 16, 32, 8, [4096], "general"), (64, 16, 32, 8, [4097], (1, 16, 1, "stand-in")), (128, 28, 16, 8, [1024], "general"),
+    (128, 28, 16, 8, [1025], (1, 28, 1, "stand-in")), (64, 16, 32, 8, [2000, 60, 0, 1500, 800], (1, 16, 1, "stand-in")),
+    (128, 28, 16, 8, [700, 1, 500, 257], (1, 14, 1, "stand-in"))])         # a launch's table holds 64 entries
+def test_shortest_calls_on_the_single_launch_kernel(d, Lyr, H, Hkv, lens, path):
+    """The last prompt on the three kernels, the first beyond it, and batches whose tiles hold as many keys."""
+    from gpu_util import assert_scores_close, gpu_score, gpu_score_batch, score_path
+    say(f"[score-line] d={d} Lyr={Lyr} lengths={lens}")
+    lengths = np.array(lens, dtype=np.int64)
+    w = dataclasses.replace(small_workload("line", Lyr, H, Hkv, d, 8, 0, cfg_id=560 + len(lens), hh=(1, 100)), batch=len(lengths))
+    q = synth.gen_q(w, len(lengths))
+    ks = [synth.gen_k_layer(w, l, q, lengths, synth.heavy_hitter_positions(w, lengths)) for l in range(Lyr)]
+    offsets = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    for mode in (0, 1):
+        got = gpu_score(q[0], ks, w.scale, mode) if len(lens) == 1 else gpu_score_batch(q, ks, offsets, w.scale, mode)
+        assert score_path() == path
+        for b, n in enumerate(lens):
+            if n:
+                sl = slice(int(offsets[b]), int(offsets[b + 1]))
+                assert_scores_close(got[sl], oracle.score(q[b], [np.ascontiguousarray(k[:, sl, :]) for k in ks], w.scale, mode))
+
+
 # More than one tile per compute unit: a workgroup owns two.
 PAIR_SHAPES = [
     # name, Lyr, H, Hkv, d, n_q, L, page_tokens (0: contiguous keys, also with lookahead keys)
