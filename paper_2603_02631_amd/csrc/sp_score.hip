@@ -29,6 +29,7 @@
 #include "sp_common.hpp"
 #include "sp_score_dev.hpp"
 #include "sp_score_fused.hpp"
+#include "sp_score_plan.hpp"
 
 #include <dlfcn.h>
 
@@ -41,11 +42,11 @@
 namespace {
 
 using namespace sp_dev;
+using namespace sp_plan;
 
 constexpr int kThreads = 256;
 constexpr int kWaves = 4;
 constexpr int kMaxPrompts = 4096;
-constexpr int kMaxGroupPrompts = 32;       // prompts one launch of the fused kernel serves
 constexpr size_t kLdsBudget = 64 * 1024;
 constexpr int kMaxLookRows = 224;           // padded query rows of the widest supported group
 constexpr int kProbTargetWgs = 1024;   // the prob pass splits layers until it has about this many workgroups
@@ -769,11 +770,6 @@ __global__ void sp_tiles_kernel(const int64_t *offsets, int n_prompts, int tile_
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-struct Plan {
-    int D, NS, NB, n_gblk, rows_pad, tile_keys, n_phases, n_layers, layer_agg;
-    size_t lds_bytes;
-};
-
 // Layers per workgroup of the prob pass: all of them once the tiles alone fill the device, and where a workgroup gets through
 // all phases of a short prompt in less time than the launch that adds up the ranges takes. Whole passes with ranges and
 // without: 2 layers x 2 kv heads of 64, 1024 tokens 26.2 / 23.8 us, 6000 (24 tiles) 29.4 / 28.9; of 128, 2500 (20 tiles) 28.8 / 28.7,
@@ -849,10 +845,6 @@ struct WsLayout {
     size_t status, part, lse, tiles, prompt_tiles, split, look, fused, total;
 };
 
-// Two blocks of query rows at head_dim 128 (bf16 keys, one tile a workgroup): their exchange area always takes the
-// place of the general path's buffers, so the workspace is as large as without them.
-bool fused_big(const Plan &p) { return p.D == 128 && p.NB == 1 && p.n_gblk == 2; }
-
 // Shapes the fused single-launch kernel can hold on chip (any L; the length test is separate).
 bool fused_shape_ok(const Plan &p)
 {
@@ -862,9 +854,7 @@ bool fused_shape_ok(const Plan &p)
 // The shapes sp_score_is_fused speaks of and the workspace reserves an exchange area for.
 bool fused_base_shape(const Plan &p) { return fused_shape_ok(p) && !fused_big(p); }
 
-// Keys a workgroup of the fused kernel owns: 512 at head_dim 64, 256 at head_dim 128 (twice the tile of
-// the two-pass path), and the fewest workgroups it is used with.
-int fused_tile(const Plan &p) { return p.D == 64 ? sp_fused::kTileKeys : sp_fused::kTileKeys / 2; }
+// The fewest workgroups the fused kernel is used with, all layers in one range.
 int fused_min_workgroups(const Plan &p) { return p.D == 64 ? sp_fused::kMinWorkgroups : sp_fused::kMinWorkgroupsWide; }
 
 int fused_workgroups(const Plan &p, int64_t L)
@@ -922,90 +912,9 @@ bool fused_applies_fp8(const Plan &p, const sp_score_desc *desc, int64_t L)
     return fp8_strides_ok(desc) && fused_applies(p, L, desc->k_stride_token);
 }
 
-// A ragged batch on the single-launch kernel: the prompts are packed into launches of at most one
-// workgroup per compute unit (first fit, longest first), each prompt with all its 512-key tiles in one
-// launch. Possible when every prompt fits a launch and the batch holds at least one tile of keys.
-struct BatchGroups {
-    std::vector<sp_fused::GroupTable> groups;
-    std::vector<int> wgs;
-    int64_t tiles = 0;              // of all prompts
-    bool short_prompt = false;      // one of them is shorter than a tile
-    bool shared = true;             // in every launch of first fit the duties can rotate over all prompts (see score_impl)
-};
-
 bool duties_shared(const Plan &p, const BatchGroups &bg, size_t g)
 {
     return !bg.short_prompt && bg.groups[g].n * (p.rows_pad / sp_fused::kDutyRows) <= bg.wgs[g];
-}
-
-bool plan_fused_batch(const Plan &p, const int64_t *offsets, int B, int64_t k_stride_token, BatchGroups &out, int ranges = 1)
-{
-    if (!fused_shape_ok(p) || k_stride_token > (int64_t(1) << 20)) return false;
-    const int units = std::min(256, device_compute_units()), cap = units / ranges, max_prompts = std::min(kMaxGroupPrompts, sp_fused::kMaxGroup / ranges);
-    if (units < sp_fused::kMinWorkgroups || offsets[B] < fused_tile(p)) return false;
-    std::vector<std::pair<int, int>> order;        // (tiles, prompt)
-    for (int b = 0; b < B; ++b) {
-        const int64_t len = offsets[b + 1] - offsets[b];
-        if (len == 0) continue;
-        out.short_prompt |= len < fused_tile(p);
-        const int64_t tiles = sp::ceil_div(len, fused_tile(p));
-        if (tiles > cap) return false;
-        order.emplace_back((int)tiles, b);
-        out.tiles += (int)tiles;
-    }
-    std::stable_sort(order.begin(), order.end(), [](const std::pair<int, int> &x, const std::pair<int, int> &y) { return x.first > y.first; });
-    auto fits = [&](const BatchGroups &bg, size_t g, int tiles) { return bg.wgs[g] + tiles <= cap && bg.groups[g].n < max_prompts; };
-    auto add = [&](BatchGroups &bg, size_t g, const std::pair<int, int> &tp) {
-        sp_fused::GroupTable &t = bg.groups[g];
-        t.prompt[t.n] = tp.second;
-        t.start[t.n] = offsets[tp.second];
-        t.len[t.n] = (int32_t)(offsets[tp.second + 1] - offsets[tp.second]);
-        t.layer0[t.n] = 0;
-        t.layers[t.n] = p.n_layers;
-        t.slice[t.n] = 0;
-        t.w0[t.n] = bg.wgs[g];
-        bg.wgs[g] += tp.first;
-        t.w0[++t.n] = bg.wgs[g];
-    };
-    auto all_shared = [&](const BatchGroups &bg) {
-        bool shared = true;
-        for (size_t g = 0; g < bg.groups.size(); ++g) shared &= duties_shared(p, bg, g);
-        return shared;
-    };
-    sp_fused::GroupTable empty;
-    std::memset(&empty, 0, sizeof empty);
-    out.groups.clear();
-    out.wgs.clear();
-    for (const auto &tp : order) {
-        size_t g = 0;
-        while (g < out.groups.size() && !fits(out, g, tp.first)) ++g;
-        if (g == out.groups.size()) {
-            out.groups.push_back(empty);
-            out.wgs.push_back(0);
-        }
-        add(out, g, tp);
-    }
-    out.shared = all_shared(out);
-    // First fit tells how many launches there are, and fills all but the last. Steps do not get shorter in proportion to a
-    // launch's workgroups (head_dim 64: 2.05 us on 144, 2.6 on 255, where HBM bounds them), so the same number of launches takes
-    // less time with the workgroups shared out evenly. Whole passes of 651 workgroups in three launches 995 -> 947 us, 279 in two
-    // 641 -> 606, 287 670 / 670; head_dim 128, 295 in two 1079 -> 1023, 260 1078 -> 1028.
-    if (out.groups.size() > 1) {
-        BatchGroups even = out;
-        even.groups.assign(out.groups.size(), empty);
-        even.wgs.assign(out.groups.size(), 0);
-        for (const auto &tp : order) {
-            size_t to = even.groups.size();
-            for (size_t g = 0; g < even.groups.size(); ++g)
-                if (fits(even, g, tp.first) && (to == even.groups.size() || even.wgs[g] < even.wgs[to])) to = g;
-            if (to == even.groups.size()) return true;       // no room left for this one: as it was
-            add(even, to, tp);
-        }
-        if (out.shared && !all_shared(even)) return true;       // what is announced stays so
-        out.groups = even.groups;       // out.shared stays as well: it tells what is announced
-        out.wgs = even.wgs;
-    }
-    return true;
 }
 
 // How many layer ranges a launch over all of `n_prompts` prompts is cut into: as many as its `tiles`
@@ -1020,98 +929,6 @@ int fused_ranges(const Plan &p, int tiles, int n_prompts, size_t room)
     while (n > 1 && sp_fused::workspace_bytes(p.rows_pad, tiles * n, n_prompts * n) > room) --n;
     if (n < 2) return 1;
     return (int)sp::ceil_div(p.n_layers, sp::ceil_div(p.n_layers, n));       // no empty range
-}
-
-// Batches the single-launch kernel takes whatever their size: every prompt fills a tile, no launch has more duty blocks
-// than workgroups, and one range of layers fills enough of the device.
-bool whole_groups_pay(const BatchGroups &bg)
-{
-    return bg.shared && bg.tiles >= sp_fused::kMinWorkgroups;
-}
-
-// A batch of several launches may do with fewer steps on more of them: launches of at most half the workgroups run their
-// layers as two ranges side by side, in half the steps. A launch costs the steps of a range and some nine more to
-// be launched, to fill and to drain; a step takes 2.05 us on up to 200 workgroups and 2.6 on 256, where HBM bounds it. Whole
-// passes, 16 x 8 phases of head_dim 64: 279 workgroups in nine prompts 606 -> 516 us, token-major 343 in fifteen 721 -> 585; 28 x 8 of head_dim
-// 128: 260 1028 -> 840, 298 in nine 1019 -> 790, in twelve 1073 -> 839.
-// Replaces `out` and tells the number of ranges; `w`: the call's workspace, which has to hold what a launch
-// exchanges and the ranges' results.
-int spread_batch(const Plan &p, const int64_t *offsets, int B, int64_t k_stride_token, const WsLayout &w, BatchGroups &out)
-{
-    if (out.groups.size() < 2) return 1;
-    const size_t result = sizeof(float) * (size_t)offsets[B] * (p.layer_agg == SP_LAYER_MAX ? 8 * p.NB : 1);      // of a range
-    auto time = [&](const BatchGroups &bg, int ranges) {
-        const int most = ranges * *std::max_element(bg.wgs.begin(), bg.wgs.end());
-        return (double)bg.groups.size() * (sp::ceil_div(p.n_layers, ranges) * (p.n_phases / p.n_layers) + 9) * std::max(0.8, most / 256.0);
-    };
-    int best = 1;
-    double least = 0.92 * time(out, 1);         // not for less than the model is worth
-    for (int ranges = 2; ranges <= std::min(4, p.n_layers) && ranges * result <= w.look - w.split; ++ranges) {
-        BatchGroups bg;
-        if (!plan_fused_batch(p, offsets, B, k_stride_token, bg, ranges) || bg.groups.size() < 2 || time(bg, ranges) >= least) continue;
-        bool room = true;
-        for (size_t g = 0; g < bg.groups.size(); ++g)
-            room &= sp_fused::workspace_bytes(p.rows_pad, bg.wgs[g] * ranges, bg.groups[g].n * ranges) <= w.split - w.part;
-        if (!room) continue;
-        least = time(bg, ranges);
-        best = ranges;
-        out = bg;
-    }
-    return best;
-}
-
-// Otherwise (few workgroups, or tiles that short prompts leave half empty): whether the single-launch kernel beats the
-// three-kernel path. A launch costs its steps (a range's phases and five more to fill and drain the pipeline); the three
-// kernels take the longer the more keys their tiles hold, `keys` with the empty places. Each variant has its line,
-// in MB of bf16 keys: `per_step` for each step, or `steep` for each step less `base` where the fixed cost of the three
-// launches counts. The lines of 32 rows lie where the present kernels cross (8-bit keys of head_dim 64 apart); the others
-// where they crossed before the single launch's steps became 5 to 25 % shorter and short prompts lost their merge launch;
-// the present kernels cross at or a little before them. Measured on these (tokens: three kernels / single launch, us; * =
-// the line still takes the slower one; 16 layers x 8 kv heads unless noted):
-//   32 rows                      3000 32 / 34, 3600 36 / 36, 4600 41 / 36, 6000 48 / 37, 9000 63 / 53, 12000 75 / 54; 28 layers,
-//                                head_dim 128: 700 33 / 34, 1000* 38 / 36, 1500 46 / 37; 4 x 4 heads, head_dim 128: 9000 29 / 29,
-//                                12000 32 / 31; 30 prompts of 1100 .. 1500 271 / 175, 24 of 60 .. 4000 364 / 189. Whole passes:
-//                                3900 51.1 / 51.4, 4200 54.0 / 50.3, 4850 56.5 / 50.6; 28 layers, 2800 57.2 / 52.2; 28 layers, head_dim
-//                                128: 1030 51.8 / 48.0, 1400 57.6 / 49.6; 16 layers, 2200 59.9 / 52.5
-//   64 rows, 9+ lookahead rows   3600 47 / 47, 4500* 51 / 48, 5000 53 / 49, 6200 58 / 51, 9000 75 / 79, 10100* 79 / 73, 12000 88 / 73,
-//                                16384 121 / 76; 24 prompts of 60 .. 4000 460 / 293, 30 of 1100 .. 1500 359 / 291
-//   64 rows, 5+ heads a kv head  4600 51 / 51, 6200 58 / 52, 9000 73 / 80, 12000* 86 / 74, 16384 117 / 78
-//   64 rows, head_dim 128        24 x 4 heads: 3000 50 / 52, 3600* 54 / 50, 4500 70 / 50; 24 prompts of 60 .. 4000 671 / 429
-//   8-bit keys, 32 rows          4500 35 / 38, 6000 43 / 38, 8192 49 / 38, 10000 56 / 56, 12000 62 / 55, 16400 86 / 73, 18000 95 / 74,
-//                                22000 105 / 94; 28 layers, head_dim 128 (32 rows): 1000 34 / 35, 1500 40 / 36, as with bf16 keys
-//   8-bit keys, 64 rows          6200 56 / 53, 9000 69 / 86, 12100 80 / 85, 13000 97 / 84, 16384 108 / 86, 18000* 122 / 113, 19000 124 / 113,
-//                                22000 137 / 142, 24500* 145 / 147, 30000 189 / 141 (no line has the crossing at 17600 as well)
-bool steps_pay(const Plan &p, bool fp8, int64_t keys, int ranges, int launches)
-{
-    struct Line { double per_step, steep, base; };
-    const bool wide = p.rows_pad > 32;
-    const Line line = p.D == 128 ? (wide ? Line{8.0, 8.0, 0} : fp8 ? Line{5.2, 5.2, 0} : Line{4.7, 4.7, 0})
-                    : fp8        ? (wide ? Line{11.0, 12.4, 59} : Line{9.35, 13.2, 77})
-                    : !wide      ? Line{5.2, 5.2, 0}
-                    : p.NB == 2  ? Line{8.0, 11.25, 68}
-                                 : Line{9.4, 14.0, 91};
-    const double steps = (double)launches * (sp::ceil_div(p.n_layers, ranges) * (p.n_phases / p.n_layers) + 5);
-    return (double)keys * p.n_phases * p.D * 2e-6 >= std::min(line.per_step * steps, line.steep * steps - line.base * launches);
-}
-
-// The table of a launch with every entry of `t` once per layer range.
-sp_fused::GroupTable split_layers(const sp_fused::GroupTable &t, int n_layers, int ranges)
-{
-    sp_fused::GroupTable r;
-    std::memset(&r, 0, sizeof r);
-    const int per_range = (int)sp::ceil_div(n_layers, ranges);
-    for (int s = 0; s < ranges; ++s)
-        for (int i = 0; i < t.n; ++i) {
-            r.prompt[r.n] = t.prompt[i];
-            r.start[r.n] = t.start[i];
-            r.len[r.n] = t.len[i];
-            r.layer0[r.n] = s * per_range;
-            r.layers[r.n] = std::min(per_range, n_layers - s * per_range);
-            r.slice[r.n] = s;
-            r.w0[r.n + 1] = r.w0[r.n] + t.w0[i + 1] - t.w0[i];
-            ++r.n;
-        }
-    return r;
 }
 
 // A single prompt on the single-launch kernel: a table of one entry.
@@ -1150,6 +967,16 @@ WsLayout ws_layout(const Plan &p, int64_t n_tiles, int n_prompts)
     }
     w.total = off;
     return w;
+}
+
+// A ragged batch on the single-launch kernel. `w`: the call's workspace, which has to hold what a launch exchanges
+// and the ranges' results.
+bool plan_fused_batch(const Plan &p, const int64_t *offsets, int B, int64_t keys, int64_t k_stride_token, const WsLayout &w, bool may_spread,
+                      BatchGroups &out)
+{
+    if (!fused_shape_ok(p) || k_stride_token > (int64_t(1) << 20)) return false;
+    const Limits lim{std::min(kMaxUnits, device_compute_units()), kMaxGroupPrompts, sp_fused::kMaxGroup, w.split - w.part, w.look - w.split};
+    return plan_batch(p, offsets, B, keys, lim, may_spread, out);
 }
 
 sp_status launch_reduce(const ScoreArgs &a, int n_splits, hipStream_t st)
@@ -1472,19 +1299,17 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     // and one that could not be ordered behind its neighbours, gives up early (see kYieldSpins) and is finished by a
     // launch that can do without that kernel.
     bool pair = may_fuse && !captured && !batch && pair_applies(p, opt.kscale != nullptr, total, desc->k_stride_token);
-    bool fused = may_fuse && !pair && (batch ? plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg)
+    bool fused = may_fuse && !pair && (batch ? plan_fused_batch(p, offsets_host, B, n_tiles * p.tile_keys, desc->k_stride_token, w, !captured, bg)
                                              : plan_fused_prompt(p, total, desc->k_stride_token, bg));
-    int ranges = 1;
     const bool big = fused_big(p);
     if (pair && big)            // no exchange area of their own: see fused_big
         pair = sp_fused::workspace_bytes(p.rows_pad, (int)sp::ceil_div(total, 2 * fused_tile(p)), 1) <= w.split - w.part;
+    int ranges = bg.ranges;
     if (fused && !captured && bg.groups.size() == 1) {
         // the exchange area of a launch in layer ranges takes the place of the general path's buffers
         ranges = fused_ranges(p, bg.wgs[0], bg.groups[0].n, w.split - w.part);
     }
-    const bool announced_batch = fused && !big && batch && whole_groups_pay(bg);
-    if (fused && batch && !captured && bg.groups.size() > 1) ranges = spread_batch(p, offsets_host, B, desc->k_stride_token, w, bg);
-    const bool announced = fused && !big && (batch ? announced_batch : bg.wgs[0] >= fused_min_workgroups(p));
+    const bool announced = fused && !big && (batch ? bg.announced : bg.wgs[0] >= fused_min_workgroups(p));
     if (fused && !announced)
         fused = !captured && (batch || ranges > 1 || bg.wgs[0] >= fused_min_workgroups(p)) && steps_pay(p, opt.kscale != nullptr, n_tiles * p.tile_keys, ranges, (int)bg.groups.size());
     if (fused && big)           // no exchange area of their own: see fused_big
@@ -1614,11 +1439,12 @@ extern "C" int32_t sp_score_batch_is_fused(const sp_score_desc *desc, const int6
     if (make_plan(desc, p) != SP_OK || !offsets_host || B < 1 || B > kMaxPrompts) return -1;
     for (int b = 0; b < B; ++b)
         if (offsets_host[b + 1] < offsets_host[b]) return -1;
-    BatchGroups bg;
-    if (!fused_base_shape(p) || !plan_fused_batch(p, offsets_host, B, desc->k_stride_token, bg) || !whole_groups_pay(bg)) return 0;
+    if (!fused_base_shape(p)) return 0;
     int64_t n_tiles = 0;
     for (int b = 0; b < B; ++b) n_tiles += sp::ceil_div(offsets_host[b + 1] - offsets_host[b], p.tile_keys);
-    (void)spread_batch(p, offsets_host, B, desc->k_stride_token, ws_layout(p, n_tiles, B), bg);
+    if (n_tiles > 0x7fffffff / 2) return 0;
+    BatchGroups bg;
+    if (!plan_fused_batch(p, offsets_host, B, n_tiles * p.tile_keys, desc->k_stride_token, ws_layout(p, n_tiles, B), true, bg) || !bg.announced) return 0;
     return (int32_t)bg.groups.size();
 }
 

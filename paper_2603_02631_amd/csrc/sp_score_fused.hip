@@ -2057,13 +2057,6 @@ void set_giveup(uint32_t spin_max, int32_t force_miss)
     g_force_miss.store(force_miss, std::memory_order_relaxed);
 }
 
-size_t exchange_words(int rows_pad, int n_wg, int n_entries) { return (size_t)kSlots * rows_pad * (n_wg + n_entries); }
-
-size_t workspace_bytes(int rows_pad, int n_wg, int n_prompts)
-{
-    return sp::align_up(sizeof(uint64_t) * exchange_words(rows_pad, n_wg, n_prompts), 256);
-}
-
 bool fits_one_per_cu()
 {
     int n1 = 0, n2 = 0;

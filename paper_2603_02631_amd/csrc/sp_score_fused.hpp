@@ -69,8 +69,11 @@ struct FusedArgs {
 };
 
 // 8-byte words of the exchange area of a launch of n_wg workgroups and n_entries entries (one prompt: 1).
-size_t exchange_words(int rows_pad, int n_wg, int n_entries);
-size_t workspace_bytes(int rows_pad, int n_wg, int n_prompts);
+inline size_t exchange_words(int rows_pad, int n_wg, int n_entries) { return (size_t)kSlots * rows_pad * (n_wg + n_entries); }
+inline size_t workspace_bytes(int rows_pad, int n_wg, int n_entries)
+{
+    return sp::align_up(sizeof(uint64_t) * exchange_words(rows_pad, n_wg, n_entries), 256);
+}
 
 // What the launch has to clear first: the exchange area and the status word (the first launch of a call), the area
 // only, or nothing, when an earlier launch on the stream has cleared both.
