@@ -238,6 +238,7 @@ inline int spread_batch(const Plan &p, const Batch &b, int64_t tokens, const Lim
     double least = 0.92 * model((double)best.wgs.size(), 1, best.most());         // not for less than the model is worth
     for (int ranges = 2; ranges <= std::min(kMaxSpread, p.n_layers) && ranges * result <= lim.results; ++ranges) {
         if (b.longest > lim.units / ranges) break;
+        if (sp::ceil_div(p.n_layers, sp::ceil_div(p.n_layers, ranges)) != ranges) continue;      // a range would be empty
         if (model((double)fewest_launches(b, lim, ranges), ranges, 0) >= least) continue;
         const int cap = lim.units / ranges, prompts = max_prompts(lim, ranges);
         const Packing k = pack(p, b, cap, prompts, first_fit(b, cap, prompts));

@@ -152,6 +152,27 @@ static void test_plans()
     EXPECT(launches > 1000 && spread > 300 && announced > 1000 && refused > 300);
 }
 
+// Small layer counts, of which some ranges would be empty (4 layers in three, 5, 6 or 9 in four), and launches of few prompts,
+// which several ranges suit better than with the device's own limits.
+static void test_ranges()
+{
+    std::mt19937 rng(13);
+    int spread = 0;
+    for (int n = 0; n < 40000; ++n) {
+        const int D = rng() % 2 ? 64 : 128;
+        const Plan p = shape(1 + (int)(rng() % 12), 1 + (int)(rng() % 8), 1 + (int)(rng() % 4), D, 8, (int)(rng() % 2));
+        Limits lim = device(64 + (int)(rng() % 193));
+        lim.prompts = 2 << rng() % 5;
+        lim.entries = 16 << rng() % 3;
+        const auto off = batch(rng, 1 + (int)(rng() % 60), 100, 100 * (1 + rng() % 300));
+        BatchGroups bg;
+        if (!plan_batch(p, off.data(), (int)off.size() - 1, keys_of(p, off), lim, true, bg)) continue;
+        check_plan(p, off, lim, bg);
+        spread += bg.ranges > 1;
+    }
+    EXPECT(spread > 1000);
+}
+
 static void test_cost()
 {
     // the documented maximum, of prompts that the three kernels take; best of some runs
@@ -187,6 +208,7 @@ int main(int argc, char **argv)
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "packing") test_packing();
     else if (what == "plans") test_plans();
+    else if (what == "ranges") test_ranges();
     else if (what == "cost") test_cost();
     else { std::printf("unknown test %s\n", what.c_str()); return 2; }
     std::printf(g_fail ? "plan driver: %d check(s) failed\n" : "plan driver: all checks passed\n", g_fail);
