@@ -971,12 +971,12 @@ WsLayout ws_layout(const Plan &p, int64_t n_tiles, int n_prompts)
 
 // A ragged batch on the single-launch kernel. `w`: the call's workspace, which has to hold what a launch exchanges
 // and the ranges' results.
-bool plan_fused_batch(const Plan &p, const int64_t *offsets, int B, int64_t keys, int64_t k_stride_token, const WsLayout &w, bool may_spread,
+bool plan_fused_batch(const Plan &p, const int64_t *offsets, int B, int64_t keys, int64_t k_stride_token, const WsLayout &w, Launches may,
                       BatchGroups &out)
 {
     if (!fused_shape_ok(p) || k_stride_token > (int64_t(1) << 20)) return false;
     const Limits lim{std::min(kMaxUnits, device_compute_units()), kMaxGroupPrompts, sp_fused::kMaxGroup, w.split - w.part, w.look - w.split};
-    return plan_batch(p, offsets, B, keys, lim, may_spread, out);
+    return plan_batch(p, offsets, B, keys, lim, may, out);
 }
 
 sp_status launch_reduce(const ScoreArgs &a, int n_splits, hipStream_t st)
@@ -1295,11 +1295,16 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     f.c = a.c; f.inv_c = a.inv_c; f.out_scale = a.out_scale;
     BatchGroups bg;
     const bool captured = may_fuse && capturing(st);
+    // On part of the device the ranges that would fill it only wait for each other. What is announced keeps its kernel
+    // where that has a compute unit for every workgroup of first fit, but they are spread over the XCDs without regard to the mask.
+    const int cus = captured || !may_fuse ? device_compute_units() : stream_compute_units(st);
+    const bool masked = cus < device_compute_units();
     // What sp_score_is_fused and sp_score_batch_is_fused announce may fail. Every other call on the single-launch kernel,
     // and one that could not be ordered behind its neighbours, gives up early (see kYieldSpins) and is finished by a
     // launch that can do without that kernel.
     bool pair = may_fuse && !captured && !batch && pair_applies(p, opt.kscale != nullptr, total, desc->k_stride_token);
-    bool fused = may_fuse && !pair && (batch ? plan_fused_batch(p, offsets_host, B, n_tiles * p.tile_keys, desc->k_stride_token, w, !captured, bg)
+    bool fused = may_fuse && !pair && (batch ? plan_fused_batch(p, offsets_host, B, n_tiles * p.tile_keys, desc->k_stride_token, w,
+                                                              masked ? Launches::kFirstFit : captured ? Launches::kEven : Launches::kRanges, bg)
                                              : plan_fused_prompt(p, total, desc->k_stride_token, bg));
     const bool big = fused_big(p);
     if (pair && big)            // no exchange area of their own: see fused_big
@@ -1315,10 +1320,6 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     if (fused && big)           // no exchange area of their own: see fused_big
         for (size_t g = 0; g < bg.groups.size(); ++g)
             fused = fused && sp_fused::workspace_bytes(p.rows_pad, bg.wgs[g], bg.groups[g].n) <= w.split - w.part;
-    // On part of the device the ranges that would fill it only wait for each other. What is announced keeps its kernel
-    // where that has a compute unit for every workgroup, but they are spread over the XCDs without regard to the mask.
-    const int cus = captured ? device_compute_units() : stream_compute_units(st);
-    const bool masked = cus < device_compute_units();
     if (masked) {
         pair = false;
         ranges = 1;
@@ -1444,7 +1445,7 @@ extern "C" int32_t sp_score_batch_is_fused(const sp_score_desc *desc, const int6
     for (int b = 0; b < B; ++b) n_tiles += sp::ceil_div(offsets_host[b + 1] - offsets_host[b], p.tile_keys);
     if (n_tiles > 0x7fffffff / 2) return 0;
     BatchGroups bg;
-    if (!plan_fused_batch(p, offsets_host, B, n_tiles * p.tile_keys, desc->k_stride_token, ws_layout(p, n_tiles, B), true, bg) || !bg.announced) return 0;
+    if (!plan_fused_batch(p, offsets_host, B, n_tiles * p.tile_keys, desc->k_stride_token, ws_layout(p, n_tiles, B), Launches::kRanges, bg) || !bg.announced) return 0;
     return (int32_t)bg.groups.size();
 }
 

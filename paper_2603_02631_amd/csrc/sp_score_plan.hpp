@@ -273,9 +273,13 @@ inline void fill_tables(const Plan &p, const int64_t *offsets, const Batch &b, c
     }
 }
 
+// What a batch of several launches may do: first fit only, even launches, or layer ranges as well. All three announce the
+// same batches.
+enum class Launches { kFirstFit, kEven, kRanges };
+
 // The launches of a ragged batch of a shape that the kernel holds; false where it has none or the three kernels are
-// certain to be faster. `keys`: of the three-kernel path's tiles. `may_spread`: several launches may run layer ranges.
-inline bool plan_batch(const Plan &p, const int64_t *offsets, int B, int64_t keys, const Limits &lim, bool may_spread, BatchGroups &out)
+// certain to be faster. `keys`: of the three-kernel path's tiles.
+inline bool plan_batch(const Plan &p, const int64_t *offsets, int B, int64_t keys, const Limits &lim, Launches may, BatchGroups &out)
 {
     if (lim.units < sp_fused::kMinWorkgroups || offsets[B] < fused_tile(p)) return false;
     Batch b;
@@ -284,8 +288,8 @@ inline bool plan_batch(const Plan &p, const int64_t *offsets, int B, int64_t key
     sort_prompts(p, offsets, B, b);
     const Packing first = first_fit(b, lim.units, lim.prompts);
     out.announced = announces(p, b, first);
-    Packing k = pack(p, b, lim.units, lim.prompts, first);
-    if (may_spread) out.ranges = spread_batch(p, b, offsets[B], lim, k);
+    Packing k = may == Launches::kFirstFit ? first : pack(p, b, lim.units, lim.prompts, first);
+    if (may == Launches::kRanges) out.ranges = spread_batch(p, b, offsets[B], lim, k);
     out.short_prompt = b.short_prompt;
     fill_tables(p, offsets, b, k, out);
     return true;

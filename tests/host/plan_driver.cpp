@@ -129,7 +129,7 @@ static void test_plans()
         const int64_t keys = keys_of(p, off);
         const Limits lim = device();
         BatchGroups bg, plain;
-        if (!plan_batch(p, off.data(), B, keys, lim, true, bg)) {
+        if (!plan_batch(p, off.data(), B, keys, lim, Launches::kRanges, bg)) {
             // refused before packing: then no number of launches and ranges is worth it
             Batch b;
             survey(p, off.data(), B, b);
@@ -146,8 +146,15 @@ static void test_plans()
         launches += bg.groups.size() > 1;
         spread += bg.ranges > 1;
         announced += bg.announced;
-        EXPECT(plan_batch(p, off.data(), B, keys, lim, false, plain) && plain.ranges == 1 && plain.announced == bg.announced);
-        check_plan(p, off, lim, plain);
+        for (Launches may : {Launches::kEven, Launches::kFirstFit}) {
+            plain = BatchGroups();
+            EXPECT(plan_batch(p, off.data(), B, keys, lim, may, plain) && plain.ranges == 1 && plain.announced == bg.announced);
+            check_plan(p, off, lim, plain);
+        }
+        Batch b;
+        survey(p, off.data(), B, b);
+        sort_prompts(p, off.data(), B, b);
+        EXPECT(plain.wgs == first_fit(b, lim.units, lim.prompts).wgs);
     }
     EXPECT(launches > 1000 && spread > 300 && announced > 1000 && refused > 300);
 }
@@ -166,7 +173,7 @@ static void test_ranges()
         lim.entries = 16 << rng() % 3;
         const auto off = batch(rng, 1 + (int)(rng() % 60), 100, 100 * (1 + rng() % 300));
         BatchGroups bg;
-        if (!plan_batch(p, off.data(), (int)off.size() - 1, keys_of(p, off), lim, true, bg)) continue;
+        if (!plan_batch(p, off.data(), (int)off.size() - 1, keys_of(p, off), lim, Launches::kRanges, bg)) continue;
         check_plan(p, off, lim, bg);
         spread += bg.ranges > 1;
     }
@@ -184,7 +191,7 @@ static void test_cost()
         for (int i = 0; i < 20; ++i) {
             BatchGroups bg;
             const auto t0 = std::chrono::steady_clock::now();
-            EXPECT(!plan_batch(p, off.data(), B, keys_of(p, off), device(), true, bg));
+            EXPECT(!plan_batch(p, off.data(), B, keys_of(p, off), device(), Launches::kRanges, bg));
             best = std::min(best, std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
         }
         std::printf("planning %d prompts of 60 to 90 tokens: %.1f us\n", B, best * 1e6);
@@ -196,7 +203,7 @@ static void test_cost()
     for (int i = 0; i < 20; ++i) {
         BatchGroups bg;
         const auto t0 = std::chrono::steady_clock::now();
-        EXPECT(plan_batch(p, off.data(), 4096, keys_of(p, off), device(), true, bg));
+        EXPECT(plan_batch(p, off.data(), 4096, keys_of(p, off), device(), Launches::kRanges, bg));
         best = std::min(best, std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
     }
     std::printf("planning 4096 prompts of 600 to 3000 tokens: %.1f us\n", best * 1e6);

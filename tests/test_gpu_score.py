@@ -957,6 +957,41 @@ def test_scores_on_a_stream_with_a_compute_unit_mask(shape):
     assert_scores_close(scores.cpu().numpy(), oracle.score(inp["q"][0], inp["k"], w.scale, 0))
 
 
+def test_batch_on_a_stream_with_a_compute_unit_mask():
+    """128 compute units and an announced batch whose first launch has more workgroups: neither even launches nor layer
+    ranges, which would fit, put it on the single-launch kernel there."""
+    import ctypes
+    import torch
+    import paper_2603_02631_amd as sp
+    from gpu_util import DEV, assert_scores_close, dev_bits, gpu_score_batch, make_desc, score_path, status_word, workspace
+    say("[score-mask] batch")
+    lengths = np.array([512 * t - 5 for t in (90, 70, 50, 40, 12)], dtype=np.int64)
+    w = dataclasses.replace(small_workload("mask", 6, 16, 8, 64, 8, 0, cfg_id=293, hh=(1, 1000)), batch=len(lengths))
+    q, T = synth.gen_q(w, len(lengths)), int(lengths.sum())
+    ks = [synth.gen_k_layer(w, l, q, lengths, synth.heavy_hitter_positions(w, lengths)) for l in range(6)]
+    offsets = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    gpu_score_batch(q, ks, offsets, w.scale, 0)
+    assert score_path()[:3] == (1, 2, 3)
+    desc = make_desc(6, 16, 8, 64, 8, w.scale, 0, "HND", T)
+    qd, kd, off_d = dev_bits(q), [dev_bits(k) for k in ks], torch.from_numpy(offsets).to(DEV)
+    scores, ws = torch.zeros(T, dtype=torch.float32, device=DEV), workspace(sp.sp_score_workspace(desc, T, len(lengths)))
+    torch.cuda.synchronize()
+    hip, stream = ctypes.CDLL("libamdhip64.so.7"), ctypes.c_void_p()
+    mask = (ctypes.c_uint32 * 8)(*[0xFFFFFFFF] * 4, *[0] * 4)
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), 8, mask) == 0
+    try:
+        sp.sp_score_batch(desc, qd, kd, [int(v) for v in offsets], off_d, scores, ws, stream=stream.value)
+        path = score_path()
+        assert hip.hipStreamSynchronize(stream) == 0
+    finally:
+        assert hip.hipStreamDestroy(stream) == 0
+    assert path == "general"
+    assert status_word(ws) == 0
+    for b in range(len(lengths)):
+        sl = slice(int(offsets[b]), int(offsets[b + 1]))
+        assert_scores_close(scores[sl].cpu().numpy(), oracle.score(q[b], [np.ascontiguousarray(k[:, sl, :]) for k in ks], w.scale, 0))
+
+
 def test_captured_score_of_a_short_prompt():
     """A captured call takes the general path; every replay agrees with the eager call."""
     import torch
