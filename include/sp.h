@@ -114,9 +114,12 @@ sp_status sp_score_workspace(const sp_score_desc *desc, int64_t total_tokens,
  * first ones after a change of stream may not be able to: they never fail either).
  * On a stream with a compute-unit mask no call fails.
  * Calls recorded into a graph take no turns: such a call uses the single-launch kernel
- * only where sp_score_is_fused answers 1, and its replays must then not overlap
- * another such call or replay. (Elsewhere the recorded call takes the
- * three-kernel path, so its scores may differ from the eager call's by rounding.)
+ * only where sp_score_is_fused (sp_score_batch_is_fused) announces it, and its replays
+ * must then not overlap another such call or replay. Its scores may differ from the eager
+ * call's by rounding: elsewhere the recorded call takes the three-kernel path, and in a
+ * single launch it runs the layers one after another where the eager call may run ranges
+ * of them side by side, so that SP_LAYER_MEAN adds them up in another order. Batches
+ * announced for several launches run recorded exactly as they do eagerly.
  */
 sp_status sp_score(const sp_score_desc *desc, const void *q_dev,
                    const void *const *k_layers_host, int64_t L,
@@ -219,7 +222,11 @@ sp_status sp_score_batch(const sp_score_desc *desc, const void *q_dev,
  * single-launch kernel in n launches (every prompt empty or at least T tokens
  * long and no longer than T tokens per compute unit, T as above; at least 64
  * workgroups in all; prompts share launches, each with all its keys in one, and
- * no launch has more blocks of four padded query rows than workgroups),
+ * packed as full as they get no launch has more blocks of four padded query rows
+ * than workgroups; several launches may be more than the fewest, run on a half to
+ * a quarter of the compute units with two to four ranges of the layers side by
+ * side; recorded calls make the same n launches, calls on a stream with a
+ * compute-unit mask the fewest, or the three-kernel path's),
  * 0 = a call that never fails (see sp_score_is_fused): the three-kernel path or,
  * where that is faster, the single-launch kernel with a stand-in; -1 = invalid
  * arguments. Same results either way (to rounding). Host-only. */

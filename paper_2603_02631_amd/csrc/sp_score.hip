@@ -1304,7 +1304,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     // launch that can do without that kernel.
     bool pair = may_fuse && !captured && !batch && pair_applies(p, opt.kscale != nullptr, total, desc->k_stride_token);
     bool fused = may_fuse && !pair && (batch ? plan_fused_batch(p, offsets_host, B, n_tiles * p.tile_keys, desc->k_stride_token, w,
-                                                              masked ? Launches::kFirstFit : captured ? Launches::kEven : Launches::kRanges, bg)
+                                                              masked ? Launches::kFirstFit : Launches::kRanges, bg)
                                              : plan_fused_prompt(p, total, desc->k_stride_token, bg));
     const bool big = fused_big(p);
     if (pair && big)            // no exchange area of their own: see fused_big

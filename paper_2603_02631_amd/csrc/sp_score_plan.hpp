@@ -273,9 +273,8 @@ inline void fill_tables(const Plan &p, const int64_t *offsets, const Batch &b, c
     }
 }
 
-// What a batch of several launches may do: first fit only, even launches, or layer ranges as well. All three announce the
-// same batches.
-enum class Launches { kFirstFit, kEven, kRanges };
+// What a batch of several launches may do: first fit only, or even launches and layer ranges. Both announce the same batches.
+enum class Launches { kFirstFit, kRanges };
 
 // The launches of a ragged batch of a shape that the kernel holds; false where it has none or the three kernels are
 // certain to be faster. `keys`: of the three-kernel path's tiles.

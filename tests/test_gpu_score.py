@@ -992,6 +992,41 @@ def test_batch_on_a_stream_with_a_compute_unit_mask():
         assert_scores_close(scores[sl].cpu().numpy(), oracle.score(q[b], [np.ascontiguousarray(k[:, sl, :]) for k in ks], w.scale, 0))
 
 
+@pytest.mark.parametrize("tiles,launches,ranges", [([90, 70, 50, 40, 12], 3, 2), ([250, 249, 120], 3, 1)], ids=["ranges", "whole"])
+def test_captured_batch_runs_as_it_is_announced(tiles, launches, ranges):
+    """An announced batch of several launches: a recorded call makes the launches that sp_score_batch_is_fused counts, and every
+    replay gives the eager call's scores bit for bit (mean over layers: the order of summation is the same)."""
+    import torch
+    import paper_2603_02631_amd as sp
+    from gpu_util import DEV, score_path, status_word, workspace
+    Lyr, H, Hkv, d, n_q, B = 6, 16, 8, 64, 8, len(tiles)
+    off = [512 * sum(tiles[:b]) - 7 * b for b in range(B + 1)]
+    say(f"[score-capture] batch of {launches} launches, {ranges} range(s)")
+    g = torch.Generator(device=DEV).manual_seed(7)
+    q = torch.randn((B, Lyr, H, n_q, d), device=DEV, generator=g).to(torch.bfloat16)
+    k = [torch.randn((Hkv, off[-1], d), device=DEV, generator=g).to(torch.bfloat16) for _ in range(Lyr)]
+    desc = sp.ScoreDesc(Lyr, H, Hkv, d, n_q, 0.125, sp.SP_LAYER_MEAN, d, off[-1] * d)
+    assert sp.sp_score_batch_is_fused(desc, off) == launches
+    ws = workspace(sp.sp_score_workspace(desc, off[-1], B))
+    od = torch.tensor(off, dtype=torch.int64, device=DEV)
+    eager, out = (torch.zeros(off[-1], dtype=torch.float32, device=DEV) for _ in range(2))
+    sp.sp_score_batch(desc, q, k, off, od, eager, ws)
+    assert score_path()[:3] == (1, ranges, launches)
+    torch.cuda.synchronize()
+    assert status_word(ws) == 0
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sp.sp_score_batch(desc, q, k, off, od, out, ws)
+    assert score_path() == (1, ranges, launches)
+    for _ in range(3):
+        out.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert status_word(ws) == 0 and torch.equal(out, eager)
+        sp.sp_score_batch(desc, q, k, off, od, eager, ws)
+        torch.cuda.synchronize()
+
+
 def test_captured_score_of_a_short_prompt():
     """A captured call takes the general path; every replay agrees with the eager call."""
     import torch
