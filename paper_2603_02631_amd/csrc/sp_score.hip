@@ -1316,7 +1316,7 @@ sp_status score_impl(const sp_score_desc *desc, const void *q_dev, const void *c
     }
     const bool announced = fused && !big && (batch ? bg.announced : bg.wgs[0] >= fused_min_workgroups(p));
     if (fused && !announced)
-        fused = !captured && (batch || ranges > 1 || bg.wgs[0] >= fused_min_workgroups(p)) && steps_pay(p, opt.kscale != nullptr, n_tiles * p.tile_keys, ranges, (int)bg.groups.size());
+        fused = !captured && (batch || ranges > 1 || bg.wgs[0] >= fused_min_workgroups(p)) && steps_pay(p, opt.kscale != nullptr, bg.prompts, n_tiles * p.tile_keys, ranges, (int)bg.groups.size());
     if (fused && big)           // no exchange area of their own: see fused_big
         for (size_t g = 0; g < bg.groups.size(); ++g)
             fused = fused && sp_fused::workspace_bytes(p.rows_pad, bg.wgs[g], bg.groups[g].n) <= w.split - w.part;

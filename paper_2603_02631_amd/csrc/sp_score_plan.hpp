@@ -45,6 +45,7 @@ struct BatchGroups {
     std::vector<sp_fused::GroupTable> groups;
     std::vector<int> wgs;
     int ranges = 1;                 // layer ranges side by side in each of several launches
+    int prompts = 1;                // that are not empty
     bool short_prompt = false;      // a prompt is shorter than a tile
     bool announced = false;         // see announces
 };
@@ -168,7 +169,9 @@ inline bool announces(const Plan &p, const Batch &b, const Packing &first)
 // three-kernel path. A launch costs its steps (a range's phases and five more to fill and drain the pipeline); the three
 // kernels take the longer the more keys their tiles hold, `keys` with the empty places. Each variant has its line,
 // in MB of bf16 keys: `per_step` for each step, or `steep` for each step less `base` where the fixed cost of the three
-// launches counts. The lines of 32 rows lie where the present kernels cross (8-bit keys of head_dim 64 apart); the others
+// launches counts. Steps of several prompts in layer ranges take the longer the more of them there are, since what exchanges
+// directly (see sp_fused::direct_max) and last tiles that are partly empty are then a larger part of a launch: with 32 rows such
+// batches have lines of their own, at head_dim 64 from 18 steps on. The lines of 32 rows lie where the present kernels cross (8-bit keys of head_dim 64 apart); the others
 // where they crossed before the single launch's steps became 5 to 25 % shorter and short prompts lost their merge launch;
 // the present kernels cross at or a little before them. Measured on these (tokens: three kernels / single launch, us; * =
 // the line still takes the slower one; 16 layers x 8 kv heads unless noted):
@@ -176,7 +179,10 @@ inline bool announces(const Plan &p, const Batch &b, const Packing &first)
 //                                head_dim 128: 700 33 / 34, 1000* 38 / 36, 1500 46 / 37; 4 x 4 heads, head_dim 128: 9000 29 / 29,
 //                                12000 32 / 31; 30 prompts of 1100 .. 1500 271 / 175, 24 of 60 .. 4000 364 / 189. Whole passes:
 //                                3900 51.1 / 51.4, 4200 54.0 / 50.3, 4850 56.5 / 50.6; 28 layers, 2800 57.2 / 52.2; 28 layers, head_dim
-//                                128: 1030 51.8 / 48.0, 1400 57.6 / 49.6; 16 layers, 2200 59.9 / 52.5
+//                                128: 1030 51.8 / 48.0, 1400 57.6 / 49.6; 16 layers, 2200 59.9 / 52.5; 16 x 16 phases, 3500 55 / 47
+//   32 rows, batches in ranges   9 prompts of 316 .. 2681 (8744 in all) 59 / 70, 22 of 317 .. 2800 134 / 168, 39 of 73 .. 3477 in two launches
+//                                of three ranges 237 / 280, 6 (16 tiles) 51 / 51; 13 steps: 4 x 4 phases, 30 (75 tiles) 39 / 35; 28 layers,
+//                                head_dim 128: 5 (2373 in all) 59 / 69, 8 (2832) 68 / 85, 3 (10 tiles) 51 / 48
 //   64 rows, 9+ lookahead rows   3600 47 / 47, 4500* 51 / 48, 5000 53 / 49, 6200 58 / 51, 9000 75 / 79, 10100* 79 / 73, 12000 88 / 73,
 //                                16384 121 / 76; 24 prompts of 60 .. 4000 460 / 293, 30 of 1100 .. 1500 359 / 291
 //   64 rows, 5+ heads a kv head  4600 51 / 51, 6200 58 / 52, 9000 73 / 80, 12000* 86 / 74, 16384 117 / 78
@@ -185,7 +191,7 @@ inline bool announces(const Plan &p, const Batch &b, const Packing &first)
 //                                22000 105 / 94; 28 layers, head_dim 128 (32 rows): 1000 34 / 35, 1500 40 / 36, as with bf16 keys
 //   8-bit keys, 64 rows          6200 56 / 53, 9000 69 / 86, 12100 80 / 85, 13000 97 / 84, 16384 108 / 86, 18000* 122 / 113, 19000 124 / 113,
 //                                22000 137 / 142, 24500* 145 / 147, 30000 189 / 141 (no line has the crossing at 17600 as well)
-inline bool steps_pay(const Plan &p, bool fp8, int64_t keys, int ranges, int launches)
+inline bool steps_pay(const Plan &p, bool fp8, int prompts, int64_t keys, int ranges, int launches)
 {
     struct Line { double per_step, steep, base; };
     const bool wide = p.rows_pad > 32;
@@ -194,8 +200,11 @@ inline bool steps_pay(const Plan &p, bool fp8, int64_t keys, int ranges, int lau
                     : !wide      ? Line{5.2, 5.2, 0}
                     : p.NB == 2  ? Line{8.0, 11.25, 68}
                                  : Line{9.4, 14.0, 91};
-    const double steps = (double)launches * (sp::ceil_div(p.n_layers, ranges) * (p.n_phases / p.n_layers) + 5);
-    return (double)keys * p.n_phases * p.D * 2e-6 >= std::min(line.per_step * steps, line.steep * steps - line.base * launches);
+    const double a_launch = (double)(sp::ceil_div(p.n_layers, ranges) * (p.n_phases / p.n_layers) + 5), steps = launches * a_launch;
+    double least = std::min(line.per_step * steps, line.steep * steps - line.base * launches);
+    if (prompts > 1 && ranges > 1 && !wide)
+        least = p.D == 128 ? std::max(least, launches * (7.2 * a_launch - 48.5)) : steps > 17 ? 6.3 * steps : least;
+    return (double)keys * p.n_phases * p.D * 2e-6 >= least;
 }
 
 // Layer ranges tried for a batch of several launches.
@@ -216,7 +225,7 @@ inline bool never_pays(const Plan &p, const Batch &b, int64_t keys, const Limits
     for (int ranges = 1; ranges <= std::min(kMaxSpread, p.n_layers); ++ranges) {
         if (b.longest > lim.units / ranges) break;
         const int64_t launches = fewest_launches(b, lim, ranges);
-        if (launches < 2 || steps_pay(p, false, keys, ranges, (int)launches)) return false;
+        if (launches < 2 || steps_pay(p, false, b.count, keys, ranges, (int)launches)) return false;
     }
     return true;
 }
@@ -290,6 +299,7 @@ inline bool plan_batch(const Plan &p, const int64_t *offsets, int B, int64_t key
     Packing k = may == Launches::kFirstFit ? first : pack(p, b, lim.units, lim.prompts, first);
     if (may == Launches::kRanges) out.ranges = spread_batch(p, b, offsets[B], lim, k);
     out.short_prompt = b.short_prompt;
+    out.prompts = b.count;
     fill_tables(p, offsets, b, k, out);
     return true;
 }

@@ -139,7 +139,7 @@ static void test_plans()
             Packing k = pack(p, b, lim.units, lim.prompts, first_fit(b, lim.units, lim.prompts));
             EXPECT(k.wgs.size() > 1 && !announces(p, b, first_fit(b, lim.units, lim.prompts)));
             const int ranges = spread_batch(p, b, off[B], lim, k);
-            EXPECT(!steps_pay(p, false, keys, ranges, (int)k.wgs.size()));
+            EXPECT(!steps_pay(p, false, b.count, keys, ranges, (int)k.wgs.size()));
             continue;
         }
         check_plan(p, off, lim, bg);
