@@ -146,16 +146,31 @@ inline bool duties_shared(const Plan &p, const Batch &b, const Packing &k)
     return shared;
 }
 
-// The launches of a batch. First fit tells how many there are, and fills all but the last. Steps do not get shorter in
-// proportion to a launch's workgroups (head_dim 64: 2.05 us on 144, 2.6 on 255, where HBM bounds them), so the same number
-// of launches takes less time with the workgroups shared out evenly. Whole passes of 656 workgroups in three launches 995 -> 956
-// us, 279 in two 641 -> 606, 287 670 / 670; head_dim 128, 295 in two 1079 -> 1023, 260 1078 -> 1028.
+// The same number of launches as first fit, shared out evenly where that is possible.
 inline Packing pack(const Plan &p, const Batch &b, int cap, int max_prompts, const Packing &first)
 {
     if (first.wgs.size() < 2) return first;
     Packing even;
     if (!share_out(b, first.wgs.size(), cap, max_prompts, even)) return first;
     return duties_shared(p, b, first) && !duties_shared(p, b, even) ? first : even;       // what is announced stays so
+}
+
+// First fit tells how many launches there are, and fills all but the last, unless it is the number of prompts that ends them.
+inline bool fills_launches(const Packing &first, int cap) { return 4 * first.most() >= 3 * cap; }
+
+// Whether launches of all layers take less time evenly filled. Steps do not get shorter in proportion to a launch's
+// workgroups (head_dim 64: 2.05 us on 144, 2.6 on 255, where HBM bounds them). Whole passes of 656 workgroups in three launches
+// 995 -> 956 us, 279 in two 641 -> 606, 287 670 / 670; head_dim 128, 295 in two 1079 -> 1023, 260 1078 -> 1028. Not where the number
+// of prompts ends the launches (33 prompts, 63 workgroups in the fullest, 628 -> 701; 3 phases of head_dim 128, 37 prompts 28
+// -> 51), nor with two blocks of query rows where many prompts exchange directly (see sp_fused::direct_max): first fit
+// leaves those to its last launches, an even share has them lengthen the steps of all (12 x 12 phases, 16 lookahead rows,
+// 24 prompts of 308 workgroups 1025 -> 1155, 36 of 409 1070 -> 1178; up to three a launch 0.82 .. 0.98 of the time).
+inline bool even_pays(const Plan &p, const Batch &b, int cap, const Packing &first)
+{
+    if (!fills_launches(first, cap)) return false;
+    if (p.rows_pad <= 32 || duties_shared(p, b, first)) return true;
+    const auto direct = std::count_if(b.tiles.begin(), b.tiles.end(), [&](int t) { return t <= sp_fused::direct_max(p.rows_pad); });
+    return direct <= 3 * (int64_t)first.wgs.size();
 }
 
 // Batches the single-launch kernel takes whatever their size: every prompt fills a tile, no launch of first fit has more
@@ -235,10 +250,9 @@ inline bool never_pays(const Plan &p, const Batch &b, int64_t keys, const Limits
 // be launched, to fill and to drain; a step takes 2.05 us on up to 200 workgroups and 2.6 on 256, where HBM bounds it. Whole
 // passes, 16 x 8 phases of head_dim 64: 279 workgroups in nine prompts 606 -> 516 us, token-major 343 in fifteen 721 -> 585; 28 x 8 of head_dim
 // 128: 260 1028 -> 840, 298 in nine 1019 -> 790, in twelve 1073 -> 839.
-// Replaces `best` and tells the number of ranges.
+// Replaces `best`, the launches of all layers evenly filled, and tells the number of ranges.
 inline int spread_batch(const Plan &p, const Batch &b, int64_t tokens, const Limits &lim, Packing &best)
 {
-    if (best.wgs.size() < 2) return 1;
     const size_t result = sizeof(float) * (size_t)tokens * (p.layer_agg == SP_LAYER_MAX ? 8 * p.NB : 1);      // of a range
     auto model = [&](double launches, int ranges, int most) {
         return launches * (sp::ceil_div(p.n_layers, ranges) * (p.n_phases / p.n_layers) + 9) * std::max(0.8, ranges * most / 256.0);
@@ -296,8 +310,13 @@ inline bool plan_batch(const Plan &p, const int64_t *offsets, int B, int64_t key
     sort_prompts(p, offsets, B, b);
     const Packing first = first_fit(b, lim.units, lim.prompts);
     out.announced = announces(p, b, first);
-    Packing k = may == Launches::kFirstFit ? first : pack(p, b, lim.units, lim.prompts, first);
-    if (may == Launches::kRanges) out.ranges = spread_batch(p, b, offsets[B], lim, k);
+    Packing k = first;
+    if (may == Launches::kRanges && first.wgs.size() > 1) {
+        k = pack(p, b, lim.units, lim.prompts, first);
+        // two blocks of query rows at head_dim 64: 59 prompts of 147 workgroups 575 us on the three kernels, 610 in ranges
+        if (p.D == 128 || p.rows_pad <= 32 || fills_launches(first, lim.units)) out.ranges = spread_batch(p, b, offsets[B], lim, k);
+        if (out.ranges == 1 && !even_pays(p, b, lim.units, first)) k = first;
+    }
     out.short_prompt = b.short_prompt;
     out.prompts = b.count;
     fill_tables(p, offsets, b, k, out);

@@ -177,6 +177,34 @@ static void test_ranges()
     EXPECT(spread > 1000);
 }
 
+// The last prompt is shorter than a tile.
+static std::vector<int> launches_of(const Plan &p, const std::vector<int> &tiles)
+{
+    std::vector<int64_t> off{0};
+    for (int t : tiles) off.push_back(off.back() + (int64_t)t * fused_tile(p));
+    off.back() -= 7;
+    BatchGroups bg;
+    EXPECT(plan_batch(p, off.data(), (int)tiles.size(), int64_t(1) << 40, device(), Launches::kRanges, bg) && bg.ranges == 1);
+    return bg.wgs;
+}
+
+// Which launches of all layers are filled evenly: where first fit fills the first ones, and with two blocks of query rows
+// where few prompts exchange directly (one layer: no ranges).
+static void test_even()
+{
+    using V = std::vector<int>;
+    const Plan narrow = shape(1, 8, 4, 64, 8), wide = shape(1, 8, 4, 64, 16), big = shape(1, 4, 8, 128, 8);
+    const V direct6 = {200, 190, 10, 9, 8, 7, 6, 1}, direct7 = {200, 190, 10, 9, 8, 7, 6, 5, 1};
+    EXPECT((launches_of(narrow, direct6) == V{216, 215}));
+    EXPECT((launches_of(narrow, direct7) == V{220, 216}));
+    EXPECT((launches_of(narrow, V(33, 1)) == V{32, 1}));               // the number of prompts ends a launch
+    for (const Plan &p : {wide, big}) {
+        EXPECT((launches_of(p, direct6) == V{216, 215}));              // three a launch
+        EXPECT((launches_of(p, direct7) == V{246, 190}));              // one more
+        EXPECT((launches_of(p, {200, 190, 20, 18, 1}) == V{218, 211}));
+    }
+}
+
 static void test_cost()
 {
     // the documented maximum, of prompts that the three kernels take; best of some runs
@@ -213,6 +241,7 @@ int main(int argc, char **argv)
     if (what == "packing") test_packing();
     else if (what == "plans") test_plans();
     else if (what == "ranges") test_ranges();
+    else if (what == "even") test_even();
     else if (what == "cost") test_cost();
     else { std::printf("unknown test %s\n", what.c_str()); return 2; }
     std::printf(g_fail ? "plan driver: %d check(s) failed\n" : "plan driver: all checks passed\n", g_fail);
