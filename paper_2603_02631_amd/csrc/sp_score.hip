@@ -49,7 +49,6 @@ constexpr int kWaves = 4;
 constexpr int kMaxPrompts = 4096;
 constexpr size_t kLdsBudget = 64 * 1024;
 constexpr int kMaxLookRows = 224;           // padded query rows of the widest supported group
-constexpr int kProbTargetWgs = 1024;   // the prob pass splits layers until it has about this many workgroups
 
 struct TileInfo {
     int64_t j0;          // first key of the tile (index into the packed token axis)
@@ -770,21 +769,6 @@ __global__ void sp_tiles_kernel(const int64_t *offsets, int n_prompts, int tile_
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-// Layers per workgroup of the prob pass: all of them once the tiles alone fill the device, and where a workgroup gets through
-// all phases of a short prompt in less time than the launch that adds up the ranges takes. Whole passes with ranges and
-// without: 2 layers x 2 kv heads of 64, 1024 tokens 26.2 / 23.8 us, 6000 (24 tiles) 29.4 / 28.9; of 128, 2500 (20 tiles) 28.8 / 28.7,
-// 6000 (47) 30.5 / 32.0; 4 x 2, 1024 tokens 25.9 / 28.1; 2 x 8 32.1 / 37.3.
-constexpr int kWholePhases = 4, kWholeTiles = 24;
-
-int prob_layers_per_split(const Plan &p, int64_t n_tiles)
-{
-    if (p.n_phases <= kWholePhases && n_tiles <= kWholeTiles) return p.n_layers;
-    int64_t want = (kProbTargetWgs + n_tiles - 1) / n_tiles;
-    if (want < 1) want = 1;
-    if (want > p.n_layers) want = p.n_layers;
-    return (int)((p.n_layers + want - 1) / want);
-}
-
 int prob_splits(const Plan &p, int64_t n_tiles)
 {
     const int lps = prob_layers_per_split(p, n_tiles);

@@ -30,6 +30,26 @@ inline bool fused_big(const Plan &p) { return p.D == 128 && p.NB == 1 && p.n_gbl
 // the two-pass path).
 inline int fused_tile(const Plan &p) { return p.D == 64 ? sp_fused::kTileKeys : sp_fused::kTileKeys / 2; }
 
+constexpr int kProbTargetWgs = 1024;       // the prob pass splits layers until it has about this many workgroups
+
+// Layers per workgroup of the prob pass: all of them once the tiles alone fill the device, and where a workgroup gets through
+// all phases of a short prompt in less time than the launch that adds up the ranges takes. A phase costs it as much for
+// every block of 32 padded query rows; the launch costs more with the maximum over layers, since it adds up 8 or 16 rows of maxima.
+// Score calls with ranges and without, us: 32 rows, four phases of head_dim 64, 1 tile 14.6 / 12.0, 12 14.9 / 13.6, 24 15.0 / 13.9,
+// of 128, 1 14.4 / 13.5, 20 15.0 / 15.2; 64 rows, two phases 1 tile 14.3 / 12.5, 24 14.9 / 14.7, three 13.0 / 13.5 (8 tiles), four
+// 14.8 / 15.5 (of head_dim 128 15.0 / 17.8); maximum over layers, four phases of 64 rows and 16 lookahead rows 16.9 / 15.2, of head_dim
+// 128 18.1 / 17.4 and with 8 lookahead rows 16.8 / 17.8; 128 rows, two phases 17.4 / 15.2, mean 14.7 / 15.3.
+inline int prob_layers_per_split(const Plan &p, int64_t n_tiles)
+{
+    const int work = p.n_phases * (p.rows_pad / 32);
+    const bool max_rows = p.layer_agg == SP_LAYER_MAX && (p.NB == 2 || p.D == 64);
+    if ((work <= 4 && n_tiles <= (p.D == 64 ? 24 : 20)) || (max_rows && work <= 8 && n_tiles <= 20)) return p.n_layers;
+    int64_t want = (kProbTargetWgs + n_tiles - 1) / n_tiles;
+    if (want < 1) want = 1;
+    if (want > p.n_layers) want = p.n_layers;
+    return (int)((p.n_layers + want - 1) / want);
+}
+
 // What the device and the call's workspace leave room for.
 struct Limits {
     int units;                             // workgroups of a launch

@@ -205,6 +205,22 @@ static void test_even()
     }
 }
 
+// Few phases: all layers of the prob pass in one workgroup, or a range of one layer each.
+static void test_whole()
+{
+    auto whole = [](const Plan &p, int tiles) { return prob_layers_per_split(p, tiles) == p.n_layers; };
+    const Plan narrow = shape(2, 2, 2, 64, 8), narrow128 = shape(2, 2, 2, 128, 8), rows64 = shape(2, 2, 2, 64, 16), three = shape(3, 1, 8, 128, 8);
+    EXPECT(whole(narrow, 1) && whole(narrow, 24) && !whole(narrow, 25));
+    EXPECT(whole(narrow128, 20) && !whole(narrow128, 21));
+    EXPECT(!whole(shape(5, 1, 4, 64, 8), 1));
+    EXPECT(!whole(rows64, 1) && !whole(three, 1) && !whole(shape(2, 1, 8, 64, 16), 1));       // two and four blocks of rows
+    EXPECT(whole(shape(2, 1, 4, 64, 16), 24) && whole(shape(2, 1, 8, 128, 8), 20));
+    EXPECT(whole(shape(2, 2, 2, 64, 16, SP_LAYER_MAX), 20) && !whole(shape(2, 2, 2, 64, 16, SP_LAYER_MAX), 21));
+    EXPECT(whole(shape(2, 2, 2, 128, 16, SP_LAYER_MAX), 1) && !whole(shape(2, 2, 8, 128, 8, SP_LAYER_MAX), 1));
+    EXPECT(!whole(shape(5, 1, 4, 64, 16, SP_LAYER_MAX), 1));
+    EXPECT(whole(shape(1, 64, 8, 64, 16), 1000) && whole(shape(16, 8, 4, 64, 8), 1024));          // nothing to split, or enough tiles
+}
+
 static void test_cost()
 {
     // the documented maximum, of prompts that the three kernels take; best of some runs
@@ -242,6 +258,7 @@ int main(int argc, char **argv)
     else if (what == "plans") test_plans();
     else if (what == "ranges") test_ranges();
     else if (what == "even") test_even();
+    else if (what == "whole") test_whole();
     else if (what == "cost") test_cost();
     else { std::printf("unknown test %s\n", what.c_str()); return 2; }
     std::printf(g_fail ? "plan driver: %d check(s) failed\n" : "plan driver: all checks passed\n", g_fail);

@@ -19,7 +19,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["packing", "plans", "ranges", "even", "cost"])
+@pytest.mark.parametrize("what", ["packing", "plans", "ranges", "even", "whole", "cost"])
 def test_plans_of_score_calls(driver, what):
     run = subprocess.run([driver, what], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert run.returncode == 0, run.stdout[-4000:]
