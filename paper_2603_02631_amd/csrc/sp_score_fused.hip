@@ -179,20 +179,24 @@ enum Kind {
 };
 
 // A workgroup's index, which says which tile it owns and where its partials go. Blocks are handed to the eight dies in
-// turn. Where a prompt has the launch to itself (contiguous bf16 keys of head_dim 64) consecutive tiles go to one die,
-// since with every eighth tile a die asks for the same few address bits all the time when a kv head's keys are a power of two
-// apart: whole passes of 131072 tokens and 8 lookahead rows 407 -> 391 us, token-major 488 -> 463, 16 rows 482 -> 478, 262144
-// tokens 797 -> 794, 100000 tokens 325 -> 322. Not elsewhere: 8-bit keys 458 -> 460, head_dim 128 two tiles a workgroup 1103 ->
-// 1110, sixteen prompts 999 -> 1001; layer ranges 8192 tokens 55.9 -> 59.3 (a range's workgroups on one die). Duties go by
-// block, so that the workgroups of a phase's duties sit on all dies (with them by tile 262144 tokens took 841).
-template <Kind KIND, bool W, bool F8>
-constexpr bool tiles_by_die = KIND == kPlain && !W && !F8;
-template <Kind KIND, bool W, bool F8>
+// turn. BY_DIE: consecutive tiles go to one die, since with every eighth tile a die asks for the same few address bits all
+// the time when a kv head's keys are a power of two apart. Duties go by block, so that the workgroups of a phase's duties sit
+// on all dies (with them by tile 262144 tokens took 841 us).
+template <bool BY_DIE>
 __device__ __forceinline__ int workgroup_index(int n_wg)
 {
     const int b = (int)blockIdx.x, die = b & 7;
-    return tiles_by_die<KIND, W, F8> ? die * (n_wg >> 3) + min(die, n_wg & 7) + (b >> 3) : b;
+    return BY_DIE ? die * (n_wg >> 3) + min(die, n_wg & 7) + (b >> 3) : b;
 }
+
+// Where a prompt has the launch to itself, contiguous bf16 keys of head_dim 64 (score calls and, *, whole passes, every eighth tile /
+// consecutive ones, us, both in turn on one card): one block of query rows, 16 x 8 phases, 131072 tokens 376 / 361, token-major 445 / 423, 100000 291 / 289 and
+// 346 / 334, 8 x 8 phases 75324 149 / 144, 2 x 2 33000 17.1 / 16.1; two tiles a workgroup 262144 776 / 773, token-major 851 / 843. With two
+// blocks of rows only in the instantiation for all compute units, * 131072 tokens 500 / 496, on another card 478 / 475; elsewhere * 75324 382 / 385, 8 x 8 phases
+// 120000 230 / 236, 2 x 4 75324 22.3 / 23.0, two tiles a workgroup * 150000 764 / 770. Not for 8-bit keys * 458 / 460, head_dim 128 two tiles a
+// workgroup * 1103 / 1110, sixteen prompts * 999 / 1001; layer ranges * 8192 tokens 55.9 / 59.3 (a range's workgroups on one die).
+template <int BLOCKS, Kind KIND, bool W, bool F8, class M>
+constexpr bool tiles_by_die = KIND == kPlain && !W && !F8 && (BLOCKS == 1 || M::kWorkgroups > 0);
 
 struct Ring {
     bf16x8 kf[kRing][kNS][kKS];           // K fragments of the phases in flight
@@ -1113,7 +1117,7 @@ struct Walk {
 // prob, 8 in stats); the bracketed ones exist on some waves or in some steps only, so every wait counts only operations
 // that are certainly issued behind the ones it needs.
 // KIND (see there): the plain variant carries none of the others' code or registers.
-template <int NB, int GB, int SLOT, int PAR, Kind KIND, bool W, bool F8, bool PAIR>
+template <int NB, int GB, int SLOT, int PAR, Kind KIND, bool W, bool F8, bool PAIR, bool BY_DIE>
 __device__ __forceinline__ void step(const FusedArgs &args, const LayerPtrs &kp, const GroupTable &gt, int s, int n_phases, Ring &ring,
                                      Acc<NB> (&accs)[PAIR ? 2 : 1], const LaneConst &lc, Walk &wk, unsigned char *lds, uint32_t lds0,
                                      uint64_t wave_off, const int (&r_ranges)[PAIR ? 2 : 1])
@@ -1138,7 +1142,7 @@ __device__ __forceinline__ void step(const FusedArgs &args, const LayerPtrs &kp,
     int tid = threadIdx.x;
     __asm__ volatile("" : "+v"(tid));
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int w = workgroup_index<KIND, W, F8>(a.n_wg);
+    const int w = workgroup_index<BY_DIE>(a.n_wg);
     // Phases this step works on; < 0 or >= n_phases: nothing to do. PAIR: step s handles tile s % 2 (= PAR) of
     // phase s / 2; publishing and duties happen in even steps, when both tiles of a phase have been seen.
     const int ps = PAIR ? s >> 1 : s;                             // statistics pass
@@ -1311,7 +1315,7 @@ __device__ __forceinline__ void step(const FusedArgs &args, const LayerPtrs &kp,
                 wk.dfirst += duty_blocks;
                 if (wk.dfirst >= duty_n) wk.dfirst -= duty_n;
             }
-            const int blk = (tiles_by_die<KIND, W, F8> ? (int)blockIdx.x : w) - duty_w0 - wk.dfirst;
+            const int blk = (BY_DIE ? (int)blockIdx.x : w) - duty_w0 - wk.dfirst;
             wk.duty_blk = blk < 0 ? blk + duty_n : blk;
             if (pd_next < 0 || pd_next >= n_phases || wk.duty_blk >= duty_blocks || direct) wk.duty_blk = -1;
         };
@@ -1586,7 +1590,7 @@ __device__ __forceinline__ void step_late(const FusedArgs &a, const LayerPtrs &k
     int tid = threadIdx.x;
     __asm__ volatile("" : "+v"(tid));
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int w = workgroup_index<KIND, false, false>(a.n_wg);
+    const int w = workgroup_index<KIND == kPlain>(a.n_wg);
     const int ps = s >> 1, pf = (s + 1) >> 1, pd = (s - 2) >> 1, pc = (s - 4) >> 1;       // pd: published, combined; pc: probability pass
     const uint32_t stride_bytes = (uint32_t)a.k_stride_token * 2u;
     int *fail = reinterpret_cast<int *>(lds + MP::kFail);
@@ -1803,7 +1807,7 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     constexpr bool BIG = W && NB * GB == 2;
     static_assert(!BIG || !F8, "head_dim 128, two blocks of query rows: bf16 keys");
     static_assert(!PROB_LAST || (W && NB * GB == 1 && KIND != kRanges && !F8 && !PAIR), "head_dim 128, one block of query rows, whole prompts");
-    constexpr bool LATE = PAIR && !W && !F8 && NB * GB == 1;
+    constexpr bool LATE = PAIR && !W && !F8 && NB * GB == 1, kByDie = tiles_by_die<NB * GB, KIND, W, F8, M>;
     using MP = typename std::conditional<LATE, LateMap, Map<BIG>>::type;
     static_assert(!F8 || KIND != kExtra, "8-bit keys: contiguous keys of one prompt");
     static_assert(!PAIR || KIND != kRanges, "pairs of tiles: whole prompts");
@@ -1817,7 +1821,7 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
     fold_model_constants<M>(a);
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, hf = lane >> 5, col = lane & 31;
-    const int w = workgroup_index<KIND, W, F8>(a.n_wg);
+    const int w = workgroup_index<kByDie>(a.n_wg);
     int n_phases = a.n_layers * a.n_kv_heads;
     // Contiguous keys: the last workgroup's tile is shifted back so that it ends with the prompt (the
     // caller guarantees L >= 512): every workgroup loads 512 real keys; rows below r_lo belong to the
@@ -1990,10 +1994,10 @@ __global__ __launch_bounds__(kFThreads, 2) void sp_fused_kernel(FusedArgs a, Lay
         }
     } else {
         for (int s0 = 0; s0 < n_steps; s0 += 4) {
-            step<NB, GB, 0, 0, KIND, W, F8, PAIR>(a, kp, gt, s0 + 0, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
-            step<NB, GB, 1, 1, KIND, W, F8, PAIR>(a, kp, gt, s0 + 1, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
-            step<NB, GB, 2, 0, KIND, W, F8, PAIR>(a, kp, gt, s0 + 2, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
-            step<NB, GB, 3, 1, KIND, W, F8, PAIR>(a, kp, gt, s0 + 3, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+            step<NB, GB, 0, 0, KIND, W, F8, PAIR, kByDie>(a, kp, gt, s0 + 0, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+            step<NB, GB, 1, 1, KIND, W, F8, PAIR, kByDie>(a, kp, gt, s0 + 1, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+            step<NB, GB, 2, 0, KIND, W, F8, PAIR, kByDie>(a, kp, gt, s0 + 2, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
+            step<NB, GB, 3, 1, KIND, W, F8, PAIR, kByDie>(a, kp, gt, s0 + 3, n_phases, ring, accs, lc, wk, lds, lds0, wave_off, r_ranges);
         }
     }
     vm_wait<0>();               // no direct-to-LDS load may outlive the workgroup
@@ -2137,7 +2141,8 @@ sp_status launch(FusedArgs a, const LayerPtrs &kp, const GroupTable *group, bool
         return sp::fail(SP_ERR_UNSUPPORTED, "fused score kernel, 8-bit keys: one prompt, contiguous keys only");
     // The fixed-model instantiations apply when every folded constant equals the call's value. Against the generic ones
     // (whole passes): 128K tokens 4 %; in layer ranges 8192 tokens 60.8 -> 58.8 us, paged 50021 tokens 241.4 -> 233.1; two
-    // tiles a workgroup, 256K tokens 946.8 -> 932.3.
+    // tiles a workgroup, 256K tokens 946.8 -> 932.3, with 16 lookahead rows 150000 tokens 784 -> 764 (262144 1005 / 1003), 8-bit
+    // keys 160000 827 -> 805.
     const bool draft = a.head_dim == kD && a.n_layers == 16 && a.n_q_heads == 32 && a.n_kv_heads == 8 && a.k_stride_token == kD &&
                        a.c == kScaleEighthLog2e && a.inv_c == 1.0f / kScaleEighthLog2e;
     if (pair) {
