@@ -179,8 +179,9 @@ enum Kind {
 };
 
 // A workgroup's index, which says which tile it owns and where its partials go. Blocks are handed to the eight dies in
-// turn. BY_DIE: consecutive tiles go to one die, since with every eighth tile a die asks for the same few address bits all
-// the time when a kv head's keys are a power of two apart. Duties go by block, so that the workgroups of a phase's duties sit
+// turn. BY_DIE: consecutive tiles go to one die, whose L2 then waits less for DRAM: 131072 tokens, 8 lookahead rows, the same
+// reads (TCC_EA0_RDREQ 1.71e7) and address translations, but TCC_EA0_RDREQ_DRAM_CREDIT_STALL 7.2e6 -> 5.0e6 and TCC_TAG_STALL 8.4e6 ->
+// 6.2e6 a launch, token-major 8.2e6 -> 7.0e6 and 10.5e6 -> 8.8e6. Duties go by block, so that the workgroups of a phase's duties sit
 // on all dies (with them by tile 262144 tokens took 841 us).
 template <bool BY_DIE>
 __device__ __forceinline__ int workgroup_index(int n_wg)
@@ -1392,7 +1393,8 @@ __device__ __forceinline__ void step(const FusedArgs &args, const LayerPtrs &kp,
 //   barrier
 // Loads return in order: every wait counts the loads certainly issued behind what it needs. Whole passes of 28 x 8
 // phases: 50000 tokens 539 -> 521 us, 54000 578 -> 545, 60000 632 -> 594, 65536 692 -> 649, token-major 779 -> 733, paged 50000
-// 620 -> 551, lookahead keys 58000 624 -> 579.
+// 620 -> 551, lookahead keys 58000 624 -> 579. At 65536 tokens a wave waits 26 % less (SQ_WAIT_ANY 4.4e8 -> 3.2e8 of 7.3e8 and 6.8e8
+// SQ_WAVE_CYCLES), and 14000 loads fewer are issued, polls for normalisers that were not there.
 template <int SLOT, int PAR, Kind KIND>
 __device__ __forceinline__ void step_prob_last(const FusedArgs &a, const LayerPtrs &kp, int s, int n_phases, Ring &ring, Acc<1> &acc,
                                                const LaneConst &lc, Walk &wk, unsigned char *lds, uint32_t lds0, uint64_t wave_off, int r_range)

@@ -22,7 +22,7 @@ struct Plan {
     size_t lds_bytes;
 };
 
-// Two blocks of query rows at head_dim 128 (bf16 keys, one tile a workgroup): their exchange area always takes the
+// Two blocks of query rows at head_dim 128 (bf16 keys, one tile a workgroup or two): their exchange area always takes the
 // place of the general path's buffers, so the workspace is as large as without them.
 inline bool fused_big(const Plan &p) { return p.D == 128 && p.NB == 1 && p.n_gblk == 2; }
 
