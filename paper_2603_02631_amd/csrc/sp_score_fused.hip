@@ -1128,8 +1128,9 @@ __device__ __forceinline__ void step(const FusedArgs &args, const LayerPtrs &kp,
     // Two blocks of query rows in layer ranges: the compiler keeps what the four unrolled steps compute from these values alive
     // across the loop, 160 to 210 scalars in vector lanes, of which a step read some 250 back, each behind wait states before
     // it can be an address. Opaque copies make every step compute them again (90 to 115 scalars; at head_dim 128 from the
-    // pointers and strides on). Whole passes: 20001 tokens of 24 x 4 heads of 128 142.0 -> 135.9 us, 30000 201.2 -> 195.0; 16 x 8
-    // heads of 64, 16 lookahead rows 40000 tokens 190.9 -> 184.1, token-major 20000 119.0 -> 114.8, 8-bit keys 20000 129.2 -> 124.8.
+    // pointers and strides on). Whole passes, in turn on one card, runs of one side up to 0.5 % apart: 20001 tokens
+    // of 24 x 4 heads of 128 144.3 -> 140.1 us, 30000 201.5 -> 196.2; 16 x 8 heads of 64, 16 lookahead rows 40000 tokens 196.4 -> 190.5,
+    // token-major 20000 119.2 -> 116.1, 8-bit keys 20000 127.9 -> 123.5.
     // With one block the step waits for memory, and the added instructions cost 1 %; pointers as well at head_dim 64: 1 %.
     constexpr bool kRecompute = RANGES && NB * GB == 2;
     typename std::conditional<kRecompute, FusedArgs, const FusedArgs &>::type a = args;
