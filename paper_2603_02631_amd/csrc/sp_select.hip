@@ -635,6 +635,27 @@ __device__ __forceinline__ void count_runs(int32_t *__restrict__ hist, int bin)
 }
 
 constexpr int kTokenThreads = 1024;
+
+// The same for a histogram by chunk: waves that lie within one chunk are added up over the workgroup first. Bins of
+// neighbouring chunks share cache lines, so where a chunk has many tokens (12 to a draft token) all workgroups in flight
+// add to the same few lines: 1572864 tokens in 1024 chunks 32.3 us a wave at a time, 21.9 this way, 149422 in 2048 13.5 / 13.6.
+__device__ __forceinline__ void count_runs_together(int32_t *__restrict__ hist, int bin)
+{
+    __shared__ int whole[kTokenThreads / 64];
+    const int lane = threadIdx.x & 63;
+    const int first = __builtin_amdgcn_readfirstlane(bin);
+    const bool one = __all(bin == first) && first >= 0;
+    if (!one) count_runs(hist, bin);
+    if (lane == 0) whole[threadIdx.x >> 6] = one ? first : -1;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    bin = lane < kTokenThreads / 64 ? whole[lane] : -1;
+    const int prev = __shfl_up(bin, 1);
+    const bool leader = lane == 0 || prev != bin;
+    const uint64_t leaders = __ballot(leader);
+    if (leader && bin >= 0) atomicAdd(&hist[bin], 64 * (__ffsll((unsigned long long)(leaders >> (lane + 1)))));
+}
+
 __global__ __launch_bounds__(kTokenThreads) void sp_token_rank_kernel(const int64_t *__restrict__ bnd, int n_chunks,
                                                                       const int64_t *__restrict__ toff, int64_t M,
                                                                       const int32_t *__restrict__ rank,
@@ -686,7 +707,7 @@ __global__ __launch_bounds__(kTokenThreads) void sp_rank_tokens_kernel(const flo
                         [&](int j) { const uint32_t k = order_key(cs[j]); if (bin == C || k > key) { bin = j; key = k; } },
                         [&](int j) { const uint32_t k = order_key(cs[j]); if (bin == C || k <= key) { bin = j; key = k; } });
     }
-    count_runs(hist, bin);
+    count_runs_together(hist, bin);
 }
 
 // kept(k) = hist[0] + .. + hist[k-1]; writes the largest k in 1..C with kept(k) <= budget (1 if none)

@@ -146,3 +146,26 @@ def test_budget_at_the_edges_of_its_kernels(C):
         np.testing.assert_array_equal(spans, oracle.merge(exact, chunk, L))
         assert oracle.project(doff, toff, spans)[2] == n_kept <= budget
         assert oracle.project(doff, toff, oracle.merge(oracle.topk(cs, k + 1), chunk, L))[2] > budget
+
+
+@pytest.mark.parametrize("C,per_chunk", [(1, 63), (1, 5000), (3, 64), (5, 1024), (64, 1500), (65, 1000), (4097, 200)])
+def test_budget_with_many_tokens_to_a_chunk(C, per_chunk):
+    """Whole waves within one chunk, workgroups of one and of several chunks, a last wave that is not full; tokens without
+    characters among them. Exact: kept chunks, kept tokens, and one chunk more would keep more than the budget."""
+    from gpu_util import gpu_select_budget
+    say(f"[budget] C={C}, {per_chunk} target tokens a chunk")
+    rng = np.random.default_rng(5600 + C + per_chunk)
+    chunk = 2
+    L, M = C * chunk, C * per_chunk + 17
+    doff = np.arange(L + 1, dtype=np.int64) * (per_chunk // 2 + 3)
+    toff = np.concatenate([[0], np.sort(rng.integers(0, doff[-1] + 1, size=M - 1)), doff[-1:]]).astype(np.int64)
+    scores = rng.integers(0, 50, size=L).astype(np.float32)
+    for budget in (M // 7, M // 2):
+        k, n_kept, sel, spans, cs = gpu_select_budget(scores, 1, chunk, doff, toff, budget)
+        exact = oracle.topk(cs.astype(np.float64), k)
+        np.testing.assert_array_equal(sel.astype(np.int64), exact)
+        np.testing.assert_array_equal(spans, oracle.merge(exact, chunk, L))
+        assert oracle.project(doff, toff, spans)[2] == n_kept
+        assert n_kept <= budget or k == 1
+        if k < C:
+            assert oracle.project(doff, toff, oracle.merge(oracle.topk(cs.astype(np.float64), k + 1), chunk, L))[2] > budget
