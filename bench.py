@@ -35,8 +35,8 @@ ROTATE_BYTES = 2 << 30          # K buffers are rotated over at least this much 
 # It is reported only while the kernel sources are the ones the counters were taken on.
 TRAFFIC = {
     "workload": "long-128k",
-    "sources_sha256": "8744d795a5a380687be798b807d5c651fcf30d32a3652a2832cd5798306aa98a",
-    "fetch_bytes": 1090453.1 * 2048,      # FETCH_SIZE 1090453.1 per dispatch; the 1 GiB copy reads 524306 -> 2 KiB per count
+    "sources_sha256": "87b5f99356cdf97ad8ad76a87326dfbdf2f68998047206210aa024433d9f4f95",
+    "fetch_bytes": 1090266.1 * 2048,      # FETCH_SIZE 1090266.1 per dispatch; the 1 GiB copy reads 524306 -> 2 KiB per count
     "write_bytes": 17024.0 * 1024,        # WRITE_SIZE 17024.0 per dispatch; the 1 GiB copy writes 1048576 -> 1 KiB per count
 }
 KERNEL_SOURCES = ["sp_score_fused.hip", "sp_score_fused.hpp", "sp_score_dev.hpp"]     # the dominant kernel and its headers
